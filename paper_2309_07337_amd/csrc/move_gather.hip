@@ -15,6 +15,12 @@ namespace {
            int64_t ntiles, int tile_rows, int nv_rt, int use_win) {                            \
     gather_body<VB, NV, LPR, U, NT>(jobs, ts, njobs, ntiles, tile_rows, nv_rt, use_win);       \
   }                                                                                            \
+  template <int VB, int U, bool NT>                                                            \
+  __global__ void __launch_bounds__(1024)                                                      \
+      NAME##_flat(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts, int njobs, \
+                  int64_t ntiles, int tile_rows, int nv) {                                     \
+    gather_flat_body<VB, U, NT>(jobs, ts, njobs, ntiles, tile_rows, nv);                       \
+  }                                                                                            \
   template <int RB, int U, bool NT, bool GAS>                                                  \
   __global__ void __launch_bounds__(1024)                                                      \
       NAME##_vec(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts, int njobs, \
@@ -36,6 +42,12 @@ namespace {
     }                                                                                          \
   };                                                                                           \
   struct NAME##_go {                                                                           \
+    template <int VB, int U, bool NT>                                                          \
+    static void flat(const LaunchTable& t, hipStream_t s, int nv) {                            \
+      hipLaunchKernelGGL((NAME##_flat<VB, U, NT>), dim3(t.grid), dim3(t.sched.block_threads),  \
+                         0, s, t.jobs.as<GatherJob>(), t.tile_start.as<int64_t>(), t.njobs,    \
+                         t.ntiles, t.sched.tile_rows, nv);                                     \
+    }                                                                                          \
     template <int VB, int NV, int LPR, int U, bool NT>                                         \
     static void go(const LaunchTable& t, hipStream_t s, int nv) {                              \
       hipLaunchKernelGGL((NAME<VB, NV, LPR, U, NT>), dim3(t.grid), dim3(t.sched.block_threads), \
@@ -70,8 +82,8 @@ void transfer_shape(const LaunchTable& t, hipStream_t s) {
   } else {
     if (nv == 1) return transfer_fixed::go<4, 1, 1, 4, false>(t, s, nv);
   }
-  if (nv >= 16) return transfer_fixed::go<VB, 0, 16, 1, false>(t, s, nv);
-  return transfer_fixed::go<VB, 0, 1, 1, false>(t, s, nv);
+  if (nv <= kFlatMaxVec) return k_transfer_go::flat<VB, 4, false>(t, s, nv);
+  return transfer_fixed::go<VB, 0, 64, 1, false>(t, s, nv);
 }
 
 // Short rows, 16 bytes per lane (the table builder set t.vec16): rows of 4

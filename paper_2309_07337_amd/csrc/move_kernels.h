@@ -254,6 +254,126 @@ __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, 
 }
 
 // ---------------------------------------------------------------------------
+// Rows of any other number of vectors (nv not one of the fixed shapes, at
+// most kFlatMaxVec): flat forms.  The rows of a tile are one stream of
+// rows * nv vectors, and lane i takes vectors i, i + blockDim, ... of it, so
+// that stores (and each row's loads) are contiguous over a wavefront and no
+// lane idles whatever nv is.  Bound by memory; one lane per row (rows of
+// 24 to 40 bytes) or 16 lanes per row (25 vectors: 7 of 32 lanes idle)
+// touches every cache line once per vector instead: 5 x FP64 pull pack
+// 189 us, unpack 93 us, sum 223 us for 2.4 M rows before; 54, 30 and 56 us
+// so (unpack 6.3 TB/s; the pack's random 40-byte rows take two sectors each).
+// ---------------------------------------------------------------------------
+// v / nv as one multiplication: exact for v < 2^32 / nv, which chunks of
+// kFlatRows rows of at most kFlatMaxVec vectors keep (2048 * 1024 * 1024 < 2^32).
+constexpr int kFlatMaxVec = 1024;
+constexpr int kFlatRows = 2048;
+struct FlatDiv {
+  uint32_t nv, m;
+  __device__ __forceinline__ explicit FlatDiv(int n) : nv((uint32_t)n), m(0xffffffffu / (uint32_t)n + 1u) {}
+  __device__ __forceinline__ uint32_t row(uint32_t v) const { return __umulhi(v, m); }
+};
+
+// Contiguous bytes (a multiple of VB, both ends VB-aligned) copied by the
+// workgroup: 16-byte vectors where source and destination are congruent,
+// else VB-byte ones.
+template <int VB, bool NT>
+__device__ __forceinline__ void flat_copy(const HX_G char* __restrict__ sp, HX_G char* __restrict__ dp, int64_t bytes) {
+  using S = typename RawVec<VB>::type;
+  constexpr int UC = 8;  // loads in flight per lane
+  auto stream = [&](auto zero, int64_t lo, int64_t hi) {  // vectors of [lo, hi) bytes
+    using W = decltype(zero);
+    const HX_G W* __restrict__ a = reinterpret_cast<const HX_G W*>(sp + lo);
+    HX_G W* __restrict__ b = reinterpret_cast<HX_G W*>(dp + lo);
+    const int64_t n = (hi - lo) / (int64_t)sizeof(W);
+    for (int64_t i = threadIdx.x; i < n; i += (int64_t)blockDim.x * UC) {
+      W c[UC];
+#pragma unroll
+      for (int u = 0; u < UC; ++u) {
+        const int64_t k = i + (int64_t)u * blockDim.x;
+        if (k < n) c[u] = ldv<W, NT>(a + k);
+      }
+#pragma unroll
+      for (int u = 0; u < UC; ++u) {
+        const int64_t k = i + (int64_t)u * blockDim.x;
+        if (k < n) stv<W, NT>(b + k, c[u]);
+      }
+    }
+  };
+  if constexpr (VB < 16) {
+    if ((((uintptr_t)sp ^ (uintptr_t)dp) & 15) != 0) {
+      stream(S{}, 0, bytes);
+      return;
+    }
+    const int64_t head = min((int64_t)((16 - ((uintptr_t)dp & 15)) & 15), bytes);
+    const int64_t body = (bytes - head) & ~(int64_t)15;
+    stream(S{}, 0, head);
+    stream(u32x4{}, head, head + body);
+    stream(S{}, head + body, bytes);
+  } else {
+    stream(S{}, 0, bytes);
+  }
+}
+
+template <int VB, int U, bool NT>
+__device__ __forceinline__ void gather_flat_body(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts,
+                                                 int njobs, int64_t ntiles, int tile_rows, int nv) {
+  using V = typename RawVec<VB>::type;
+  const FlatDiv div(nv);
+  int64_t t0, t1;
+  tile_range(ntiles, &t0, &t1);
+  if (t0 >= t1) return;
+  int j = find_job(ts, njobs, t0);
+  const int bd = blockDim.x, tid = threadIdx.x;
+  const int64_t rb = (int64_t)nv * VB;
+  for (int64_t t = t0; t < t1; ++t) {
+    while (t >= ts[j + 1]) ++j;
+    const HX_G char* __restrict__ src = (const HX_G char*)jobs[j].src;
+    HX_G char* __restrict__ dst = (HX_G char*)jobs[j].dst;
+    const HX_G int32_t* __restrict__ idx = (const HX_G int32_t*)jobs[j].idx;
+    const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
+    const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
+    if (idx == nullptr) {
+      flat_copy<VB, NT>(src + r0 * rb, dst + r0 * rb, (r1 - r0) * rb);
+      signal_tile(jobs[j].ready, r1 - r0);
+      continue;
+    }
+    for (int64_t rc = r0; rc < r1; rc += kFlatRows) {
+      const int nvec = (int)min((int64_t)kFlatRows, r1 - rc) * nv;
+      const HX_G int32_t* __restrict__ ix = idx + rc;
+      HX_G V* __restrict__ dp = reinterpret_cast<HX_G V*>(dst + rc * rb);
+      // source rows of a lane's U vectors of the pass at base (lanes past the
+      // end reload the last vector: valid loads; only stores are predicated)
+      auto load_idx = [&](int base, int32_t (&s)[U], uint32_t (&c)[U]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const uint32_t k = (uint32_t)min(base + tid + u * bd, nvec - 1);
+          const uint32_t r = div.row(k);
+          c[u] = k - r * (uint32_t)nv;
+          s[u] = ldv<int32_t, NT>(ix + r);
+        }
+      };
+      int32_t s[U];
+      uint32_t c[U];
+      load_idx(0, s, c);
+      for (int base = 0; base < nvec; base += bd * U) {
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = reinterpret_cast<const HX_G V*>(src + (int64_t)s[u] * rb)[c[u]];
+        // the next pass's indices are in flight while this pass's rows arrive
+        if (base + bd * U < nvec) load_idx(base + bd * U, s, c);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k = base + tid + u * bd;
+          if (k < nvec) stv<V, NT>(dp + k, v[u]);
+        }
+      }
+    }
+    signal_tile(jobs[j].ready, r1 - r0);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Pull of short rows (RB = 4 or 8 bytes), 16 bytes of rows per lane: a group
 // of V = 16 / RB consecutive rows takes one V-wide load of its indices, V
 // row reads and one 16-byte store, so a wavefront's index loads and stores
@@ -589,6 +709,85 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
   }
 }
 
+// The push form for rows of any other number of vectors: a staged tile's
+// entries are one stream of entries * nv vectors over the lanes (see the flat
+// gather); tiles that are not staged take the stream of their rows' vectors,
+// each lane writing its vector to every slot of its row.
+template <int VB, int U, bool NT>
+__device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
+                                                  const int2* __restrict__ te, int njobs, int64_t ntiles,
+                                                  int tile_rows, int nv) {
+  using V = typename RawVec<VB>::type;
+  const FlatDiv div(nv);
+  __shared__ int32_t s_ptr[STAGE_ROWS + 1];
+  __shared__ int32_t s_idx[STAGE_ENTRIES];
+  __shared__ int16_t s_row[STAGE_ENTRIES];
+  int64_t t0, t1;
+  tile_range(ntiles, &t0, &t1);
+  if (t0 >= t1) return;
+  int j = find_job(ts, njobs, t0);
+  const int bd = blockDim.x, tid = threadIdx.x;
+  const int64_t rb = (int64_t)nv * VB;
+  for (int64_t t = t0; t < t1; ++t) {
+    while (t >= ts[j + 1]) ++j;
+    const HX_G char* __restrict__ in = (const HX_G char*)jobs[j].in;
+    HX_G char* __restrict__ out = (HX_G char*)jobs[j].out;
+    const HX_G int32_t* __restrict__ ptr = (const HX_G int32_t*)jobs[j].ptr;
+    const HX_G int32_t* __restrict__ idx = (const HX_G int32_t*)jobs[j].idx;
+    const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
+    const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
+    const int nt = (int)(r1 - r0);
+    const int2 er = te[t];
+    const int32_t P0 = er.x;
+    const int ne = er.y - P0;
+    if (nt <= STAGE_ROWS && ne <= STAGE_ENTRIES) {
+      const int nl = max(nt + 1, ne);
+      for (int i = tid; i < nl; i += bd) {
+        int32_t pv = 0, iv = 0;
+        if (i <= nt) pv = ptr[r0 + i];
+        if (i < ne) iv = ldv<int32_t, NT>(idx + P0 + i);
+        if (i <= nt) s_ptr[i] = pv;
+        if (i < ne) s_idx[i] = iv;
+      }
+      __syncthreads();
+      for (int i = tid; i < nt; i += bd)
+        for (int32_t e = s_ptr[i]; e < s_ptr[i + 1]; ++e) s_row[e - P0] = (int16_t)i;
+      __syncthreads();
+      const int nvec = ne * nv;
+      for (int base = tid; base < nvec; base += bd * U) {
+        V v[U];
+        int32_t d[U];
+        uint32_t c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const uint32_t k = (uint32_t)min(base + u * bd, nvec - 1);  // valid load, no branch
+          const uint32_t e = div.row(k);
+          c[u] = k - e * (uint32_t)nv;
+          d[u] = s_idx[e];
+          v[u] = ldv<V, NT>(reinterpret_cast<const HX_G V*>(in + (r0 + s_row[e]) * rb) + c[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (base + u * bd < nvec) stv<V, NT>(reinterpret_cast<HX_G V*>(out + (int64_t)d[u] * rb) + c[u], v[u]);
+      }
+      __syncthreads();  // the next tile overwrites the staged indices
+      continue;
+    }
+    for (int64_t rc = r0; rc < r1; rc += kFlatRows) {
+      const int nvec = (int)min((int64_t)kFlatRows, r1 - rc) * nv;
+      for (int k = tid; k < nvec; k += bd) {
+        const uint32_t r = div.row((uint32_t)k);
+        const uint32_t c = (uint32_t)k - r * (uint32_t)nv;
+        const int32_t p0 = ptr[rc + r], p1 = ptr[rc + r + 1];
+        if (p0 >= p1) continue;
+        const V v = reinterpret_cast<const HX_G V*>(in + (rc + r) * rb)[c];
+        for (int32_t e = p0; e < p1; ++e)
+          stv<V, NT>(reinterpret_cast<HX_G V*>(out + (int64_t)ldv<int32_t, NT>(idx + e) * rb) + c, v);
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Fixed-order segmented sum: out[r] = in[idx[ptr[r]]] + in[idx[ptr[r]+1]] + ...
 // Additions in T, strictly in ascending position, the accumulator starting
@@ -811,6 +1010,116 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
         }
       }
     }
+  }
+}
+
+// The segmented sum for rows of any other number of vectors.  A staged tile
+// goes chunk by chunk as above, with the chunk's terms, then its sums, as one
+// stream of vectors over the lanes (see the flat gather); other tiles, and a
+// row with more terms than the buffer holds, add straight from memory.  Each
+// lane adds its vector's terms in ascending entry order, the first term first.
+template <class T, int VB, int U, bool NT>
+__device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
+                                                 const int2* __restrict__ te, int njobs, int64_t ntiles,
+                                                 int tile_rows, int nv, int cap_terms) {
+  using V = typename NumVec<T, VB>::type;
+  const FlatDiv div(nv);
+  __shared__ int32_t s_ptr[STAGE_ROWS + 1];
+  __shared__ int32_t s_idx[STAGE_ENTRIES];
+  extern __shared__ __align__(16) unsigned char s_dyn[];
+  V* const s_val = reinterpret_cast<V*>(s_dyn);
+  int64_t t0, t1;
+  tile_range(ntiles, &t0, &t1);
+  if (t0 >= t1) return;
+  int j = find_job(ts, njobs, t0);
+  const int bd = blockDim.x, tid = threadIdx.x;
+  const size_t rb = (size_t)nv * VB;
+  for (int64_t t = t0; t < t1; ++t) {
+    while (t >= ts[j + 1]) ++j;
+    const char* __restrict__ in = jobs[j].in;
+    const int32_t split = jobs[j].split;
+    const char* __restrict__ in2 = jobs[j].in2;
+    char* __restrict__ out = jobs[j].out;
+    const int32_t* __restrict__ ptr = jobs[j].ptr;
+    const int32_t* __restrict__ idx = jobs[j].idx;
+    const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
+    const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
+    const int nt = (int)(r1 - r0);
+    const int2 er = te[t];
+    const int32_t P0 = er.x;
+    const int ne = er.y - P0;
+    // sums of rows [r, r + n) straight from memory
+    auto from_memory = [&](int64_t r, int n) {
+      V* dp = reinterpret_cast<V*>(out + r * (int64_t)rb);
+      const int nvec = n * nv;
+      for (int k = tid; k < nvec; k += bd) {
+        const uint32_t q = div.row((uint32_t)k);
+        const uint32_t c = (uint32_t)k - q * (uint32_t)nv;
+        const int32_t p0 = ptr[r + q], p1 = ptr[r + q + 1];
+        V acc = (V)(T)0;
+        for (int32_t e = p0; e < p1; ++e) {
+          const V v = reinterpret_cast<const V*>(term_row(in, in2, split, ldv<int32_t, NT>(idx + e), rb))[c];
+          acc = e == p0 ? v : acc + v;
+        }
+        stv<V, NT>(dp + k, acc);
+      }
+    };
+    if (nt > STAGE_ROWS || ne > STAGE_ENTRIES || cap_terms <= 0) {
+      for (int64_t rc = r0; rc < r1; rc += kFlatRows) from_memory(rc, (int)min((int64_t)kFlatRows, r1 - rc));
+      continue;
+    }
+    const int nl = max(nt + 1, ne);
+    for (int i = tid; i < nl; i += bd) {
+      int32_t pv = 0, iv = 0;
+      if (i <= nt) pv = ptr[r0 + i];
+      if (i < ne) iv = ldv<int32_t, NT>(idx + P0 + i);
+      if (i <= nt) s_ptr[i] = pv;
+      if (i < ne) s_idx[i] = iv;
+    }
+    __syncthreads();
+    int ra = 0;
+    while (ra < nt) {
+      int lo = ra, hi = nt;  // last row boundary whose terms still fit
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (s_ptr[mid] - s_ptr[ra] <= cap_terms) lo = mid; else hi = mid - 1;
+      }
+      if (lo == ra) {  // one row with more terms than fit
+        from_memory(r0 + ra, 1);
+        ++ra;
+        continue;
+      }
+      const int rq = lo;
+      const int ea = s_ptr[ra] - P0, tvec = (s_ptr[rq] - s_ptr[ra]) * nv;
+      for (int base = tid; base < tvec; base += bd * U) {
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const uint32_t k = (uint32_t)min(base + u * bd, tvec - 1);  // valid load, no branch
+          const uint32_t e = div.row(k);
+          v[u] = ldv<V, NT>(reinterpret_cast<const V*>(term_row(in, in2, split, s_idx[ea + e], rb)) +
+                            (k - e * (uint32_t)nv));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (base + u * bd < tvec) s_val[base + u * bd] = v[u];
+      }
+      __syncthreads();
+      V* dp = reinterpret_cast<V*>(out + (r0 + ra) * (int64_t)rb);
+      const int nvec = (rq - ra) * nv;
+      for (int k = tid; k < nvec; k += bd) {
+        const uint32_t q = div.row((uint32_t)k);
+        const uint32_t c = (uint32_t)k - q * (uint32_t)nv;
+        const int a = s_ptr[ra + q] - P0 - ea, len = s_ptr[ra + q + 1] - s_ptr[ra + q];
+        V acc = (V)(T)0;
+        if (len > 0) acc = s_val[a * nv + c];
+        for (int d = 1; d < len; ++d) acc = acc + s_val[(a + d) * nv + c];
+        stv<V, NT>(dp + k, acc);
+      }
+      __syncthreads();  // s_val, s_ptr and s_idx are reused next
+      ra = rq;
+    }
+    __syncthreads();  // (a tile may end with a row summed from memory)
   }
 }
 

@@ -17,7 +17,7 @@ inline int unroll_bucket(int u) {
 
 // Calls F::template go<VB, NV, LPR, U, NT>(t, s, nv) for the table's shape.
 // Fixed shapes (one 16/8/4-byte vector per lane, LPR lanes per row) take
-// U in {1, 2, 4}; other row sizes use the runtime-size loop with U = 1.
+// U in {1, 2, 4}; other row sizes use the flat forms.
 template <class F, int VB, int NV, int LPR>
 void by_unroll(const LaunchTable& t, hipStream_t s, int nv) {
   const bool nt = t.sched.nontemporal != 0;
@@ -37,10 +37,22 @@ void by_unroll(const LaunchTable& t, hipStream_t s, int nv) {
   }
 }
 
-template <class F, int VB, int LPR>
+// Any other number of vectors per row: the flat forms (U vectors per lane in
+// flight); rows of more than kFlatMaxVec vectors (16 KiB and more, several
+// passes of a wavefront per row) take one wavefront per row.
+template <class F, int VB>
 void generic(const LaunchTable& t, hipStream_t s, int nv) {
-  if (t.sched.nontemporal) F::template go<VB, 0, LPR, 1, true>(t, s, nv);
-  else F::template go<VB, 0, LPR, 1, false>(t, s, nv);
+  const bool nt = t.sched.nontemporal != 0;
+  if (nv > kFlatMaxVec) {
+    if (nt) F::template go<VB, 0, 64, 1, true>(t, s, nv);
+    else F::template go<VB, 0, 64, 1, false>(t, s, nv);
+    return;
+  }
+  switch (unroll_bucket(t.sched.unroll)) {
+    case 1: nt ? F::template flat<VB, 1, true>(t, s, nv) : F::template flat<VB, 1, false>(t, s, nv); break;
+    case 2: nt ? F::template flat<VB, 2, true>(t, s, nv) : F::template flat<VB, 2, false>(t, s, nv); break;
+    default: nt ? F::template flat<VB, 4, true>(t, s, nv) : F::template flat<VB, 4, false>(t, s, nv); break;
+  }
 }
 
 template <class F, int VB>
@@ -59,13 +71,10 @@ void by_shape(const LaunchTable& t, hipStream_t s) {
     }
   } else if constexpr (VB == 8) {
     if (nv == 1) return by_unroll<F, 8, 1, 1>(t, s, nv);
-    if (nv == 3) return by_unroll<F, 8, 3, 1>(t, s, nv);
   } else {
     if (nv == 1) return by_unroll<F, 4, 1, 1>(t, s, nv);
   }
-  if (nv >= 64) return generic<F, VB, 64>(t, s, nv);
-  if (nv >= 16) return generic<F, VB, 16>(t, s, nv);
-  return generic<F, VB, 1>(t, s, nv);
+  return generic<F, VB>(t, s, nv);
 }
 
 template <class F>

@@ -21,6 +21,12 @@ namespace {
                  int64_t ntiles, int tile_rows, int nv_rt) {                                         \
     segsum_win_body<T, VB, NV, LPR, U, NT>(jobs, ts, njobs, ntiles, tile_rows, nv_rt);               \
   }                                                                                                  \
+  template <class T, int VB, int U, bool NT>                                                         \
+  __global__ void __launch_bounds__(1024)                                                            \
+      NAME##_flat(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts, int njobs,     \
+                  const int2* __restrict__ te, int64_t ntiles, int tile_rows, int nv, int cap_terms) { \
+    segsum_flat_body<T, VB, U, NT>(jobs, ts, te, njobs, ntiles, tile_rows, nv, cap_terms);           \
+  }                                                                                                  \
   template <class T, int U, int D, bool NT>                                                          \
   __global__ void __launch_bounds__(1024)                                                            \
       NAME##_vec(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts, int njobs,      \
@@ -37,6 +43,17 @@ namespace {
   };                                                                                                 \
   template <class T>                                                                                 \
   struct NAME##_go {                                                                                 \
+    template <int VB, int U, bool NT>                                                                \
+    static void flat(const LaunchTable& t, hipStream_t s, int nv) {                                  \
+      if constexpr ((size_t)VB < sizeof(T)) {                                                        \
+        (void)t; (void)s; (void)nv; /* excluded when the table is built */                           \
+      } else {                                                                                       \
+        hipLaunchKernelGGL((NAME##_flat<T, VB, U, NT>), dim3(t.grid), dim3(t.sched.block_threads),   \
+                           (unsigned)t.val_bytes, s, t.jobs.as<SegSumJob>(),                         \
+                           t.tile_start.as<int64_t>(), t.njobs, t.tile_terms.as<int2>(), t.ntiles,   \
+                           t.sched.tile_rows, nv, t.val_bytes / (nv * VB));                          \
+      }                                                                                              \
+    }                                                                                                \
     template <int VB, int NV, int LPR, int U, bool NT>                                               \
     static void go(const LaunchTable& t, hipStream_t s, int nv) {                                    \
       if constexpr ((size_t)VB < sizeof(T)) {                                                        \
