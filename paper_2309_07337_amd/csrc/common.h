@@ -98,6 +98,10 @@ struct GatherJob {
   unsigned long long* ready = nullptr;
   // set by the table builder: every index of the job lies in its window
   int32_t win_all = 0;
+  // second destination (a message's delivery, simulated): row r also goes to
+  // dst2[idx2[r], :] where the launch asks for it
+  char* dst2 = nullptr;
+  const int32_t* idx2 = nullptr;
 };
 // out[i, :] = in[idx[ptr[i]], :] + in[idx[ptr[i]+1], :] + ... (ascending,
 // first term first; empty -> +0) for i < nrows.  Terms t >= split come from
@@ -114,6 +118,10 @@ struct SegSumJob {
   // be staged in LDS (win_rows = 0: none)
   int64_t win_lo = 0;
   int64_t win_rows = 0;
+  // push pack: the value of entry e also goes to out2[idx2[e], :] where the
+  // launch asks for it (a message's delivery, simulated)
+  char* out2 = nullptr;
+  const int32_t* idx2 = nullptr;
 };
 
 // Gather: pull rows through an index (GatherJob).  Segsum: fixed-order sum
@@ -177,6 +185,7 @@ struct LaunchTable {
   int vec16 = 0;      // gathers of 4- or 8-byte rows in 16-byte groups per lane (alignment allows it);
                       // segmented sums of rows of one value: one row per lane
   int vec_depth = 4;  // one-value segmented sums: terms per row loaded together (4 or 16)
+  int deliver = 0;      // every job names a second destination (launch_table's deliver)
   int partial_win = 0;  // row-group gathers: some job's window misses some of its indices
   Sched sched;
   int njobs = 0;
@@ -205,7 +214,8 @@ inline int64_t segsum_area_max_tiles(size_t area_bytes) {
 }
 int build_scatter_table(const std::vector<SegSumJob>& jobs, int dtype, int row_bytes,
                         const Sched& s, LaunchTable* t, int tag = TAG_PACK);
-int launch_table(const LaunchTable& t, hipStream_t stream);
+// deliver: rows also go to the jobs' second destinations (t.deliver tables).
+int launch_table(const LaunchTable& t, hipStream_t stream, bool deliver = false);
 
 // Split a gather job per message (per neighbor) using the message counts.
 void split_gather_by_counts(const GatherJob& j, const std::vector<int32_t>& counts,

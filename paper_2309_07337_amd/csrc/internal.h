@@ -99,7 +99,7 @@ struct hx_batch {
   hx::LaunchTable lt[4];
   std::vector<hx::LaunchTable> plain[4];
   bool plain_built[4] = {false, false, false, false};
-  hx::LaunchTable lt_xfer[4];               // simulated transfers: stage 1, stage 2, reverse of stage 1, of stage 2
+  hx::LaunchTable lt_back[2];               // the backward's simulated transfers: reverse of stage 1, of stage 2
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t graph[3] = {nullptr, nullptr, nullptr};
   bool has_graph[3] = {false, false, false};
@@ -119,10 +119,12 @@ struct hx_batch {
   int64_t E1_tot = 0, E2_tot = 0, R1_tot = 0, R2_tot = 0, H_tot = 0;
   bool unpack_identity = true;
   hx::DevMem send_all, recv_all;             // [S1 | S2], [RECV1 | RECV2] of all ranks
-  hx::DevMem gidx_pack, gidx_redist, gidx_unpack, gidx_x1, gidx_x2, gidx_back;
+  hx::DevMem gidx_pack, gidx_redist, gidx_unpack;
+  hx::DevMem gidx_to1, gidx_to2;             // stage-1 / stage-2 send slot -> the row of recv_all it is delivered to
   hx::DevMem g_send_all;                     // plain worlds: gradients of every rank's send slots
   hx::DevMem wb_ptr, wb_idx;                 // adjoint CSR: global column -> halo_all rows
   hx::DevMem wp_ptr, wp_idx;                 // transpose of the pack map: global row -> send_all rows
+  mutable hx::DevMem wp_to;                  // gidx_to1 of wp_idx's entries (made when a push pack first needs it)
   // staged backward of a locality world (forwarder sums, owner sums)
   bool staged_bwd = false;
   hx::DevMem gidx_back2;                     // stage-2 send slot -> halo row whose gradient it carries back
@@ -151,6 +153,8 @@ int batch_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
 int batch_build_table(const hx_batch* b, int phase, const Sched& sc, LaunchTable* t);
 int batch_build_plain(hx_batch* b, int phase);
 int batch_prepare(hx_batch* b);
+// Start and Wait also deliver each message into its receiver's arena.
+inline bool sim_transfer(const hx_batch* b) { return b->world && (b->flags & HX_WORLD_SIM_TRANSFER); }
 int batch_run_start(hx_batch* b, hipStream_t s);
 int batch_run_wait(hx_batch* b, hipStream_t s);
 int batch_run_backward(hx_batch* b, hipStream_t s);

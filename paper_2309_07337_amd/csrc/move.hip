@@ -198,7 +198,7 @@ uintptr_t align_of(const std::vector<SegSumJob>& jobs, int row_bytes) {
   uintptr_t a = (uintptr_t)row_bytes;
   for (const auto& j : jobs) {
     if (j.nrows <= 0) continue;
-    a |= (uintptr_t)j.in | (uintptr_t)j.out;
+    a |= (uintptr_t)j.in | (uintptr_t)j.out | (uintptr_t)j.out2;
     if (j.in2) a |= (uintptr_t)j.in2;
   }
   return a;
@@ -212,7 +212,7 @@ int build_gather_table(const std::vector<GatherJob>& jobs, int dtype, int row_by
   uintptr_t a = (uintptr_t)row_bytes;
   for (const auto& j : jobs) {
     if (j.nrows <= 0) continue;
-    a |= (uintptr_t)j.src | (uintptr_t)j.dst;
+    a |= (uintptr_t)j.src | (uintptr_t)j.dst | (uintptr_t)j.dst2;
   }
   // short rows in 16-byte groups per lane: rows of 4 or 8 bytes whose
   // buffers are aligned to the row size, and every index list congruent
@@ -223,8 +223,9 @@ int build_gather_table(const std::vector<GatherJob>& jobs, int dtype, int row_by
     const uintptr_t V = 16 / (uintptr_t)row_bytes;
     for (const auto& j : jobs) {
       if (j.nrows <= 0 || j.idx == nullptr) continue;
-      if (((uintptr_t)j.idx % 4) != 0 || ((uintptr_t)j.idx / 4) % V != ((uintptr_t)j.dst / row_bytes) % V)
-        vec = false;
+      for (const int32_t* ix : {j.idx, j.idx2})
+        if (ix && (((uintptr_t)ix % 4) != 0 || ((uintptr_t)ix / 4) % V != ((uintptr_t)j.dst / row_bytes) % V))
+          vec = false;
     }
   }
   // source windows: kept where the schedule asks for them and they fit (the
@@ -253,6 +254,9 @@ int build_gather_table(const std::vector<GatherJob>& jobs, int dtype, int row_by
   t->win_bytes = t->ntiles > 0 ? (int)((win_bytes + 15) / 16 * 16) : 0;
   t->vec16 = t->ntiles > 0 && vec ? 1 : 0;
   t->partial_win = 0;
+  t->deliver = 1;
+  for (const auto& j : w)
+    if (j.nrows > 0 && (j.dst2 == nullptr || j.idx == nullptr)) t->deliver = 0;
   for (const auto& j : w)
     if (j.nrows > 0 && j.win_rows > 0 && !j.win_all) t->partial_win = 1;
   return HX_SUCCESS;
@@ -389,13 +393,17 @@ int build_scatter_table(const std::vector<SegSumJob>& jobs, int dtype, int row_b
   Sched sc = s;
   sc.block_threads = std::min(sc.block_threads, 512);  // the push pack runs at most 512 lanes
   HX_TRY(build_table(jobs, KIND_SCATTER, dtype, row_bytes, sc, t, align_of(jobs, row_bytes)));
+  t->deliver = 1;
+  for (const auto& j : jobs)
+    if (j.nrows > 0 && j.out2 == nullptr) t->deliver = 0;
   return fill_tile_terms(t);
 }
 
-int launch_table(const LaunchTable& t, hipStream_t s) {
+int launch_table(const LaunchTable& t, hipStream_t s, bool deliver) {
   if (t.ntiles == 0) return HX_SUCCESS;
-  if (t.kind == KIND_GATHER) launch_gather_kernels(t, s);
-  else if (t.kind == KIND_SCATTER) launch_scatter_kernels(t, s);
+  if (deliver && !t.deliver) return fail(HX_ERR_STATE, "a launch table without second destinations");
+  if (t.kind == KIND_GATHER) launch_gather_kernels(t, s, deliver);
+  else if (t.kind == KIND_SCATTER) launch_scatter_kernels(t, s, deliver);
   else launch_segsum_kernels(t, s);
   HX_HIP(hipGetLastError());
   return HX_SUCCESS;
@@ -409,6 +417,7 @@ void split_gather_by_counts(const GatherJob& j, const std::vector<int32_t>& coun
       GatherJob g = j;
       g.dst = j.dst + off * (int64_t)row_bytes;
       g.idx = j.idx ? j.idx + off : nullptr;
+      g.idx2 = j.idx2 ? j.idx2 + off : nullptr;
       g.src = j.idx ? j.src : j.src + off * (int64_t)row_bytes;
       g.nrows = c;
       out->push_back(g);
@@ -419,6 +428,7 @@ void split_gather_by_counts(const GatherJob& j, const std::vector<int32_t>& coun
     GatherJob g = j;
     g.dst = j.dst + off * (int64_t)row_bytes;
     g.idx = j.idx ? j.idx + off : nullptr;
+    g.idx2 = j.idx2 ? j.idx2 + off : nullptr;
     g.src = j.idx ? j.src : j.src + off * (int64_t)row_bytes;
     g.nrows = j.nrows - off;
     out->push_back(g);

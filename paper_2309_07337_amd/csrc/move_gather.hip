@@ -1,5 +1,5 @@
 // Pull-form row gathers: pack (Start), redistribution pack and unpack (Wait),
-// and the simulated transfer; short rows also in 16-byte groups per lane
+// and the backward's simulated transfers; short rows also in 16-byte groups per lane
 // (the *_vec symbols).  One kernel symbol per phase (same body), so
 // profiles attribute time to each phase separately.
 #include "move_launch.h"
@@ -9,48 +9,50 @@ namespace kern {
 namespace {
 
 #define HX_GATHER_KERNEL(NAME)                                                                 \
-  template <int VB, int NV, int LPR, int U, bool NT>                                           \
+  template <int VB, int NV, int LPR, int U, bool NT, bool X>                                   \
   __global__ void __launch_bounds__(1024)                                                      \
       NAME(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts, int njobs,      \
            int64_t ntiles, int tile_rows, int nv_rt, int use_win) {                            \
-    gather_body<VB, NV, LPR, U, NT>(jobs, ts, njobs, ntiles, tile_rows, nv_rt, use_win);       \
+    gather_body<VB, NV, LPR, U, NT, X>(jobs, ts, njobs, ntiles, tile_rows, nv_rt, use_win);    \
   }                                                                                            \
-  template <int VB, int U, bool NT>                                                            \
+  template <int VB, int U, bool NT, bool X>                                                    \
   __global__ void __launch_bounds__(1024)                                                      \
       NAME##_flat(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts, int njobs, \
                   int64_t ntiles, int tile_rows, int nv) {                                     \
-    gather_flat_body<VB, U, NT>(jobs, ts, njobs, ntiles, tile_rows, nv);                       \
+    gather_flat_body<VB, U, NT, X>(jobs, ts, njobs, ntiles, tile_rows, nv);                    \
   }                                                                                            \
-  template <int RB, int U, bool NT, bool GAS>                                                  \
+  template <int RB, int U, bool NT, bool GAS, bool X>                                          \
   __global__ void __launch_bounds__(1024)                                                      \
       NAME##_vec(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts, int njobs, \
                  int64_t ntiles, int tile_rows, int stream_win) {                              \
-    gather_vec_body<RB, U, NT, GAS>(jobs, ts, njobs, ntiles, tile_rows, stream_win);           \
+    gather_vec_body<RB, U, NT, GAS, X>(jobs, ts, njobs, ntiles, tile_rows, stream_win);        \
   }                                                                                            \
+  template <bool X>                                                                            \
   struct NAME##_vgo {                                                                          \
     template <int RB, int U, bool NT>                                                          \
     static void go(const LaunchTable& t, hipStream_t s) {                                      \
       const int sw = t.sched.nontemporal >= 2 ? 1 : 0; /* streaming window staging */          \
       if (t.partial_win)                                                                       \
-        hipLaunchKernelGGL((NAME##_vec<RB, U, NT, false>), dim3(t.grid), dim3(t.sched.block_threads), \
+        hipLaunchKernelGGL((NAME##_vec<RB, U, NT, false, X>), dim3(t.grid), dim3(t.sched.block_threads), \
                            (unsigned)t.win_bytes, s, t.jobs.as<GatherJob>(),                   \
                            t.tile_start.as<int64_t>(), t.njobs, t.ntiles, t.sched.tile_rows, sw); \
       else                                                                                     \
-        hipLaunchKernelGGL((NAME##_vec<RB, U, NT, true>), dim3(t.grid), dim3(t.sched.block_threads), \
+        hipLaunchKernelGGL((NAME##_vec<RB, U, NT, true, X>), dim3(t.grid), dim3(t.sched.block_threads), \
                            (unsigned)t.win_bytes, s, t.jobs.as<GatherJob>(),                   \
                            t.tile_start.as<int64_t>(), t.njobs, t.ntiles, t.sched.tile_rows, sw); \
     }                                                                                          \
   };                                                                                           \
+  template <bool X>                                                                            \
   struct NAME##_go {                                                                           \
     template <int VB, int U, bool NT>                                                          \
     static void flat(const LaunchTable& t, hipStream_t s, int nv) {                            \
-      hipLaunchKernelGGL((NAME##_flat<VB, U, NT>), dim3(t.grid), dim3(t.sched.block_threads),  \
+      hipLaunchKernelGGL((NAME##_flat<VB, U, NT, X>), dim3(t.grid), dim3(t.sched.block_threads), \
                          0, s, t.jobs.as<GatherJob>(), t.tile_start.as<int64_t>(), t.njobs,    \
                          t.ntiles, t.sched.tile_rows, nv);                                     \
     }                                                                                          \
     template <int VB, int NV, int LPR, int U, bool NT>                                         \
     static void go(const LaunchTable& t, hipStream_t s, int nv) {                              \
-      hipLaunchKernelGGL((NAME<VB, NV, LPR, U, NT>), dim3(t.grid), dim3(t.sched.block_threads), \
+      hipLaunchKernelGGL((NAME<VB, NV, LPR, U, NT, X>), dim3(t.grid), dim3(t.sched.block_threads), \
                          (unsigned)t.win_bytes, s, t.jobs.as<GatherJob>(),                     \
                          t.tile_start.as<int64_t>(), t.njobs, t.ntiles, t.sched.tile_rows, nv, \
                          t.win_bytes > 0 ? 1 : 0);                                             \
@@ -66,7 +68,7 @@ HX_GATHER_KERNEL(k_transfer)
 struct transfer_fixed {
   template <int VB, int NV, int LPR, int U, bool NT>
   static void go(const LaunchTable& t, hipStream_t s, int nv) {
-    k_transfer_go::go<VB, NV, LPR, (NV > 0 ? 4 : 1), false>(t, s, nv);
+    k_transfer_go<false>::go<VB, NV, LPR, (NV > 0 ? 4 : 1), false>(t, s, nv);
   }
 };
 
@@ -82,7 +84,7 @@ void transfer_shape(const LaunchTable& t, hipStream_t s) {
   } else {
     if (nv == 1) return transfer_fixed::go<4, 1, 1, 4, false>(t, s, nv);
   }
-  if (nv <= kFlatMaxVec) return k_transfer_go::flat<VB, 4, false>(t, s, nv);
+  if (nv <= kFlatMaxVec) return k_transfer_go<false>::flat<VB, 4, false>(t, s, nv);
   return transfer_fixed::go<VB, 0, 64, 1, false>(t, s, nv);
 }
 
@@ -107,20 +109,26 @@ void vec_launch(const LaunchTable& t, hipStream_t s) {
 }  // namespace
 }  // namespace kern
 
-void launch_gather_kernels(const LaunchTable& t, hipStream_t s) {
+void launch_gather_kernels(const LaunchTable& t, hipStream_t s, bool deliver) {
   using namespace kern;
+  if (deliver) {  // the pack and the redistribution only
+    const bool pack = t.tag == TAG_PACK;
+    if (t.vec16) pack ? vec_launch<k_pack_vgo<true>>(t, s) : vec_launch<k_redist_vgo<true>>(t, s);
+    else pack ? by_vec<k_pack_go<true>>(t, s) : by_vec<k_redist_go<true>>(t, s);
+    return;
+  }
   if (t.vec16) {
     switch (t.tag) {
-      case TAG_PACK: vec_launch<k_pack_vgo>(t, s); return;
-      case TAG_REDIST: vec_launch<k_redist_vgo>(t, s); return;
-      case TAG_UNPACK: vec_launch<k_unpack_vgo>(t, s); return;
+      case TAG_PACK: vec_launch<k_pack_vgo<false>>(t, s); return;
+      case TAG_REDIST: vec_launch<k_redist_vgo<false>>(t, s); return;
+      case TAG_UNPACK: vec_launch<k_unpack_vgo<false>>(t, s); return;
       default: break;  // the simulated transfer keeps its fixed variants
     }
   }
   switch (t.tag) {
-    case TAG_PACK: by_vec<k_pack_go>(t, s); break;
-    case TAG_REDIST: by_vec<k_redist_go>(t, s); break;
-    case TAG_UNPACK: by_vec<k_unpack_go>(t, s); break;
+    case TAG_PACK: by_vec<k_pack_go<false>>(t, s); break;
+    case TAG_REDIST: by_vec<k_redist_go<false>>(t, s); break;
+    case TAG_UNPACK: by_vec<k_unpack_go<false>>(t, s); break;
     default:
       if (t.vec_bytes == 16) transfer_shape<16>(t, s);
       else if (t.vec_bytes == 8) transfer_shape<8>(t, s);

@@ -110,7 +110,12 @@ __device__ __forceinline__ int find_job(const int64_t* __restrict__ ts, int njob
 // a new such job and then gathers rows inside it from LDS, the others from
 // global memory: one wide read of the window instead of one L2 request per
 // (usually short, scattered) row.
-template <int VB, int NV, int LPR, int U, bool NT>
+// X (delivery): every row also goes to row idx2[r] of the job's second
+// destination, so that a message is sent and received in one pass over its
+// rows.  A transfer of its own reads the rows and one index per row back from
+// memory: 8-byte rows cost 20 bytes a row there, 12 here (figures at
+// gather_vec_body).  Jobs without an index list have none.
+template <int VB, int NV, int LPR, int U, bool NT, bool X>
 __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                             int njobs, int64_t ntiles, int tile_rows, int nv_rt, int use_win) {
   using V = typename RawVec<VB>::type;
@@ -131,6 +136,8 @@ __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, 
     const HX_G char* __restrict__ src = (const HX_G char*)jobs[j].src;
     HX_G char* __restrict__ dst = (HX_G char*)jobs[j].dst;
     const HX_G int32_t* __restrict__ idx = (const HX_G int32_t*)jobs[j].idx;
+    HX_G char* __restrict__ dst2 = X ? (HX_G char*)jobs[j].dst2 : nullptr;
+    const HX_G int32_t* __restrict__ idx2 = X ? (const HX_G int32_t*)jobs[j].idx2 : nullptr;
     const int64_t nrows = jobs[j].nrows;
     const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, nrows);
@@ -196,10 +203,12 @@ __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, 
       for (int64_t base = r0 + rsub; base < r1; base += (int64_t)rows_per_pass * U) {
         V v[U][NVPL];
         int64_t srow[U];
+        int32_t drow[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int64_t r = min(base + (int64_t)u * rows_per_pass, r1 - 1);
           srow[u] = idx ? (int64_t)ldv<int32_t, NT>(idx + r) : r;
+          if constexpr (X) drow[u] = ldv<int32_t, NT>(idx2 + r);
         }
         if (in_lds) {
           // rows inside the window from LDS, the others from global memory
@@ -238,6 +247,14 @@ __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, 
               const int vi = lane_v + k * LPR;
               if (NV % LPR == 0 || vi < NV) stv<V, NT>(dp + vi, v[u][k]);
             }
+            if constexpr (X) {
+              HX_G V* dp2 = reinterpret_cast<HX_G V*>(dst2 + drow[u] * (int64_t)rb);
+#pragma unroll
+              for (int k = 0; k < NVPL; ++k) {
+                const int vi = lane_v + k * LPR;
+                if (NV % LPR == 0 || vi < NV) stv<V, NT>(dp2 + vi, v[u][k]);
+              }
+            }
           }
         }
       }
@@ -246,7 +263,16 @@ __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, 
         const int64_t s = idx ? (int64_t)ldv<int32_t, NT>(idx + r) : r;
         const HX_G V* sp = reinterpret_cast<const HX_G V*>(src + s * rb);
         HX_G V* dp = reinterpret_cast<HX_G V*>(dst + r * rb);
-        for (int vi = lane_v; vi < nv; vi += LPR) stv<V, NT>(dp + vi, sp[vi]);
+        if constexpr (X) {
+          HX_G V* dp2 = reinterpret_cast<HX_G V*>(dst2 + ldv<int32_t, NT>(idx2 + r) * (int64_t)rb);
+          for (int vi = lane_v; vi < nv; vi += LPR) {
+            const V v = sp[vi];
+            stv<V, NT>(dp + vi, v);
+            stv<V, NT>(dp2 + vi, v);
+          }
+        } else {
+          for (int vi = lane_v; vi < nv; vi += LPR) stv<V, NT>(dp + vi, sp[vi]);
+        }
       }
     }
     signal_tile(jobs[j].ready, r1 - r0);
@@ -315,7 +341,7 @@ __device__ __forceinline__ void flat_copy(const HX_G char* __restrict__ sp, HX_G
   }
 }
 
-template <int VB, int U, bool NT>
+template <int VB, int U, bool NT, bool X>
 __device__ __forceinline__ void gather_flat_body(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                                  int njobs, int64_t ntiles, int tile_rows, int nv) {
   using V = typename RawVec<VB>::type;
@@ -331,6 +357,8 @@ __device__ __forceinline__ void gather_flat_body(const GatherJob* __restrict__ j
     const HX_G char* __restrict__ src = (const HX_G char*)jobs[j].src;
     HX_G char* __restrict__ dst = (HX_G char*)jobs[j].dst;
     const HX_G int32_t* __restrict__ idx = (const HX_G int32_t*)jobs[j].idx;
+    HX_G char* __restrict__ dst2 = X ? (HX_G char*)jobs[j].dst2 : nullptr;
+    const HX_G int32_t* __restrict__ idx2 = X ? (const HX_G int32_t*)jobs[j].idx2 : nullptr;
     const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
     if (idx == nullptr) {
@@ -344,28 +372,36 @@ __device__ __forceinline__ void gather_flat_body(const GatherJob* __restrict__ j
       HX_G V* __restrict__ dp = reinterpret_cast<HX_G V*>(dst + rc * rb);
       // source rows of a lane's U vectors of the pass at base (lanes past the
       // end reload the last vector: valid loads; only stores are predicated)
-      auto load_idx = [&](int base, int32_t (&s)[U], uint32_t (&c)[U]) {
+      auto load_idx = [&](int base, int32_t (&s)[U], int32_t (&d)[U], uint32_t (&c)[U]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const uint32_t k = (uint32_t)min(base + tid + u * bd, nvec - 1);
           const uint32_t r = div.row(k);
           c[u] = k - r * (uint32_t)nv;
           s[u] = ldv<int32_t, NT>(ix + r);
+          if constexpr (X) d[u] = ldv<int32_t, NT>(idx2 + rc + r);
         }
       };
-      int32_t s[U];
+      int32_t s[U], d[U];
       uint32_t c[U];
-      load_idx(0, s, c);
+      load_idx(0, s, d, c);
       for (int base = 0; base < nvec; base += bd * U) {
         V v[U];
+        HX_G V* dp2[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = reinterpret_cast<const HX_G V*>(src + (int64_t)s[u] * rb)[c[u]];
+        for (int u = 0; u < U; ++u) {
+          v[u] = reinterpret_cast<const HX_G V*>(src + (int64_t)s[u] * rb)[c[u]];
+          if constexpr (X) dp2[u] = reinterpret_cast<HX_G V*>(dst2 + (int64_t)d[u] * rb) + c[u];
+        }
         // the next pass's indices are in flight while this pass's rows arrive
-        if (base + bd * U < nvec) load_idx(base + bd * U, s, c);
+        if (base + bd * U < nvec) load_idx(base + bd * U, s, d, c);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int k = base + tid + u * bd;
-          if (k < nvec) stv<V, NT>(dp + k, v[u]);
+          if (k < nvec) {
+            stv<V, NT>(dp + k, v[u]);
+            if constexpr (X) stv<V, NT>(dp2[u], v[u]);
+          }
         }
       }
     }
@@ -411,7 +447,29 @@ __device__ __forceinline__ auto gas_ptr(T* p) {
 // address space (FLAT), so that a row inside or outside the window is one
 // load of either address: measured faster on gfx950, for tables whose
 // windows miss some indices, than an LDS read plus a sparse global load.
-template <int RB, int U, bool NT, bool GAS>
+// X: every row also goes to its slot of the second destination.  Messages are
+// runs of consecutive slots, so a group most often is one 16-byte store there
+// too (to an address aligned to the row only).  Bound by memory: 4096 ranks of
+// the 2^22-row random matrix, FP64, pack 109 + transfer 157 us -> 200 us in one
+// (4.4 TB/s), redistribution 157 + transfer 174 -> 269 us (4.5 TB/s).
+template <int RB>
+__device__ __forceinline__ void deliver_group(HX_G char* __restrict__ dst2, const typename IdxVec<RB>::type d,
+                                              const typename RawVec<RB>::type (&v)[16 / RB]) {
+  using R = typename RawVec<RB>::type;
+  constexpr int V = 16 / RB;
+  typedef unsigned int u32x4u __attribute__((ext_vector_type(4), aligned(4)));
+  bool run = true;
+#pragma unroll
+  for (int k = 1; k < V; ++k) run = run && d[k] == d[0] + k;
+  if (run) {
+    *reinterpret_cast<HX_G u32x4u*>(dst2 + (int64_t)d[0] * RB) = pack16<RB>(v);
+  } else {
+#pragma unroll
+    for (int k = 0; k < V; ++k) *reinterpret_cast<HX_G R*>(dst2 + (int64_t)d[k] * RB) = v[k];
+  }
+}
+
+template <int RB, int U, bool NT, bool GAS, bool X>
 __device__ __forceinline__ void gather_vec_body(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                                 int njobs, int64_t ntiles, int tile_rows, int stream_win) {
   constexpr int V = 16 / RB;
@@ -434,6 +492,8 @@ __device__ __forceinline__ void gather_vec_body(const GatherJob* __restrict__ jo
     const auto src = gas_ptr<GAS>(jobs[j].src);
     const auto dst = gas_ptr<GAS>(jobs[j].dst);
     const auto idx = gas_ptr<GAS>(jobs[j].idx);
+    HX_G char* __restrict__ dst2 = X ? (HX_G char*)jobs[j].dst2 : nullptr;
+    const HX_G int32_t* __restrict__ idx2 = X ? (const HX_G int32_t*)jobs[j].idx2 : nullptr;
     const int64_t nrows = jobs[j].nrows;
     const int32_t win_lo = (int32_t)jobs[j].win_lo;
     const uint32_t win_rows = (uint32_t)jobs[j].win_rows;
@@ -449,8 +509,9 @@ __device__ __forceinline__ void gather_vec_body(const GatherJob* __restrict__ jo
     // this lane's row outside the groups (if any): its index is loaded first
     const bool has_edge = tid < ne;
     const int64_t er = tid < nh ? r0 + tid : tail0 + (tid - nh);
-    int32_t esr = 0;
+    int32_t esr = 0, edr = 0;
     if (has_edge) esr = idx ? idx[er] : (int32_t)er;
+    if (X && has_edge) edr = idx2[er];
     // a row's value: from the staged window when it lies there, else global memory
     auto read_row = [&](int32_t sr) -> R {
       const uint32_t w = (uint32_t)(sr - win_lo);
@@ -518,13 +579,23 @@ __device__ __forceinline__ void gather_vec_body(const GatherJob* __restrict__ jo
       }
       __syncthreads();  // the window is visible to every lane
     }
-    if (ng == 0 && has_edge) stv<R, NT>(reinterpret_cast<RP>(dst + er * RB), read_row(esr));
+    auto store_edge = [&](R ev) {
+      stv<R, NT>(reinterpret_cast<RP>(dst + er * RB), ev);
+      if constexpr (X) *reinterpret_cast<HX_G R*>(dst2 + (int64_t)edr * RB) = ev;
+    };
+    if (ng == 0 && has_edge) store_edge(read_row(esr));
     // passes of U groups per lane (a tile is usually one pass); the next
     // pass's indices are loaded while this pass's rows are read and stored,
     // and the lane's row outside the groups goes with the first pass
     for (int64_t g0 = 0; g0 < ng; g0 += (int64_t)bd * U) {
       R v[U][V];
       R ev;
+      IV dv[U];
+      if constexpr (X) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          dv[u] = ldv<IV, NT>(reinterpret_cast<const HX_G IV*>(idx2 + a) + min(g0 + tid + (int64_t)u * bd, ng - 1));
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -535,9 +606,12 @@ __device__ __forceinline__ void gather_vec_body(const GatherJob* __restrict__ jo
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t g = g0 + tid + (int64_t)u * bd;
-        if (g < ng) stv<u32x4, NT>(reinterpret_cast<VP>(dst + a * RB) + g, pack16<RB>(v[u]));
+        if (g < ng) {
+          stv<u32x4, NT>(reinterpret_cast<VP>(dst + a * RB) + g, pack16<RB>(v[u]));
+          if constexpr (X) deliver_group<RB>(dst2, dv[u], v[u]);
+        }
       }
-      if (g0 == 0 && has_edge) stv<R, NT>(reinterpret_cast<RP>(dst + er * RB), ev);
+      if (g0 == 0 && has_edge) store_edge(ev);
     }
     signal_tile(jobs[j].ready, r1 - r0);
   }
@@ -555,7 +629,7 @@ __device__ __forceinline__ void gather_vec_body(const GatherJob* __restrict__ jo
 constexpr int STAGE_ROWS = kStageRows;
 constexpr int STAGE_ENTRIES = kStageEntries;
 
-template <int VB, int NV, int LPR, int U, bool NT>
+template <int VB, int NV, int LPR, int U, bool NT, bool X>
 __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                              const int2* __restrict__ te, int njobs, int64_t ntiles,
                                              int tile_rows, int nv_rt) {
@@ -567,6 +641,7 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
   const int rows_per_pass = blockDim.x / LPR;
   __shared__ int32_t s_ptr[STAGE_ROWS + 1];
   __shared__ int32_t s_idx[STAGE_ENTRIES];
+  __shared__ int32_t s_idx2[X ? STAGE_ENTRIES : 1];
   __shared__ int16_t s_row[STAGE_ENTRIES];
   const bool stage_ptr = NV > 0 && tile_rows <= STAGE_ROWS;
   int64_t t0, t1;
@@ -579,6 +654,8 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
     HX_G char* __restrict__ out = (HX_G char*)jobs[j].out;
     const HX_G int32_t* __restrict__ ptr = (const HX_G int32_t*)jobs[j].ptr;
     const HX_G int32_t* __restrict__ idx = (const HX_G int32_t*)jobs[j].idx;
+    HX_G char* __restrict__ out2 = X ? (HX_G char*)jobs[j].out2 : nullptr;
+    const HX_G int32_t* __restrict__ idx2 = X ? (const HX_G int32_t*)jobs[j].idx2 : nullptr;
     const int64_t nrows = jobs[j].nrows;
     const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, nrows);
@@ -596,11 +673,13 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
         stage_idx = ne <= STAGE_ENTRIES;
         const int nl = max(nt + 1, stage_idx ? ne : 0);
         for (int i = threadIdx.x; i < nl; i += blockDim.x) {
-          int32_t pv = 0, iv = 0;
+          int32_t pv = 0, iv = 0, dv = 0;
           if (i <= nt) pv = ptr[r0 + i];
           if (stage_idx && i < ne) iv = ldv<int32_t, NT>(idx + P0 + i);
+          if (X && stage_idx && i < ne) dv = ldv<int32_t, NT>(idx2 + P0 + i);
           if (i <= nt) s_ptr[i] = pv;
           if (stage_idx && i < ne) s_idx[i] = iv;
+          if (X && stage_idx && i < ne) s_idx2[i] = dv;
         }
         __syncthreads();
         if (stage_idx) {
@@ -618,11 +697,12 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
           // lanes past the last entry re-read it (valid loads, no branch
           // between a lane's U loads); only the stores are predicated
           V v[U][NVPL];
-          int32_t dsl[U];
+          int32_t dsl[U], dsl2[U];
 #pragma unroll
           for (int u = 0; u < U; ++u) {
             const int e = min(base + u * rows_per_pass, ne - 1);
             dsl[u] = s_idx[e];
+            if constexpr (X) dsl2[u] = s_idx2[e];
             // (streaming loads under NT: the row's entries sit together, so
             // its reads coalesce in one pass rather than hit the cache later)
             const HX_G V* sp = reinterpret_cast<const HX_G V*>(in + (r0 + s_row[e]) * (int64_t)rb);
@@ -640,6 +720,14 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
               for (int k = 0; k < NVPL; ++k) {
                 const int vi = lane_v + k * LPR;
                 if (NV % LPR == 0 || vi < NV) stv<V, NT>(dp + vi, v[u][k]);
+              }
+              if constexpr (X) {
+                HX_G V* dp2 = reinterpret_cast<HX_G V*>(out2 + (int64_t)dsl2[u] * rb);
+#pragma unroll
+                for (int k = 0; k < NVPL; ++k) {
+                  const int vi = lane_v + k * LPR;
+                  if (NV % LPR == 0 || vi < NV) stv<V, NT>(dp2 + vi, v[u][k]);
+                }
               }
             }
           }
@@ -689,6 +777,14 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
                 const int vi = lane_v + k * LPR;
                 if (NV % LPR == 0 || vi < NV) stv<V, NT>(dp + vi, v[u][k]);
               }
+              if constexpr (X) {
+                HX_G V* dp2 = reinterpret_cast<HX_G V*>(out2 + (int64_t)ldv<int32_t, NT>(idx2 + a[u] + d) * rb);
+#pragma unroll
+                for (int k = 0; k < NVPL; ++k) {
+                  const int vi = lane_v + k * LPR;
+                  if (NV % LPR == 0 || vi < NV) stv<V, NT>(dp2 + vi, v[u][k]);
+                }
+              }
             }
           }
         }
@@ -701,8 +797,10 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
         for (int vi = lane_v; vi < nv; vi += LPR) {
           if (p0 >= p1) break;
           const V v = sp[vi];
-          for (int32_t e = p0; e < p1; ++e)
+          for (int32_t e = p0; e < p1; ++e) {
             stv<V, NT>(reinterpret_cast<HX_G V*>(out + (int64_t)idx[e] * rb) + vi, v);
+            if constexpr (X) stv<V, NT>(reinterpret_cast<HX_G V*>(out2 + (int64_t)idx2[e] * rb) + vi, v);
+          }
         }
       }
     }
@@ -713,7 +811,7 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
 // entries are one stream of entries * nv vectors over the lanes (see the flat
 // gather); tiles that are not staged take the stream of their rows' vectors,
 // each lane writing its vector to every slot of its row.
-template <int VB, int U, bool NT>
+template <int VB, int U, bool NT, bool X>
 __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                                   const int2* __restrict__ te, int njobs, int64_t ntiles,
                                                   int tile_rows, int nv) {
@@ -721,6 +819,7 @@ __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ 
   const FlatDiv div(nv);
   __shared__ int32_t s_ptr[STAGE_ROWS + 1];
   __shared__ int32_t s_idx[STAGE_ENTRIES];
+  __shared__ int32_t s_idx2[X ? STAGE_ENTRIES : 1];
   __shared__ int16_t s_row[STAGE_ENTRIES];
   int64_t t0, t1;
   tile_range(ntiles, &t0, &t1);
@@ -734,6 +833,8 @@ __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ 
     HX_G char* __restrict__ out = (HX_G char*)jobs[j].out;
     const HX_G int32_t* __restrict__ ptr = (const HX_G int32_t*)jobs[j].ptr;
     const HX_G int32_t* __restrict__ idx = (const HX_G int32_t*)jobs[j].idx;
+    HX_G char* __restrict__ out2 = X ? (HX_G char*)jobs[j].out2 : nullptr;
+    const HX_G int32_t* __restrict__ idx2 = X ? (const HX_G int32_t*)jobs[j].idx2 : nullptr;
     const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
     const int nt = (int)(r1 - r0);
@@ -743,11 +844,13 @@ __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ 
     if (nt <= STAGE_ROWS && ne <= STAGE_ENTRIES) {
       const int nl = max(nt + 1, ne);
       for (int i = tid; i < nl; i += bd) {
-        int32_t pv = 0, iv = 0;
+        int32_t pv = 0, iv = 0, dv = 0;
         if (i <= nt) pv = ptr[r0 + i];
         if (i < ne) iv = ldv<int32_t, NT>(idx + P0 + i);
+        if (X && i < ne) dv = ldv<int32_t, NT>(idx2 + P0 + i);
         if (i <= nt) s_ptr[i] = pv;
         if (i < ne) s_idx[i] = iv;
+        if (X && i < ne) s_idx2[i] = dv;
       }
       __syncthreads();
       for (int i = tid; i < nt; i += bd)
@@ -756,7 +859,7 @@ __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ 
       const int nvec = ne * nv;
       for (int base = tid; base < nvec; base += bd * U) {
         V v[U];
-        int32_t d[U];
+        int32_t d[U], d2[U];
         uint32_t c[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -764,11 +867,15 @@ __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ 
           const uint32_t e = div.row(k);
           c[u] = k - e * (uint32_t)nv;
           d[u] = s_idx[e];
+          if constexpr (X) d2[u] = s_idx2[e];
           v[u] = ldv<V, NT>(reinterpret_cast<const HX_G V*>(in + (r0 + s_row[e]) * rb) + c[u]);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
-          if (base + u * bd < nvec) stv<V, NT>(reinterpret_cast<HX_G V*>(out + (int64_t)d[u] * rb) + c[u], v[u]);
+          if (base + u * bd < nvec) {
+            stv<V, NT>(reinterpret_cast<HX_G V*>(out + (int64_t)d[u] * rb) + c[u], v[u]);
+            if constexpr (X) stv<V, NT>(reinterpret_cast<HX_G V*>(out2 + (int64_t)d2[u] * rb) + c[u], v[u]);
+          }
       }
       __syncthreads();  // the next tile overwrites the staged indices
       continue;
@@ -781,8 +888,11 @@ __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ 
         const int32_t p0 = ptr[rc + r], p1 = ptr[rc + r + 1];
         if (p0 >= p1) continue;
         const V v = reinterpret_cast<const HX_G V*>(in + (rc + r) * rb)[c];
-        for (int32_t e = p0; e < p1; ++e)
+        for (int32_t e = p0; e < p1; ++e) {
           stv<V, NT>(reinterpret_cast<HX_G V*>(out + (int64_t)ldv<int32_t, NT>(idx + e) * rb) + c, v);
+          if constexpr (X)
+            stv<V, NT>(reinterpret_cast<HX_G V*>(out2 + (int64_t)ldv<int32_t, NT>(idx2 + e) * rb) + c, v);
+        }
       }
     }
   }
@@ -1391,8 +1501,8 @@ __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jo
 }  // namespace kern
 
 // Launchers implemented in the move_*.hip translation units.
-void launch_gather_kernels(const LaunchTable& t, hipStream_t s);
-void launch_scatter_kernels(const LaunchTable& t, hipStream_t s);
+void launch_gather_kernels(const LaunchTable& t, hipStream_t s, bool deliver);
+void launch_scatter_kernels(const LaunchTable& t, hipStream_t s, bool deliver);
 void launch_segsum_kernels(const LaunchTable& t, hipStream_t s);
 
 }  // namespace hx

@@ -712,16 +712,12 @@ int hx::batch_prepare(hx_batch* b) {
 }
 
 int hx::batch_run_start(hx_batch* b, hipStream_t s) {
-  HX_TRY(launch_table(b->lt[PH_PACK], s));
-  if (b->world && (b->flags & HX_WORLD_SIM_TRANSFER)) HX_TRY(launch_table(b->lt_xfer[0], s));
-  return HX_SUCCESS;
+  return launch_table(b->lt[PH_PACK], s, sim_transfer(b));
 }
 
 int hx::batch_run_wait(hx_batch* b, hipStream_t s) {
-  HX_TRY(launch_table(b->lt[PH_REDIST], s));
-  if (b->world && (b->flags & HX_WORLD_SIM_TRANSFER)) HX_TRY(launch_table(b->lt_xfer[1], s));
-  HX_TRY(launch_table(b->lt[PH_UNPACK], s));
-  return HX_SUCCESS;
+  HX_TRY(launch_table(b->lt[PH_REDIST], s, sim_transfer(b)));
+  return launch_table(b->lt[PH_UNPACK], s);
 }
 
 static std::string cache_key(const hx_batch* b, int phase) {
@@ -912,8 +908,7 @@ extern "C" int hx_batch_start_plain(hx_batch* b, void* stream) {
   if (b->active) return fail(HX_ERR_STATE, "batch already active");
   hipStream_t s = (hipStream_t)stream;
   if (!b->plain_built[PH_PACK]) HX_TRY(batch_build_plain(b, PH_PACK));
-  for (auto& t : b->plain[PH_PACK]) HX_TRY(launch_table(t, s));
-  if (b->world && (b->flags & HX_WORLD_SIM_TRANSFER)) HX_TRY(launch_table(b->lt_xfer[0], s));
+  for (auto& t : b->plain[PH_PACK]) HX_TRY(launch_table(t, s, sim_transfer(b)));
   b->active = true;
   return HX_SUCCESS;
 }
@@ -924,8 +919,7 @@ extern "C" int hx_batch_wait_plain(hx_batch* b, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   if (!b->plain_built[PH_REDIST]) HX_TRY(batch_build_plain(b, PH_REDIST));
   if (!b->plain_built[PH_UNPACK]) HX_TRY(batch_build_plain(b, PH_UNPACK));
-  for (auto& t : b->plain[PH_REDIST]) HX_TRY(launch_table(t, s));
-  if (b->world && (b->flags & HX_WORLD_SIM_TRANSFER)) HX_TRY(launch_table(b->lt_xfer[1], s));
+  for (auto& t : b->plain[PH_REDIST]) HX_TRY(launch_table(t, s, sim_transfer(b)));
   for (auto& t : b->plain[PH_UNPACK]) HX_TRY(launch_table(t, s));
   b->active = false;
   return HX_SUCCESS;
@@ -945,8 +939,8 @@ extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
     // plain world: halo gradients travel back to the senders' slots (the
     // simulated reverse transfer), then each rank sums its own slots
     HX_TRY(b->g_send_all.alloc((size_t)b->E1_tot * b->row_bytes));
-    std::vector<GatherJob> xb{GatherJob{b->g_in, b->g_send_all.as<char>(), b->gidx_back.as<int32_t>(), b->E1_tot}};
-    HX_TRY(build_gather_table(xb, b->dtype, rbi, gsc, &b->lt_xfer[2]));
+    std::vector<GatherJob> xb{GatherJob{b->g_in, b->g_send_all.as<char>(), b->gidx_to1.as<int32_t>(), b->E1_tot}};
+    HX_TRY(build_gather_table(xb, b->dtype, rbi, gsc, &b->lt_back[0]));
   } else if (b->staged_bwd) {
     // locality world, staged: forwarder sums read the halo gradients (own
     // terms) and the stage-2 send-slot gradients (split = H)
@@ -954,10 +948,10 @@ extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
     HX_TRY(b->g_r1.alloc((size_t)b->R1_tot * b->row_bytes));
     HX_TRY(b->g_send_all.alloc((size_t)b->E1_tot * b->row_bytes));
     std::vector<GatherJob> x2{GatherJob{b->g_in, b->g_s2.as<char>(), b->gidx_back2.as<int32_t>(), b->E2_tot}};
-    HX_TRY(build_gather_table(x2, b->dtype, rbi, gsc, &b->lt_xfer[3]));
-    std::vector<GatherJob> x1{GatherJob{b->g_r1.as<char>(), b->g_send_all.as<char>(), b->gidx_back.as<int32_t>(),
+    HX_TRY(build_gather_table(x2, b->dtype, rbi, gsc, &b->lt_back[1]));
+    std::vector<GatherJob> x1{GatherJob{b->g_r1.as<char>(), b->g_send_all.as<char>(), b->gidx_to1.as<int32_t>(),
                                         b->E1_tot}};
-    HX_TRY(build_gather_table(x1, b->dtype, rbi, gsc, &b->lt_xfer[2]));
+    HX_TRY(build_gather_table(x1, b->dtype, rbi, gsc, &b->lt_back[0]));
   }
   // the backward's shape (and so its tuning-cache key) exists only now
   Sched cached;
@@ -970,13 +964,13 @@ extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
 // worlds: [reverse stage-2 transfer], forwarder sums, [reverse stage-1
 // transfer], owner sums.  Others: the fixed-order sums.
 static int run_backward(hx_batch* b, hipStream_t s, bool plain_form) {
-  const bool sim = b->world && (b->flags & HX_WORLD_SIM_TRANSFER);
+  const bool sim = sim_transfer(b);
   if (b->world && b->staged_bwd) {
-    if (sim) HX_TRY(launch_table(b->lt_xfer[3], s));
+    if (sim) HX_TRY(launch_table(b->lt_back[1], s));
     HX_TRY(launch_table(b->lt_fwd_sum, s));
-    if (sim) HX_TRY(launch_table(b->lt_xfer[2], s));
+    if (sim) HX_TRY(launch_table(b->lt_back[0], s));
   } else if (b->world && b->unpack_identity && sim) {
-    HX_TRY(launch_table(b->lt_xfer[2], s));
+    HX_TRY(launch_table(b->lt_back[0], s));
   }
   if (!plain_form) return launch_table(b->lt[PH_BWD], s);
   for (auto& t : b->plain[PH_BWD]) HX_TRY(launch_table(t, s));

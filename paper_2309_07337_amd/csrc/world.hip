@@ -6,8 +6,8 @@
 // and turns each phase into one gather over global row indices, so a phase
 // of all ranks is a single launch (one job per rank where the job's LDS
 // window is its own rank's rows or arena).  The simulated transfer of a stage
-// is one more gather, from each sender's message segment into the receiver's
-// slots.  The backward is the closed-form adjoint over halo_all rows, or, for
+// is a second destination of its pack: the row of recv_all each send slot's
+// message lands on.  The backward is the closed-form adjoint over halo_all rows, or, for
 // a locality plan with HX_WORLD_STAGED_BACKWARD, the forward's stages in
 // reverse (forwarder sums, then owner sums).
 #include <hip/hip_runtime.h>
@@ -78,18 +78,6 @@ __global__ void k_fill_neg(int32_t* p, int64_t n) {
   GRID_STRIDE(i, n) p[i] = -1;
 }
 
-__global__ void k_fill_zero(int32_t* p, int64_t n) {
-  GRID_STRIDE(i, n) p[i] = 0;
-}
-
-// inv[map[i]] = i for a permutation map (out-of-range targets are skipped and
-// leave -1, which the range check then reports).
-__global__ void k_invert(const int32_t* __restrict__ map, int64_t n, int32_t* inv) {
-  GRID_STRIDE(i, n) {
-    const int32_t t = map[i];
-    if (t >= 0 && t < n) inv[t] = (int32_t)i;
-  }
-}
 
 // inv[map[i] - lo] = i for the n entries of an injective map (targets
 // outside [lo, lo + range) are skipped; untouched entries keep their fill).
@@ -100,10 +88,9 @@ __global__ void k_invert_range(const int32_t* __restrict__ map, int64_t n, int64
   }
 }
 
-// out[e] = b[off + a[e]] (composition of two maps).
-__global__ void k_compose(const int32_t* __restrict__ a, int64_t n, const int32_t* __restrict__ b, int64_t off,
-                          int32_t* out) {
-  GRID_STRIDE(e, n) out[e] = b[off + a[e]];
+// out[e] = b[a[e]] (composition of two maps).
+__global__ void k_compose(const int32_t* __restrict__ a, int64_t n, const int32_t* __restrict__ b, int32_t* out) {
+  GRID_STRIDE(e, n) out[e] = b[a[e]];
 }
 
 // Number of terms of every forwarder sum: the own-halo term when the slot's
@@ -139,34 +126,34 @@ __global__ void k_world_unpack(const int32_t* __restrict__ u, int64_t n, const i
   }
 }
 
-// Simulated transfer of one stage: for every receive slot, the row of the
-// sender's send arena holding it.  Receive lists (procs, displs, entry
-// offsets) of each rank and send lists of each rank, all ascending.
-__global__ void k_transfer_map(int64_t nslots, int R, const int64_t* __restrict__ roff,
-                               const int64_t* __restrict__ rp_off, const int32_t* __restrict__ r_procs,
-                               const int32_t* __restrict__ r_counts, const int32_t* __restrict__ r_displs,
-                               const int64_t* __restrict__ soff, const int64_t* __restrict__ sp_off,
-                               const int32_t* __restrict__ s_procs, const int32_t* __restrict__ s_counts,
-                               const int32_t* __restrict__ s_displs, int64_t send_base, int32_t* out,
-                               int* err) {
+// Simulated transfer of one stage: for every send slot, the row of recv_all it
+// is delivered to (recv_base: the first row of the stage's receive slots).
+// Send lists (procs, counts, displs, entry offsets) of each rank and receive
+// lists of each rank, all ascending.
+__global__ void k_transfer_map(int64_t nslots, int R, const int64_t* __restrict__ soff,
+                               const int64_t* __restrict__ sp_off, const int32_t* __restrict__ s_procs,
+                               const int32_t* __restrict__ s_counts, const int32_t* __restrict__ s_displs,
+                               const int64_t* __restrict__ roff, const int64_t* __restrict__ rp_off,
+                               const int32_t* __restrict__ r_procs, const int32_t* __restrict__ r_counts,
+                               const int32_t* __restrict__ r_displs, int64_t recv_base, int32_t* out, int* err) {
   GRID_STRIDE(i, nslots) {
-    const int r = upper_rank(roff, R, i);
-    const int64_t il = i - roff[r];
-    if (rp_off[r + 1] <= rp_off[r]) {
+    const int q = upper_rank(soff, R, i);
+    const int64_t il = i - soff[q];
+    if (sp_off[q + 1] <= sp_off[q]) {
       atomicOr(err, 1);
       out[i] = 0;
       continue;
     }
-    const int64_t l = upper_in(r_displs, rp_off[r], rp_off[r + 1], il);
-    const int q = r_procs[l];
-    const int64_t a = sp_off[q], b = sp_off[q + 1];
-    const int64_t pos = upper_in(s_procs, a, b, r);
-    if (b <= a || s_procs[pos] != r || s_counts[pos] != r_counts[l]) {
+    const int64_t l = upper_in(s_displs, sp_off[q], sp_off[q + 1], il);
+    const int r = s_procs[l];
+    const int64_t a = rp_off[r], b = rp_off[r + 1];
+    const int64_t pos = upper_in(r_procs, a, b, q);
+    if (b <= a || r_procs[pos] != q || r_counts[pos] != s_counts[l]) {
       atomicOr(err, 1);
       out[i] = 0;
       continue;
     }
-    out[i] = (int32_t)(send_base + soff[q] + s_displs[pos] + (il - r_displs[l]));
+    out[i] = (int32_t)(recv_base + roff[r] + r_displs[pos] + (il - s_displs[l]));
   }
 }
 
@@ -177,6 +164,16 @@ int check_err(const DevMem& err, const char* what) {
   return HX_SUCCESS;
 }
 
+// The push pack's deliveries: gidx_to1 in the order of wp_idx.
+int make_push_deliveries(const hx_batch* b) {
+  HX_TRY(b->wp_to.alloc((size_t)b->E1_tot * 4));
+  hipLaunchKernelGGL(k_compose, dim3(blocks_for(b->E1_tot)), dim3(TB), 0, 0, b->wp_idx.as<int32_t>(), b->E1_tot,
+                     b->gidx_to1.as<int32_t>(), b->wp_to.as<int32_t>());
+  HX_HIP(hipGetLastError());
+  HX_HIP(hipStreamSynchronize(0));
+  return HX_SUCCESS;
+}
+
 }  // namespace
 
 int world_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
@@ -184,21 +181,34 @@ int world_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
   const int64_t rb = (int64_t)b->row_bytes;
   const char* sa = b->send_all.as<char>();
   const char* ra = b->recv_all.as<char>();
+  // where the messages of a stage are delivered
+  const bool sim = sim_transfer(b);
+  char* const to = sim ? (char*)ra : nullptr;
   switch (phase) {
     case PH_PACK:
       if (sc.push_pack) {
         if (b->E1_tot == 0) break;
+        if (sim && !b->wp_to.p) HX_TRY(make_push_deliveries(b));
+        std::vector<SegSumJob> v;
         if (merged) {
-          s->push_back({SegSumJob{b->x_global, (char*)sa, b->wp_ptr.as<int32_t>(), b->wp_idx.as<int32_t>(), b->n}});
+          v.push_back(SegSumJob{b->x_global, (char*)sa, b->wp_ptr.as<int32_t>(), b->wp_idx.as<int32_t>(), b->n});
         } else {
           for (int r = 0; r < b->R; ++r) {
             const int64_t r0 = b->row_starts[r];
-            s->push_back({SegSumJob{b->x_global + r0 * rb, (char*)sa, b->wp_ptr.as<int32_t>() + r0,
-                                    b->wp_idx.as<int32_t>(), b->row_starts[r + 1] - r0}});
+            v.push_back(SegSumJob{b->x_global + r0 * rb, (char*)sa, b->wp_ptr.as<int32_t>() + r0,
+                                  b->wp_idx.as<int32_t>(), b->row_starts[r + 1] - r0});
           }
         }
+        for (auto& x : v) {
+          x.out2 = to;
+          x.idx2 = sim ? b->wp_to.as<int32_t>() : nullptr;
+          s->push_back({x});
+        }
       } else if (merged && !sc.lds_window) {
-        g->push_back({GatherJob{b->x_global, (char*)sa, b->gidx_pack.as<int32_t>(), b->E1_tot}});
+        GatherJob j{b->x_global, (char*)sa, b->gidx_pack.as<int32_t>(), b->E1_tot};
+        j.dst2 = to;
+        j.idx2 = sim ? b->gidx_to1.as<int32_t>() : nullptr;
+        g->push_back({j});
       } else {
         // one job per rank: its indices stay inside its own rows (the window)
         std::vector<GatherJob> v;
@@ -206,13 +216,20 @@ int world_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
           v.push_back(GatherJob{b->x_global, (char*)sa + b->s1_off[r] * rb, b->gidx_pack.as<int32_t>() + b->s1_off[r],
                                 b->s1_off[r + 1] - b->s1_off[r], b->row_starts[r],
                                 b->row_starts[r + 1] - b->row_starts[r]});
+        for (int r = 0; r < b->R; ++r) {
+          v[r].dst2 = to;
+          v[r].idx2 = sim ? b->gidx_to1.as<int32_t>() + b->s1_off[r] : nullptr;
+        }
         if (merged) g->push_back(v);
         else for (auto& x : v) g->push_back({x});
       }
       break;
     case PH_REDIST:
       if (merged && !sc.lds_window) {
-        g->push_back({GatherJob{ra, (char*)sa + b->E1_tot * rb, b->gidx_redist.as<int32_t>(), b->E2_tot}});
+        GatherJob j{ra, (char*)sa + b->E1_tot * rb, b->gidx_redist.as<int32_t>(), b->E2_tot};
+        j.dst2 = to;
+        j.idx2 = sim ? b->gidx_to2.as<int32_t>() : nullptr;
+        g->push_back({j});
       } else {
         // one job per rank: it forwards values from its own stage-1 receive arena
         std::vector<GatherJob> v;
@@ -220,6 +237,10 @@ int world_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
           v.push_back(GatherJob{ra, (char*)sa + (b->E1_tot + b->s2_off[r]) * rb,
                                 b->gidx_redist.as<int32_t>() + b->s2_off[r], b->s2_off[r + 1] - b->s2_off[r],
                                 b->r1_off[r], b->r1_off[r + 1] - b->r1_off[r]});
+        for (int r = 0; r < b->R; ++r) {
+          v[r].dst2 = to;
+          v[r].idx2 = sim ? b->gidx_to2.as<int32_t>() + b->s2_off[r] : nullptr;
+        }
         if (merged) g->push_back(v);
         else for (auto& x : v) g->push_back({x});
       }
@@ -498,27 +519,27 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
   HX_HIP(hipGetLastError());
   // simulated transfers
   {
+    if (b->E1_tot != b->R1_tot || b->E2_tot != b->R2_tot)
+      return fail(HX_ERR_ARG, "plan: sends and receives of a stage differ in size");
     DevMem rp1, sp1, rp2, sp2;
     HX_TRY(upload_vec(rp1, p->off[HX_F_R1_PROCS]));
     HX_TRY(upload_vec(sp1, p->off[HX_F_S1_PROCS]));
     HX_TRY(upload_vec(rp2, p->off[HX_F_R2_PROCS]));
     HX_TRY(upload_vec(sp2, p->off[HX_F_S2_PROCS]));
-    HX_TRY(b->gidx_x1.alloc((size_t)b->R1_tot * 4));
-    HX_TRY(b->gidx_x2.alloc((size_t)b->R2_tot * 4));
-    if (b->R1_tot)
-      hipLaunchKernelGGL(k_transfer_map, dim3(blocks_for(b->R1_tot)), dim3(TB), 0, s, b->R1_tot, R, r1o.as<int64_t>(),
-                         rp1.as<int64_t>(), p->d[HX_F_R1_PROCS].as<int32_t>(), p->d[HX_F_R1_COUNTS].as<int32_t>(),
-                         p->d[HX_F_R1_DISPLS].as<int32_t>(), s1o.as<int64_t>(), sp1.as<int64_t>(),
-                         p->d[HX_F_S1_PROCS].as<int32_t>(), p->d[HX_F_S1_COUNTS].as<int32_t>(),
-                         p->d[HX_F_S1_DISPLS].as<int32_t>(), (int64_t)0, b->gidx_x1.as<int32_t>(),
-                         err.as<int>());
-    if (b->R2_tot)
-      hipLaunchKernelGGL(k_transfer_map, dim3(blocks_for(b->R2_tot)), dim3(TB), 0, s, b->R2_tot, R, r2o.as<int64_t>(),
-                         rp2.as<int64_t>(), p->d[HX_F_R2_PROCS].as<int32_t>(), p->d[HX_F_R2_COUNTS].as<int32_t>(),
-                         p->d[HX_F_R2_DISPLS].as<int32_t>(), s2o.as<int64_t>(), sp2.as<int64_t>(),
-                         p->d[HX_F_S2_PROCS].as<int32_t>(), p->d[HX_F_S2_COUNTS].as<int32_t>(),
-                         p->d[HX_F_S2_DISPLS].as<int32_t>(), b->E1_tot, b->gidx_x2.as<int32_t>(),
-                         err.as<int>());
+    HX_TRY(b->gidx_to1.alloc((size_t)b->E1_tot * 4));
+    HX_TRY(b->gidx_to2.alloc((size_t)b->E2_tot * 4));
+    if (b->E1_tot)
+      hipLaunchKernelGGL(k_transfer_map, dim3(blocks_for(b->E1_tot)), dim3(TB), 0, s, b->E1_tot, R, s1o.as<int64_t>(),
+                         sp1.as<int64_t>(), p->d[HX_F_S1_PROCS].as<int32_t>(), p->d[HX_F_S1_COUNTS].as<int32_t>(),
+                         p->d[HX_F_S1_DISPLS].as<int32_t>(), r1o.as<int64_t>(), rp1.as<int64_t>(),
+                         p->d[HX_F_R1_PROCS].as<int32_t>(), p->d[HX_F_R1_COUNTS].as<int32_t>(),
+                         p->d[HX_F_R1_DISPLS].as<int32_t>(), (int64_t)0, b->gidx_to1.as<int32_t>(), err.as<int>());
+    if (b->E2_tot)
+      hipLaunchKernelGGL(k_transfer_map, dim3(blocks_for(b->E2_tot)), dim3(TB), 0, s, b->E2_tot, R, s2o.as<int64_t>(),
+                         sp2.as<int64_t>(), p->d[HX_F_S2_PROCS].as<int32_t>(), p->d[HX_F_S2_COUNTS].as<int32_t>(),
+                         p->d[HX_F_S2_DISPLS].as<int32_t>(), r2o.as<int64_t>(), rp2.as<int64_t>(),
+                         p->d[HX_F_R2_PROCS].as<int32_t>(), p->d[HX_F_R2_COUNTS].as<int32_t>(),
+                         p->d[HX_F_R2_DISPLS].as<int32_t>(), b->R1_tot, b->gidx_to2.as<int32_t>(), err.as<int>());
     HX_HIP(hipGetLastError());
     HX_HIP(hipDeviceSynchronize());
     HX_TRY(check_err(err, "world transfer"));
@@ -532,72 +553,35 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
     HX_TRY(dev_check_range(b->gidx_unpack.as<int32_t>(), b->H_tot, b->R1_tot + b->R2_tot, "unpack map", s));
   else if (b->R1_tot != b->H_tot || b->R2_tot != 0)
     return fail(HX_ERR_ARG, "plain plan with a receive arena that is not the halo");
-  HX_TRY(dev_check_range(b->gidx_x1.as<int32_t>(), b->R1_tot, b->E1_tot, "stage-1 transfer", s));
-  HX_TRY(dev_check_range(b->gidx_x2.as<int32_t>(), b->R2_tot, b->E1_tot + b->E2_tot, "stage-2 transfer", s));
+  HX_TRY(dev_check_range(b->gidx_to1.as<int32_t>(), b->E1_tot, b->R1_tot, "stage-1 transfer", s));
+  HX_TRY(dev_check_range(b->gidx_to2.as<int32_t>(), b->E2_tot, b->R1_tot + b->R2_tot, "stage-2 transfer", s));
   // adjoint CSR: global column -> rows of halo_all, ascending (= ascending rank)
   HX_TRY(b->wb_ptr.alloc((size_t)(b->n + 1) * 4));
   HX_TRY(b->wb_idx.alloc((size_t)b->H_tot * 4));
   HX_TRY(dev_group_by_key(p->d[HX_F_HALO].as<int32_t>(), b->H_tot, b->n, b->wb_ptr.as<int32_t>(),
                           b->wb_idx.as<int32_t>(), s));
-  // transfer launch tables
-  {
-    const Sched sc = default_sched(KIND_GATHER, (int)rb);
-    std::vector<GatherJob> x1{GatherJob{b->send_all.as<char>(), b->recv_all.as<char>(), b->gidx_x1.as<int32_t>(),
-                                        b->R1_tot}};
-    std::vector<GatherJob> x2{GatherJob{b->send_all.as<char>(), b->recv_all.as<char>() + b->R1_tot * (int64_t)rb,
-                                        b->gidx_x2.as<int32_t>(), b->R2_tot}};
-    HX_TRY(build_gather_table(x1, dtype, (int)rb, sc, &b->lt_xfer[0]));
-    HX_TRY(build_gather_table(x2, dtype, (int)rb, sc, &b->lt_xfer[1]));
-  }
-  // plain worlds: the reverse of the stage-1 transfer (send slot -> the halo
-  // row that received it), used to deliver halo gradients back to the senders
-  if (b->unpack_identity && b->E1_tot > 0) {
-    if (b->E1_tot != b->R1_tot) return fail(HX_ERR_ARG, "plain plan: sends and receives differ in size");
-    HX_TRY(b->gidx_back.alloc((size_t)b->E1_tot * 4));
-    hipLaunchKernelGGL(k_fill_neg, dim3(blocks_for(b->E1_tot)), dim3(TB), 0, s, b->gidx_back.as<int32_t>(), b->E1_tot);
-    hipLaunchKernelGGL(k_invert, dim3(blocks_for(b->R1_tot)), dim3(TB), 0, s, b->gidx_x1.as<int32_t>(), b->R1_tot,
-                       b->gidx_back.as<int32_t>());
-    HX_HIP(hipGetLastError());
-    HX_TRY(dev_check_range(b->gidx_back.as<int32_t>(), b->E1_tot, b->H_tot, "reverse transfer", s));
-  }
   // staged backward of a locality plan (the forward's stages reversed):
   //   reverse unpack   a relabelling: the gradient of receive slot k is the
   //                    halo gradient row that read it (inv_unpack[k])
-  //   reverse stage 2  g_s2[e] = g_halo[inv_unpack[R1 + inv2[e]]]   (transport)
+  //   reverse stage 2  g_s2[e] = g_halo[inv_unpack[to2[e]]]   (transport)
   //   forwarder sums   g_r1[k] = g_halo[own row of k] (when read), then
   //                    g_s2[e] for the entries e forwarding k, ascending
-  //   reverse stage 1  g_send[e] = g_r1[inv1[e]]                     (transport)
+  //   reverse stage 1  g_send[e] = g_r1[to1[e]]                      (transport)
   //   owner sums       g_x = pack transpose over g_send (as the plain world)
   if ((flags & HX_WORLD_STAGED_BACKWARD) && !b->unpack_identity) {
     b->staged_bwd = true;
     const int64_t S = b->R1_tot + b->R2_tot;
-    if (b->E1_tot != b->R1_tot || b->E2_tot != b->R2_tot)
-      return fail(HX_ERR_ARG, "plan: sends and receives of a stage differ in size");
     if (b->H_tot + b->E2_tot >= INT32_MAX) return fail(HX_ERR_UNSUPPORTED, "halo + stage-2 rows beyond 2^31");
-    DevMem inv_unpack, inv2, gp, gperm, lens;
+    DevMem inv_unpack, gp, gperm, lens;
     HX_TRY(inv_unpack.alloc((size_t)std::max<int64_t>(S, 1) * 4));
-    HX_TRY(inv2.alloc((size_t)std::max<int64_t>(b->E2_tot, 1) * 4));
-    HX_TRY(b->gidx_back.alloc((size_t)b->E1_tot * 4));
     HX_TRY(b->gidx_back2.alloc((size_t)b->E2_tot * 4));
     hipLaunchKernelGGL(k_fill_neg, dim3(blocks_for(S + 1)), dim3(TB), 0, s, inv_unpack.as<int32_t>(), S);
     if (b->H_tot)
       hipLaunchKernelGGL(k_invert_range, dim3(blocks_for(b->H_tot)), dim3(TB), 0, s, b->gidx_unpack.as<int32_t>(),
                          b->H_tot, (int64_t)0, S, inv_unpack.as<int32_t>());
-    if (b->E1_tot) {
-      hipLaunchKernelGGL(k_fill_neg, dim3(blocks_for(b->E1_tot)), dim3(TB), 0, s, b->gidx_back.as<int32_t>(), b->E1_tot);
-      hipLaunchKernelGGL(k_invert_range, dim3(blocks_for(b->R1_tot)), dim3(TB), 0, s, b->gidx_x1.as<int32_t>(),
-                         b->R1_tot, (int64_t)0, b->E1_tot, b->gidx_back.as<int32_t>());
-    }
-    if (b->E2_tot) {
-      hipLaunchKernelGGL(k_fill_neg, dim3(blocks_for(b->E2_tot)), dim3(TB), 0, s, inv2.as<int32_t>(), b->E2_tot);
-      hipLaunchKernelGGL(k_invert_range, dim3(blocks_for(b->R2_tot)), dim3(TB), 0, s, b->gidx_x2.as<int32_t>(),
-                         b->R2_tot, b->E1_tot, b->E2_tot, inv2.as<int32_t>());
-    }
-    HX_HIP(hipGetLastError());
-    HX_TRY(dev_check_range(inv2.as<int32_t>(), b->E2_tot, b->R2_tot, "reverse stage-2 transfer", s));
     if (b->E2_tot)
-      hipLaunchKernelGGL(k_compose, dim3(blocks_for(b->E2_tot)), dim3(TB), 0, s, inv2.as<int32_t>(), b->E2_tot,
-                         inv_unpack.as<int32_t>(), b->R1_tot, b->gidx_back2.as<int32_t>());
+      hipLaunchKernelGGL(k_compose, dim3(blocks_for(b->E2_tot)), dim3(TB), 0, s, b->gidx_to2.as<int32_t>(),
+                         b->E2_tot, inv_unpack.as<int32_t>(), b->gidx_back2.as<int32_t>());
     HX_HIP(hipGetLastError());
     // forwarder-sum CSR; own rows are inv_unpack over the stage-1 slots
     HX_TRY(gp.alloc((size_t)(b->R1_tot + 1) * 4));
@@ -621,7 +605,6 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
                          b->fwd_idx.as<int32_t>());
     HX_HIP(hipGetLastError());
     HX_HIP(hipDeviceSynchronize());
-    HX_TRY(dev_check_range(b->gidx_back.as<int32_t>(), b->E1_tot, b->R1_tot, "reverse stage-1 transfer", s));
     HX_TRY(dev_check_range(b->gidx_back2.as<int32_t>(), b->E2_tot, b->H_tot, "reverse stage-2 transfer", s));
     HX_TRY(dev_check_range(b->fwd_idx.as<int32_t>(), nterms, b->H_tot + b->E2_tot, "forwarder sums", s));
   }
