@@ -122,7 +122,8 @@ struct hx_batch {
   hx::DevMem gidx_pack, gidx_redist, gidx_unpack;
   hx::DevMem gidx_to1, gidx_to2;             // stage-1 / stage-2 send slot -> the row of recv_all it is delivered to
   hx::DevMem g_send_all;                     // plain worlds: gradients of every rank's send slots
-  hx::DevMem wb_ptr, wb_idx;                 // adjoint CSR: global column -> halo_all rows
+  hx::DevMem halo_cols;                      // halo_all's columns, until the adjoint CSR is built from them
+  hx::DevMem wb_ptr, wb_idx;                 // adjoint CSR: global column -> halo_all rows (world_adjoint)
   hx::DevMem wp_ptr, wp_idx;                 // transpose of the pack map: global row -> send_all rows
   mutable hx::DevMem wp_to;                  // gidx_to1 of wp_idx's entries (made when a push pack first needs it)
   // staged backward of a locality world (forwarder sums, owner sums)
@@ -162,10 +163,16 @@ int batch_init_scheds(hx_batch* b, const hx_sched* sched);
 int world_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
                      std::vector<std::vector<GatherJob>>* g, std::vector<std::vector<SegSumJob>>* s);
 
+// Builds the closed-form adjoint of a locality world, once.
+int world_adjoint(hx_batch* b);
+
 // Device helpers implemented in plan.hip.
 int dev_exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, hipStream_t s);  // out[n] = total
 // HX_ERR_RANGE unless every idx[i] is in [0, hi).
 int dev_check_range(const int32_t* idx, int64_t n, int64_t hi, const char* what, hipStream_t s);
+// How many of the n segments [ptr[i], ptr[i + 1]) are not empty.
+int dev_count_nonempty(const int32_t* ptr, int64_t n, int64_t* count, hipStream_t s);
+// How many values of [0, domain) the indices take.
 int dev_count_nonzero_flags(const int32_t* idx, int64_t n, int64_t domain, int64_t* distinct,
                             hipStream_t s);
 // Stable grouping of entries by key: for each key k in [0, nkeys), the

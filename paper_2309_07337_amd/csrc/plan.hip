@@ -26,11 +26,12 @@
 
 #include "common.h"
 #include "internal.h"
+#include "ranked.h"
 
 namespace hx {
 namespace {
 
-constexpr int TB = 256;
+constexpr int TB = kWalkThreads;
 
 unsigned blocks_for(int64_t n, int per = TB) {
   int64_t b = (n + per - 1) / per;
@@ -39,16 +40,6 @@ unsigned blocks_for(int64_t n, int per = TB) {
 
 #define GRID_STRIDE(i, n) \
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < (n); i += (int64_t)gridDim.x * blockDim.x)
-
-// Largest p in [0, R) with starts[p] <= v.
-__device__ __forceinline__ int upper_rank(const int64_t* __restrict__ starts, int R, int64_t v) {
-  int lo = 0, hi = R - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (starts[mid] <= v) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
 
 // Placement of R ranks on NN = ceil(R / ppn) nodes (Sec. 2.2 groups ranks by
 // node without fixing which ranks share one).  Block: node p / ppn, local rank
@@ -136,19 +127,22 @@ __device__ __forceinline__ int32_t bit_rank(const uint32_t* __restrict__ NB, con
 // ---------------------------------------------------------------------------
 // Generic device utilities
 // ---------------------------------------------------------------------------
-__global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
-  GRID_STRIDE(i, n) p[i] = v;
-}
-
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_BLOCK = TB * SCAN_ITEMS;
 
+// POPC: the scan of the words' popcounts instead of the values themselves.
+template <bool POPC>
+__device__ __forceinline__ int32_t scan_value(const int32_t* __restrict__ in, int64_t i) {
+  return POPC ? __popc((uint32_t)in[i]) : in[i];
+}
+
+template <bool POPC>
 __global__ void k_scan_partials(const int32_t* __restrict__ in, int64_t n, int64_t* __restrict__ part) {
   const int64_t base = (int64_t)blockIdx.x * SCAN_BLOCK;
   int64_t s = 0;
   for (int k = 0; k < SCAN_ITEMS; ++k) {
     const int64_t i = base + (int64_t)k * TB + threadIdx.x;
-    if (i < n) s += in[i];
+    if (i < n) s += scan_value<POPC>(in, i);
   }
   s = block_sum(s);
   if (threadIdx.x == 0) part[blockIdx.x] = s;
@@ -167,6 +161,7 @@ __global__ void k_scan_part_scan(int64_t* part, int64_t nparts) {
   if (threadIdx.x == 0) part[nparts] = base;
 }
 
+template <bool POPC>
 __global__ void k_scan_final(const int32_t* __restrict__ in, int64_t n, const int64_t* __restrict__ part,
                              int32_t* __restrict__ out) {
   const int64_t base = (int64_t)blockIdx.x * SCAN_BLOCK;
@@ -175,7 +170,7 @@ __global__ void k_scan_final(const int32_t* __restrict__ in, int64_t n, const in
   int64_t v[SCAN_ITEMS];
   int64_t s = 0;
   for (int k = 0; k < SCAN_ITEMS; ++k) {
-    v[k] = (i0 + k < n) ? in[i0 + k] : 0;
+    v[k] = (i0 + k < n) ? scan_value<POPC>(in, i0 + k) : 0;
     s += v[k];
   }
   int64_t tot;
@@ -185,6 +180,20 @@ __global__ void k_scan_final(const int32_t* __restrict__ in, int64_t n, const in
     run += v[k];
   }
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = (int32_t)part[gridDim.x];
+}
+
+// The scan's launches alone; part holds scan_parts(n) values.
+int64_t scan_parts(int64_t n) { return std::max<int64_t>(1, (n + SCAN_BLOCK - 1) / SCAN_BLOCK) + 1; }
+template <bool POPC = false>
+int scan_launch(const int32_t* in, int32_t* out, int64_t n, int64_t* part, hipStream_t s) {
+  const int64_t nb = scan_parts(n) - 1;
+  hipLaunchKernelGGL(k_scan_partials<POPC>, dim3((unsigned)nb), dim3(TB), 0, s, in, n, part);
+  HX_HIP(hipGetLastError());
+  hipLaunchKernelGGL(k_scan_part_scan, dim3(1), dim3(1024), 0, s, part, nb);
+  HX_HIP(hipGetLastError());
+  hipLaunchKernelGGL(k_scan_final<POPC>, dim3((unsigned)nb), dim3(TB), 0, s, in, n, part, out);
+  HX_HIP(hipGetLastError());
+  return HX_SUCCESS;
 }
 
 // Grouping entries by key is a stable radix sort of (key, entry): groups come
@@ -348,16 +357,26 @@ __global__ void k_check_range(const int32_t* __restrict__ idx, int64_t n, int64_
   }
 }
 
-__global__ void k_flag(const int32_t* __restrict__ idx, int64_t n, int64_t domain, int32_t* flags) {
+__global__ void k_flag(const int32_t* __restrict__ idx, int64_t n, int64_t domain, unsigned char* flags) {
   GRID_STRIDE(i, n) {
     const int32_t v = idx[i];
     if (v >= 0 && v < domain) flags[v] = 1;
   }
 }
 
-__global__ void k_sum_i32(const int32_t* __restrict__ a, int64_t n, unsigned long long* out) {
+// *out += number of set flags (nwords words of four).  One atomic a block, so
+// few blocks: 4096 blocks adding to one address took 420 us for 1 M flags.
+__global__ void k_count_flags(const uint32_t* __restrict__ flags, int64_t nwords, unsigned long long* out) {
   int64_t s = 0;
-  GRID_STRIDE(i, n) s += a[i];
+  GRID_STRIDE(i, nwords) s += __popc(flags[i]);
+  s = block_sum(s);
+  if (threadIdx.x == 0) atomicAdd(out, (unsigned long long)s);
+}
+
+// *out += number of segments of a CSR that are not empty.
+__global__ void k_count_nonempty(const int32_t* __restrict__ ptr, int64_t n, unsigned long long* out) {
+  int64_t s = 0;
+  GRID_STRIDE(i, n) s += ptr[i + 1] > ptr[i] ? 1 : 0;
   s = block_sum(s);
   if (threadIdx.x == 0) atomicAdd(out, (unsigned long long)s);
 }
@@ -365,87 +384,193 @@ __global__ void k_sum_i32(const int32_t* __restrict__ a, int64_t n, unsigned lon
 // ---------------------------------------------------------------------------
 // Halo discovery
 // ---------------------------------------------------------------------------
-// Marks every off-rank column of each row in its rank's bitmap.
-// Rows [i0, i0 + rows) belong to ranks r0, r0 + 1, ...; their bitmaps are the
-// rows of B counted from r0.
-__global__ void k_mark_csr(const int64_t* __restrict__ rs, int R, int64_t n, int64_t i0, int64_t rows, int r0,
-                           const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ cols, uint32_t* B,
-                           int64_t W, int* err) {
-  GRID_STRIDE(k, rows) {
-    const int64_t i = i0 + k;
-    const int r = upper_rank(rs, R, i);
-    const int64_t lo = rs[r], hi = rs[r + 1];
-    const int64_t e0 = row_ptr[i], e1 = row_ptr[i + 1];
-    if (e1 < e0) {
-      atomicOr(err, 8);
-      continue;
-    }
-    uint32_t* Br = B + (size_t)(r - r0) * W;
-    for (int64_t e = e0; e < e1; ++e) {
-      const int64_t c = cols[e];
-      if (c < 0 || c >= n) {
-        atomicOr(err, 1);
-        continue;
-      }
-      if (c >= lo && c < hi) continue;
-      atomicOr(Br + (c >> 5), 1u << (c & 31));
-    }
-  }
+// Checks the row pointers of rows [i0, i0 + rows) (err |= 8 where they
+// decrease) and notes where the entries of ranks r0, r0 + 1, ... r0 + g - 1
+// start and end.
+__global__ void k_rank_entries(const int64_t* __restrict__ rs, int64_t i0, int64_t rows, int r0, int g,
+                               const int64_t* __restrict__ row_ptr, int64_t* __restrict__ ent, int* err) {
+  bool bad = false;
+  GRID_STRIDE(k, rows) bad |= row_ptr[i0 + k + 1] < row_ptr[i0 + k];
+  if (bad) atomicOr(err, 8);
+  GRID_STRIDE(r, (int64_t)g + 1) ent[r] = row_ptr[rs[r0 + r]];
 }
 
+// Marks the off-rank columns of the entries of ranks r0 .. r0 + g - 1 in their
+// ranks' bitmaps (rows of Wp words of B, counted from r0).  Entry-parallel: a
+// workgroup streams chunks of consecutive entries, whose rank rarely changes
+// within a chunk.  Bound by the stream of columns and the atomics of the
+// off-rank ones; a bit that is seen set already needs none (a 27-point rank
+// names a halo column nine times).  A lane walking its own row read 27 columns
+// at a stride of 108 bytes instead: 899 us for the 56.6 M entries of 512
+// ranks; 171 us so.  (33.6 M random entries of 1024 ranks, 10 M of them marks
+// all over 134 MB: 441 and 455 us.)
+// Writes nothing where the row pointers were found to decrease (their range
+// is then not known to be the columns').
+constexpr int kMarkItems = 16;
+// (bitmap rows are whole 16-byte vectors)
+__device__ __forceinline__ int popc4(const uint4 v) { return __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w); }
+__global__ void __launch_bounds__(TB) k_mark_csr(const int64_t* __restrict__ rs, int64_t n, int r0, int g,
+                                                 const int64_t* __restrict__ ent, const int32_t* __restrict__ cols,
+                                                 uint32_t* B, int64_t Wp, int* err) {
+  if (*(volatile int*)err & 8) return;
+  const int64_t end = ent[g], step = (int64_t)gridDim.x * (TB * kMarkItems);
+  bool bad = false;
+  for (int64_t c0 = ent[0] + (int64_t)blockIdx.x * (TB * kMarkItems); c0 < end; c0 += step) {
+    int32_t c[kMarkItems];
+#pragma unroll
+    for (int k = 0; k < kMarkItems; ++k) {
+      const int64_t e = c0 + threadIdx.x + k * TB;
+      c[k] = e < end ? __builtin_nontemporal_load(cols + e) : 0;
+    }
+    int r = upper_rank(ent, g, c0);
+    int64_t lo = rs[r0 + r], hi = rs[r0 + r + 1], next = ent[r + 1];
+#pragma unroll
+    for (int k = 0; k < kMarkItems; ++k) {
+      const int64_t e = c0 + threadIdx.x + k * TB;
+      if (e >= end) break;
+      if (e >= next) {
+        r = seek_rank(ent, g, r, e);
+        lo = rs[r0 + r], hi = rs[r0 + r + 1], next = ent[r + 1];
+      }
+      if (c[k] < 0 || c[k] >= n) bad = true;
+      else if (c[k] < lo || c[k] >= hi) {
+        uint32_t* w = B + (size_t)r * Wp + (c[k] >> 5);
+        const uint32_t bit = 1u << (c[k] & 31);
+        if ((*w & bit) == 0) atomicOr(w, bit);
+      }
+    }
+  }
+  if (bad) atomicOr(err, 1);
+}
+
+// The same with the bitmap of one rank and 2^kMarkSegBits columns in LDS: a
+// workgroup streams its rank's entries once, then writes the segment's words
+// whole (nothing is cleared beforehand) and counts them.  Workgroups of one
+// rank are dispatched one after the other on one XCD, whose L2 then serves
+// the later streams.  171 -> 109 us and 455 -> 63 us for the matrices above,
+// without the clearing and counting passes (25 + 21 us).
+constexpr int kMarkSegBits = 20;  // 128 KiB
+constexpr int kMarkThreads = 1024;
+constexpr int kMarkMaxSegs = 4;   // streams of the entries at most
+constexpr int kMarkMinRanks = 8;  // workgroups at least, below which the chip is idle
+__global__ void __launch_bounds__(kMarkThreads) k_mark_lds(const int64_t* __restrict__ rs, int64_t n, int r0, int g,
+                                                           int nseg, const int64_t* __restrict__ ent,
+                                                           const int32_t* __restrict__ cols, uint32_t* __restrict__ B,
+                                                           int64_t Wp, unsigned long long* cnt, int* err) {
+  extern __shared__ __align__(16) uint32_t s_bits[];
+  const int r = (int)(blockIdx.x / (8 * nseg)) * 8 + (int)(blockIdx.x & 7), seg = (int)(blockIdx.x >> 3) % nseg;
+  if (r >= g || (*(volatile int*)err & 8)) return;
+  const int64_t w0 = (int64_t)seg << (kMarkSegBits - 5);
+  const int nv = (int)(min((int64_t)1 << (kMarkSegBits - 5), Wp - w0) / 4);  // 16-byte vectors of the segment
+  uint4* s_vec = reinterpret_cast<uint4*>(s_bits);
+  for (int i = threadIdx.x; i < nv; i += kMarkThreads) s_vec[i] = make_uint4(0, 0, 0, 0);
+  __syncthreads();
+  const int64_t c0 = (int64_t)seg << kMarkSegBits, lo = rs[r0 + r], hi = rs[r0 + r + 1], e1 = ent[r + 1];
+  bool bad = false;
+  for (int64_t e0 = ent[r] + threadIdx.x; e0 < e1; e0 += kMarkThreads * kMarkItems) {
+    int32_t c[kMarkItems];
+#pragma unroll
+    for (int k = 0; k < kMarkItems; ++k) {
+      const int64_t e = e0 + k * kMarkThreads;
+      c[k] = e < e1 ? cols[e] : (int32_t)lo;  // (an own column is left out)
+    }
+#pragma unroll
+    for (int k = 0; k < kMarkItems; ++k) {
+      const bool in = c[k] >= 0 && c[k] < n, own = c[k] >= lo && c[k] < hi;
+      bad |= !in && e0 + k * kMarkThreads < e1;
+      const int64_t o = c[k] - c0;
+      if (in && !own && (uint64_t)o >> kMarkSegBits == 0) atomicOr(&s_bits[o >> 5], 1u << (o & 31));
+    }
+  }
+  if (bad) atomicOr(err, 1);
+  __syncthreads();
+  int total = 0;
+  uint4* out = reinterpret_cast<uint4*>(B + (size_t)r * Wp + w0);
+  for (int i = threadIdx.x; i < nv; i += kMarkThreads) {
+    const uint4 v = s_vec[i];
+    total += popc4(v);
+    out[i] = v;
+  }
+  const int64_t t = block_sum((int64_t)total);
+  if (threadIdx.x == 0 && t) atomicAdd(cnt + r, (unsigned long long)t);
+}
+
+// Bitmap rows are read by workgroups of kBitThreads.
+constexpr int kBitThreads = 1024;
+
 // Number of set bits of each rank's bitmap (one block per rank).
-__global__ void k_popc_rows(const uint32_t* __restrict__ B, int64_t W, int64_t* cnt) {
-  const uint32_t* Br = B + (size_t)blockIdx.x * W;
-  int64_t s = 0;
-  for (int64_t w = threadIdx.x; w < W; w += blockDim.x) s += __popc(Br[w]);
-  s = block_sum(s);
-  if (threadIdx.x == 0) cnt[blockIdx.x] = s;
+__global__ void __launch_bounds__(kBitThreads) k_popc_rows(const uint32_t* __restrict__ B, int64_t Wp, int64_t* cnt) {
+  const uint4* __restrict__ Br = reinterpret_cast<const uint4*>(B + (size_t)blockIdx.x * Wp);
+  const int64_t nv = Wp / 4;
+  int s = 0;
+#pragma unroll 4
+  for (int64_t w = threadIdx.x; w < nv; w += kBitThreads) s += popc4(Br[w]);
+  const int64_t t = block_sum((int64_t)s);
+  if (threadIdx.x == 0) cnt[blockIdx.x] = t;
 }
 
 // Writes the set bits of each rank's bitmap as ascending column ids.
-__global__ void k_compact_bits(const uint32_t* __restrict__ B, int64_t W, const int64_t* __restrict__ off,
-                               int32_t* __restrict__ out) {
-  const uint32_t* Br = B + (size_t)blockIdx.x * W;
-  const int64_t end = off[blockIdx.x + 1];
+__global__ void __launch_bounds__(kBitThreads) k_compact_bits(const uint32_t* __restrict__ B, int64_t Wp,
+                                                              const int64_t* __restrict__ off,
+                                                              int32_t* __restrict__ out) {
+  const uint4* __restrict__ Br = reinterpret_cast<const uint4*>(B + (size_t)blockIdx.x * Wp);
+  const int64_t end = off[blockIdx.x + 1], nv = Wp / 4;
   int64_t base = off[blockIdx.x];
-  for (int64_t w0 = 0; w0 < W; w0 += blockDim.x) {
-    const int64_t w = w0 + threadIdx.x;
-    uint32_t bits = w < W ? Br[w] : 0u;
-    int64_t tot;
-    int64_t o = base + block_exscan((int64_t)__popc(bits), &tot);
-    while (bits) {
-      const int b = __ffs(bits) - 1;
-      if (o < end) out[o] = (int32_t)(w * 32 + b);
-      ++o;
-      bits &= bits - 1u;
+  const uint4 none = make_uint4(0, 0, 0, 0);
+  uint4 next = threadIdx.x < nv ? Br[threadIdx.x] : none;
+  for (int64_t w0 = 0; w0 < nv; w0 += kBitThreads) {
+    const uint4 v = next;
+    const int64_t w = w0 + threadIdx.x, wn = w + kBitThreads;
+    next = wn < nv ? Br[wn] : none;  // in flight during this round's scan
+    int tot;
+    int64_t o = base + block_exscan(popc4(v), &tot);
+    const uint32_t words[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      uint32_t bits = words[k];
+      while (bits) {
+        const int b = __ffs(bits) - 1;
+        if (o < end) out[o] = (int32_t)((w * 4 + k) * 32 + b);
+        ++o;
+        bits &= bits - 1u;
+      }
     }
     base += tot;
   }
 }
 
-// Per halo entry: its rank, its owner, and the rank-pair count M[r][q].
+// Per halo entry: its rank, its owner, and the rank-pair count M[r][q].  A
+// rank's halo is sorted, so the entries of a pair are one run: its first entry
+// subtracts its position, its last adds the next one (two atomics a pair that
+// do not meet, instead of one an entry that mostly do).  8.3 M entries of 1024
+// ranks: 436 -> 77 us.
 __global__ void k_entry_info(const int32_t* __restrict__ hcol, int64_t nH, const int64_t* __restrict__ hoff,
                              const int64_t* __restrict__ rs, int R, int64_t n, int check, int32_t* hrank,
                              int32_t* own, int32_t* M, int* err) {
-  GRID_STRIDE(e, nH) {
-    const int r = upper_rank(hoff, R, e);
+  for_ranked(nH, hoff, R, [&](int64_t e, int r) {
     const int64_t c = hcol[e];
+    const bool first = e == hoff[r], last = e + 1 == hoff[r + 1];
+    const int64_t before = first ? -1 : hcol[e - 1], after = last ? n : hcol[e + 1];
     if (check) {
       if (c < 0 || c >= n) {
         atomicOr(err, 1);
-        continue;
+        return;
       }
-      if (e > hoff[r] && hcol[e - 1] >= c) atomicOr(err, 2);
+      if (before >= c) atomicOr(err, 2);
       if (c >= rs[r] && c < rs[r + 1]) {
         atomicOr(err, 4);
-        continue;
+        return;
       }
     }
-    const int q = upper_rank(rs, R, c);
+    const int q = guess_rank(rs, R, c);
     hrank[e] = r;
     own[e] = q;
-    atomicAdd(M + (size_t)r * R + q, 1);
-  }
+    int32_t* m = M + (size_t)r * R + q;
+    const bool starts = first || before < rs[q], ends = last || after >= rs[q + 1];
+    if (starts && ends) atomicAdd(m, 1);
+    else if (starts) atomicAdd(m, -(int32_t)e);
+    else if (ends) atomicAdd(m, (int32_t)(e + 1));
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -510,27 +635,49 @@ __global__ void k_row_compact(const int32_t* __restrict__ A, const int32_t* __re
 // ---------------------------------------------------------------------------
 // Locality-aware (2-step) tables
 // ---------------------------------------------------------------------------
-__global__ void k_node_mark(const int32_t* __restrict__ hcol, const int32_t* __restrict__ hrank, int64_t nH,
-                            Place P, uint32_t* NB, int64_t W1) {
-  GRID_STRIDE(e, nH) {
-    const int64_t c = hcol[e];
-    const int m = P.node(hrank[e]);
-    atomicOr(NB + (size_t)m * W1 + (c >> 5), 1u << (c & 31));
+// NB: one workgroup per node and segment of 2^seg_bits columns gathers the
+// segment's bits in LDS from the sorted halos of the node's ranks and writes
+// its words whole (no clearing, no atomics on memory).  8.3 M entries on 32
+// nodes: 139 -> 25 us.
+constexpr int kSegBitsMin = 13, kSegBitsMax = 19;  // 1 to 64 KiB of LDS
+__device__ __forceinline__ int64_t lower_entry(const int32_t* __restrict__ v, int64_t lo, int64_t hi, int64_t x) {
+  while (lo < hi) {  // first entry with v >= x
+    const int64_t mid = (lo + hi) >> 1;
+    if (v[mid] < x) lo = mid + 1; else hi = mid;
   }
+  return lo;
 }
-
-// Exclusive word prefix of popcounts per node row (block per row).
-__global__ void k_word_exscan(const uint32_t* __restrict__ NB, int64_t W1, int32_t* NBP) {
-  const size_t m = blockIdx.x;
-  int64_t base = 0;
-  for (int64_t w0 = 0; w0 < W1; w0 += blockDim.x) {
-    const int64_t w = w0 + threadIdx.x;
-    const int64_t v = w < W1 ? __popc(NB[m * W1 + w]) : 0;
-    int64_t tot;
-    const int64_t pre = block_exscan(v, &tot);
-    if (w < W1) NBP[m * W1 + w] = (int32_t)(base + pre);
-    base += tot;
+__global__ void __launch_bounds__(512) k_node_mark(const int32_t* __restrict__ hcol, const int64_t* __restrict__ hoff,
+                                                   Place P, int seg_bits, uint32_t* __restrict__ NB, int64_t W1) {
+  extern __shared__ uint32_t s_bits[];
+  const int nseg = gridDim.x / P.NN;
+  const int m = blockIdx.x / nseg;
+  const int64_t c0 = (int64_t)(blockIdx.x % nseg) << seg_bits, c1 = c0 + ((int64_t)1 << seg_bits);
+  const int nw = 1 << (seg_bits - 5);
+  for (int i = threadIdx.x; i < nw; i += blockDim.x) s_bits[i] = 0;
+  __syncthreads();
+  // the ranges of up to 256 ranks at a time (one search a lane), then a
+  // wavefront per rank
+  __shared__ int64_t s_at[512];
+  const int cnt = P.cnt(m), waves = blockDim.x >> 6, lane = threadIdx.x & 63;
+  for (int l0 = 0; l0 < cnt; l0 += 256) {
+    const int l = l0 + (threadIdx.x >> 1);
+    __syncthreads();
+    if (l < cnt) {
+      const int r = P.rank_at(m, l);
+      s_at[threadIdx.x] = lower_entry(hcol, hoff[r], hoff[r + 1], (threadIdx.x & 1) ? c1 : c0);
+    }
+    __syncthreads();
+    for (int k = threadIdx.x >> 6; k < min(256, cnt - l0); k += waves)
+      for (int64_t e = s_at[2 * k] + lane; e < s_at[2 * k + 1]; e += 64) {
+        const int32_t c = (int32_t)(hcol[e] - c0);
+        atomicOr(&s_bits[c >> 5], 1u << (c & 31));
+      }
   }
+  __syncthreads();
+  const int64_t w0 = c0 >> 5;
+  for (int i = threadIdx.x; i < nw; i += blockDim.x)
+    if (w0 + i < W1) NB[(size_t)m * W1 + w0 + i] = s_bits[i];
 }
 
 // MD[m][q] = |D(q -> m)| for q off node m (else 0).  3-step: |D(n -> m)| of
@@ -682,11 +829,12 @@ __global__ void k_s1_agg(const uint32_t* __restrict__ NB, const int32_t* __restr
     const uint32_t* nb = NB + (size_t)m * W1;
     const int32_t* np = NBP + (size_t)m * W1;
     uint32_t bits = nb[w];
+    int q = -1;
     while (bits) {
       const int b = __ffs(bits) - 1;
       bits &= bits - 1u;
       const int64_t c = w * 32 + b;
-      const int q = upper_rank(rs, R, c);
+      if (q < 0 || c >= rs[q + 1]) q = guess_rank(rs, R, c);  // (a word's columns mostly share their owner)
       if (P.node(q) == m) continue;
       const int t = fwd_of(P, q, m, v3);
       const int a = agg_sender(P, q, m, v3);
@@ -775,10 +923,7 @@ __global__ void k_unpack_map(const int32_t* __restrict__ hcol, const int32_t* __
 // the 3-step plan), so one stable grouping yields every rank's transpose.
 __global__ void k_pack_keys(const int32_t* __restrict__ s1_idx, int64_t E, const int64_t* __restrict__ s1_off,
                             const int64_t* __restrict__ koff, int R, int32_t* keys) {
-  GRID_STRIDE(k, E) {
-    const int q = upper_rank(s1_off, R, k);
-    keys[k] = (int32_t)(koff[q] + s1_idx[k]);
-  }
+  for_ranked(E, s1_off, R, [&](int64_t k, int q) { keys[k] = (int32_t)(koff[q] + s1_idx[k]); });
 }
 
 // Per-rank transpose arrays from that grouping (pack rows of rank q occupy
@@ -786,19 +931,15 @@ __global__ void k_pack_keys(const int32_t* __restrict__ s1_idx, int64_t E, const
 __global__ void k_local_bt_ptr(const int32_t* __restrict__ gptr, const int64_t* __restrict__ bt_off,
                                const int64_t* __restrict__ koff, const int64_t* __restrict__ s1_off, int R,
                                int64_t total, int32_t* bt_ptr) {
-  GRID_STRIDE(i, total) {
-    const int q = upper_rank(bt_off, R, i);
+  for_ranked(total, bt_off, R, [&](int64_t i, int q) {
     const int64_t li = i - bt_off[q];
     bt_ptr[i] = (int32_t)(gptr[koff[q] + li] - s1_off[q]);
-  }
+  });
 }
 
 __global__ void k_local_bt_perm(const int32_t* __restrict__ gperm, int64_t E, const int64_t* __restrict__ s1_off,
                                 int R, int32_t* bt_perm) {
-  GRID_STRIDE(k, E) {
-    const int q = upper_rank(s1_off, R, k);
-    bt_perm[k] = (int32_t)(gperm[k] - s1_off[q]);
-  }
+  for_ranked(E, s1_off, R, [&](int64_t k, int q) { bt_perm[k] = (int32_t)(gperm[k] - s1_off[q]); });
 }
 
 // ---------------------------------------------------------------------------
@@ -909,7 +1050,7 @@ int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff,
   Dense M;
   HX_TRY(zeros(&M.A, (size_t)R * R * 4, s));
   if (nH > 0) {
-    hipLaunchKernelGGL(k_entry_info, dim3(blocks_for(nH)), dim3(TB), 0, s, hcol.as<int32_t>(), nH,
+    hipLaunchKernelGGL(k_entry_info, dim3(walk_blocks(nH)), dim3(TB), 0, s, hcol.as<int32_t>(), nH,
                        hoff_d.as<int64_t>(), p->row_starts_d.as<int64_t>(), R, n, check, hrank.as<int32_t>(),
                        own.as<int32_t>(), M.A.as<int32_t>(), err.as<int>());
     HX_HIP(hipGetLastError());
@@ -930,15 +1071,20 @@ int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff,
   Dense S1, R1, S2, R2;
   DevMem QP;
   if (loc) {
-    HX_TRY(zeros(&NB, (size_t)NN * W1 * 4, s));
-    HX_TRY(NBP.alloc((size_t)NN * W1 * 4));
-    if (nH > 0) {
-      hipLaunchKernelGGL(k_node_mark, dim3(blocks_for(nH)), dim3(TB), 0, s, p->d[HX_F_HALO].as<int32_t>(),
-                         hrank.as<int32_t>(), nH, PL, NB.as<uint32_t>(), W1);
-      HX_HIP(hipGetLastError());
-    }
-    hipLaunchKernelGGL(k_word_exscan, dim3(NN), dim3(TB), 0, s, NB.as<uint32_t>(), W1, NBP.as<int32_t>());
+    HX_TRY(NB.alloc((size_t)NN * W1 * 4));
+    // the scan runs over the rows of all nodes at once: only differences
+    // within a row are used
+    DevMem part;
+    HX_TRY(NBP.alloc((size_t)(NN * W1 + 1) * 4));
+    HX_TRY(part.alloc((size_t)scan_parts(NN * W1) * 8));
+    // segments: about 1024 workgroups where the columns allow it
+    int seg_bits = kSegBitsMax;
+    while (seg_bits > kSegBitsMin && (((W1 * 32) >> seg_bits) + 1) * NN < 1024) --seg_bits;
+    const int64_t nseg = (W1 * 32 + ((int64_t)1 << seg_bits) - 1) >> seg_bits;
+    hipLaunchKernelGGL(k_node_mark, dim3((unsigned)(nseg * NN)), dim3(512), (size_t)4 << (seg_bits - 5), s,
+                       p->d[HX_F_HALO].as<int32_t>(), hoff_d.as<int64_t>(), PL, seg_bits, NB.as<uint32_t>(), W1);
     HX_HIP(hipGetLastError());
+    HX_TRY(scan_launch<true>(NB.as<int32_t>(), NBP.as<int32_t>(), NN * W1, part.as<int64_t>(), s));
     HX_TRY(MD.alloc((size_t)NN * R * 4));
     hipLaunchKernelGGL(k_dedup_counts, dim3(blocks_for((int64_t)NN * R)), dim3(TB), 0, s, NB.as<uint32_t>(),
                        NBP.as<int32_t>(), W1, p->row_starts_d.as<int64_t>(), PL, v3, MD.as<int32_t>());
@@ -1062,18 +1208,18 @@ int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff,
     HX_TRY(upload_vec(bto_d, bt_off));
     HX_TRY(upload_vec(koff_d, koff));
     if (E1 > 0) {
-      hipLaunchKernelGGL(k_pack_keys, dim3(blocks_for(E1)), dim3(TB), 0, s, p->d[HX_F_S1_IDX].as<int32_t>(), E1,
+      hipLaunchKernelGGL(k_pack_keys, dim3(walk_blocks(E1)), dim3(TB), 0, s, p->d[HX_F_S1_IDX].as<int32_t>(), E1,
                          s1o_d.as<int64_t>(), koff_d.as<int64_t>(), R, keys.as<int32_t>());
       HX_HIP(hipGetLastError());
     }
     HX_TRY(dev_check_range(keys.as<int32_t>(), E1, koff.back(), "pack rows", s));
     HX_TRY(dev_group_by_key(keys.as<int32_t>(), E1, koff.back(), gptr.as<int32_t>(), gperm.as<int32_t>(), s));
-    hipLaunchKernelGGL(k_local_bt_ptr, dim3(blocks_for(bt_off.back())), dim3(TB), 0, s, gptr.as<int32_t>(),
+    hipLaunchKernelGGL(k_local_bt_ptr, dim3(walk_blocks(bt_off.back())), dim3(TB), 0, s, gptr.as<int32_t>(),
                        bto_d.as<int64_t>(), koff_d.as<int64_t>(), s1o_d.as<int64_t>(), R, bt_off.back(),
                        p->d[HX_F_BT_PTR].as<int32_t>());
     HX_HIP(hipGetLastError());
     if (E1 > 0) {
-      hipLaunchKernelGGL(k_local_bt_perm, dim3(blocks_for(E1)), dim3(TB), 0, s, gperm.as<int32_t>(), E1,
+      hipLaunchKernelGGL(k_local_bt_perm, dim3(walk_blocks(E1)), dim3(TB), 0, s, gperm.as<int32_t>(), E1,
                          s1o_d.as<int64_t>(), R, p->d[HX_F_BT_PERM].as<int32_t>());
       HX_HIP(hipGetLastError());
     }
@@ -1123,19 +1269,6 @@ int plan_alloc(int nranks, const int64_t* row_starts, const hx_info* info, std::
 // ---------------------------------------------------------------------------
 // Exported device utilities
 // ---------------------------------------------------------------------------
-// The scan's launches alone; part holds scan_parts(n) values.
-static int64_t scan_parts(int64_t n) { return std::max<int64_t>(1, (n + SCAN_BLOCK - 1) / SCAN_BLOCK) + 1; }
-static int scan_launch(const int32_t* in, int32_t* out, int64_t n, int64_t* part, hipStream_t s) {
-  const int64_t nb = scan_parts(n) - 1;
-  hipLaunchKernelGGL(k_scan_partials, dim3((unsigned)nb), dim3(TB), 0, s, in, n, part);
-  HX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_scan_part_scan, dim3(1), dim3(1024), 0, s, part, nb);
-  HX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_scan_final, dim3((unsigned)nb), dim3(TB), 0, s, in, n, part, out);
-  HX_HIP(hipGetLastError());
-  return HX_SUCCESS;
-}
-
 int dev_exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, hipStream_t s) {
   DevMem part;
   HX_TRY(part.alloc((size_t)scan_parts(n) * 8));
@@ -1205,16 +1338,32 @@ int dev_check_range(const int32_t* idx, int64_t n, int64_t hi, const char* what,
   return check_err(err, what);
 }
 
+int dev_count_nonempty(const int32_t* ptr, int64_t n, int64_t* count, hipStream_t s) {
+  *count = 0;
+  if (n <= 0) return HX_SUCCESS;
+  DevMem acc;
+  HX_TRY(zeros(&acc, 8, s));
+  hipLaunchKernelGGL(k_count_nonempty, dim3(std::min(blocks_for(n), 512u)), dim3(TB), 0, s, ptr, n,
+                     acc.as<unsigned long long>());
+  HX_HIP(hipGetLastError());
+  unsigned long long h = 0;
+  HX_HIP(hipMemcpyAsync(&h, acc.p, 8, hipMemcpyDeviceToHost, s));
+  HX_HIP(hipStreamSynchronize(s));
+  *count = (int64_t)h;
+  return HX_SUCCESS;
+}
+
 int dev_count_nonzero_flags(const int32_t* idx, int64_t n, int64_t domain, int64_t* distinct, hipStream_t s) {
   *distinct = 0;
   if (n <= 0 || domain <= 0) return HX_SUCCESS;
   DevMem flags, acc;
-  HX_TRY(zeros(&flags, (size_t)domain * 4, s));
+  const int64_t nwords = (domain + 3) / 4;
+  HX_TRY(zeros(&flags, (size_t)nwords * 4, s));
   HX_TRY(zeros(&acc, 8, s));
-  hipLaunchKernelGGL(k_flag, dim3(blocks_for(n)), dim3(TB), 0, s, idx, n, domain, flags.as<int32_t>());
+  hipLaunchKernelGGL(k_flag, dim3(blocks_for(n)), dim3(TB), 0, s, idx, n, domain, flags.as<unsigned char>());
   HX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_sum_i32, dim3(blocks_for(domain)), dim3(TB), 0, s, flags.as<int32_t>(), domain,
-                     acc.as<unsigned long long>());
+  hipLaunchKernelGGL(k_count_flags, dim3(std::min(blocks_for(nwords), 512u)), dim3(TB), 0, s, flags.as<uint32_t>(),
+                     nwords, acc.as<unsigned long long>());
   HX_HIP(hipGetLastError());
   unsigned long long h = 0;
   HX_HIP(hipMemcpyAsync(&h, acc.p, 8, hipMemcpyDeviceToHost, s));
@@ -1238,33 +1387,49 @@ extern "C" int hx_plan_from_csr(int nranks, const int64_t* row_starts, const hx_
   hipStream_t s = (hipStream_t)stream;
   std::unique_ptr<hx_plan> p;
   HX_TRY(plan_alloc(nranks, row_starts, info, &p));
-  const int64_t W = (n + 31) / 32;
+  const int64_t W = (n + 127) / 128 * 4;  // words of a bitmap row (whole 16-byte vectors)
   // Halo discovery marks one bit per (rank, column).  The bitmaps of a group
   // of ranks are built, counted and compacted before the next group, so the
   // bitmap memory stays within a budget whatever the rank count.
   int64_t budget = (int64_t)1 << 30;
   if (const char* e = std::getenv("HX_PLAN_BITMAP_BYTES")) budget = std::max<int64_t>(1, std::atoll(e));
   const int64_t group = std::max<int64_t>(1, std::min<int64_t>(nranks, budget / std::max<int64_t>(W * 4, 1)));
-  DevMem B, err, cnt;
+  DevMem B, err, cnt, ent;
   HX_TRY(B.alloc((size_t)std::max<int64_t>(group * W * 4, 4)));
   HX_TRY(zeros(&err, 4, s));
   HX_TRY(cnt.alloc((size_t)group * 8));
+  HX_TRY(ent.alloc((size_t)(group + 1) * 8));
   std::vector<int64_t> hoff(1, 0);
   std::vector<DevMem> parts;
   for (int r0 = 0; r0 < nranks; r0 += (int)group) {
     const int g = (int)std::min<int64_t>(group, nranks - r0);
     const int64_t i0 = row_starts[r0], rows = row_starts[r0 + g] - i0;
-    if (W > 0) HX_HIP(hipMemsetAsync(B.p, 0, (size_t)g * W * 4, s));
+    // a rank's bitmap is built in LDS where a few segments hold it (the
+    // entries are streamed once a segment) and there are enough ranks
+    const int nseg = (int)std::min<int64_t>((n + ((int64_t)1 << kMarkSegBits) - 1) >> kMarkSegBits, kMarkMaxSegs + 1);
+    const int64_t lds = std::min<int64_t>(W * 4, (int64_t)1 << (kMarkSegBits - 3));
+    const bool in_lds = rows > 0 && nseg <= kMarkMaxSegs && g >= kMarkMinRanks && lds <= device_lds_per_block() - 1024;
+    if (W > 0 && !in_lds) HX_HIP(hipMemsetAsync(B.p, 0, (size_t)g * W * 4, s));
+    HX_HIP(hipMemsetAsync(cnt.p, 0, (size_t)g * 8, s));
     if (rows > 0) {
-      hipLaunchKernelGGL(k_mark_csr, dim3(blocks_for(rows)), dim3(TB), 0, s, p->row_starts_d.as<int64_t>(), nranks,
-                         n, i0, rows, r0, row_ptr, cols, B.as<uint32_t>(), W, err.as<int>());
+      hipLaunchKernelGGL(k_rank_entries, dim3(std::min(blocks_for(std::max<int64_t>(rows, g + 1)), 2048u)), dim3(TB), 0,
+                         s, p->row_starts_d.as<int64_t>(), i0, rows, r0, g, row_ptr, ent.as<int64_t>(), err.as<int>());
+      if (in_lds)
+        hipLaunchKernelGGL(k_mark_lds, dim3((unsigned)((g + 7) / 8 * 8 * nseg)), dim3(kMarkThreads), (size_t)lds, s,
+                           p->row_starts_d.as<int64_t>(), n, r0, g, nseg, ent.as<int64_t>(), cols, B.as<uint32_t>(), W,
+                           cnt.as<unsigned long long>(), err.as<int>());
+      else
+        hipLaunchKernelGGL(k_mark_csr, dim3((unsigned)(8 * device_cus())), dim3(TB), 0, s,
+                           p->row_starts_d.as<int64_t>(), n, r0, g, ent.as<int64_t>(), cols, B.as<uint32_t>(), W,
+                           err.as<int>());
+      HX_HIP(hipGetLastError());
+    }
+    if (!in_lds) {
+      hipLaunchKernelGGL(k_popc_rows, dim3(g), dim3(kBitThreads), 0, s, B.as<uint32_t>(), W, cnt.as<int64_t>());
       HX_HIP(hipGetLastError());
     }
     HX_HIP(hipStreamSynchronize(s));
     HX_TRY(check_err(err, "csr"));
-    hipLaunchKernelGGL(k_popc_rows, dim3(g), dim3(TB), 0, s, B.as<uint32_t>(), W, cnt.as<int64_t>());
-    HX_HIP(hipGetLastError());
-    HX_HIP(hipStreamSynchronize(s));
     std::vector<int64_t> hc;
     HX_TRY(to_host64(cnt, g, &hc));
     std::vector<int64_t> off = prefix(hc);
@@ -1275,7 +1440,7 @@ extern "C" int hx_plan_from_csr(int nranks, const int64_t* row_starts, const hx_
       DevMem off_d;
       HX_TRY(upload_vec(off_d, off));
       HX_TRY(parts.back().alloc((size_t)off.back() * 4));
-      hipLaunchKernelGGL(k_compact_bits, dim3(g), dim3(TB), 0, s, B.as<uint32_t>(), W, off_d.as<int64_t>(),
+      hipLaunchKernelGGL(k_compact_bits, dim3(g), dim3(kBitThreads), 0, s, B.as<uint32_t>(), W, off_d.as<int64_t>(),
                          parts.back().as<int32_t>());
       HX_HIP(hipGetLastError());
       HX_HIP(hipStreamSynchronize(s));
