@@ -930,6 +930,7 @@ extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
   if (!b->world) return fail(HX_ERR_ARG, "member batches use each member's hx_req_bind_grad");
   // (empty buffers may be null: a decomposition without halo entries, or without rows)
   if ((!g_in && b->H_tot > 0) || (!g_out && b->n > 0)) return fail(HX_ERR_ARG, "null gradient buffer");
+  if (!b->unpack_identity && !b->staged_bwd) HX_TRY(world_adjoint(b));
   b->g_in = static_cast<const char*>(g_in);
   b->g_out = static_cast<char*>(g_out);
   b->plain_built[PH_BWD] = false;

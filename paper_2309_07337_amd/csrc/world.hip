@@ -18,11 +18,12 @@
 
 #include "common.h"
 #include "internal.h"
+#include "ranked.h"
 
 namespace hx {
 namespace {
 
-constexpr int TB = 256;
+constexpr int TB = kWalkThreads;
 
 unsigned blocks_for(int64_t n) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + TB - 1) / TB, 1 << 16));
@@ -30,15 +31,6 @@ unsigned blocks_for(int64_t n) {
 
 #define GRID_STRIDE(i, n) \
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < (n); i += (int64_t)gridDim.x * blockDim.x)
-
-__device__ __forceinline__ int upper_rank(const int64_t* __restrict__ starts, int R, int64_t v) {
-  int lo = 0, hi = R - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (starts[mid] <= v) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
 
 // Largest l in [a, b) with v[l] <= x (v ascending).
 __device__ __forceinline__ int64_t upper_in(const int32_t* __restrict__ v, int64_t a, int64_t b, int64_t x) {
@@ -50,34 +42,41 @@ __device__ __forceinline__ int64_t upper_in(const int32_t* __restrict__ v, int64
   return lo;
 }
 
-// out[k] = base[rank(k)] + in[k], rank(k) from the entry offsets.
+// Bits of the build's error word: which map holds an index outside its source.
+enum MapError { ERR_LISTS = 1, ERR_PACK = 2, ERR_PUSH = 4, ERR_PUSH_PTR = 8, ERR_REDIST = 16, ERR_UNPACK = 32, ERR_TO = 64 };
+
+// out[k] = base[rank(k)] + in[k], rank(k) from the entry offsets; *err |= bit
+// where that is outside [0, hi).  (Each map is checked as it is made: a pass
+// over it and a read-back of its own cost as much again.)
 __global__ void k_add_rank_base(const int32_t* __restrict__ in, int64_t n, const int64_t* __restrict__ off, int R,
-                                const int64_t* __restrict__ base, int32_t* out) {
-  GRID_STRIDE(k, n) {
-    const int r = upper_rank(off, R, k);
-    out[k] = (int32_t)(base[r] + in[k]);
-  }
+                                const int64_t* __restrict__ base, int64_t hi, int bit, int32_t* out, int* err) {
+  bool bad = false;
+  for_ranked(n, off, R, [&](int64_t k, int r) {
+    const int64_t v = base[r] + in[k];
+    bad |= v < 0 || v >= hi;
+    out[k] = (int32_t)v;
+  });
+  if (bad) atomicOr(err, bit);
 }
 
 // Transpose of the pack map in world coordinates: global row -> rows of
 // send_all, from the per-rank transposes (local rows, local slots).
 __global__ void k_world_pack_ptr(const int32_t* __restrict__ bt_ptr, const int64_t* __restrict__ bt_off,
                                  const int64_t* __restrict__ rs, const int64_t* __restrict__ s1_off, int R, int64_t n,
-                                 int64_t E1_tot, int32_t* out) {
-  GRID_STRIDE(g, n + 1) {
-    if (g == n) {
-      out[g] = (int32_t)E1_tot;
-      continue;
-    }
-    const int q = upper_rank(rs, R, g);
-    out[g] = (int32_t)(bt_ptr[bt_off[q] + (g - rs[q])] + s1_off[q]);
-  }
+                                 int64_t E1_tot, int32_t* out, int* err) {
+  bool bad = false;
+  for_ranked(n, rs, R, [&](int64_t g, int q) {
+    const int64_t v = bt_ptr[bt_off[q] + (g - rs[q])] + s1_off[q];
+    bad |= v < 0 || v > E1_tot;
+    out[g] = (int32_t)v;
+  });
+  if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = (int32_t)E1_tot;
+  if (bad) atomicOr(err, ERR_PUSH_PTR);
 }
 
 __global__ void k_fill_neg(int32_t* p, int64_t n) {
   GRID_STRIDE(i, n) p[i] = -1;
 }
-
 
 // inv[map[i] - lo] = i for the n entries of an injective map (targets
 // outside [lo, lo + range) are skipped; untouched entries keep their fill).
@@ -114,53 +113,69 @@ __global__ void k_forward_terms(const int32_t* __restrict__ own, const int32_t* 
 }
 
 // Unpack map in world coordinates: slot u of rank r's [stage-1 | stage-2]
-// receive arena -> row of recv_all.
+// receive arena -> row of recv_all (R1_tot + R2_tot rows).
 __global__ void k_world_unpack(const int32_t* __restrict__ u, int64_t n, const int64_t* __restrict__ hoff, int R,
                                const int64_t* __restrict__ r1_off, const int64_t* __restrict__ r2_off,
-                               int64_t R1_tot, int32_t* out) {
-  GRID_STRIDE(e, n) {
-    const int r = upper_rank(hoff, R, e);
+                               int64_t R1_tot, int64_t rows, int32_t* out, int* err) {
+  bool bad = false;
+  for_ranked(n, hoff, R, [&](int64_t e, int r) {
     const int64_t R1r = r1_off[r + 1] - r1_off[r];
-    const int64_t v = u[e];
-    out[e] = (int32_t)(v < R1r ? r1_off[r] + v : R1_tot + r2_off[r] + (v - R1r));
-  }
+    const int64_t w = u[e], v = w < R1r ? r1_off[r] + w : R1_tot + r2_off[r] + (w - R1r);
+    bad |= v < 0 || v >= rows;
+    out[e] = (int32_t)v;
+  });
+  if (bad) atomicOr(err, ERR_UNPACK);
 }
 
 // Simulated transfer of one stage: for every send slot, the row of recv_all it
-// is delivered to (recv_base: the first row of the stage's receive slots).
-// Send lists (procs, counts, displs, entry offsets) of each rank and receive
-// lists of each rank, all ascending.
-__global__ void k_transfer_map(int64_t nslots, int R, const int64_t* __restrict__ soff,
-                               const int64_t* __restrict__ sp_off, const int32_t* __restrict__ s_procs,
-                               const int32_t* __restrict__ s_counts, const int32_t* __restrict__ s_displs,
-                               const int64_t* __restrict__ roff, const int64_t* __restrict__ rp_off,
-                               const int32_t* __restrict__ r_procs, const int32_t* __restrict__ r_counts,
-                               const int32_t* __restrict__ r_displs, int64_t recv_base, int32_t* out, int* err) {
-  GRID_STRIDE(i, nslots) {
-    const int q = upper_rank(soff, R, i);
-    const int64_t il = i - soff[q];
-    if (sp_off[q + 1] <= sp_off[q]) {
-      atomicOr(err, 1);
-      out[i] = 0;
-      continue;
-    }
-    const int64_t l = upper_in(s_displs, sp_off[q], sp_off[q + 1], il);
-    const int r = s_procs[l];
+// is delivered to (recv_base: the first row of the stage's receive slots, hi:
+// their end).  Send lists (procs, counts, displs, entry offsets) of each rank
+// and receive lists of each rank, all ascending.  kMsgLanes lanes a message:
+// its receiver is searched once, its slots are consecutive on both sides (a
+// search per slot: 263 us for both stages of 1024 ranks, 41 so).
+constexpr int kMsgLanes = 16;
+__global__ void __launch_bounds__(TB) k_transfer_map(int64_t nmsg, int R, const int64_t* __restrict__ soff,
+                                                     const int64_t* __restrict__ sp_off,
+                                                     const int32_t* __restrict__ s_procs,
+                                                     const int32_t* __restrict__ s_counts,
+                                                     const int32_t* __restrict__ s_displs,
+                                                     const int64_t* __restrict__ roff,
+                                                     const int64_t* __restrict__ rp_off,
+                                                     const int32_t* __restrict__ r_procs,
+                                                     const int32_t* __restrict__ r_counts,
+                                                     const int32_t* __restrict__ r_displs, int64_t recv_base,
+                                                     int64_t hi, int32_t* out, int* err) {
+  const int lane = threadIdx.x % kMsgLanes;
+  const int64_t step = (int64_t)gridDim.x * (TB / kMsgLanes);
+  for (int64_t l = (int64_t)blockIdx.x * (TB / kMsgLanes) + threadIdx.x / kMsgLanes; l < nmsg; l += step) {
+    const int q = upper_rank(sp_off, R, l), r = s_procs[l], len = s_counts[l];
     const int64_t a = rp_off[r], b = rp_off[r + 1];
-    const int64_t pos = upper_in(r_procs, a, b, q);
-    if (b <= a || r_procs[pos] != q || r_counts[pos] != s_counts[l]) {
-      atomicOr(err, 1);
-      out[i] = 0;
+    const int64_t pos = b > a ? upper_in(r_procs, a, b, q) : a;
+    if (b <= a || r_procs[pos] != q || r_counts[pos] != len) {
+      if (lane == 0) atomicOr(err, ERR_LISTS);
       continue;
     }
-    out[i] = (int32_t)(recv_base + roff[r] + r_displs[pos] + (il - s_displs[l]));
+    const int64_t s0 = soff[q] + s_displs[l], d0 = recv_base + roff[r] + r_displs[pos];
+    if (s0 < soff[q] || s0 + len > soff[q + 1] || d0 < recv_base || d0 + len > hi) {
+      if (lane == 0) atomicOr(err, ERR_TO);
+      continue;
+    }
+    for (int i = lane; i < len; i += kMsgLanes) out[s0 + i] = (int32_t)(d0 + i);
   }
 }
 
-int check_err(const DevMem& err, const char* what) {
+int check_maps(const DevMem& err) {
   int h = 0;
   HX_HIP(hipMemcpy(&h, err.p, sizeof h, hipMemcpyDeviceToHost));
-  if (h) return fail(HX_ERR_ARG, "%s: send and receive lists do not match", what);
+  if (h & ERR_LISTS) return fail(HX_ERR_ARG, "world transfer: send and receive lists do not match");
+  const char* what = h & ERR_PACK       ? "pack map"
+                     : h & ERR_PUSH     ? "pack transpose"
+                     : h & ERR_PUSH_PTR ? "pack transpose pointers"
+                     : h & ERR_REDIST   ? "redistribution map"
+                     : h & ERR_UNPACK   ? "unpack map"
+                     : h & ERR_TO       ? "transfer"
+                                        : nullptr;
+  if (what) return fail(HX_ERR_RANGE, "%s: an index is outside its range", what);
   return HX_SUCCESS;
 }
 
@@ -299,6 +314,19 @@ int world_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
     default:
       return fail(HX_ERR_ARG, "bad phase");
   }
+  return HX_SUCCESS;
+}
+
+// Adjoint CSR: global column -> rows of halo_all, ascending (= ascending rank).
+int world_adjoint(hx_batch* b) {
+  if (b->wb_ptr.p) return HX_SUCCESS;
+  DevMem ptr, idx;
+  HX_TRY(ptr.alloc((size_t)(b->n + 1) * 4));
+  HX_TRY(idx.alloc((size_t)b->H_tot * 4));
+  HX_TRY(dev_group_by_key(b->halo_cols.as<int32_t>(), b->H_tot, b->n, ptr.as<int32_t>(), idx.as<int32_t>(), nullptr));
+  b->wb_ptr = std::move(ptr);
+  b->wb_idx = std::move(idx);
+  b->halo_cols.release();
   return HX_SUCCESS;
 }
 
@@ -477,89 +505,74 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
   HX_TRY(upload_vec(pbase_d, pbase));
   HX_TRY(b->gidx_pack.alloc((size_t)b->E1_tot * 4));
   if (b->E1_tot)
-    hipLaunchKernelGGL(k_add_rank_base, dim3(blocks_for(b->E1_tot)), dim3(TB), 0, s, p->d[HX_F_S1_IDX].as<int32_t>(),
-                       b->E1_tot, s1o.as<int64_t>(), R, pbase_d.as<int64_t>(), b->gidx_pack.as<int32_t>());
+    hipLaunchKernelGGL(k_add_rank_base, dim3(walk_blocks(b->E1_tot)), dim3(TB), 0, s, p->d[HX_F_S1_IDX].as<int32_t>(),
+                       b->E1_tot, s1o.as<int64_t>(), R, pbase_d.as<int64_t>(), b->n, (int)ERR_PACK,
+                       b->gidx_pack.as<int32_t>(), err.as<int>());
   HX_HIP(hipGetLastError());
   // push form of the pack: global row -> send_all rows (ascending)
+  DevMem bto;
+  HX_TRY(b->wp_ptr.alloc((size_t)(b->n + 1) * 4));
+  HX_TRY(b->wp_idx.alloc((size_t)std::max<int64_t>(b->E1_tot, 1) * 4));
   if (v3) {
     // senders other than the owner: group the global pack map directly
-    HX_TRY(dev_check_range(b->gidx_pack.as<int32_t>(), b->E1_tot, b->n, "pack map", s));
-    HX_TRY(b->wp_ptr.alloc((size_t)(b->n + 1) * 4));
-    HX_TRY(b->wp_idx.alloc((size_t)std::max<int64_t>(b->E1_tot, 1) * 4));
+    HX_TRY(check_maps(err));
     HX_TRY(dev_group_by_key(b->gidx_pack.as<int32_t>(), b->E1_tot, b->n, b->wp_ptr.as<int32_t>(),
                             b->wp_idx.as<int32_t>(), s));
   } else {
-    DevMem bto;
     HX_TRY(upload_vec(bto, p->off[HX_F_BT_PTR]));
-    HX_TRY(b->wp_ptr.alloc((size_t)(b->n + 1) * 4));
-    HX_TRY(b->wp_idx.alloc((size_t)b->E1_tot * 4));
-    hipLaunchKernelGGL(k_world_pack_ptr, dim3(blocks_for(b->n + 1)), dim3(TB), 0, s, p->d[HX_F_BT_PTR].as<int32_t>(),
+    hipLaunchKernelGGL(k_world_pack_ptr, dim3(walk_blocks(b->n)), dim3(TB), 0, s, p->d[HX_F_BT_PTR].as<int32_t>(),
                        bto.as<int64_t>(), rs_d.as<int64_t>(), s1o.as<int64_t>(), R, b->n, b->E1_tot,
-                       b->wp_ptr.as<int32_t>());
+                       b->wp_ptr.as<int32_t>(), err.as<int>());
     if (b->E1_tot)
-      hipLaunchKernelGGL(k_add_rank_base, dim3(blocks_for(b->E1_tot)), dim3(TB), 0, s,
+      hipLaunchKernelGGL(k_add_rank_base, dim3(walk_blocks(b->E1_tot)), dim3(TB), 0, s,
                          p->d[HX_F_BT_PERM].as<int32_t>(), b->E1_tot, s1o.as<int64_t>(), R, s1o.as<int64_t>(),
-                         b->wp_idx.as<int32_t>());
-    HX_HIP(hipGetLastError());
-    HX_HIP(hipDeviceSynchronize());
+                         b->E1_tot, (int)ERR_PUSH, b->wp_idx.as<int32_t>(), err.as<int>());
   }
   // redistribution: rows of recv_all (stage-1 part of the forwarder)
   HX_TRY(b->gidx_redist.alloc((size_t)b->E2_tot * 4));
   if (b->E2_tot)
-    hipLaunchKernelGGL(k_add_rank_base, dim3(blocks_for(b->E2_tot)), dim3(TB), 0, s, p->d[HX_F_S2_SRC].as<int32_t>(),
-                       b->E2_tot, s2o.as<int64_t>(), R, r1o.as<int64_t>(), b->gidx_redist.as<int32_t>());
+    hipLaunchKernelGGL(k_add_rank_base, dim3(walk_blocks(b->E2_tot)), dim3(TB), 0, s, p->d[HX_F_S2_SRC].as<int32_t>(),
+                       b->E2_tot, s2o.as<int64_t>(), R, r1o.as<int64_t>(), b->R1_tot, (int)ERR_REDIST,
+                       b->gidx_redist.as<int32_t>(), err.as<int>());
   // unpack
   if (!b->unpack_identity) {
     HX_TRY(b->gidx_unpack.alloc((size_t)b->H_tot * 4));
     if (b->H_tot)
-      hipLaunchKernelGGL(k_world_unpack, dim3(blocks_for(b->H_tot)), dim3(TB), 0, s,
+      hipLaunchKernelGGL(k_world_unpack, dim3(walk_blocks(b->H_tot)), dim3(TB), 0, s,
                          p->d[HX_F_UNPACK_SRC].as<int32_t>(), b->H_tot, ho.as<int64_t>(), R, r1o.as<int64_t>(),
-                         r2o.as<int64_t>(), b->R1_tot, b->gidx_unpack.as<int32_t>());
+                         r2o.as<int64_t>(), b->R1_tot, b->R1_tot + b->R2_tot, b->gidx_unpack.as<int32_t>(),
+                         err.as<int>());
+  } else if (b->R1_tot != b->H_tot || b->R2_tot != 0) {
+    return fail(HX_ERR_ARG, "plain plan with a receive arena that is not the halo");
   }
   HX_HIP(hipGetLastError());
   // simulated transfers
-  {
-    if (b->E1_tot != b->R1_tot || b->E2_tot != b->R2_tot)
-      return fail(HX_ERR_ARG, "plan: sends and receives of a stage differ in size");
-    DevMem rp1, sp1, rp2, sp2;
-    HX_TRY(upload_vec(rp1, p->off[HX_F_R1_PROCS]));
-    HX_TRY(upload_vec(sp1, p->off[HX_F_S1_PROCS]));
-    HX_TRY(upload_vec(rp2, p->off[HX_F_R2_PROCS]));
-    HX_TRY(upload_vec(sp2, p->off[HX_F_S2_PROCS]));
-    HX_TRY(b->gidx_to1.alloc((size_t)b->E1_tot * 4));
-    HX_TRY(b->gidx_to2.alloc((size_t)b->E2_tot * 4));
-    if (b->E1_tot)
-      hipLaunchKernelGGL(k_transfer_map, dim3(blocks_for(b->E1_tot)), dim3(TB), 0, s, b->E1_tot, R, s1o.as<int64_t>(),
-                         sp1.as<int64_t>(), p->d[HX_F_S1_PROCS].as<int32_t>(), p->d[HX_F_S1_COUNTS].as<int32_t>(),
-                         p->d[HX_F_S1_DISPLS].as<int32_t>(), r1o.as<int64_t>(), rp1.as<int64_t>(),
-                         p->d[HX_F_R1_PROCS].as<int32_t>(), p->d[HX_F_R1_COUNTS].as<int32_t>(),
-                         p->d[HX_F_R1_DISPLS].as<int32_t>(), (int64_t)0, b->gidx_to1.as<int32_t>(), err.as<int>());
-    if (b->E2_tot)
-      hipLaunchKernelGGL(k_transfer_map, dim3(blocks_for(b->E2_tot)), dim3(TB), 0, s, b->E2_tot, R, s2o.as<int64_t>(),
-                         sp2.as<int64_t>(), p->d[HX_F_S2_PROCS].as<int32_t>(), p->d[HX_F_S2_COUNTS].as<int32_t>(),
-                         p->d[HX_F_S2_DISPLS].as<int32_t>(), r2o.as<int64_t>(), rp2.as<int64_t>(),
-                         p->d[HX_F_R2_PROCS].as<int32_t>(), p->d[HX_F_R2_COUNTS].as<int32_t>(),
-                         p->d[HX_F_R2_DISPLS].as<int32_t>(), b->R1_tot, b->gidx_to2.as<int32_t>(), err.as<int>());
-    HX_HIP(hipGetLastError());
-    HX_HIP(hipDeviceSynchronize());
-    HX_TRY(check_err(err, "world transfer"));
-  }
+  if (b->E1_tot != b->R1_tot || b->E2_tot != b->R2_tot)
+    return fail(HX_ERR_ARG, "plan: sends and receives of a stage differ in size");
+  DevMem rp1, sp1, rp2, sp2;
+  HX_TRY(upload_vec(rp1, p->off[HX_F_R1_PROCS]));
+  HX_TRY(upload_vec(sp1, p->off[HX_F_S1_PROCS]));
+  HX_TRY(upload_vec(rp2, p->off[HX_F_R2_PROCS]));
+  HX_TRY(upload_vec(sp2, p->off[HX_F_S2_PROCS]));
+  HX_TRY(b->gidx_to1.alloc((size_t)b->E1_tot * 4));
+  HX_TRY(b->gidx_to2.alloc((size_t)b->E2_tot * 4));
+  auto transfer_map = [&](int f_s, int f_r, const DevMem& so, const DevMem& sp, const DevMem& ro, const DevMem& rp,
+                          int64_t base, int64_t hi, DevMem& out) {
+    const int64_t nmsg = p->tot(f_s);
+    if (nmsg == 0) return;
+    const int64_t blocks = (nmsg + TB / kMsgLanes - 1) / (TB / kMsgLanes);
+    hipLaunchKernelGGL(k_transfer_map, dim3((unsigned)std::min<int64_t>(blocks, 1 << 16)), dim3(TB), 0, s, nmsg, R,
+                       so.as<int64_t>(), sp.as<int64_t>(), p->d[f_s].as<int32_t>(), p->d[f_s + 1].as<int32_t>(),
+                       p->d[f_s + 2].as<int32_t>(), ro.as<int64_t>(), rp.as<int64_t>(), p->d[f_r].as<int32_t>(),
+                       p->d[f_r + 1].as<int32_t>(), p->d[f_r + 2].as<int32_t>(), base, hi, out.as<int32_t>(),
+                       err.as<int>());
+  };
+  static_assert(HX_F_S1_COUNTS == HX_F_S1_PROCS + 1 && HX_F_S1_DISPLS == HX_F_S1_PROCS + 2, "list fields");
+  transfer_map(HX_F_S1_PROCS, HX_F_R1_PROCS, s1o, sp1, r1o, rp1, 0, b->R1_tot, b->gidx_to1);
+  transfer_map(HX_F_S2_PROCS, HX_F_R2_PROCS, s2o, sp2, r2o, rp2, b->R1_tot, b->R1_tot + b->R2_tot, b->gidx_to2);
+  HX_HIP(hipGetLastError());
   // every index a kernel will follow stays inside its source
-  HX_TRY(dev_check_range(b->gidx_pack.as<int32_t>(), b->E1_tot, b->n, "pack map", s));
-  HX_TRY(dev_check_range(b->wp_idx.as<int32_t>(), b->E1_tot, b->E1_tot, "pack transpose", s));
-  HX_TRY(dev_check_range(b->wp_ptr.as<int32_t>(), b->n + 1, b->E1_tot + 1, "pack transpose pointers", s));
-  HX_TRY(dev_check_range(b->gidx_redist.as<int32_t>(), b->E2_tot, b->R1_tot, "redistribution map", s));
-  if (!b->unpack_identity)
-    HX_TRY(dev_check_range(b->gidx_unpack.as<int32_t>(), b->H_tot, b->R1_tot + b->R2_tot, "unpack map", s));
-  else if (b->R1_tot != b->H_tot || b->R2_tot != 0)
-    return fail(HX_ERR_ARG, "plain plan with a receive arena that is not the halo");
-  HX_TRY(dev_check_range(b->gidx_to1.as<int32_t>(), b->E1_tot, b->R1_tot, "stage-1 transfer", s));
-  HX_TRY(dev_check_range(b->gidx_to2.as<int32_t>(), b->E2_tot, b->R1_tot + b->R2_tot, "stage-2 transfer", s));
-  // adjoint CSR: global column -> rows of halo_all, ascending (= ascending rank)
-  HX_TRY(b->wb_ptr.alloc((size_t)(b->n + 1) * 4));
-  HX_TRY(b->wb_idx.alloc((size_t)b->H_tot * 4));
-  HX_TRY(dev_group_by_key(p->d[HX_F_HALO].as<int32_t>(), b->H_tot, b->n, b->wb_ptr.as<int32_t>(),
-                          b->wb_idx.as<int32_t>(), s));
+  HX_TRY(check_maps(err));
   // staged backward of a locality plan (the forward's stages reversed):
   //   reverse unpack   a relabelling: the gradient of receive slot k is the
   //                    halo gradient row that read it (inv_unpack[k])
@@ -568,8 +581,14 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
   //                    g_s2[e] for the entries e forwarding k, ascending
   //   reverse stage 1  g_send[e] = g_r1[to1[e]]                      (transport)
   //   owner sums       g_x = pack transpose over g_send (as the plain world)
-  if ((flags & HX_WORLD_STAGED_BACKWARD) && !b->unpack_identity) {
-    b->staged_bwd = true;
+  b->staged_bwd = (flags & HX_WORLD_STAGED_BACKWARD) && !b->unpack_identity;
+  // locality worlds whose backward is the closed-form adjoint build it from the
+  // halo when gradients are bound (world_adjoint); others never read it
+  if (!b->unpack_identity && !b->staged_bwd && b->H_tot) {
+    HX_TRY(b->halo_cols.alloc((size_t)b->H_tot * 4));
+    HX_HIP(hipMemcpyAsync(b->halo_cols.p, p->d[HX_F_HALO].p, (size_t)b->H_tot * 4, hipMemcpyDeviceToDevice, s));
+  }
+  if (b->staged_bwd) {
     const int64_t S = b->R1_tot + b->R2_tot;
     if (b->H_tot + b->E2_tot >= INT32_MAX) return fail(HX_ERR_UNSUPPORTED, "halo + stage-2 rows beyond 2^31");
     DevMem inv_unpack, gp, gperm, lens;
@@ -611,8 +630,8 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
   // algorithmic bytes per phase
   {
     int64_t U1 = 0, U2 = 0;
-    HX_TRY(dev_count_nonzero_flags(b->gidx_pack.as<int32_t>(), b->E1_tot, b->n, &U1, s));
-    HX_TRY(dev_count_nonzero_flags(b->gidx_redist.as<int32_t>(), b->E2_tot, b->R1_tot + b->R2_tot, &U2, s));
+    HX_TRY(dev_count_nonempty(b->wp_ptr.as<int32_t>(), b->n, &U1, s));
+    HX_TRY(dev_count_nonzero_flags(b->gidx_redist.as<int32_t>(), b->E2_tot, b->R1_tot, &U2, s));
     const int64_t rbi = (int64_t)rb;
     b->bytes[PH_PACK] = (b->E1_tot + U1) * rbi + 4 * b->E1_tot;
     b->bytes[PH_REDIST] = (b->E2_tot + U2) * rbi + 4 * b->E2_tot;
