@@ -5,7 +5,7 @@ Headline workload ("batched256"): 256 independent persistent exchange plans,
 halo sizes log-uniform in [1e3, 1e6) rows, 1..4096 neighbors, 16 FP64
 columns per row.  One step = Start + Wait of all plans (pack, unpack) plus
 the backward of the pack (fixed-order transpose sum), each phase one
-multi-job kernel replayed from a hipGraph (or launched directly, as tuned).
+multi-job kernel launched from a table prepared at init.
 The same work as one launch per plan per phase ("plain") is timed beside it.
 
 With the headline workload the line also carries ``configs``: every other
@@ -28,7 +28,7 @@ dominant kernel against the HBM roofline):
 ``--workload`` runs one of them alone as the headline (``copy`` is the 1 GiB
 calibration copy for the PMC scale factors).  ``--sched-json`` applies
 recorded schedules instead of tuning (per phase, as hx_batch_get_sched
-reports them), ``--replay`` fixes the replay mode.
+reports them), ``--replay`` sets the replay mode (both launch the same tables).
 
 Prints one JSON line (rank 0, one GPU).
 """

@@ -453,7 +453,7 @@ int hx_req_free(hx_req** req);
 
 /* ---------------------------------------------------------------------------
  * Batches: many persistent requests driven as one (one multi-job kernel per
- * phase, captured in a hipGraph at init and replayed by start/wait).
+ * phase, its launch table prepared at init).
  *
  * hx_batch_init: members are existing requests (same dtype and ncols); they
  *   stay owned by the caller and must outlive the batch.  sched NULL = use a
@@ -476,22 +476,20 @@ int hx_req_free(hx_req** req);
  *   ascending slot.  The two travels are the simulated transport (run with
  *   HX_WORLD_SIM_TRANSFER).  Plain plans: the flag changes nothing (their
  *   backward is already the owner sums after the reverse stage-1 travel).
- * hx_batch_start / hx_batch_wait: Start / Wait of all members (graph launch).
+ * hx_batch_start / hx_batch_wait: Start / Wait of all members.
  * hx_batch_start_plain / hx_batch_wait_plain: the same work as one launch per
  *   member (the plain one-plan-per-launch form, for comparison).
  * hx_batch_tune: times candidate schedules on the batch's own buffers (the
  *   candidates write the same arenas/halos a start/wait would), keeps the
- *   fastest, re-captures the graphs, and records it in the tuning cache
+ *   fastest, and records it in the tuning cache
  *   (file named by HX_TUNE_CACHE, if set).  Search per phase: tile size x
  *   rows per lane x pack form x LDS windows x rows per lane pairing (8-byte
  *   rows), then launch shape (persistent or one-shot grid, workgroup size) x
  *   streaming hints, then the first dimensions again, then rows per lane x
  *   launch shape together; each candidate is the average of three
  *   back-to-back launches (short kernels: about a millisecond of launches,
- *   at most 50), best of two trials.  Then the
- *   replay (see hx_batch_set_replay): graph or direct launches, whichever
- *   runs 20 start + wait steps faster.  With HX_TUNE_LOG set, every
- *   candidate's time goes to stderr.
+ *   at most 50), best of two trials.  With HX_TUNE_LOG
+ *   set, every candidate's time goes to stderr.
  * ------------------------------------------------------------------------- */
 enum { HX_WORLD_SIM_TRANSFER = 1, HX_WORLD_STAGED_BACKWARD = 2 };
 int hx_batch_init(hx_req* const* reqs, int n, const hx_sched* sched, hx_batch** out);
@@ -510,7 +508,7 @@ int hx_batch_backward_plain(hx_batch* b, void* stream);
 int hx_batch_tune(hx_batch* b, void* stream);
 /* hx_batch_launch_phase: launch the kernel of one phase alone
  *   (0 pack, 1 redistribution, 2 unpack, 3 backward) from the same launch
- *   table the graphs replay, outside the Start/Wait state machine, so that a
+ *   table start / wait / backward launch, outside the Start/Wait state machine, so that a
  *   caller can time each kernel; the simulated transfers are not run.
  *   HX_ERR_STATE while a Start is pending, or for the backward before
  *   gradients are bound (members: before the first hx_batch_backward after
@@ -519,20 +517,18 @@ int hx_batch_launch_phase(hx_batch* b, int phase, void* stream);
 /* The schedule in use for a phase (0 pack, 1 redistribution, 2 unpack, 3 backward). */
 int hx_batch_get_sched(const hx_batch* b, int phase, hx_sched* out);
 /* Sets the schedule of one phase (zero fields: library defaults, as for
- * hx_batch_init) and rebuilds the launch tables and graphs, so that a
+ * hx_batch_init) and rebuilds the launch tables, so that a
  * schedule recorded with hx_batch_get_sched (or tuned elsewhere) can be
  * applied without tuning; the tuning cache is not written.  HX_ERR_ARG
  * (null, bad phase, an invalid schedule: the batch then keeps its previous
  * one), HX_ERR_STATE while a Start is pending. */
 int hx_batch_set_sched(hx_batch* b, int phase, const hx_sched* sched);
-/* Replay of start / wait / backward: HX_REPLAY_GRAPH (default) launches the
- * graph captured at init; HX_REPLAY_DIRECT launches the same prepared launch
- * tables one by one (no per-call setup either way, same results).  A graph
- * launch has a fixed cost (about 15 us measured on MI355X, whatever the
- * graph holds) against about 3 us per directly launched kernel, so steps of
- * a few short kernels replay faster directly; hx_batch_tune measures a
- * start + wait both ways and keeps the faster.  Mode other than these two:
- * HX_ERR_ARG. */
+/* Replay of start / wait / backward.  Both modes (HX_REPLAY_GRAPH is the
+ * default) launch the prepared launch tables one by one (no per-call setup,
+ * same results): a graph launch has a fixed cost (about 15 us measured on
+ * MI355X, whatever the graph holds) against about 3 us per directly launched
+ * kernel, and no step has more than four.  The mode is kept and reported;
+ * hx_batch_tune leaves it as it is.  Mode other than these two: HX_ERR_ARG. */
 enum { HX_REPLAY_GRAPH = 0, HX_REPLAY_DIRECT = 1 };
 int hx_batch_set_replay(hx_batch* b, int mode);
 int hx_batch_get_replay(const hx_batch* b, int* mode);

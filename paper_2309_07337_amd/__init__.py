@@ -4,7 +4,7 @@ The rank-local work under a persistent neighborhood all-to-all-v (MPI
 Advance, Sec. 2.2): GPU plan building (halo discovery, send-list transpose,
 locality-aware node dedup and on-node redistribution lists), the pack
 gather (Start), the redistribution pack and unpack (Wait), batched launches
-captured in hipGraphs with a schedule tuner, and a fixed-order backward.
+with a schedule tuner, and a fixed-order backward.
 
 ``_lib`` is the ctypes binding of ``libhx.so`` (names as in include/hx.h);
 ``autograd`` adds the differentiable whole-decomposition exchange.

@@ -172,8 +172,8 @@ Sched resolve_sched(const hx_sched* s, int kind, int row_bytes);
 hx_sched to_public(const Sched& s);
 
 // A prepared launch: jobs and their tile prefix in device memory, plus the
-// launch shape.  Launch reads the tables at run time, so a captured graph
-// stays valid as long as the table lives.
+// launch shape.  Launch reads the tables at run time, so a caller's captured
+// graph of it stays valid as long as the table lives.
 struct LaunchTable {
   int kind = KIND_GATHER;
   int tag = TAG_TRANSFER;

@@ -100,14 +100,11 @@ struct hx_batch {
   std::vector<hx::LaunchTable> plain[4];
   bool plain_built[4] = {false, false, false, false};
   hx::LaunchTable lt_back[2];               // the backward's simulated transfers: reverse of stage 1, of stage 2
-  hipStream_t cap_stream = nullptr;
-  hipGraphExec_t graph[3] = {nullptr, nullptr, nullptr};
-  bool has_graph[3] = {false, false, false};
-  bool replay_direct = false;  // start / wait / backward launch the tables directly instead of the graphs
+  int replay = HX_REPLAY_GRAPH;             // as set (hx_batch_set_replay)
   bool active = false;
   bool tuning = false;                      // hx_batch_tune running: candidates skip completion counters
   int64_t bytes[4] = {0, 0, 0, 0};
-  std::vector<uint64_t> bwd_gens_captured;  // members' grad_gen when the backward tables were built
+  std::vector<uint64_t> bwd_gens_built;  // members' grad_gen when the backward tables were built
   // world (all ranks of a plan over flat arrays)
   int R = 0;
   int64_t n = 0;
@@ -134,7 +131,6 @@ struct hx_batch {
   hx::DevMem g_s2;                           // gradients of every stage-2 send slot
   hx::DevMem g_r1;                           // forwarder sums (stage-1 receive slot gradients)
   hx::LaunchTable lt_fwd_sum;                // forwarder sums
-  ~hx_batch();
 };
 
 namespace hx {
@@ -148,7 +144,6 @@ int req_fill_from_plan(const hx_plan* p, int rank, const void* x_local, void* ha
                        hx_req* r);
 // HX_ERR_STATE for a request whose collective init has not completed.
 int req_usable(const hx_req* r);
-void batch_destroy_graphs(hx_batch* b);
 int batch_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
                      std::vector<std::vector<GatherJob>>* g, std::vector<std::vector<SegSumJob>>* s);
 int batch_build_table(const hx_batch* b, int phase, const Sched& sc, LaunchTable* t);

@@ -1,6 +1,6 @@
 // Host runtime of the C ABI: errors, device memory, topology handles,
-// persistent requests (init / Start / Wait / backward), batches captured in
-// hipGraphs, the plain one-launch-per-member form, and the schedule tuner.
+// persistent requests (init / Start / Wait / backward), batches, the plain
+// one-launch-per-member form, and the schedule tuner.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -559,31 +559,6 @@ extern "C" int hx_req_free(hx_req** r) {
 // ===========================================================================
 namespace {
 
-int capture_graph(hipStream_t cap, const std::function<int(hipStream_t)>& body, hipGraphExec_t* exec,
-                  bool* has) {
-  *has = false;
-  HX_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-  int rc = body(cap);
-  hipGraph_t g = nullptr;
-  hipError_t e = hipStreamEndCapture(cap, &g);
-  if (rc != HX_SUCCESS) {
-    if (e == hipSuccess && g) (void)hipGraphDestroy(g);
-    return rc;
-  }
-  HX_HIP(e);
-  size_t nn = 0;
-  (void)hipGraphGetNodes(g, nullptr, &nn);
-  if (nn == 0) {
-    (void)hipGraphDestroy(g);
-    return HX_SUCCESS;
-  }
-  hipError_t ie = hipGraphInstantiate(exec, g, nullptr, nullptr, 0);
-  (void)hipGraphDestroy(g);
-  HX_HIP(ie);
-  *has = true;
-  return HX_SUCCESS;
-}
-
 std::string arch_name() {
   int dev = 0;
   hipDeviceProp_t p;
@@ -602,18 +577,6 @@ int ilog2(int64_t v) {
 std::mutex g_cache_mu;
 
 }  // namespace
-
-void hx::batch_destroy_graphs(hx_batch* b) {
-  for (int i = 0; i < 3; ++i) {
-    if (b->has_graph[i]) (void)hipGraphExecDestroy(b->graph[i]);
-    b->has_graph[i] = false;
-  }
-}
-
-hx_batch::~hx_batch() {
-  batch_destroy_graphs(this);
-  if (cap_stream) (void)hipStreamDestroy(cap_stream);
-}
 
 int hx::batch_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
                          std::vector<std::vector<GatherJob>>* g, std::vector<std::vector<SegSumJob>>* s) {
@@ -665,8 +628,6 @@ int hx::batch_build_plain(hx_batch* b, int phase) {
   return HX_SUCCESS;
 }
 
-// (Re)builds the batched tables for the current schedules and captures the
-// start / wait / backward graphs.
 // Forwarder sums of a staged locality world (bound gradients), one job per
 // forwarder: its terms are its own halo's rows and, mostly, its own stage-2
 // slots (the window).  Runs on the backward phase's schedule.
@@ -687,8 +648,8 @@ static int build_fwd_sum_table(const hx_batch* b, const Sched& sc, LaunchTable* 
   return build_segsum_table(fjs, b->dtype, (int)b->row_bytes, sc, t, TAG_FWD_SUM);
 }
 
-// Gradient bindings of a member batch's requests (the backward tables and
-// graph hold their g_send / g_x pointers).
+// Gradient bindings of a member batch's requests (the backward tables
+// hold their g_send / g_x pointers).
 static std::vector<uint64_t> member_grad_gens(const hx_batch* b) {
   std::vector<uint64_t> v;
   v.reserve(b->members.size());
@@ -696,19 +657,15 @@ static std::vector<uint64_t> member_grad_gens(const hx_batch* b) {
   return v;
 }
 
+// (Re)builds the batched tables for the current schedules.  Start, Wait and the
+// backward launch them one by one.  A hipGraph of them costs about 15 us a
+// launch whatever it holds, a kernel launched from its table 2.7 us, and the
+// longest of the three steps has four: captured graphs were never the faster
+// replay (27-point world of 512 ranks, Start + Wait: 45.2 us from graphs, 26.8 so).
 int hx::batch_prepare(hx_batch* b) {
-  batch_destroy_graphs(b);
-  if (!b->world) b->bwd_gens_captured = member_grad_gens(b);
+  if (!b->world) b->bwd_gens_built = member_grad_gens(b);
   for (int ph = 0; ph < 4; ++ph) HX_TRY(batch_build_table(b, ph, b->sched[ph], &b->lt[ph]));
-  HX_TRY(build_fwd_sum_table(b, b->sched[PH_BWD], &b->lt_fwd_sum));
-  if (!b->cap_stream) HX_HIP(hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
-  HX_TRY(capture_graph(b->cap_stream, [&](hipStream_t s) { return batch_run_start(b, s); }, &b->graph[0],
-                       &b->has_graph[0]));
-  HX_TRY(capture_graph(b->cap_stream, [&](hipStream_t s) { return batch_run_wait(b, s); }, &b->graph[1],
-                       &b->has_graph[1]));
-  HX_TRY(capture_graph(b->cap_stream, [&](hipStream_t s) { return batch_run_backward(b, s); },
-                       &b->graph[2], &b->has_graph[2]));
-  return HX_SUCCESS;
+  return build_fwd_sum_table(b, b->sched[PH_BWD], &b->lt_fwd_sum);
 }
 
 int hx::batch_run_start(hx_batch* b, hipStream_t s) {
@@ -821,19 +778,6 @@ extern "C" int hx_batch_init(hx_req* const* reqs, int n, const hx_sched* sched, 
   return HX_SUCCESS;
 }
 
-// Replays start (0), wait (1) or backward (2): the captured graph, or the
-// same launch tables directly.
-static int launch_graph(hx_batch* b, int which, hipStream_t s) {
-  if (b->replay_direct) {
-    if (which == 0) return batch_run_start(b, s);
-    if (which == 1) return batch_run_wait(b, s);
-    return batch_run_backward(b, s);
-  }
-  if (!b->has_graph[which]) return HX_SUCCESS;
-  HX_HIP(hipGraphLaunch(b->graph[which], s));
-  return HX_SUCCESS;
-}
-
 extern "C" int hx_batch_set_sched(hx_batch* b, int phase, const hx_sched* sched) {
   if (!b || !sched) return fail(HX_ERR_ARG, "null argument");
   if (phase < 0 || phase > 3) return fail(HX_ERR_ARG, "bad phase %d", phase);
@@ -854,43 +798,20 @@ extern "C" int hx_batch_set_sched(hx_batch* b, int phase, const hx_sched* sched)
 extern "C" int hx_batch_set_replay(hx_batch* b, int mode) {
   if (!b) return fail(HX_ERR_ARG, "null batch");
   if (mode != HX_REPLAY_GRAPH && mode != HX_REPLAY_DIRECT) return fail(HX_ERR_ARG, "bad replay mode %d", mode);
-  b->replay_direct = mode == HX_REPLAY_DIRECT;
+  b->replay = mode;
   return HX_SUCCESS;
 }
 
 extern "C" int hx_batch_get_replay(const hx_batch* b, int* mode) {
   if (!b || !mode) return fail(HX_ERR_ARG, "null argument");
-  *mode = b->replay_direct ? HX_REPLAY_DIRECT : HX_REPLAY_GRAPH;
+  *mode = b->replay;
   return HX_SUCCESS;
-}
-
-// Average time of `reps` start + wait steps in one replay mode (after one
-// warm-up step); the batch keeps that mode.
-static int time_replay(hx_batch* b, hipStream_t s, bool direct, int reps, float* ms) {
-  b->replay_direct = direct;
-  hipEvent_t e0, e1;
-  HX_HIP(hipEventCreate(&e0));
-  HX_HIP(hipEventCreate(&e1));
-  int rc = launch_graph(b, 0, s);
-  if (rc == HX_SUCCESS) rc = launch_graph(b, 1, s);
-  if (rc == HX_SUCCESS && hipEventRecord(e0, s) != hipSuccess) rc = fail(HX_ERR_HIP, "event record");
-  for (int i = 0; i < reps && rc == HX_SUCCESS; ++i) {
-    rc = launch_graph(b, 0, s);
-    if (rc == HX_SUCCESS) rc = launch_graph(b, 1, s);
-  }
-  if (rc == HX_SUCCESS && (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
-                           hipEventElapsedTime(ms, e0, e1) != hipSuccess))
-    rc = fail(HX_ERR_HIP, "event timing");
-  if (rc == HX_SUCCESS) *ms /= (float)reps;
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  return rc;
 }
 
 extern "C" int hx_batch_start(hx_batch* b, void* stream) {
   if (!b) return fail(HX_ERR_ARG, "null batch");
   if (b->active) return fail(HX_ERR_STATE, "batch already active");
-  HX_TRY(launch_graph(b, 0, (hipStream_t)stream));
+  HX_TRY(batch_run_start(b, (hipStream_t)stream));
   b->active = true;
   return HX_SUCCESS;
 }
@@ -898,7 +819,7 @@ extern "C" int hx_batch_start(hx_batch* b, void* stream) {
 extern "C" int hx_batch_wait(hx_batch* b, void* stream) {
   if (!b) return fail(HX_ERR_ARG, "null batch");
   if (!b->active) return HX_SUCCESS;
-  HX_TRY(launch_graph(b, 1, (hipStream_t)stream));
+  HX_TRY(batch_run_wait(b, (hipStream_t)stream));
   b->active = false;
   return HX_SUCCESS;
 }
@@ -979,10 +900,9 @@ static int run_backward(hx_batch* b, hipStream_t s, bool plain_form) {
 }
 
 // Member gradients bound (or rebound to other buffers) since the backward
-// tables were built: rebuild the tables (batched and plain) and recapture
-// the graphs.
+// tables were built: rebuild the tables (batched and plain).
 static int refresh_member_grads(hx_batch* b) {
-  if (b->world || member_grad_gens(b) == b->bwd_gens_captured) return HX_SUCCESS;
+  if (b->world || member_grad_gens(b) == b->bwd_gens_built) return HX_SUCCESS;
   b->plain_built[PH_BWD] = false;
   Sched cached;  // gradients bound after the batch was made: the backward's cache key changes
   if (b->sched_from_cache[PH_BWD] && cache_lookup(cache_key(b, PH_BWD), &cached)) b->sched[PH_BWD] = cached;
@@ -993,7 +913,7 @@ extern "C" int hx_batch_backward(hx_batch* b, void* stream) {
   if (!b) return fail(HX_ERR_ARG, "null batch");
   if (b->world && !b->g_out) return fail(HX_ERR_STATE, "no gradient buffers bound");
   HX_TRY(refresh_member_grads(b));
-  return launch_graph(b, 2, (hipStream_t)stream);
+  return batch_run_backward(b, (hipStream_t)stream);
 }
 
 extern "C" int hx_batch_backward_plain(hx_batch* b, void* stream) {
@@ -1007,14 +927,14 @@ extern "C" int hx_batch_backward_plain(hx_batch* b, void* stream) {
 int hx::batch_run_backward(hx_batch* b, hipStream_t s) { return run_backward(b, s, false); }
 
 // One phase's kernel on its own, launched directly from the same
-// launch table the graphs replay (for per-kernel timing).
+// launch table Start, Wait and the backward launch (for per-kernel timing).
 extern "C" int hx_batch_launch_phase(hx_batch* b, int phase, void* stream) {
   if (!b) return fail(HX_ERR_ARG, "null batch");
   if (phase < 0 || phase > 3) return fail(HX_ERR_ARG, "bad phase %d", phase);
   if (b->active) return fail(HX_ERR_STATE, "batch active: call hx_batch_wait first");
   if (phase == PH_BWD) {
     if (b->world && !b->g_out) return fail(HX_ERR_STATE, "no gradient buffers bound");
-    if (!b->world && member_grad_gens(b) != b->bwd_gens_captured)
+    if (!b->world && member_grad_gens(b) != b->bwd_gens_built)
       return fail(HX_ERR_STATE, "gradients bound after the last backward: call hx_batch_backward once first");
   }
   if (phase == PH_BWD && b->world && b->staged_bwd)  // the staged backward's forwarder sums first
@@ -1229,21 +1149,8 @@ extern "C" int hx_batch_tune(hx_batch* b, void* stream) {
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   HX_TRY(rc);
-  // replay: the captured graphs, or the same tables launched directly where
-  // that measures faster (a graph launch has a fixed cost).  The trial runs
-  // on tables built while tuning, which signal no completion counters.
-  HX_TRY(batch_prepare(b));
-  float ms_graph = 0, ms_direct = 0;
-  int rr = time_replay(b, s, false, 20, &ms_graph);
-  if (rr == HX_SUCCESS) rr = time_replay(b, s, true, 20, &ms_direct);
-  const bool direct = rr == HX_SUCCESS && ms_direct < ms_graph * 0.98f;
-  if (log && rr == HX_SUCCESS)
-    std::fprintf(stderr, "hx tune replay: graph %.4f ms, direct %.4f ms per start + wait -> %s\n", ms_graph,
-                 ms_direct, direct ? "direct" : "graph");
   b->tuning = false;  // the tables kept for Start/Wait signal their counters again
-  HX_TRY(batch_prepare(b));
-  b->replay_direct = direct;
-  return rr;
+  return batch_prepare(b);
 }
 
 extern "C" int hx_batch_free(hx_batch** b) {
