@@ -127,8 +127,9 @@ typedef struct {
   int push_pack;      /* pack phase only: 1 = push form (walk the transpose of
                          the pack map, read each source row once and write it
                          to all its slots); 2 = pull form (gather per slot);
-                         0 = default (push for rows of 64 bytes or more,
-                         else pull) */
+                         0 = default (push for rows of 64 bytes or more, and
+                         for shorter ones packed from more than an XCD's L2
+                         holds, 4 MiB; else pull) */
   int lds_window;     /* gathers: 1 = a job whose indices mostly stay inside
                          a known window of source rows (the pack: the rank's
                          own rows; the redistribution: its stage-1 receive
@@ -138,8 +139,9 @@ typedef struct {
                          counted on the device when the launch table is
                          built) and gathers rows inside it from LDS, the
                          others from global memory; 2 = gather from global
-                         memory; 0 = default (1 for rows of 16 bytes or
-                         less, else 2) */
+                         memory; 0 = default (1 for redistributions and
+                         unpacks of 2^23 or more 4- or 8-byte rows, else
+                         2) */
   int pair_rows;      /* gathers of 4- or 8-byte rows: 1 = 16 bytes of rows
                          per lane (a group of four or two consecutive rows
                          takes one vector load of its indices and one
@@ -147,9 +149,11 @@ typedef struct {
                          staged while the tile's indices are in flight),
                          taken where every job's index list is congruent
                          with its destination (one first row aligns both);
-                         2 = one row per lane; 0 = default (1 for rows of
-                         4 or 8 bytes, with 16384-row tiles, 512 lanes, one
-                         workgroup per tile and 4 groups per lane) */
+                         2 = one row per lane; 0 = default (1 for gathers of
+                         4- or 8-byte rows, and for sums of one value per
+                         row whose terms an XCD's L2 holds).  Jobs without
+                         an index list (the plain unpack) are copied as
+                         contiguous bytes whatever this says */
 } hx_sched;
 
 /* ---------------------------------------------------------------------------

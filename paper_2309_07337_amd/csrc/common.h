@@ -146,7 +146,17 @@ struct Sched {
   int lds_window = 0; // gathers stage each job's source window in LDS
   int pair_rows = 0;  // gathers of 4- or 8-byte rows: 16 bytes of rows per lane (2 or 4 rows)
 };
-Sched default_sched(int kind, int row_bytes);
+// What a default schedule is chosen for (zero: unknown).
+struct SchedFor {
+  int phase = -1;        // hx::Phase
+  int64_t rows = 0;      // output rows of all jobs
+  int64_t jobs = 0;
+  int64_t bytes = 0;     // bytes the phase moves (hx_batch_bytes)
+  int64_t source = 0;    // source rows' bytes of a job, averaged over the bytes (a rank's own rows, ...)
+  bool identity = false; // contiguous copies
+  bool fresh = false;    // a world's: what it reads was written by the phase before
+};
+Sched default_sched(int kind, int row_bytes, const SchedFor& w = SchedFor());
 
 // LDS staging in the CSR-driven kernels (push pack, segmented sum): tiles of
 // at most kStageRows rows stage their row pointers, and their entry indices
@@ -168,7 +178,7 @@ constexpr int kWinBytes = 80 << 10;
 // Same for a segmented sum's term window (its workgroups also hold about
 // 6.5 KiB of staged pointers and indices).
 constexpr int kSegWinBytes = 72 << 10;
-Sched resolve_sched(const hx_sched* s, int kind, int row_bytes);
+Sched resolve_sched(const hx_sched* s, int kind, int row_bytes, const SchedFor& w = SchedFor());
 hx_sched to_public(const Sched& s);
 
 // A prepared launch: jobs and their tile prefix in device memory, plus the
@@ -185,6 +195,7 @@ struct LaunchTable {
   int vec16 = 0;      // gathers of 4- or 8-byte rows in 16-byte groups per lane (alignment allows it);
                       // segmented sums of rows of one value: one row per lane
   int vec_depth = 4;  // one-value segmented sums: terms per row loaded together (4 or 16)
+  int identity = 0;     // gathers: contiguous copies (no index lists)
   int deliver = 0;      // every job names a second destination (launch_table's deliver)
   int partial_win = 0;  // row-group gathers: some job's window misses some of its indices
   Sched sched;

@@ -89,6 +89,7 @@ struct hx_plan {
 struct hx_batch {
   bool world = false;
   int variant = HX_PLAIN;  // worlds: the plan's variant (part of the tuning-cache key)
+  int ppn = 1;             // worlds: the plan's ranks per node
   int dtype = HX_F64;
   int ncols = 1;
   size_t row_bytes = 8;
@@ -136,6 +137,8 @@ struct hx_batch {
 namespace hx {
 int req_jobs(const hx_req* r, int phase, const Sched& sc, std::vector<GatherJob>* g,
              std::vector<SegSumJob>* s);
+SchedFor req_sched_for(const hx_req* r, int phase);
+SchedFor batch_sched_for(const hx_batch* b, int phase);
 int build_phase_table(int phase, const Sched& sc, int dtype, int row_bytes, const std::vector<GatherJob>& g,
                       const std::vector<SegSumJob>& s, LaunchTable* t);
 void req_compute_bytes(hx_req* r);

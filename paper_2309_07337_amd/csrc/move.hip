@@ -254,6 +254,13 @@ int build_gather_table(const std::vector<GatherJob>& jobs, int dtype, int row_by
   t->win_bytes = t->ntiles > 0 ? (int)((win_bytes + 15) / 16 * 16) : 0;
   t->vec16 = t->ntiles > 0 && vec ? 1 : 0;
   t->partial_win = 0;
+  t->identity = 0;
+  for (const auto& j : w)
+    if (j.nrows > 0 && j.idx == nullptr) t->identity = 1;
+  for (const auto& j : w)
+    if (j.nrows > 0 && t->identity && j.idx != nullptr)
+      return fail(HX_ERR_STATE, "copies and indexed gathers in one launch");
+  if (t->identity) t->vec16 = 0;
   t->deliver = 1;
   for (const auto& j : w)
     if (j.nrows > 0 && (j.dst2 == nullptr || j.idx == nullptr)) t->deliver = 0;

@@ -64,6 +64,21 @@ HX_GATHER_KERNEL(k_unpack)
 HX_GATHER_KERNEL(k_transfer)
 #undef HX_GATHER_KERNEL
 
+// Contiguous copies (the plain unpack).
+template <int VB, bool NT>
+__global__ void __launch_bounds__(1024)
+    k_unpack_copy(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts, int njobs, int64_t ntiles,
+                  int tile_rows, int row_bytes) {
+  copy_body<VB, NT>(jobs, ts, njobs, ntiles, tile_rows, row_bytes);
+}
+
+template <int VB>
+void copy_launch(const LaunchTable& t, hipStream_t s) {
+  auto* kernel = t.sched.nontemporal ? k_unpack_copy<VB, true> : k_unpack_copy<VB, false>;
+  hipLaunchKernelGGL(kernel, dim3(t.grid), dim3(t.sched.block_threads), 0, s, t.jobs.as<GatherJob>(),
+                     t.tile_start.as<int64_t>(), t.njobs, t.ntiles, t.sched.tile_rows, t.row_bytes);
+}
+
 // The simulated transfer is not tuned: one fixed variant per shape.
 struct transfer_fixed {
   template <int VB, int NV, int LPR, int U, bool NT>
@@ -115,6 +130,12 @@ void launch_gather_kernels(const LaunchTable& t, hipStream_t s, bool deliver) {
     const bool pack = t.tag == TAG_PACK;
     if (t.vec16) pack ? vec_launch<k_pack_vgo<true>>(t, s) : vec_launch<k_redist_vgo<true>>(t, s);
     else pack ? by_vec<k_pack_go<true>>(t, s) : by_vec<k_redist_go<true>>(t, s);
+    return;
+  }
+  if (t.identity) {
+    if (t.vec_bytes == 16) copy_launch<16>(t, s);
+    else if (t.vec_bytes == 8) copy_launch<8>(t, s);
+    else copy_launch<4>(t, s);
     return;
   }
   if (t.vec16) {

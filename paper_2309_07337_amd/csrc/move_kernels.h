@@ -99,7 +99,7 @@ __device__ __forceinline__ int find_job(const int64_t* __restrict__ ts, int njob
 }
 
 // ---------------------------------------------------------------------------
-// Pull: dst[r] = src[idx ? idx[r] : r].  NV vectors of VB bytes per row
+// Pull: dst[r] = src[idx[r]].  NV vectors of VB bytes per row
 // (NV = 0: runtime nv, then U must be 1), LPR lanes per row.
 // ---------------------------------------------------------------------------
 // Source windows (use_win != 0, fixed shapes only): a job with win_rows > 0
@@ -114,7 +114,7 @@ __device__ __forceinline__ int find_job(const int64_t* __restrict__ ts, int njob
 // destination, so that a message is sent and received in one pass over its
 // rows.  A transfer of its own reads the rows and one index per row back from
 // memory: 8-byte rows cost 20 bytes a row there, 12 here (figures at
-// gather_vec_body).  Jobs without an index list have none.
+// gather_vec_body).
 template <int VB, int NV, int LPR, int U, bool NT, bool X>
 __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                             int njobs, int64_t ntiles, int tile_rows, int nv_rt, int use_win) {
@@ -144,7 +144,7 @@ __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, 
     const size_t rb = (size_t)nv * VB;
     int64_t win_lo = 0, win_rows = 0;
     if constexpr (NV > 0) {
-      if (use_win && idx != nullptr && jobs[j].win_rows > 0) {
+      if (use_win && jobs[j].win_rows > 0) {
         win_lo = jobs[j].win_lo;
         win_rows = jobs[j].win_rows;
         if (staged != j) {
@@ -170,31 +170,6 @@ __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, 
         }
       }
     }
-    if constexpr (NV > 0 && VB == 16) {
-      if (idx == nullptr) {
-        // identity job: the tile is one contiguous byte range; copy it as a
-        // flat stream of 16-byte vectors, 8 in flight per lane
-        constexpr int UC = 8;
-        const HX_G V* __restrict__ sp = reinterpret_cast<const HX_G V*>(src + r0 * rb);
-        HX_G V* __restrict__ dp = reinterpret_cast<HX_G V*>(dst + r0 * rb);
-        const int64_t nvec = (r1 - r0) * NV;
-        for (int64_t i = threadIdx.x; i < nvec; i += (int64_t)blockDim.x * UC) {
-          V c[UC];
-#pragma unroll
-          for (int u = 0; u < UC; ++u) {
-            const int64_t k = i + (int64_t)u * blockDim.x;
-            if (k < nvec) c[u] = ldv<V, NT>(sp + k);
-          }
-#pragma unroll
-          for (int u = 0; u < UC; ++u) {
-            const int64_t k = i + (int64_t)u * blockDim.x;
-            if (k < nvec) stv<V, NT>(dp + k, c[u]);
-          }
-        }
-        signal_tile(jobs[j].ready, r1 - r0);
-        continue;
-      }
-    }
     if constexpr (NV > 0) {
       // Lanes past the tile's end re-read its last row, so every index and
       // row load is valid and the U loads of a lane go out together (no
@@ -207,7 +182,7 @@ __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, 
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const int64_t r = min(base + (int64_t)u * rows_per_pass, r1 - 1);
-          srow[u] = idx ? (int64_t)ldv<int32_t, NT>(idx + r) : r;
+          srow[u] = ldv<int32_t, NT>(idx + r);
           if constexpr (X) drow[u] = ldv<int32_t, NT>(idx2 + r);
         }
         if (in_lds) {
@@ -233,7 +208,7 @@ __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, 
 #pragma unroll
             for (int k = 0; k < NVPL; ++k) {
               const int vi = lane_v + k * LPR;
-              if (NV % LPR == 0 || vi < NV) v[u][k] = idx ? sp[vi] : ldv<V, NT>(sp + vi);
+              if (NV % LPR == 0 || vi < NV) v[u][k] = sp[vi];
             }
           }
         }
@@ -260,7 +235,7 @@ __device__ __forceinline__ void gather_body(const GatherJob* __restrict__ jobs, 
       }
     } else {
       for (int64_t r = r0 + rsub; r < r1; r += rows_per_pass) {
-        const int64_t s = idx ? (int64_t)ldv<int32_t, NT>(idx + r) : r;
+        const int64_t s = ldv<int32_t, NT>(idx + r);
         const HX_G V* sp = reinterpret_cast<const HX_G V*>(src + s * rb);
         HX_G V* dp = reinterpret_cast<HX_G V*>(dst + r * rb);
         if constexpr (X) {
@@ -341,6 +316,23 @@ __device__ __forceinline__ void flat_copy(const HX_G char* __restrict__ sp, HX_G
   }
 }
 
+// Jobs that copy their rows in order (the plain unpack), whatever the row size.
+template <int VB, bool NT>
+__device__ __forceinline__ void copy_body(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts,
+                                          int njobs, int64_t ntiles, int tile_rows, int row_bytes) {
+  int64_t t0, t1;
+  tile_range(ntiles, &t0, &t1);
+  if (t0 >= t1) return;
+  int j = find_job(ts, njobs, t0);
+  for (int64_t t = t0; t < t1; ++t) {
+    while (t >= ts[j + 1]) ++j;
+    const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
+    const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
+    flat_copy<VB, NT>((const HX_G char*)jobs[j].src + r0 * row_bytes, (HX_G char*)jobs[j].dst + r0 * row_bytes,
+                      (r1 - r0) * row_bytes);
+  }
+}
+
 template <int VB, int U, bool NT, bool X>
 __device__ __forceinline__ void gather_flat_body(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                                  int njobs, int64_t ntiles, int tile_rows, int nv) {
@@ -361,11 +353,6 @@ __device__ __forceinline__ void gather_flat_body(const GatherJob* __restrict__ j
     const HX_G int32_t* __restrict__ idx2 = X ? (const HX_G int32_t*)jobs[j].idx2 : nullptr;
     const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
-    if (idx == nullptr) {
-      flat_copy<VB, NT>(src + r0 * rb, dst + r0 * rb, (r1 - r0) * rb);
-      signal_tile(jobs[j].ready, r1 - r0);
-      continue;
-    }
     for (int64_t rc = r0; rc < r1; rc += kFlatRows) {
       const int nvec = (int)min((int64_t)kFlatRows, r1 - rc) * nv;
       const HX_G int32_t* __restrict__ ix = idx + rc;
@@ -505,12 +492,12 @@ __device__ __forceinline__ void gather_vec_body(const GatherJob* __restrict__ jo
     const int64_t ng = (r1 - a) / V;  // groups of the tile
     const int64_t tail0 = a + ng * V;
     const int nh = (int)(a - r0), ne = nh + (int)(r1 - tail0);  // rows outside the groups: < V before, < V after
-    const bool use_win = win_rows > 0 && idx != nullptr;
+    const bool use_win = win_rows > 0;
     // this lane's row outside the groups (if any): its index is loaded first
     const bool has_edge = tid < ne;
     const int64_t er = tid < nh ? r0 + tid : tail0 + (tid - nh);
     int32_t esr = 0, edr = 0;
-    if (has_edge) esr = idx ? idx[er] : (int32_t)er;
+    if (has_edge) esr = idx[er];
     if (X && has_edge) edr = idx2[er];
     // a row's value: from the staged window when it lies there, else global memory
     auto read_row = [&](int32_t sr) -> R {
@@ -528,12 +515,7 @@ __device__ __forceinline__ void gather_vec_body(const GatherJob* __restrict__ jo
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t g = min(g0 + tid + (int64_t)u * bd, max(ng - 1, (int64_t)0));
-        if (idx) {
-          iv[u] = ldv<IV, NT>(reinterpret_cast<CIVP>(idx + a) + g);
-        } else {
-#pragma unroll
-          for (int k = 0; k < V; ++k) iv[u][k] = (int)(a + g * V + k);
-        }
+        iv[u] = ldv<IV, NT>(reinterpret_cast<CIVP>(idx + a) + g);
       }
     };
     IV iv[U];

@@ -3,6 +3,7 @@
 // allocate device memory during the call).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -51,7 +52,10 @@ extern "C" int hx_backward_noalloc(hx_req* r, const void* g_send, void* g_x, voi
   hx::SegSumJob job{static_cast<const char*>(g_send), static_cast<char*>(g_x), r->bt_ptr.as<int32_t>(),
                     r->bt_perm.as<int32_t>(), r->n_local};
   job.win_rows = r->E1;  // the terms are the request's own send-slot gradients
-  const hx::Sched sc = hx::default_sched(hx::KIND_SEGSUM, (int)r->row_bytes);
+  hx::Sched sc = hx::default_sched(hx::KIND_SEGSUM, (int)r->row_bytes, hx::req_sched_for(r, hx::PH_BWD));
+  // many rows: the tiles the documented limit is stated in
+  const int limit_rows = std::min(512, std::max(64, (64 << 10) / (int)r->row_bytes));
+  if (sc.tile_rows > limit_rows || r->n_local / limit_rows >= 2 * hx::device_cus()) sc.tile_rows = limit_rows;
   return hx::launch_segsum_in_area(job, r->dtype, (int)r->row_bytes, sc, area, HX_NOALLOC_SCRATCH_BYTES,
                                    (hipStream_t)stream);
 }

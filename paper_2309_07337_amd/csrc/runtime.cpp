@@ -142,53 +142,106 @@ int device_lds_per_block() {
   return cached[dev];
 }
 
-Sched default_sched(int kind, int row_bytes) {
+// The default schedule of a phase.  The lines lie where sweeps over row sizes
+// put them (4 to 256 bytes; 40 uneven requests of 76 to 131 MB a buffer, worlds
+// of 509 to 4096 ranks and 18 to 600 MB a phase); us a call, the other side of
+// a line first.
+Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
+  constexpr int64_t kL2 = 4 << 20;  // one XCD's
+  const int rb = std::max(row_bytes, 1);
+  const bool one = rb == 4 || rb == 8;
+  const bool pow2 = (rb & (rb - 1)) == 0;
+  // streaming hints, for phases that move more than this: what a world's phase
+  // reads was just written by the one before and is still in the 256 MB
+  // Infinity Cache (copies of 400 MB 76 -> 63 without), a request's was not
+  // (copies of 262 MB 58 -> 51 with)
+  const bool streams = w.bytes >= (w.fresh ? (int64_t)1 << 30 : (int64_t)64 << 20);
   Sched s;
-  s.block_threads = 256;
-  s.blocks_per_cu = 8;
-  s.nontemporal = 0;
-  s.per_neighbor = 0;
-  // about 32 KiB of output per tile
-  int rows = std::max(64, (32 << 10) / std::max(row_bytes, 1));
-  rows = std::min(rows, 8192);
-  // segmented sum: the largest tile whose row pointers are staged in LDS
-  if (kind == KIND_SEGSUM) rows = std::min(kStageRows, std::max(64, (64 << 10) / std::max(row_bytes, 1)));
-  s.tile_rows = rows;
-  // rows in flight per lane: 4, except for rows of 16 bytes or less, whose
-  // gathers measure best with 1 (more lanes, not more rows per lane)
-  s.unroll = row_bytes <= 16 && kind == KIND_GATHER ? 1 : 4;
-  // segmented sums: 512 lanes, 1024 for rows of 64 B and more (more terms in
-  // flight per chunk; such rows read no term windows by default)
-  if (kind == KIND_SEGSUM) s.block_threads = row_bytes >= 64 ? 1024 : 512;
-  // rows of 64 B and more: push by default (on gfx950 scattered full-line
-  // writes run as fast as scattered reads, and the push form reads each
-  // source row once instead of once per slot); short rows: pull
-  s.push_pack = kind == KIND_GATHER && row_bytes >= 64 ? 1 : 0;
-  // short rows: gathers and segmented sums read their jobs' windows from LDS
-  s.lds_window = row_bytes <= 16 ? 1 : 0;
-  // gathers without windows: one workgroup per tile (a window would be
-  // staged again by every workgroup); segmented sums of rows of 64 B and
-  // more: the same, two terms per lane in flight
-  if (kind == KIND_GATHER && !s.lds_window) s.blocks_per_cu = kOneShotBpc;
-  if (kind == KIND_SEGSUM && row_bytes >= 64) {
-    s.blocks_per_cu = kOneShotBpc;
-    s.unroll = 2;
-  }
-  // gathers of 4- and 8-byte rows: 16-byte row groups per lane, one
-  // workgroup of 512 lanes per (up to) 16384-row tile, the job's window (if
-  // it has one) staged once per tile while the tile's indices are in flight
-  if (kind == KIND_GATHER && (row_bytes == 4 || row_bytes == 8)) {
-    s.pair_rows = 1;
-    s.tile_rows = 16384;
+  s.blocks_per_cu = kOneShotBpc;
+  s.unroll = 4;
+  if (kind == KIND_SEGSUM) {
+    if (rb >= 64) {
+      // the largest tile whose row pointers are staged in LDS; 1024 lanes: more
+      // terms in flight per chunk, two each; a term is read once, so its loads
+      // stream (128-B rows, 2.2 GB: 448 -> 422; 64 to 256 B: 5 to 12 %)
+      s.tile_rows = std::min(kStageRows, std::max(64, (64 << 10) / rb));
+      s.block_threads = 1024;
+      s.unroll = 2;
+      s.nontemporal = streams ? 1 : 0;
+    } else if (one && w.source <= kL2) {
+      // one row per lane, terms from LDS windows (1024 ranks staged backward,
+      // FP32 189 -> 145, in tiles of 4096 rows 168: forwarders stage their
+      // windows twice; 509 ranks plain, FP64 63 -> 48)
+      s.pair_rows = 1;
+      s.lds_window = 1;
+      s.tile_rows = 8192;
+      s.block_threads = 256;
+    } else {
+      // a persistent grid of 512-row tiles before: 8 B 143 -> 104, 12 B 101 ->
+      // 75, 16 B 91 -> 77, 32 B 71 -> 65, 40 B 76 -> 70, 56 B 77 -> 64
+      s.tile_rows = one ? kStageRows : 256;
+      s.block_threads = rb < 40 ? 256 : 512;
+      if (one) s.unroll = 2;
+    }
+  } else if (w.identity) {
+    // contiguous copies: 16 or 32 KiB a workgroup (one row per lane before:
+    // 8-B rows, 153 MB: 40 -> 31)
+    s.block_threads = streams ? 512 : 256;
+    s.tile_rows = std::max(1, (streams ? 32 << 10 : 16 << 10) / rb);
+    s.nontemporal = streams ? 1 : 0;
+  } else if (w.phase == PH_PACK && (rb >= 64 || w.source > kL2)) {
+    // push: scattered full-line writes run as fast as scattered reads, and each
+    // source row is read once; of shorter rows where the source is beyond the
+    // L2, so that a pull's reads of parts of a line would go to memory (8 B
+    // 103 -> 90, 16 B 70 -> 59, 24 B 68 -> 58, 40 B 67 -> 59; from a rank's own
+    // rows, in the L2, 24 B 66 pulled and 85 pushed).  Its writes merge in the
+    // L2: no streaming hints (24 B 58, 152 with)
+    s.push_pack = 1;
+    s.tile_rows = rb <= 48 ? kStageRows : std::max(64, std::min(256, (32 << 10) / rb));
+    s.block_threads = pow2 ? 256 : 512;
+  } else if (one) {
+    s.pair_rows = 1;  // 16-byte row groups per lane
+    if (w.phase == PH_PACK) {
+      // a rank's own rows are hot in the L2: no window (4096 ranks 200 -> 165)
+      s.nontemporal = w.bytes >= (int64_t)256 << 20 ? 1 : 0;
+      s.tile_rows = s.nontemporal ? 4096 : 2048;
+      s.block_threads = s.nontemporal ? 512 : 256;
+      if (rb == 4) s.unroll = 2;
+    } else if (w.rows >= 1 << 23) {
+      // the job's window (if it has one) staged once per (up to) 16384-row tile
+      // while the tile's indices are in flight (redistribution and unpack of 39
+      // M rows 476 -> 460, of 9 M FP32 ones 97 -> 89)
+      s.lds_window = 1;
+      s.tile_rows = 16384;
+      s.block_threads = 512;
+    } else {
+      // what the windows hold is in the caches anyhow (4.7 M rows: 86 -> 66)
+      s.tile_rows = 1024;
+      s.block_threads = 256;
+    }
+  } else {
+    // (24-B rows, packs 73 -> 66, redistribution and unpack 160 -> 150; 12 B
+    // 45 -> 42)
+    s.tile_rows = rb <= 16 ? 2048 : rb <= 32 ? 512 : 256;
     s.block_threads = 512;
-    s.blocks_per_cu = kOneShotBpc;
-    s.unroll = 4;
+  }
+  // few rows: smaller tiles, down to 4 KiB of output, until every CU has two
+  // (a window would then be staged by every one of them)
+  const int64_t cus = device_cus();
+  const int least = std::max(16, (4 << 10) / rb);
+  if (w.rows > 0 && w.jobs < cus && s.tile_rows > least && w.rows / s.tile_rows < 2 * cus) {
+    while (s.tile_rows > least && w.rows / s.tile_rows < 2 * cus) s.tile_rows = std::max(least, s.tile_rows / 2);
+    s.lds_window = 0;
+    if (!s.push_pack && kind == KIND_GATHER) {
+      s.block_threads = 256;
+      s.unroll = 1;
+    }
   }
   return s;
 }
 
-Sched resolve_sched(const hx_sched* p, int kind, int row_bytes) {
-  Sched s = default_sched(kind, row_bytes);
+Sched resolve_sched(const hx_sched* p, int kind, int row_bytes, const SchedFor& w) {
+  Sched s = default_sched(kind, row_bytes, w);
   if (!p) return s;
   if (p->tile_rows > 0) s.tile_rows = p->tile_rows;
   if (p->block_threads > 0) s.block_threads = p->block_threads;
@@ -286,13 +339,28 @@ int hx::build_phase_table(int phase, const Sched& sc, int dtype, int row_bytes, 
   return build_gather_table(g, dtype, row_bytes, sc, t, phase);
 }
 
+SchedFor hx::req_sched_for(const hx_req* r, int phase) {
+  const int64_t rb = (int64_t)r->row_bytes;
+  SchedFor w;
+  w.phase = phase;
+  w.jobs = 1;
+  w.bytes = r->bytes[phase];
+  switch (phase) {
+    case PH_PACK: w.rows = r->E1; w.source = r->n_local * rb; break;
+    case PH_REDIST: w.rows = r->E2; w.source = r->R1 * rb; break;
+    case PH_UNPACK: w.rows = r->H; w.source = (r->R1 + r->R2) * rb; w.identity = r->unpack_identity; break;
+    default: w.rows = r->n_local; w.source = r->E1 * rb; break;
+  }
+  return w;
+}
+
 static int build_req_tables(hx_req* r) {
   if (r->tables_built) return HX_SUCCESS;
   for (int ph = 0; ph < 4; ++ph) {
     std::vector<GatherJob> g;
     std::vector<SegSumJob> s;
     const int kind = ph == PH_BWD ? KIND_SEGSUM : KIND_GATHER;
-    const Sched sc = default_sched(kind, (int)r->row_bytes);
+    const Sched sc = default_sched(kind, (int)r->row_bytes, req_sched_for(r, ph));
     HX_TRY(req_phase_jobs(r, ph, sc, &g, &s));
     HX_TRY(build_phase_table(ph, sc, r->dtype, (int)r->row_bytes, g, s, &r->lt[ph]));
   }
@@ -530,7 +598,7 @@ extern "C" int hx_req_bind_grad(hx_req* r, const void* g_send, void* g_x) {
   r->lt[PH_BWD] = LaunchTable();
   std::vector<GatherJob> g;
   std::vector<SegSumJob> s;
-  const Sched sc = default_sched(KIND_SEGSUM, (int)r->row_bytes);
+  const Sched sc = default_sched(KIND_SEGSUM, (int)r->row_bytes, req_sched_for(r, PH_BWD));
   HX_TRY(req_phase_jobs(r, PH_BWD, sc, &g, &s));
   HX_TRY(build_segsum_table(s, r->dtype, (int)r->row_bytes, sc, &r->lt[PH_BWD]));
   return HX_SUCCESS;
@@ -608,13 +676,50 @@ int hx::batch_build_table(const hx_batch* b, int phase, const Sched& sc, LaunchT
   return build_phase_table(phase, sc, b->dtype, (int)b->row_bytes, ga, sa, t);
 }
 
+SchedFor hx::batch_sched_for(const hx_batch* b, int phase) {
+  SchedFor w;
+  if (b->world) {
+    // a rank's share: its own rows (3-step: its node's), arena or slots
+    const int64_t rb = (int64_t)b->row_bytes, R = std::max(b->R, 1);
+    w.jobs = b->R;
+    w.bytes = b->bytes[phase];
+    w.fresh = true;
+    const int64_t node = b->variant == HX_LOCALITY_3STEP ? b->ppn : 1;
+    switch (phase) {
+      case PH_PACK: w.rows = b->E1_tot; w.source = b->n / R * node * rb; break;
+      case PH_REDIST: w.rows = b->E2_tot; w.source = b->R1_tot / R * rb; break;
+      case PH_UNPACK: w.rows = b->H_tot; w.source = b->R2_tot / R * rb; w.identity = b->unpack_identity; break;
+      default:
+        w.rows = b->n;
+        // (the closed-form adjoint reads every rank's halo)
+        w.source = b->unpack_identity || b->staged_bwd ? b->E1_tot / R * rb : b->H_tot * rb;
+        break;
+    }
+  } else {
+    double bytes = 0, weighted = 0;
+    for (const hx_req* r : b->members) {
+      const SchedFor m = req_sched_for(r, phase);
+      w.rows += m.rows;
+      w.jobs += m.rows > 0 ? 1 : 0;
+      w.bytes += m.bytes;
+      w.identity = m.identity;
+      bytes += (double)m.bytes;
+      weighted += (double)m.bytes * (double)m.source;
+    }
+    w.source = bytes > 0 ? (int64_t)(weighted / bytes) : 0;
+    for (const hx_req* r : b->members) w.identity = w.identity && r->unpack_identity;
+  }
+  w.phase = phase;
+  return w;
+}
+
 // One launch per member: the plain form, with the library's default schedule.
 int hx::batch_build_plain(hx_batch* b, int phase) {
   b->plain[phase].clear();
   std::vector<std::vector<GatherJob>> g;
   std::vector<std::vector<SegSumJob>> s;
   const int kind = phase == PH_BWD ? KIND_SEGSUM : KIND_GATHER;
-  const Sched sc = default_sched(kind, (int)b->row_bytes);
+  const Sched sc = default_sched(kind, (int)b->row_bytes, batch_sched_for(b, phase));
   HX_TRY(batch_phase_jobs(b, phase, sc, false, &g, &s));
   const size_t nm = std::max(g.size(), s.size());
   b->plain[phase].resize(nm);
@@ -740,10 +845,10 @@ int hx::batch_init_scheds(hx_batch* b, const hx_sched* sched) {
     b->sched_from_cache[ph] = sched == nullptr;
     const int kind = ph == PH_BWD ? KIND_SEGSUM : KIND_GATHER;
     if (sched) {
-      b->sched[ph] = resolve_sched(sched, kind, (int)b->row_bytes);
+      b->sched[ph] = resolve_sched(sched, kind, (int)b->row_bytes, batch_sched_for(b, ph));
     } else {
       Sched s;
-      b->sched[ph] = cache_lookup(cache_key(b, ph), &s) ? s : default_sched(kind, (int)b->row_bytes);
+      b->sched[ph] = cache_lookup(cache_key(b, ph), &s) ? s : default_sched(kind, (int)b->row_bytes, batch_sched_for(b, ph));
     }
   }
   if (batch_has_ready(b)) b->sched[PH_PACK].push_pack = 0;
@@ -784,7 +889,7 @@ extern "C" int hx_batch_set_sched(hx_batch* b, int phase, const hx_sched* sched)
   if (b->active) return fail(HX_ERR_STATE, "batch is active");
   const int kind = phase == PH_BWD ? KIND_SEGSUM : KIND_GATHER;
   const Sched old = b->sched[phase];
-  b->sched[phase] = resolve_sched(sched, kind, (int)b->row_bytes);
+  b->sched[phase] = resolve_sched(sched, kind, (int)b->row_bytes, batch_sched_for(b, phase));
   b->sched_from_cache[phase] = false;
   if (phase == PH_PACK && batch_has_ready(b)) b->sched[PH_PACK].push_pack = 0;
   const int rc = batch_prepare(b);
@@ -996,7 +1101,10 @@ extern "C" int hx_batch_tune(hx_batch* b, void* stream) {
     if (b->lt[ph].empty()) continue;
     const int kind = ph == PH_BWD ? KIND_SEGSUM : KIND_GATHER;
     const int rb = (int)b->row_bytes;
-    const int base = default_sched(kind, rb).tile_rows;
+    // tiles around 32 KiB of output (segmented sums: the largest staged tile)
+    const int base = kind == KIND_SEGSUM ? std::min(kStageRows, std::max(64, (64 << 10) / rb))
+                     : rb == 4 || rb == 8 ? 16384
+                                          : std::min(8192, std::max(64, (32 << 10) / rb));
     Sched best = b->sched[ph];
     float best_ms = 1e30f;
     auto consider = [&](const Sched& c) {

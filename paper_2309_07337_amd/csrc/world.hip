@@ -458,6 +458,7 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
   if (!b) return fail(HX_ERR_NOMEM, "out of host memory");
   b->world = true;
   b->variant = p->variant;
+  b->ppn = p->ppn;
   b->dtype = dtype;
   b->ncols = ncols;
   b->row_bytes = (size_t)ncols * dtype_bytes(dtype);
