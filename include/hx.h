@@ -509,6 +509,15 @@ int hx_batch_wait_plain(hx_batch* b, void* stream);
 int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out);
 int hx_batch_backward(hx_batch* b, void* stream);
 int hx_batch_backward_plain(hx_batch* b, void* stream);
+/* A world's Start + Wait, or its backward, with a copy in and a copy out made
+ * by the same kernels: as if x had been copied into the bound x_global before
+ * and halo_all into halo after (g_in into the bound gradients before, the
+ * bound g_out into g_out after).  NULL, or the bound buffer: no copy.  The
+ * buffers have the bound ones' shapes, do not overlap them, and are aligned as
+ * they are modulo 16 bytes (HX_ERR_ARG otherwise, as for a batch that is no
+ * world).  HX_ERR_STATE while a Start is pending, or without bound gradients. */
+int hx_batch_exchange(hx_batch* b, const void* x, void* halo, void* stream);
+int hx_batch_adjoint(hx_batch* b, const void* g_in, void* g_out, void* stream);
 int hx_batch_tune(hx_batch* b, void* stream);
 /* hx_batch_launch_phase: launch the kernel of one phase alone
  *   (0 pack, 1 redistribution, 2 unpack, 3 backward) from the same launch

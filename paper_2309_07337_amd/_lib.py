@@ -43,7 +43,8 @@ EXPORTED = (
     "hx_plan_field_copy", "hx_plan_field_all", "hx_plan_describe", "hx_req_from_plan", "hx_start", "hx_wait", "hx_req_arena",
     "hx_req_bind_grad", "hx_req_enable_ready", "hx_backward", "hx_backward_noalloc", "hx_req_free", "hx_batch_init", "hx_batch_from_plan",
     "hx_batch_start", "hx_batch_wait", "hx_batch_start_plain", "hx_batch_wait_plain",
-    "hx_batch_bind_grad", "hx_batch_backward", "hx_batch_backward_plain", "hx_batch_tune",
+    "hx_batch_bind_grad", "hx_batch_backward", "hx_batch_backward_plain", "hx_batch_exchange", "hx_batch_adjoint",
+    "hx_batch_tune",
     "hx_batch_launch_phase", "hx_batch_get_sched", "hx_batch_set_sched", "hx_batch_set_replay", "hx_batch_get_replay",
     "hx_batch_arena", "hx_batch_arena_offset", "hx_batch_bytes", "hx_batch_free",
 )
@@ -123,6 +124,8 @@ def load() -> C.CDLL:
         "hx_batch_bind_grad": (C.c_int, [VP, VP, VP]),
         "hx_batch_backward": (C.c_int, [VP, VP]),
         "hx_batch_backward_plain": (C.c_int, [VP, VP]),
+        "hx_batch_exchange": (C.c_int, [VP, VP, VP, VP]),
+        "hx_batch_adjoint": (C.c_int, [VP, VP, VP, VP]),
         "hx_batch_tune": (C.c_int, [VP, VP]),
         "hx_req_enable_ready": (C.c_int, [VP, PP]),
         "hx_batch_launch_phase": (C.c_int, [VP, C.c_int, VP]),
@@ -501,6 +504,20 @@ def hx_batch_backward(b: Batch, stream=None) -> None:
 
 def hx_batch_backward_plain(b: Batch, stream=None) -> None:
     _check(load().hx_batch_backward_plain(b.ptr, _stream(stream)))
+
+
+def _ptr_or_none(t):
+    return None if t is None else t.data_ptr()
+
+
+def hx_batch_exchange(b: Batch, x=None, halo=None, stream=None) -> None:
+    """A world's Start + Wait; x copied into the bound vector, the bound halo into halo (tensors or None)."""
+    _check(load().hx_batch_exchange(b.ptr, _ptr_or_none(x), _ptr_or_none(halo), _stream(stream)))
+
+
+def hx_batch_adjoint(b: Batch, g_in=None, g_out=None, stream=None) -> None:
+    """A world's backward; g_in copied into the bound gradients, the bound g_out into g_out (tensors or None)."""
+    _check(load().hx_batch_adjoint(b.ptr, _ptr_or_none(g_in), _ptr_or_none(g_out), _stream(stream)))
 
 
 def hx_batch_launch_phase(b: Batch, phase: int, stream=None) -> None:

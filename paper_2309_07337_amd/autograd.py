@@ -14,8 +14,10 @@ Buffers and copies.  The library reads ``ex.x`` and writes ``ex.halo``
 (forward), reads ``ex.g_halo`` and writes ``ex.g_x`` (backward), all bound
 once.  ``halo_gather(x, ex)`` copies ``x`` into ``ex.x`` unless ``x`` is
 ``ex.x`` itself, and returns a fresh tensor (a copy of ``ex.halo``), so a
-later forward on the same exchange cannot change an earlier output.  The
-zero-copy path: write the input into ``ex.x`` in place, call
+later forward on the same exchange cannot change an earlier output.  Where a
+tensor is laid out as the buffer it meets (type, device, shape, contiguous,
+alignment), the copy is made by the exchange's own kernels (hx_batch_exchange,
+hx_batch_adjoint).  The zero-copy path: write the input into ``ex.x`` in place, call
 ``halo_gather(ex.x, ex, copy_out=False)`` (the output then IS ``ex.halo``),
 and give the backward its gradient in ``ex.g_halo`` (a gradient tensor that
 is ``ex.g_halo`` is not copied).  An aliased output is guarded: its backward
@@ -59,16 +61,46 @@ class HaloExchange:
         return self.g_x
 
 
+def _beside(t: torch.Tensor, bound: torch.Tensor) -> bool:
+    """Whether the library may copy between t and a bound buffer itself."""
+    return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.layout == torch.strided and t.dtype == bound.dtype
+            and t.device == bound.device and t.shape == bound.shape and t.is_contiguous() and not t.is_neg()
+            and t.numel() > 0 and (t.data_ptr() - bound.data_ptr()) % 16 == 0
+            and t.untyped_storage().data_ptr() != bound.untyped_storage().data_ptr())
+
+
+def _copy_in(t: torch.Tensor, bound: torch.Tensor):
+    """t if the library copies it into the bound buffer; otherwise copied here."""
+    if _beside(t, bound):
+        return t
+    bound.copy_(t)
+    return None
+
+
+def _copy_out(bound: torch.Tensor, run):
+    """A fresh copy of the bound buffer after run(tensor or None)."""
+    out = torch.empty_like(bound)
+    if _beside(out, bound):
+        run(out)
+        return out
+    run(None)
+    return bound.clone()
+
+
 class HaloGather(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x: torch.Tensor, ex: HaloExchange, copy_out: bool = True):
-        if x.data_ptr() != ex.x.data_ptr():
-            ex.x.copy_(x)
-        ex.forward()
+        src = _copy_in(x, ex.x) if x.data_ptr() != ex.x.data_ptr() else None
         ctx.ex = ex
-        ctx.generation = ex.generation
         ctx.copy_out = copy_out
-        return ex.halo.clone() if copy_out else ex.halo.detach()
+        if copy_out:
+            y = _copy_out(ex.halo, lambda out: L.hx_batch_exchange(ex.batch, src, out))
+        else:
+            L.hx_batch_exchange(ex.batch, src)
+            y = ex.halo.detach()
+        ex.generation += 1
+        ctx.generation = ex.generation
+        return y
 
     @staticmethod
     def backward(ctx, g: torch.Tensor):
@@ -76,10 +108,9 @@ class HaloGather(torch.autograd.Function):
         if not ctx.copy_out and ex.generation != ctx.generation:
             raise RuntimeError("halo_gather: the aliased output of this forward was overwritten by a later "
                                "forward on the same exchange before its backward ran")
-        if g.data_ptr() != ex.g_halo.data_ptr() or not g.is_contiguous():
-            ex.g_halo.copy_(g)
-        ex.backward()
-        return ex.g_x.clone(), None, None
+        own = g.data_ptr() == ex.g_halo.data_ptr() and g.is_contiguous()
+        src = None if own else _copy_in(g, ex.g_halo)
+        return _copy_out(ex.g_x, lambda out: L.hx_batch_adjoint(ex.batch, src, out)), None, None
 
 
 def halo_gather(x: torch.Tensor, ex: HaloExchange, copy_out: bool = True) -> torch.Tensor:

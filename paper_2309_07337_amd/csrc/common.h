@@ -225,8 +225,13 @@ inline int64_t segsum_area_max_tiles(size_t area_bytes) {
 }
 int build_scatter_table(const std::vector<SegSumJob>& jobs, int dtype, int row_bytes,
                         const Sched& s, LaunchTable* t, int tag = TAG_PACK);
-// deliver: rows also go to the jobs' second destinations (t.deliver tables).
-int launch_table(const LaunchTable& t, hipStream_t stream, bool deliver = false);
+struct LaunchOpt {
+  bool deliver = false;  // rows also go to the jobs' second destinations (t.deliver tables)
+  // a caller's buffers beside the named ones (kern::Beside); src: push packs
+  // and copies that deliver, dst: copies and segmented sums
+  int64_t src = 0, dst = 0;
+};
+int launch_table(const LaunchTable& t, hipStream_t stream, const LaunchOpt& o = LaunchOpt());
 
 // Split a gather job per message (per neighbor) using the message counts.
 void split_gather_by_counts(const GatherJob& j, const std::vector<int32_t>& counts,

@@ -101,6 +101,8 @@ struct hx_batch {
   std::vector<hx::LaunchTable> plain[4];
   bool plain_built[4] = {false, false, false, false};
   hx::LaunchTable lt_back[2];               // the backward's simulated transfers: reverse of stage 1, of stage 2
+  hx::DevMem gidx_from1;                     // plain worlds: halo_all row -> the send slot it was delivered from
+  hx::LaunchTable lt_back_copy;              // plain worlds: a caller's halo gradients into the bound ones and back
   int replay = HX_REPLAY_GRAPH;             // as set (hx_batch_set_replay)
   bool active = false;
   bool tuning = false;                      // hx_batch_tune running: candidates skip completion counters
@@ -156,13 +158,16 @@ int batch_prepare(hx_batch* b);
 inline bool sim_transfer(const hx_batch* b) { return b->world && (b->flags & HX_WORLD_SIM_TRANSFER); }
 int batch_run_start(hx_batch* b, hipStream_t s);
 int batch_run_wait(hx_batch* b, hipStream_t s);
-int batch_run_backward(hx_batch* b, hipStream_t s);
+// g_in, g_out: a caller's buffers beside the bound ones (bytes from them; 0: none)
+int batch_run_backward(hx_batch* b, hipStream_t s, int64_t g_in = 0, int64_t g_out = 0);
 int batch_init_scheds(hx_batch* b, const hx_sched* sched);
 int world_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
                      std::vector<std::vector<GatherJob>>* g, std::vector<std::vector<SegSumJob>>* s);
 
 // Builds the closed-form adjoint of a locality world, once.
 int world_adjoint(hx_batch* b);
+// Builds gidx_from1 of a plain world, once.
+int world_from_map(hx_batch* b);
 
 // Device helpers implemented in plan.hip.
 int dev_exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, hipStream_t s);  // out[n] = total

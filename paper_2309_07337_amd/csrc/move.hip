@@ -263,7 +263,8 @@ int build_gather_table(const std::vector<GatherJob>& jobs, int dtype, int row_by
   if (t->identity) t->vec16 = 0;
   t->deliver = 1;
   for (const auto& j : w)
-    if (j.nrows > 0 && (j.dst2 == nullptr || j.idx == nullptr)) t->deliver = 0;
+    if (j.nrows > 0 && j.dst2 == nullptr) t->deliver = 0;
+  if (t->identity && row_bytes / t->vec_bytes > kern::kFlatMaxVec) t->deliver = 0;
   for (const auto& j : w)
     if (j.nrows > 0 && j.win_rows > 0 && !j.win_all) t->partial_win = 1;
   return HX_SUCCESS;
@@ -406,12 +407,12 @@ int build_scatter_table(const std::vector<SegSumJob>& jobs, int dtype, int row_b
   return fill_tile_terms(t);
 }
 
-int launch_table(const LaunchTable& t, hipStream_t s, bool deliver) {
+int launch_table(const LaunchTable& t, hipStream_t s, const LaunchOpt& o) {
   if (t.ntiles == 0) return HX_SUCCESS;
-  if (deliver && !t.deliver) return fail(HX_ERR_STATE, "a launch table without second destinations");
-  if (t.kind == KIND_GATHER) launch_gather_kernels(t, s, deliver);
-  else if (t.kind == KIND_SCATTER) launch_scatter_kernels(t, s, deliver);
-  else launch_segsum_kernels(t, s);
+  if (o.deliver && !t.deliver) return fail(HX_ERR_STATE, "a launch table without second destinations");
+  if (t.kind == KIND_GATHER) launch_gather_kernels(t, s, o);
+  else if (t.kind == KIND_SCATTER) launch_scatter_kernels(t, s, o);
+  else launch_segsum_kernels(t, s, o);
   HX_HIP(hipGetLastError());
   return HX_SUCCESS;
 }

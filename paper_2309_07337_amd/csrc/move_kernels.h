@@ -64,6 +64,17 @@ __device__ __forceinline__ void stv(P p, T v) {
   else *p = v;
 }
 
+// A caller's buffers beside the ones a launch table names (worlds, see
+// hx_batch_exchange), in bytes from them, multiples of 16; 0: none.  src: read
+// in place of the named buffer, which gets a copy of what it holds; dst: gets a
+// copy of what is written to the named one.  The copies are stores of rows that
+// the kernel has in registers or in the L2; made before and after it they are
+// passes of their own over memory (a training step of 2.1 M rows of 256 bytes:
+// COPY_T).
+struct Beside {
+  int64_t src, dst;
+};
+
 // Contiguous tile range of this workgroup; workgroups of one XCD get
 // neighbouring ranges.  gridDim.x is a multiple of 8.
 __device__ __forceinline__ void tile_range(int64_t ntiles, int64_t* t0, int64_t* t1) {
@@ -272,14 +283,16 @@ constexpr int kFlatRows = 2048;
 struct FlatDiv {
   uint32_t nv, m;
   __device__ __forceinline__ explicit FlatDiv(int n) : nv((uint32_t)n), m(0xffffffffu / (uint32_t)n + 1u) {}
-  __device__ __forceinline__ uint32_t row(uint32_t v) const { return __umulhi(v, m); }
+  // (nv = 1: the multiplier is 2^32, which wraps to 0)
+  __device__ __forceinline__ uint32_t row(uint32_t v) const { return m ? __umulhi(v, m) : v; }
 };
 
 // Contiguous bytes (a multiple of VB, both ends VB-aligned) copied by the
 // workgroup: 16-byte vectors where source and destination are congruent,
-// else VB-byte ones.
+// else VB-byte ones.  beside != 0: to dp + beside too (a multiple of 16).
 template <int VB, bool NT>
-__device__ __forceinline__ void flat_copy(const HX_G char* __restrict__ sp, HX_G char* __restrict__ dp, int64_t bytes) {
+__device__ __forceinline__ void flat_copy(const HX_G char* __restrict__ sp, HX_G char* __restrict__ dp, int64_t bytes,
+                                          int64_t beside) {
   using S = typename RawVec<VB>::type;
   constexpr int UC = 8;  // loads in flight per lane
   auto stream = [&](auto zero, int64_t lo, int64_t hi) {  // vectors of [lo, hi) bytes
@@ -297,7 +310,10 @@ __device__ __forceinline__ void flat_copy(const HX_G char* __restrict__ sp, HX_G
 #pragma unroll
       for (int u = 0; u < UC; ++u) {
         const int64_t k = i + (int64_t)u * blockDim.x;
-        if (k < n) stv<W, NT>(b + k, c[u]);
+        if (k < n) {
+          stv<W, NT>(b + k, c[u]);
+          if (beside != 0) stv<W, NT>(reinterpret_cast<HX_G W*>(dp + lo + beside) + k, c[u]);
+        }
       }
     }
   };
@@ -319,7 +335,7 @@ __device__ __forceinline__ void flat_copy(const HX_G char* __restrict__ sp, HX_G
 // Jobs that copy their rows in order (the plain unpack), whatever the row size.
 template <int VB, bool NT>
 __device__ __forceinline__ void copy_body(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts,
-                                          int njobs, int64_t ntiles, int tile_rows, int row_bytes) {
+                                          int njobs, int64_t ntiles, int tile_rows, int row_bytes, Beside also) {
   int64_t t0, t1;
   tile_range(ntiles, &t0, &t1);
   if (t0 >= t1) return;
@@ -329,7 +345,55 @@ __device__ __forceinline__ void copy_body(const GatherJob* __restrict__ jobs, co
     const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
     flat_copy<VB, NT>((const HX_G char*)jobs[j].src + r0 * row_bytes, (HX_G char*)jobs[j].dst + r0 * row_bytes,
-                      (r1 - r0) * row_bytes);
+                      (r1 - r0) * row_bytes, also.dst);
+  }
+}
+
+// The copy into the named source and the reverse transfer in one pass over the
+// caller's rows: row r goes to row r of src and to row idx2[r] of dst2.
+template <int VB, int U>
+__device__ __forceinline__ void copy_deliver_body(const GatherJob* __restrict__ jobs, const int64_t* __restrict__ ts,
+                                                  int njobs, int64_t ntiles, int tile_rows, int nv, Beside also) {
+  using V = typename RawVec<VB>::type;
+  const FlatDiv div(nv);
+  int64_t t0, t1;
+  tile_range(ntiles, &t0, &t1);
+  if (t0 >= t1) return;
+  int j = find_job(ts, njobs, t0);
+  const int bd = blockDim.x, tid = threadIdx.x;
+  const int64_t rb = (int64_t)nv * VB;
+  for (int64_t t = t0; t < t1; ++t) {
+    while (t >= ts[j + 1]) ++j;
+    const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
+    const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
+    const HX_G char* __restrict__ in = (const HX_G char*)(jobs[j].src + also.src);
+    HX_G char* __restrict__ named = (HX_G char*)const_cast<char*>(jobs[j].src);
+    HX_G char* __restrict__ dst2 = (HX_G char*)jobs[j].dst2;
+    const HX_G int32_t* __restrict__ idx2 = (const HX_G int32_t*)jobs[j].idx2;
+    for (int64_t rc = r0; rc < r1; rc += kFlatRows) {
+      const int nvec = (int)min((int64_t)kFlatRows, r1 - rc) * nv;
+      const HX_G V* __restrict__ sp = reinterpret_cast<const HX_G V*>(in + rc * rb);
+      HX_G V* __restrict__ dp = reinterpret_cast<HX_G V*>(named + rc * rb);
+      for (int base = tid; base < nvec; base += bd * U) {
+        V v[U];
+        HX_G V* to[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const uint32_t k = (uint32_t)min(base + u * bd, nvec - 1);  // valid load, no branch
+          const uint32_t r = div.row(k);
+          to[u] = reinterpret_cast<HX_G V*>(dst2 + (int64_t)idx2[rc + r] * rb) + (k - r * (uint32_t)nv);
+          v[u] = sp[k];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k = base + u * bd;
+          if (k < nvec) {
+            stv<V, false>(dp + k, v[u]);
+            stv<V, false>(to[u], v[u]);
+          }
+        }
+      }
+    }
   }
 }
 
@@ -614,7 +678,7 @@ constexpr int STAGE_ENTRIES = kStageEntries;
 template <int VB, int NV, int LPR, int U, bool NT, bool X>
 __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                              const int2* __restrict__ te, int njobs, int64_t ntiles,
-                                             int tile_rows, int nv_rt) {
+                                             int tile_rows, int nv_rt, Beside also) {
   using V = typename RawVec<VB>::type;
   const int nv = NV > 0 ? NV : nv_rt;
   constexpr int NVPL = NV > 0 ? (NV + LPR - 1) / LPR : 1;
@@ -632,7 +696,7 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
   int j = find_job(ts, njobs, t0);
   for (int64_t t = t0; t < t1; ++t) {
     while (t >= ts[j + 1]) ++j;
-    const HX_G char* __restrict__ in = (const HX_G char*)jobs[j].in;
+    const HX_G char* __restrict__ in = (const HX_G char*)(jobs[j].in + also.src);
     HX_G char* __restrict__ out = (HX_G char*)jobs[j].out;
     const HX_G int32_t* __restrict__ ptr = (const HX_G int32_t*)jobs[j].ptr;
     const HX_G int32_t* __restrict__ idx = (const HX_G int32_t*)jobs[j].idx;
@@ -642,6 +706,10 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
     const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, nrows);
     const size_t rb = (size_t)nv * VB;
+    // (before the entries: they then find the rows in the L2)
+    if (also.src != 0)
+      flat_copy<VB, false>(in + r0 * (int64_t)rb, (HX_G char*)const_cast<char*>(jobs[j].in) + r0 * (int64_t)rb,
+                           (r1 - r0) * (int64_t)rb, 0);
     if constexpr (NV > 0) {
       int32_t P0 = 0, ne = 0;
       bool stage_idx = false;
@@ -796,7 +864,7 @@ __device__ __forceinline__ void scatter_body(const SegSumJob* __restrict__ jobs,
 template <int VB, int U, bool NT, bool X>
 __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                                   const int2* __restrict__ te, int njobs, int64_t ntiles,
-                                                  int tile_rows, int nv) {
+                                                  int tile_rows, int nv, Beside also) {
   using V = typename RawVec<VB>::type;
   const FlatDiv div(nv);
   __shared__ int32_t s_ptr[STAGE_ROWS + 1];
@@ -811,7 +879,7 @@ __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ 
   const int64_t rb = (int64_t)nv * VB;
   for (int64_t t = t0; t < t1; ++t) {
     while (t >= ts[j + 1]) ++j;
-    const HX_G char* __restrict__ in = (const HX_G char*)jobs[j].in;
+    const HX_G char* __restrict__ in = (const HX_G char*)(jobs[j].in + also.src);
     HX_G char* __restrict__ out = (HX_G char*)jobs[j].out;
     const HX_G int32_t* __restrict__ ptr = (const HX_G int32_t*)jobs[j].ptr;
     const HX_G int32_t* __restrict__ idx = (const HX_G int32_t*)jobs[j].idx;
@@ -819,6 +887,10 @@ __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ 
     const HX_G int32_t* __restrict__ idx2 = X ? (const HX_G int32_t*)jobs[j].idx2 : nullptr;
     const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
+    // (before the entries: they then find the rows in the L2)
+    if (also.src != 0)
+      flat_copy<VB, false>(in + r0 * (int64_t)rb, (HX_G char*)const_cast<char*>(jobs[j].in) + r0 * (int64_t)rb,
+                           (r1 - r0) * (int64_t)rb, 0);
     const int nt = (int)(r1 - r0);
     const int2 er = te[t];
     const int32_t P0 = er.x;
@@ -894,6 +966,13 @@ __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ 
 // coalesced loads, so each row then costs one dependent global access (its
 // terms) instead of three.
 
+// A row's sum, also into the caller's buffer where there is one.
+template <class V, bool NT, class P>
+__device__ __forceinline__ void store_sum(P p, V v, const Beside& also) {
+  stv<V, NT>(p, v);
+  if (also.dst != 0) stv<V, NT>(reinterpret_cast<P>((uintptr_t)p + (uintptr_t)also.dst), v);
+}
+
 // Address of term t of a segmented sum: row t of the first input, or row
 // t - split of the second one.
 template <class CP>
@@ -904,7 +983,7 @@ __device__ __forceinline__ CP term_row(CP in, CP in2, int32_t split, int32_t t, 
 template <class T, int VB, int NV, int LPR, int U, bool NT>
 __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                             const int2* __restrict__ te, int njobs, int64_t ntiles,
-                                            int tile_rows, int nv_rt, int cap_terms) {
+                                            int tile_rows, int nv_rt, int cap_terms, Beside also) {
   using V = typename NumVec<T, VB>::type;
   const int nv = NV > 0 ? NV : nv_rt;
   constexpr int NVPL = NV > 0 ? (NV + LPR - 1) / LPR : 1;
@@ -986,7 +1065,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
                   V acc = reinterpret_cast<const V*>(term_row(in, in2, split, s_idx[a], rb))[vi];
                   for (int32_t d = 1; d < len; ++d)
                     acc = acc + reinterpret_cast<const V*>(term_row(in, in2, split, s_idx[a + d], rb))[vi];
-                  stv<V, NT>(dp + vi, acc);
+                  store_sum<V, NT>(dp + vi, acc, also);
                 }
               }
             }
@@ -1032,7 +1111,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
                 V acc = (V)(T)0;
                 if (len > 0) acc = s_val[a * NV + vi];
                 for (int d = 1; d < len; ++d) acc = acc + s_val[(a + d) * NV + vi];
-                stv<V, NT>(dp + vi, acc);
+                store_sum<V, NT>(dp + vi, acc, also);
               }
             }
           }
@@ -1083,7 +1162,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
 #pragma unroll
         for (int k = 0; k < NVPL; ++k) {
           const int vi = lane_v + k * LPR;
-          if (NV % LPR == 0 || vi < NV) stv<V, NT>(dp + vi, acc[k]);
+          if (NV % LPR == 0 || vi < NV) store_sum<V, NT>(dp + vi, acc[k], also);
         }
       }
       if (stage_ptr) __syncthreads();  // the next tile overwrites the staged indices
@@ -1098,7 +1177,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
             const V v = reinterpret_cast<const V*>(term_row(in, in2, split, ldv<int32_t, NT>(idx + e), rb))[vi];
             acc = (e == p0) ? v : acc + v;
           }
-          stv<V, NT>(dp + vi, acc);
+          store_sum<V, NT>(dp + vi, acc, also);
         }
       }
     }
@@ -1113,7 +1192,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
 template <class T, int VB, int U, bool NT>
 __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                                  const int2* __restrict__ te, int njobs, int64_t ntiles,
-                                                 int tile_rows, int nv, int cap_terms) {
+                                                 int tile_rows, int nv, int cap_terms, Beside also) {
   using V = typename NumVec<T, VB>::type;
   const FlatDiv div(nv);
   __shared__ int32_t s_ptr[STAGE_ROWS + 1];
@@ -1153,7 +1232,7 @@ __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ j
           const V v = reinterpret_cast<const V*>(term_row(in, in2, split, ldv<int32_t, NT>(idx + e), rb))[c];
           acc = e == p0 ? v : acc + v;
         }
-        stv<V, NT>(dp + k, acc);
+        store_sum<V, NT>(dp + k, acc, also);
       }
     };
     if (nt > STAGE_ROWS || ne > STAGE_ENTRIES || cap_terms <= 0) {
@@ -1206,7 +1285,7 @@ __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ j
         V acc = (V)(T)0;
         if (len > 0) acc = s_val[a * nv + c];
         for (int d = 1; d < len; ++d) acc = acc + s_val[(a + d) * nv + c];
-        stv<V, NT>(dp + k, acc);
+        store_sum<V, NT>(dp + k, acc, also);
       }
       __syncthreads();  // s_val, s_ptr and s_idx are reused next
       ra = rq;
@@ -1227,7 +1306,7 @@ __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ j
 // ---------------------------------------------------------------------------
 template <class T, int VB, int NV, int LPR, int U, bool NT>
 __device__ __forceinline__ void segsum_win_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
-                                                int njobs, int64_t ntiles, int tile_rows, int nv_rt) {
+                                                int njobs, int64_t ntiles, int tile_rows, int nv_rt, Beside also) {
   using V = typename NumVec<T, VB>::type;
   static_assert(NV > 0, "windowed segmented sums use fixed row shapes");
   constexpr int NVPL = (NV + LPR - 1) / LPR;
@@ -1321,7 +1400,7 @@ __device__ __forceinline__ void segsum_win_body(const SegSumJob* __restrict__ jo
 #pragma unroll
         for (int k = 0; k < NVPL; ++k) {
           const int vi = lane_v + k * LPR;
-          if (NV % LPR == 0 || vi < NV) stv<V, NT>(dp + vi, acc[k]);
+          if (NV % LPR == 0 || vi < NV) store_sum<V, NT>(dp + vi, acc[k], also);
         }
       }
     }
@@ -1344,7 +1423,7 @@ __device__ __forceinline__ void segsum_win_body(const SegSumJob* __restrict__ jo
 // ---------------------------------------------------------------------------
 template <class T, int U, int D, bool NT>
 __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
-                                                int njobs, int64_t ntiles, int tile_rows) {
+                                                int njobs, int64_t ntiles, int tile_rows, Beside also) {
   constexpr int RB = (int)sizeof(T);
   extern __shared__ __align__(16) unsigned char s_dyn[];
   int64_t t0, t1;
@@ -1465,7 +1544,7 @@ __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jo
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t r = base + tid + (int64_t)u * bd;
-        if (r < r1) stv<T, NT>(reinterpret_cast<HX_G T*>(out + r * RB), acc[u]);
+        if (r < r1) store_sum<T, NT>(reinterpret_cast<HX_G T*>(out + r * RB), acc[u], also);
       }
       if (more) {
 #pragma unroll
@@ -1483,8 +1562,8 @@ __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jo
 }  // namespace kern
 
 // Launchers implemented in the move_*.hip translation units.
-void launch_gather_kernels(const LaunchTable& t, hipStream_t s, bool deliver);
-void launch_scatter_kernels(const LaunchTable& t, hipStream_t s, bool deliver);
-void launch_segsum_kernels(const LaunchTable& t, hipStream_t s);
+void launch_gather_kernels(const LaunchTable& t, hipStream_t s, const LaunchOpt& o);
+void launch_scatter_kernels(const LaunchTable& t, hipStream_t s, const LaunchOpt& o);
+void launch_segsum_kernels(const LaunchTable& t, hipStream_t s, const LaunchOpt& o);
 
 }  // namespace hx

@@ -15,24 +15,24 @@ inline int unroll_bucket(int u) {
   return 4;
 }
 
-// Calls F::template go<VB, NV, LPR, U, NT>(t, s, nv) for the table's shape.
+// Calls F::template go<VB, NV, LPR, U, NT>(t, s, o, nv) for the table's shape.
 // Fixed shapes (one 16/8/4-byte vector per lane, LPR lanes per row) take
 // U in {1, 2, 4}; other row sizes use the flat forms.
 template <class F, int VB, int NV, int LPR>
-void by_unroll(const LaunchTable& t, hipStream_t s, int nv) {
+void by_unroll(const LaunchTable& t, hipStream_t s, const LaunchOpt& o, int nv) {
   const bool nt = t.sched.nontemporal != 0;
   switch (unroll_bucket(t.sched.unroll)) {
     case 1:
-      if (nt) F::template go<VB, NV, LPR, 1, true>(t, s, nv);
-      else F::template go<VB, NV, LPR, 1, false>(t, s, nv);
+      if (nt) F::template go<VB, NV, LPR, 1, true>(t, s, o, nv);
+      else F::template go<VB, NV, LPR, 1, false>(t, s, o, nv);
       break;
     case 2:
-      if (nt) F::template go<VB, NV, LPR, 2, true>(t, s, nv);
-      else F::template go<VB, NV, LPR, 2, false>(t, s, nv);
+      if (nt) F::template go<VB, NV, LPR, 2, true>(t, s, o, nv);
+      else F::template go<VB, NV, LPR, 2, false>(t, s, o, nv);
       break;
     default:
-      if (nt) F::template go<VB, NV, LPR, 4, true>(t, s, nv);
-      else F::template go<VB, NV, LPR, 4, false>(t, s, nv);
+      if (nt) F::template go<VB, NV, LPR, 4, true>(t, s, o, nv);
+      else F::template go<VB, NV, LPR, 4, false>(t, s, o, nv);
       break;
   }
 }
@@ -41,47 +41,47 @@ void by_unroll(const LaunchTable& t, hipStream_t s, int nv) {
 // flight); rows of more than kFlatMaxVec vectors (16 KiB and more, several
 // passes of a wavefront per row) take one wavefront per row.
 template <class F, int VB>
-void generic(const LaunchTable& t, hipStream_t s, int nv) {
+void generic(const LaunchTable& t, hipStream_t s, const LaunchOpt& o, int nv) {
   const bool nt = t.sched.nontemporal != 0;
   if (nv > kFlatMaxVec) {
-    if (nt) F::template go<VB, 0, 64, 1, true>(t, s, nv);
-    else F::template go<VB, 0, 64, 1, false>(t, s, nv);
+    if (nt) F::template go<VB, 0, 64, 1, true>(t, s, o, nv);
+    else F::template go<VB, 0, 64, 1, false>(t, s, o, nv);
     return;
   }
   switch (unroll_bucket(t.sched.unroll)) {
-    case 1: nt ? F::template flat<VB, 1, true>(t, s, nv) : F::template flat<VB, 1, false>(t, s, nv); break;
-    case 2: nt ? F::template flat<VB, 2, true>(t, s, nv) : F::template flat<VB, 2, false>(t, s, nv); break;
-    default: nt ? F::template flat<VB, 4, true>(t, s, nv) : F::template flat<VB, 4, false>(t, s, nv); break;
+    case 1: nt ? F::template flat<VB, 1, true>(t, s, o, nv) : F::template flat<VB, 1, false>(t, s, o, nv); break;
+    case 2: nt ? F::template flat<VB, 2, true>(t, s, o, nv) : F::template flat<VB, 2, false>(t, s, o, nv); break;
+    default: nt ? F::template flat<VB, 4, true>(t, s, o, nv) : F::template flat<VB, 4, false>(t, s, o, nv); break;
   }
 }
 
 template <class F, int VB>
-void by_shape(const LaunchTable& t, hipStream_t s) {
+void by_shape(const LaunchTable& t, hipStream_t s, const LaunchOpt& o) {
   const int nv = t.row_bytes / VB;
   if constexpr (VB == 16) {
     switch (nv) {
-      case 1: return by_unroll<F, 16, 1, 1>(t, s, nv);
-      case 2: return by_unroll<F, 16, 2, 2>(t, s, nv);
-      case 4: return by_unroll<F, 16, 4, 4>(t, s, nv);
-      case 8: return by_unroll<F, 16, 8, 8>(t, s, nv);
-      case 16: return by_unroll<F, 16, 16, 16>(t, s, nv);
-      case 32: return by_unroll<F, 16, 32, 32>(t, s, nv);
-      case 64: return by_unroll<F, 16, 64, 64>(t, s, nv);
+      case 1: return by_unroll<F, 16, 1, 1>(t, s, o, nv);
+      case 2: return by_unroll<F, 16, 2, 2>(t, s, o, nv);
+      case 4: return by_unroll<F, 16, 4, 4>(t, s, o, nv);
+      case 8: return by_unroll<F, 16, 8, 8>(t, s, o, nv);
+      case 16: return by_unroll<F, 16, 16, 16>(t, s, o, nv);
+      case 32: return by_unroll<F, 16, 32, 32>(t, s, o, nv);
+      case 64: return by_unroll<F, 16, 64, 64>(t, s, o, nv);
       default: break;
     }
   } else if constexpr (VB == 8) {
-    if (nv == 1) return by_unroll<F, 8, 1, 1>(t, s, nv);
+    if (nv == 1) return by_unroll<F, 8, 1, 1>(t, s, o, nv);
   } else {
-    if (nv == 1) return by_unroll<F, 4, 1, 1>(t, s, nv);
+    if (nv == 1) return by_unroll<F, 4, 1, 1>(t, s, o, nv);
   }
-  return generic<F, VB>(t, s, nv);
+  return generic<F, VB>(t, s, o, nv);
 }
 
 template <class F>
-void by_vec(const LaunchTable& t, hipStream_t s) {
-  if (t.vec_bytes == 16) by_shape<F, 16>(t, s);
-  else if (t.vec_bytes == 8) by_shape<F, 8>(t, s);
-  else by_shape<F, 4>(t, s);
+void by_vec(const LaunchTable& t, hipStream_t s, const LaunchOpt& o) {
+  if (t.vec_bytes == 16) by_shape<F, 16>(t, s, o);
+  else if (t.vec_bytes == 8) by_shape<F, 8>(t, s, o);
+  else by_shape<F, 4>(t, s, o);
 }
 
 }  // namespace kern

@@ -774,11 +774,11 @@ int hx::batch_prepare(hx_batch* b) {
 }
 
 int hx::batch_run_start(hx_batch* b, hipStream_t s) {
-  return launch_table(b->lt[PH_PACK], s, sim_transfer(b));
+  return launch_table(b->lt[PH_PACK], s, {sim_transfer(b), 0, 0});
 }
 
 int hx::batch_run_wait(hx_batch* b, hipStream_t s) {
-  HX_TRY(launch_table(b->lt[PH_REDIST], s, sim_transfer(b)));
+  HX_TRY(launch_table(b->lt[PH_REDIST], s, {sim_transfer(b), 0, 0}));
   return launch_table(b->lt[PH_UNPACK], s);
 }
 
@@ -934,7 +934,7 @@ extern "C" int hx_batch_start_plain(hx_batch* b, void* stream) {
   if (b->active) return fail(HX_ERR_STATE, "batch already active");
   hipStream_t s = (hipStream_t)stream;
   if (!b->plain_built[PH_PACK]) HX_TRY(batch_build_plain(b, PH_PACK));
-  for (auto& t : b->plain[PH_PACK]) HX_TRY(launch_table(t, s, sim_transfer(b)));
+  for (auto& t : b->plain[PH_PACK]) HX_TRY(launch_table(t, s, {sim_transfer(b), 0, 0}));
   b->active = true;
   return HX_SUCCESS;
 }
@@ -945,7 +945,7 @@ extern "C" int hx_batch_wait_plain(hx_batch* b, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   if (!b->plain_built[PH_REDIST]) HX_TRY(batch_build_plain(b, PH_REDIST));
   if (!b->plain_built[PH_UNPACK]) HX_TRY(batch_build_plain(b, PH_UNPACK));
-  for (auto& t : b->plain[PH_REDIST]) HX_TRY(launch_table(t, s, sim_transfer(b)));
+  for (auto& t : b->plain[PH_REDIST]) HX_TRY(launch_table(t, s, {sim_transfer(b), 0, 0}));
   for (auto& t : b->plain[PH_UNPACK]) HX_TRY(launch_table(t, s));
   b->active = false;
   return HX_SUCCESS;
@@ -968,6 +968,14 @@ extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
     HX_TRY(b->g_send_all.alloc((size_t)b->E1_tot * b->row_bytes));
     std::vector<GatherJob> xb{GatherJob{b->g_in, b->g_send_all.as<char>(), b->gidx_to1.as<int32_t>(), b->E1_tot}};
     HX_TRY(build_gather_table(xb, b->dtype, rbi, gsc, &b->lt_back[0]));
+    // the same from a caller's buffer, which the bound one gets a copy of
+    HX_TRY(world_from_map(b));
+    GatherJob cb{b->g_in, nullptr, nullptr, b->H_tot};
+    cb.dst2 = b->g_send_all.as<char>();
+    cb.idx2 = b->gidx_from1.as<int32_t>();
+    SchedFor cw;
+    cw.identity = cw.fresh = true;
+    HX_TRY(build_gather_table({cb}, b->dtype, rbi, default_sched(KIND_GATHER, rbi, cw), &b->lt_back_copy));
   } else if (b->staged_bwd) {
     // locality world, staged: forwarder sums read the halo gradients (own
     // terms) and the stage-2 send-slot gradients (split = H)
@@ -986,20 +994,35 @@ extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
   return batch_prepare(b);
 }
 
+static bool overlap(const void* p, size_t n, const DevMem& m) {
+  return (const char*)p < m.as<char>() + m.bytes && m.as<char>() < (const char*)p + n;
+}
+
 // Backward of a batch.  Plain worlds: with the simulated transport the
 // reverse stage-1 transfer first, then the owner sums.  Staged locality
 // worlds: [reverse stage-2 transfer], forwarder sums, [reverse stage-1
 // transfer], owner sums.  Others: the fixed-order sums.
-static int run_backward(hx_batch* b, hipStream_t s, bool plain_form) {
+static int run_backward(hx_batch* b, hipStream_t s, bool plain_form, int64_t g_in, int64_t g_out) {
   const bool sim = sim_transfer(b);
+  const bool plain_world = b->world && b->unpack_identity;
+  if (g_in != 0) {
+    const size_t gb = (size_t)b->H_tot * b->row_bytes;
+    if (plain_world && sim && (b->lt_back_copy.empty() || b->lt_back_copy.deliver) &&
+        !overlap(b->g_in + g_in, gb, b->g_send_all))
+      HX_TRY(launch_table(b->lt_back_copy, s, {true, g_in, 0}));
+    else {
+      HX_HIP(hipMemcpyAsync(const_cast<char*>(b->g_in), b->g_in + g_in, gb, hipMemcpyDeviceToDevice, s));
+      g_in = 0;
+    }
+  }
   if (b->world && b->staged_bwd) {
     if (sim) HX_TRY(launch_table(b->lt_back[1], s));
     HX_TRY(launch_table(b->lt_fwd_sum, s));
     if (sim) HX_TRY(launch_table(b->lt_back[0], s));
-  } else if (b->world && b->unpack_identity && sim) {
+  } else if (plain_world && sim && g_in == 0) {
     HX_TRY(launch_table(b->lt_back[0], s));
   }
-  if (!plain_form) return launch_table(b->lt[PH_BWD], s);
+  if (!plain_form) return launch_table(b->lt[PH_BWD], s, {false, 0, g_out});
   for (auto& t : b->plain[PH_BWD]) HX_TRY(launch_table(t, s));
   return HX_SUCCESS;
 }
@@ -1026,10 +1049,53 @@ extern "C" int hx_batch_backward_plain(hx_batch* b, void* stream) {
   if (b->world && !b->g_out) return fail(HX_ERR_STATE, "no gradient buffers bound");
   HX_TRY(refresh_member_grads(b));
   if (!b->plain_built[PH_BWD]) HX_TRY(batch_build_plain(b, PH_BWD));
-  return run_backward(b, (hipStream_t)stream, true);
+  return run_backward(b, (hipStream_t)stream, true, 0, 0);
 }
 
-int hx::batch_run_backward(hx_batch* b, hipStream_t s) { return run_backward(b, s, false); }
+int hx::batch_run_backward(hx_batch* b, hipStream_t s, int64_t g_in, int64_t g_out) {
+  return run_backward(b, s, false, g_in, g_out);
+}
+
+// Bytes from a bound buffer to a caller's (null, or the bound one itself: 0).
+static int beside(const void* given, const void* bound, const char* what, int64_t* out) {
+  *out = given ? (int64_t)((uintptr_t)given - (uintptr_t)bound) : 0;
+  if (*out % 16 != 0) return fail(HX_ERR_ARG, "%s: not aligned as the bound buffer (modulo 16 bytes)", what);
+  return HX_SUCCESS;
+}
+
+extern "C" int hx_batch_exchange(hx_batch* b, const void* x, void* halo, void* stream) {
+  if (!b) return fail(HX_ERR_ARG, "null batch");
+  if (!b->world) return fail(HX_ERR_ARG, "not a world batch");
+  if (b->active) return fail(HX_ERR_STATE, "batch already active");
+  hipStream_t s = (hipStream_t)stream;
+  int64_t dx = 0, dh = 0;
+  HX_TRY(beside(x, b->x_global, "x_global", &dx));
+  HX_TRY(beside(halo, b->halo_all, "halo_all", &dh));
+  const size_t xb = (size_t)b->n * b->row_bytes;
+  // (a push pack copies the rows as it goes; not from an arena that it writes)
+  if (dx != 0 && (b->lt[PH_PACK].empty() || b->lt[PH_PACK].kind != KIND_SCATTER || overlap(x, xb, b->send_all) ||
+                  overlap(x, xb, b->recv_all))) {
+    HX_HIP(hipMemcpyAsync(const_cast<char*>(b->x_global), x, xb, hipMemcpyDeviceToDevice, s));
+    dx = 0;
+  }
+  HX_TRY(launch_table(b->lt[PH_PACK], s, {sim_transfer(b), dx, 0}));
+  HX_TRY(launch_table(b->lt[PH_REDIST], s, {sim_transfer(b), 0, 0}));
+  const bool fused = b->lt[PH_UNPACK].identity != 0;
+  HX_TRY(launch_table(b->lt[PH_UNPACK], s, {false, 0, fused ? dh : 0}));
+  if (dh != 0 && !fused)
+    HX_HIP(hipMemcpyAsync(halo, b->halo_all, (size_t)b->H_tot * b->row_bytes, hipMemcpyDeviceToDevice, s));
+  return HX_SUCCESS;
+}
+
+extern "C" int hx_batch_adjoint(hx_batch* b, const void* g_in, void* g_out, void* stream) {
+  if (!b) return fail(HX_ERR_ARG, "null batch");
+  if (!b->world) return fail(HX_ERR_ARG, "not a world batch");
+  if (!b->g_out) return fail(HX_ERR_STATE, "no gradient buffers bound");
+  int64_t di = 0, dout = 0;
+  HX_TRY(beside(g_in, b->g_in, "g_in", &di));
+  HX_TRY(beside(g_out, b->g_out, "g_out", &dout));
+  return batch_run_backward(b, (hipStream_t)stream, di, dout);
+}
 
 // One phase's kernel on its own, launched directly from the same
 // launch table Start, Wait and the backward launch (for per-kernel timing).

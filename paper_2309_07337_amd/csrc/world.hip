@@ -317,6 +317,18 @@ int world_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
   return HX_SUCCESS;
 }
 
+int world_from_map(hx_batch* b) {
+  if (b->gidx_from1.p || b->E1_tot == 0) return HX_SUCCESS;
+  DevMem m;
+  HX_TRY(m.alloc((size_t)b->R1_tot * 4));
+  hipLaunchKernelGGL(k_invert_range, dim3(blocks_for(b->E1_tot)), dim3(TB), 0, 0, b->gidx_to1.as<int32_t>(), b->E1_tot,
+                     (int64_t)0, b->R1_tot, m.as<int32_t>());
+  HX_HIP(hipGetLastError());
+  HX_HIP(hipStreamSynchronize(0));
+  b->gidx_from1 = std::move(m);
+  return HX_SUCCESS;
+}
+
 // Adjoint CSR: global column -> rows of halo_all, ascending (= ascending rank).
 int world_adjoint(hx_batch* b) {
   if (b->wb_ptr.p) return HX_SUCCESS;
