@@ -88,7 +88,8 @@ void copy_launch(const LaunchTable& t, hipStream_t s, const LaunchOpt& o) {
                        Beside{o.src, 0});
     return;
   }
-  auto* kernel = t.sched.nontemporal ? k_unpack_copy<VB, true> : k_unpack_copy<VB, false>;
+  // (with a second copy, streaming: it is read later than the caches hold)
+  auto* kernel = t.sched.nontemporal || o.dst != 0 ? k_unpack_copy<VB, true> : k_unpack_copy<VB, false>;
   hipLaunchKernelGGL(kernel, dim3(t.grid), dim3(t.sched.block_threads), 0, s, t.jobs.as<GatherJob>(),
                      t.tile_start.as<int64_t>(), t.njobs, t.ntiles, t.sched.tile_rows, t.row_bytes, Beside{0, o.dst});
 }

@@ -167,7 +167,7 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
       s.tile_rows = std::min(kStageRows, std::max(64, (64 << 10) / rb));
       s.block_threads = 1024;
       s.unroll = 2;
-      s.nontemporal = streams ? 1 : 0;
+      s.nontemporal = w.bytes >= (w.fresh ? (int64_t)256 << 20 : (int64_t)64 << 20) ? 1 : 0;
     } else if (one && w.source <= kL2) {
       // one row per lane, terms from LDS windows (1024 ranks staged backward,
       // FP32 189 -> 145, in tiles of 4096 rows 168: forwarders stage their
@@ -197,7 +197,8 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     // rows, in the L2, 24 B 66 pulled and 85 pushed).  Its writes merge in the
     // L2: no streaming hints (24 B 58, 152 with)
     s.push_pack = 1;
-    s.tile_rows = rb <= 48 ? kStageRows : std::max(64, std::min(256, (32 << 10) / rb));
+    // (400-B rows in tiles of 81 rows 181, of 40 155)
+    s.tile_rows = rb <= 48 ? kStageRows : std::max(16, std::min(256, (rb <= 192 ? 32 << 10 : 16 << 10) / rb));
     s.block_threads = pow2 ? 256 : 512;
   } else if (one) {
     s.pair_rows = 1;  // 16-byte row groups per lane
