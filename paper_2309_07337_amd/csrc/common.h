@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <string>
@@ -76,6 +77,22 @@ template <class T>
 int upload_vec(DevMem& dst, const std::vector<T>& v) {
   return upload(dst, v.data(), v.size() * sizeof(T));
 }
+
+// Host arrays uploaded together (a copy of a few KB costs 10 to 16 us whatever
+// it holds): add() each, upload() once, then at() is an array's device address.
+struct HostPack {
+  std::vector<char> host;
+  DevMem dev;
+  template <class T>
+  size_t add(const std::vector<T>& v) {
+    const size_t at = host.size();
+    host.resize(at + (v.size() * sizeof(T) + 15) / 16 * 16);
+    std::copy(v.begin(), v.end(), reinterpret_cast<T*>(host.data() + at));
+    return at;
+  }
+  int upload() { return upload_vec(dev, host); }
+  template <class T> T* at(size_t offset) const { return reinterpret_cast<T*>(dev.as<char>() + offset); }
+};
 
 int device_cus();  // number of compute units of the current device
 int device_lds_per_block();  // LDS bytes one workgroup may use on the current device

@@ -173,13 +173,15 @@ int world_from_map(hx_batch* b);
 int dev_exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, hipStream_t s);  // out[n] = total
 // HX_ERR_RANGE unless every idx[i] is in [0, hi).
 int dev_check_range(const int32_t* idx, int64_t n, int64_t hi, const char* what, hipStream_t s);
-// How many of the n segments [ptr[i], ptr[i + 1]) are not empty.
-int dev_count_nonempty(const int32_t* ptr, int64_t n, int64_t* count, hipStream_t s);
-// How many values of [0, domain) the indices take.
-int dev_count_nonzero_flags(const int32_t* idx, int64_t n, int64_t domain, int64_t* distinct,
-                            hipStream_t s);
+// *acc += how many of the n segments [ptr[i], ptr[i + 1]) are not empty.
+int dev_count_nonempty(const int32_t* ptr, int64_t n, unsigned long long* acc, hipStream_t s);
+// *acc += how many values of [0, domain) the indices take; flags: a workspace
+// that has to live until the stream has passed the call.
+int dev_count_distinct(const int32_t* idx, int64_t n, int64_t domain, DevMem* flags, unsigned long long* acc,
+                       hipStream_t s);
 // Stable grouping of entries by key: for each key k in [0, nkeys), the
 // entries e with keys[e] == k in ascending e.  ptr [nkeys+1], perm [n].
+// checked: the keys are known to lie in [0, nkeys).
 int dev_group_by_key(const int32_t* keys, int64_t n, int64_t nkeys, int32_t* ptr, int32_t* perm,
-                     hipStream_t s);
+                     hipStream_t s, bool checked = false);
 }  // namespace hx

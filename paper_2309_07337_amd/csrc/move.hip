@@ -169,16 +169,26 @@ int shape_table(const std::vector<J>& jobs, int kind, int dtype, int row_bytes, 
   return HX_SUCCESS;
 }
 
+// Jobs and tile prefix to the device, in one copy.
+template <class J>
+int upload_table(const std::vector<J>& kept, const std::vector<int64_t>& ts, LaunchTable* t) {
+  if (t->ntiles == 0) return HX_SUCCESS;
+  HostPack up;
+  up.add(kept);
+  const size_t at_ts = up.add(ts);
+  HX_TRY(up.upload());
+  t->jobs = std::move(up.dev);
+  t->tile_start.borrow(t->jobs.as<char>() + at_ts, ts.size() * sizeof(int64_t));
+  return HX_SUCCESS;
+}
+
 template <class J>
 int build_table(const std::vector<J>& jobs, int kind, int dtype, int row_bytes, const Sched& s0, LaunchTable* t,
                 uintptr_t align_or) {
   std::vector<J> kept;
   std::vector<int64_t> ts;
   HX_TRY(shape_table(jobs, kind, dtype, row_bytes, s0, t, align_or, &kept, &ts));
-  if (t->ntiles == 0) return HX_SUCCESS;
-  HX_TRY(upload_vec(t->jobs, kept));
-  HX_TRY(upload_vec(t->tile_start, ts));
-  return HX_SUCCESS;
+  return upload_table(kept, ts, t);
 }
 
 // Entry range of every tile of a CSR-driven table (segmented sum, push
@@ -350,8 +360,7 @@ int build_segsum_table(const std::vector<SegSumJob>& jobs, int dtype, int row_by
   std::vector<int64_t> ts;
   HX_TRY(shape_segsum_table(jobs, dtype, row_bytes, s, t, tag, &kept, &ts));
   if (t->ntiles == 0) return HX_SUCCESS;
-  HX_TRY(upload_vec(t->jobs, kept));
-  HX_TRY(upload_vec(t->tile_start, ts));
+  HX_TRY(upload_table(kept, ts, t));
   if (t->vec16) {
     // one-value sums: 16 terms per row loaded together (one row per lane)
     // where rows average more than three terms (the owner sums of high

@@ -922,8 +922,14 @@ __global__ void k_unpack_map(const int32_t* __restrict__ hcol, const int32_t* __
 // [koff[q], koff[q+1]) of one key space (its own rows; its node's rows for
 // the 3-step plan), so one stable grouping yields every rank's transpose.
 __global__ void k_pack_keys(const int32_t* __restrict__ s1_idx, int64_t E, const int64_t* __restrict__ s1_off,
-                            const int64_t* __restrict__ koff, int R, int32_t* keys) {
-  for_ranked(E, s1_off, R, [&](int64_t k, int q) { keys[k] = (int32_t)(koff[q] + s1_idx[k]); });
+                            const int64_t* __restrict__ koff, int R, int32_t* keys, int* err) {
+  bool bad = false;
+  for_ranked(E, s1_off, R, [&](int64_t k, int q) {
+    const int64_t key = koff[q] + s1_idx[k];
+    bad |= key < koff[q] || key >= koff[q + 1];
+    keys[k] = (int32_t)key;
+  });
+  if (bad) atomicOr(err, 16);
 }
 
 // Per-rank transpose arrays from that grouping (pack rows of rank q occupy
@@ -955,15 +961,11 @@ int err_of(int h, const char* what) {
   return HX_SUCCESS;
 }
 
-int check_err(const DevMem& err, const char* what) {
-  int h = 0;
-  HX_HIP(hipMemcpy(&h, err.p, sizeof h, hipMemcpyDeviceToHost));
-  return err_of(h, what);
-}
-
-int to_host64(const DevMem& d, int64_t n, std::vector<int64_t>* out) {
+// Copies n values of 64 bits back (ordered after the work on s).
+int to_host64(const void* d, int64_t n, std::vector<int64_t>* out, hipStream_t s) {
   out->resize((size_t)n);
-  if (n) HX_HIP(hipMemcpy(out->data(), d.p, (size_t)n * 8, hipMemcpyDeviceToHost));
+  if (n) HX_HIP(hipMemcpyAsync(out->data(), d, (size_t)n * 8, hipMemcpyDeviceToHost, s));
+  HX_HIP(hipStreamSynchronize(s));
   return HX_SUCCESS;
 }
 
@@ -978,40 +980,38 @@ struct Dense {
   std::vector<int64_t> sum, nnz;  // host per-row sums and nonzero counts
 };
 
-// Prefix sums, row sums and nonzero counts of a dense R x R table.
-int dense_stats(Dense* t, int R, hipStream_t s) {
+// Prefix sums of a dense R x R table, its row sums (stat[0 .. R)) and nonzero
+// counts (stat[R .. 2 R)).
+int dense_prefix(Dense* t, int R, int64_t* stat, hipStream_t s) {
   HX_TRY(t->P.alloc((size_t)R * R * 4));
-  DevMem sum, nnz;
-  HX_TRY(sum.alloc((size_t)R * 8));
-  HX_TRY(nnz.alloc((size_t)R * 8));
-  hipLaunchKernelGGL(k_row_exscan, dim3(R), dim3(TB), 0, s, t->A.as<int32_t>(), t->P.as<int32_t>(), R,
-                     sum.as<int64_t>(), nnz.as<int64_t>());
+  hipLaunchKernelGGL(k_row_exscan, dim3(R), dim3(TB), 0, s, t->A.as<int32_t>(), t->P.as<int32_t>(), R, stat, stat + R);
   HX_HIP(hipGetLastError());
-  HX_HIP(hipStreamSynchronize(s));
-  HX_TRY(to_host64(sum, R, &t->sum));
-  HX_TRY(to_host64(nnz, R, &t->nnz));
+  return HX_SUCCESS;
+}
+
+// Those sums and counts, copied back.
+int dense_stats(Dense* t, int R, const int64_t* stat) {
+  t->sum.assign(stat, stat + R);
+  t->nnz.assign(stat + R, stat + 2 * R);
   for (int64_t v : t->sum)
     if (v >= INT32_MAX) return fail(HX_ERR_UNSUPPORTED, "a rank's list exceeds 2^31 entries");
   return HX_SUCCESS;
 }
 
-// Emits the (procs, counts, displs) lists of the rows of a dense table.
-int dense_lists(const Dense& t, int R, hipStream_t s, hx_plan* p, int f_procs) {
-  std::vector<int64_t> off = prefix(t.nnz);
-  DevMem off_d;
-  HX_TRY(upload_vec(off_d, off));
+// Emits the (procs, counts, displs) lists of the rows of a dense table, whose
+// offsets are off (off_d on the device).
+int dense_lists(const Dense& t, int R, const std::vector<int64_t>& off, const int64_t* off_d, hipStream_t s,
+                hx_plan* p, int f_procs) {
   const int64_t tot = off.back();
   for (int k = 0; k < 3; ++k) {
     p->off[f_procs + k] = off;
     HX_TRY(p->d[f_procs + k].alloc((size_t)tot * 4));
   }
   if (tot > 0) {
-    hipLaunchKernelGGL(k_row_compact, dim3(R), dim3(TB), 0, s, t.A.as<int32_t>(), t.P.as<int32_t>(), R,
-                       off_d.as<int64_t>(), p->d[f_procs].as<int32_t>(), p->d[f_procs + 1].as<int32_t>(),
-                       p->d[f_procs + 2].as<int32_t>());
+    hipLaunchKernelGGL(k_row_compact, dim3(R), dim3(TB), 0, s, t.A.as<int32_t>(), t.P.as<int32_t>(), R, off_d,
+                       p->d[f_procs].as<int32_t>(), p->d[f_procs + 1].as<int32_t>(), p->d[f_procs + 2].as<int32_t>());
     HX_HIP(hipGetLastError());
   }
-  HX_HIP(hipStreamSynchronize(s));
   return HX_SUCCESS;
 }
 
@@ -1029,8 +1029,10 @@ int zeros(DevMem* d, size_t bytes, hipStream_t s) {
   return HX_SUCCESS;
 }
 
-// Builds every plan array from the halos of all ranks (device hcol, host offsets).
-int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff, int check, hipStream_t s) {
+// Builds every plan array from the halos of all ranks (device hcol, host
+// offsets; hoff_d: the offsets on the device, uploaded here when empty).
+int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff, DevMem& hoff_d, int check,
+                     hipStream_t s) {
   const int R = p->R;
   const int ppn = p->ppn;
   const int64_t n = p->n;
@@ -1042,24 +1044,31 @@ int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff,
   const int64_t W = (n + 31) / 32;
   const int64_t W1 = W + 1;
 
-  DevMem hoff_d, hrank, own, err;
-  HX_TRY(upload_vec(hoff_d, hoff));
+  // what the host needs of the tables, read back twice: [error word | sums and
+  // nonzero counts of M | of S1 | R1 | S2 | R2]
+  DevMem hrank, own, stat;
+  HX_TRY(stat.alloc((size_t)(1 + 10 * (int64_t)R) * 8));
+  int* err = stat.as<int>();
+  int64_t* const st = stat.as<int64_t>() + 1;
+  if (!hoff_d.p) HX_TRY(upload_vec(hoff_d, hoff));
   HX_TRY(hrank.alloc((size_t)nH * 4));
   HX_TRY(own.alloc((size_t)nH * 4));
-  HX_TRY(zeros(&err, 4, s));
+  HX_HIP(hipMemsetAsync(err, 0, 8, s));
   Dense M;
   HX_TRY(zeros(&M.A, (size_t)R * R * 4, s));
   if (nH > 0) {
     hipLaunchKernelGGL(k_entry_info, dim3(walk_blocks(nH)), dim3(TB), 0, s, hcol.as<int32_t>(), nH,
                        hoff_d.as<int64_t>(), p->row_starts_d.as<int64_t>(), R, n, check, hrank.as<int32_t>(),
-                       own.as<int32_t>(), M.A.as<int32_t>(), err.as<int>());
+                       own.as<int32_t>(), M.A.as<int32_t>(), err);
     HX_HIP(hipGetLastError());
   }
-  HX_HIP(hipStreamSynchronize(s));
-  HX_TRY(check_err(err, "halo"));
-  HX_TRY(dense_stats(&M, R, s));
+  HX_TRY(dense_prefix(&M, R, st, s));
   DevMem MT;
   HX_TRY(dense_transpose(M.A, &MT, R, s));
+  std::vector<int64_t> back;
+  HX_TRY(to_host64(stat.p, 1 + 2 * (int64_t)R, &back, s));
+  HX_TRY(err_of((int)back[0], "halo"));
+  HX_TRY(dense_stats(&M, R, back.data() + 1));
 
   // halo field
   p->off[HX_F_HALO] = hoff;
@@ -1103,13 +1112,20 @@ int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff,
     HX_HIP(hipGetLastError());
     HX_TRY(dense_transpose(S1.A, &R1.A, R, s));
     HX_TRY(dense_transpose(S2.A, &R2.A, R, s));
-    HX_TRY(dense_stats(&S1, R, s));
-    HX_TRY(dense_stats(&R1, R, s));
-    HX_TRY(dense_stats(&S2, R, s));
-    HX_TRY(dense_stats(&R2, R, s));
+    HX_TRY(dense_prefix(&S1, R, st + 2 * R, s));
+    HX_TRY(dense_prefix(&R1, R, st + 4 * R, s));
+    HX_TRY(dense_prefix(&S2, R, st + 6 * R, s));
+    HX_TRY(dense_prefix(&R2, R, st + 8 * R, s));
+    HX_TRY(to_host64(st + 2 * R, 8 * (int64_t)R, &back, s));
+    HX_TRY(dense_stats(&S1, R, back.data()));
+    HX_TRY(dense_stats(&R1, R, back.data() + 2 * R));
+    HX_TRY(dense_stats(&S2, R, back.data() + 4 * R));
+    HX_TRY(dense_stats(&R2, R, back.data() + 6 * R));
   } else {
     S1.A = std::move(MT);
-    HX_TRY(dense_stats(&S1, R, s));
+    HX_TRY(dense_prefix(&S1, R, st + 2 * R, s));
+    HX_TRY(to_host64(st + 2 * R, 2 * (int64_t)R, &back, s));
+    HX_TRY(dense_stats(&S1, R, back.data()));
     // stage-1 receive = M (its prefix sums are the receive displacements)
     R1.A = std::move(M.A);
     R1.P = std::move(M.P);
@@ -1117,16 +1133,12 @@ int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff,
     R1.nnz = M.nnz;
   }
 
-  // lists
-  HX_TRY(dense_lists(S1, R, s, p, HX_F_S1_PROCS));
-  HX_TRY(dense_lists(R1, R, s, p, HX_F_R1_PROCS));
+  // offsets of every list
   std::vector<int64_t> s1_off = prefix(S1.sum);
   std::vector<int64_t> s2_off, r1_tot = R1.sum;
   p->off[HX_F_S1_IDX] = s1_off;
   p->off[HX_F_BT_PERM] = s1_off;
   if (loc) {
-    HX_TRY(dense_lists(S2, R, s, p, HX_F_S2_PROCS));
-    HX_TRY(dense_lists(R2, R, s, p, HX_F_R2_PROCS));
     s2_off = prefix(S2.sum);
   } else {
     std::vector<int64_t> z((size_t)R + 1, 0);
@@ -1141,52 +1153,7 @@ int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff,
   const int64_t E1 = s1_off.back(), E2 = s2_off.back();
   if (E1 >= INT32_MAX || E2 >= INT32_MAX || nH >= INT32_MAX)
     return fail(HX_ERR_UNSUPPORTED, "plan lists beyond 2^31 entries");
-  DevMem s1o_d, s2o_d, r1t_d;
-  HX_TRY(upload_vec(s1o_d, s1_off));
-  HX_TRY(upload_vec(s2o_d, s2_off));
-  HX_TRY(upload_vec(r1t_d, r1_tot));
-  HX_TRY(p->d[HX_F_S1_IDX].alloc((size_t)E1 * 4));
-  HX_TRY(p->d[HX_F_S2_SRC].alloc((size_t)E2 * 4));
-  HX_TRY(p->d[HX_F_UNPACK_SRC].alloc((size_t)nH * 4));
-  const int32_t* PM = loc ? M.P.as<int32_t>() : R1.P.as<int32_t>();
-  if (nH > 0) {
-    hipLaunchKernelGGL(k_s1_direct, dim3(blocks_for(nH)), dim3(TB), 0, s, p->d[HX_F_HALO].as<int32_t>(),
-                       hrank.as<int32_t>(), own.as<int32_t>(), nH, hoff_d.as<int64_t>(),
-                       p->row_starts_d.as<int64_t>(), PL, loc ? 1 : 0, v3, S1.P.as<int32_t>(), PM,
-                       s1o_d.as<int64_t>(), p->d[HX_F_S1_IDX].as<int32_t>(), err.as<int>());
-    HX_HIP(hipGetLastError());
-  }
-  if (loc) {
-    if (NN * W > 0) {
-      hipLaunchKernelGGL(k_s1_agg, dim3(blocks_for((int64_t)NN * W)), dim3(TB), 0, s, NB.as<uint32_t>(),
-                         NBP.as<int32_t>(), W1, W, p->row_starts_d.as<int64_t>(), PL, v3,
-                         S1.P.as<int32_t>(), s1o_d.as<int64_t>(), p->d[HX_F_S1_IDX].as<int32_t>(), err.as<int>());
-      HX_HIP(hipGetLastError());
-    }
-    if (nH > 0) {
-      hipLaunchKernelGGL(k_s2_src, dim3(blocks_for(nH)), dim3(TB), 0, s, p->d[HX_F_HALO].as<int32_t>(),
-                         hrank.as<int32_t>(), own.as<int32_t>(), nH, hoff_d.as<int64_t>(),
-                         p->row_starts_d.as<int64_t>(), PL, S2.P.as<int32_t>(), QP.as<int32_t>(), PM,
-                         R1.P.as<int32_t>(), NB.as<uint32_t>(), NBP.as<int32_t>(), W1, s2o_d.as<int64_t>(), v3,
-                         p->d[HX_F_S2_SRC].as<int32_t>(), err.as<int>());
-      HX_HIP(hipGetLastError());
-    }
-  }
-  if (nH > 0) {
-    hipLaunchKernelGGL(k_unpack_map, dim3(blocks_for(nH)), dim3(TB), 0, s, p->d[HX_F_HALO].as<int32_t>(),
-                       hrank.as<int32_t>(), own.as<int32_t>(), nH, hoff_d.as<int64_t>(),
-                       p->row_starts_d.as<int64_t>(), PL, loc ? 1 : 0, v3, PM, R1.P.as<int32_t>(),
-                       loc ? R2.P.as<int32_t>() : nullptr, loc ? QP.as<int32_t>() : nullptr,
-                       loc ? NB.as<uint32_t>() : nullptr, loc ? NBP.as<int32_t>() : nullptr, W1,
-                       r1t_d.as<int64_t>(), p->d[HX_F_UNPACK_SRC].as<int32_t>());
-    HX_HIP(hipGetLastError());
-  }
-
-  HX_HIP(hipStreamSynchronize(s));
-  HX_TRY(check_err(err, "plan lists"));
-
-  // transpose of the pack map, per rank over its pack rows (its own rows;
-  // its node's rows for the 3-step plan)
+  // rows of the pack map's transpose: a rank's own rows, its node's for the 3-step plan
   std::vector<int64_t> pack_rows((size_t)R);
   for (int q = 0; q < R; ++q) {
     const int nq = q / ppn;
@@ -1198,33 +1165,82 @@ int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff,
   std::vector<int64_t> bt_off((size_t)R + 1, 0);
   for (int q = 0; q < R; ++q) bt_off[q + 1] = bt_off[q] + pack_rows[q] + 1;
   p->off[HX_F_BT_PTR] = bt_off;
+  const std::vector<int64_t> l_s1 = prefix(S1.nnz), l_r1 = prefix(R1.nnz), l_s2 = prefix(S2.nnz), l_r2 = prefix(R2.nnz);
+  HostPack up;
+  const size_t at_s1 = up.add(s1_off), at_s2 = up.add(s2_off), at_r1 = up.add(r1_tot), at_bt = up.add(bt_off),
+               at_k = up.add(koff), at_ls1 = up.add(l_s1), at_lr1 = up.add(l_r1), at_ls2 = up.add(l_s2),
+               at_lr2 = up.add(l_r2);
+  HX_TRY(up.upload());
+  const int64_t *s1o_d = up.at<int64_t>(at_s1), *s2o_d = up.at<int64_t>(at_s2), *r1t_d = up.at<int64_t>(at_r1),
+                *bto_d = up.at<int64_t>(at_bt), *koff_d = up.at<int64_t>(at_k);
+  // lists
+  HX_TRY(dense_lists(S1, R, l_s1, up.at<int64_t>(at_ls1), s, p, HX_F_S1_PROCS));
+  HX_TRY(dense_lists(R1, R, l_r1, up.at<int64_t>(at_lr1), s, p, HX_F_R1_PROCS));
+  if (loc) {
+    HX_TRY(dense_lists(S2, R, l_s2, up.at<int64_t>(at_ls2), s, p, HX_F_S2_PROCS));
+    HX_TRY(dense_lists(R2, R, l_r2, up.at<int64_t>(at_lr2), s, p, HX_F_R2_PROCS));
+  }
+  HX_TRY(p->d[HX_F_S1_IDX].alloc((size_t)E1 * 4));
+  HX_TRY(p->d[HX_F_S2_SRC].alloc((size_t)E2 * 4));
+  HX_TRY(p->d[HX_F_UNPACK_SRC].alloc((size_t)nH * 4));
+  const int32_t* PM = loc ? M.P.as<int32_t>() : R1.P.as<int32_t>();
+  if (nH > 0) {
+    hipLaunchKernelGGL(k_s1_direct, dim3(blocks_for(nH)), dim3(TB), 0, s, p->d[HX_F_HALO].as<int32_t>(),
+                       hrank.as<int32_t>(), own.as<int32_t>(), nH, hoff_d.as<int64_t>(),
+                       p->row_starts_d.as<int64_t>(), PL, loc ? 1 : 0, v3, S1.P.as<int32_t>(), PM,
+                       s1o_d, p->d[HX_F_S1_IDX].as<int32_t>(), err);
+    HX_HIP(hipGetLastError());
+  }
+  if (loc) {
+    if (NN * W > 0) {
+      hipLaunchKernelGGL(k_s1_agg, dim3(blocks_for((int64_t)NN * W)), dim3(TB), 0, s, NB.as<uint32_t>(),
+                         NBP.as<int32_t>(), W1, W, p->row_starts_d.as<int64_t>(), PL, v3,
+                         S1.P.as<int32_t>(), s1o_d, p->d[HX_F_S1_IDX].as<int32_t>(), err);
+      HX_HIP(hipGetLastError());
+    }
+    if (nH > 0) {
+      hipLaunchKernelGGL(k_s2_src, dim3(blocks_for(nH)), dim3(TB), 0, s, p->d[HX_F_HALO].as<int32_t>(),
+                         hrank.as<int32_t>(), own.as<int32_t>(), nH, hoff_d.as<int64_t>(),
+                         p->row_starts_d.as<int64_t>(), PL, S2.P.as<int32_t>(), QP.as<int32_t>(), PM,
+                         R1.P.as<int32_t>(), NB.as<uint32_t>(), NBP.as<int32_t>(), W1, s2o_d, v3,
+                         p->d[HX_F_S2_SRC].as<int32_t>(), err);
+      HX_HIP(hipGetLastError());
+    }
+  }
+  if (nH > 0) {
+    hipLaunchKernelGGL(k_unpack_map, dim3(blocks_for(nH)), dim3(TB), 0, s, p->d[HX_F_HALO].as<int32_t>(),
+                       hrank.as<int32_t>(), own.as<int32_t>(), nH, hoff_d.as<int64_t>(),
+                       p->row_starts_d.as<int64_t>(), PL, loc ? 1 : 0, v3, PM, R1.P.as<int32_t>(),
+                       loc ? R2.P.as<int32_t>() : nullptr, loc ? QP.as<int32_t>() : nullptr,
+                       loc ? NB.as<uint32_t>() : nullptr, loc ? NBP.as<int32_t>() : nullptr, W1,
+                       r1t_d, p->d[HX_F_UNPACK_SRC].as<int32_t>());
+    HX_HIP(hipGetLastError());
+  }
+
+  // transpose of the pack map, per rank over its pack rows
   HX_TRY(p->d[HX_F_BT_PTR].alloc((size_t)bt_off.back() * 4));
   HX_TRY(p->d[HX_F_BT_PERM].alloc((size_t)E1 * 4));
-  {
-    DevMem keys, gptr, gperm, bto_d, koff_d;
-    HX_TRY(keys.alloc((size_t)E1 * 4));
-    HX_TRY(gptr.alloc((size_t)(koff.back() + 1) * 4));
-    HX_TRY(gperm.alloc((size_t)E1 * 4));
-    HX_TRY(upload_vec(bto_d, bt_off));
-    HX_TRY(upload_vec(koff_d, koff));
-    if (E1 > 0) {
-      hipLaunchKernelGGL(k_pack_keys, dim3(walk_blocks(E1)), dim3(TB), 0, s, p->d[HX_F_S1_IDX].as<int32_t>(), E1,
-                         s1o_d.as<int64_t>(), koff_d.as<int64_t>(), R, keys.as<int32_t>());
-      HX_HIP(hipGetLastError());
-    }
-    HX_TRY(dev_check_range(keys.as<int32_t>(), E1, koff.back(), "pack rows", s));
-    HX_TRY(dev_group_by_key(keys.as<int32_t>(), E1, koff.back(), gptr.as<int32_t>(), gperm.as<int32_t>(), s));
-    hipLaunchKernelGGL(k_local_bt_ptr, dim3(walk_blocks(bt_off.back())), dim3(TB), 0, s, gptr.as<int32_t>(),
-                       bto_d.as<int64_t>(), koff_d.as<int64_t>(), s1o_d.as<int64_t>(), R, bt_off.back(),
-                       p->d[HX_F_BT_PTR].as<int32_t>());
+  DevMem keys, gptr, gperm;
+  HX_TRY(keys.alloc((size_t)E1 * 4));
+  HX_TRY(gptr.alloc((size_t)(koff.back() + 1) * 4));
+  HX_TRY(gperm.alloc((size_t)E1 * 4));
+  if (E1 > 0) {
+    hipLaunchKernelGGL(k_pack_keys, dim3(walk_blocks(E1)), dim3(TB), 0, s, p->d[HX_F_S1_IDX].as<int32_t>(), E1, s1o_d,
+                       koff_d, R, keys.as<int32_t>(), err);
     HX_HIP(hipGetLastError());
-    if (E1 > 0) {
-      hipLaunchKernelGGL(k_local_bt_perm, dim3(walk_blocks(E1)), dim3(TB), 0, s, gperm.as<int32_t>(), E1,
-                         s1o_d.as<int64_t>(), R, p->d[HX_F_BT_PERM].as<int32_t>());
-      HX_HIP(hipGetLastError());
-    }
-    HX_HIP(hipStreamSynchronize(s));
   }
+  HX_TRY(to_host64(stat.p, 1, &back, s));
+  HX_TRY(err_of((int)back[0], "plan lists"));
+  HX_TRY(dev_group_by_key(keys.as<int32_t>(), E1, koff.back(), gptr.as<int32_t>(), gperm.as<int32_t>(), s, true));
+  hipLaunchKernelGGL(k_local_bt_ptr, dim3(walk_blocks(bt_off.back())), dim3(TB), 0, s, gptr.as<int32_t>(), bto_d,
+                     koff_d, s1o_d, R, bt_off.back(), p->d[HX_F_BT_PTR].as<int32_t>());
+  HX_HIP(hipGetLastError());
+  if (E1 > 0) {
+    hipLaunchKernelGGL(k_local_bt_perm, dim3(walk_blocks(E1)), dim3(TB), 0, s, gperm.as<int32_t>(), E1, s1o_d, R,
+                       p->d[HX_F_BT_PERM].as<int32_t>());
+    HX_HIP(hipGetLastError());
+  }
+  HX_HIP(hipStreamSynchronize(s));
   return HX_SUCCESS;
 }
 
@@ -1277,7 +1293,8 @@ int dev_exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, hipStream
   return HX_SUCCESS;
 }
 
-int dev_group_by_key(const int32_t* keys, int64_t n, int64_t nkeys, int32_t* ptr, int32_t* perm, hipStream_t s) {
+int dev_group_by_key(const int32_t* keys, int64_t n, int64_t nkeys, int32_t* ptr, int32_t* perm, hipStream_t s,
+                     bool checked) {
   DevMem work;
   const int32_t* sorted = keys;
   int* err = nullptr;
@@ -1298,14 +1315,14 @@ int dev_group_by_key(const int32_t* keys, int64_t n, int64_t nkeys, int32_t* ptr
     int32_t* vbuf = kbuf + nk;
     int32_t* hist = vbuf + nv;
     int32_t* offs = hist + table;
-    HX_HIP(hipMemsetAsync(err, 0, 4, s));
+    if (!checked) HX_HIP(hipMemsetAsync(err, 0, 4, s));
     const int32_t* vals = nullptr;
     for (int p = 0; p < passes; ++p) {
       // the values end in perm: they alternate between perm and vbuf backwards from the last pass
       int32_t* vout = (passes - 1 - p) % 2 == 0 ? perm : vbuf;
       int32_t* kout = kbuf + (p % 2) * n;
       hipLaunchKernelGGL(k_radix_hist, dim3(nblocks), dim3(TB), 0, s, sorted, n, nkeys, p * bits, bits, hist,
-                         nblocks, p == 0 ? err : nullptr);
+                         nblocks, p == 0 && !checked ? err : nullptr);
       HX_HIP(hipGetLastError());
       HX_TRY(scan_launch(hist, offs, table, part, s));
       hipLaunchKernelGGL(k_radix_scatter, dim3(nblocks), dim3(TB), 0, s, sorted, vals, n, p * bits, bits, offs,
@@ -1318,7 +1335,7 @@ int dev_group_by_key(const int32_t* keys, int64_t n, int64_t nkeys, int32_t* ptr
   hipLaunchKernelGGL(k_group_ptr, dim3(blocks_for(std::max(n, (nkeys + 1) / 4), CHUNK)), dim3(TB), 0, s, sorted, n,
                      nkeys, ptr);
   HX_HIP(hipGetLastError());
-  if (err) {
+  if (err && !checked) {
     int h = 0;
     HX_HIP(hipMemcpyAsync(&h, err, sizeof h, hipMemcpyDeviceToHost, s));
     HX_HIP(hipStreamSynchronize(s));
@@ -1331,44 +1348,31 @@ int dev_group_by_key(const int32_t* keys, int64_t n, int64_t nkeys, int32_t* ptr
 int dev_check_range(const int32_t* idx, int64_t n, int64_t hi, const char* what, hipStream_t s) {
   if (n <= 0) return HX_SUCCESS;
   DevMem err;
-  HX_TRY(zeros(&err, 4, s));
+  HX_TRY(zeros(&err, 8, s));
   hipLaunchKernelGGL(k_check_range, dim3(blocks_for(n)), dim3(TB), 0, s, idx, n, hi, err.as<int>());
   HX_HIP(hipGetLastError());
-  HX_HIP(hipStreamSynchronize(s));
-  return check_err(err, what);
+  std::vector<int64_t> back;
+  HX_TRY(to_host64(err.p, 1, &back, s));
+  return err_of((int)back[0], what);
 }
 
-int dev_count_nonempty(const int32_t* ptr, int64_t n, int64_t* count, hipStream_t s) {
-  *count = 0;
+int dev_count_nonempty(const int32_t* ptr, int64_t n, unsigned long long* acc, hipStream_t s) {
   if (n <= 0) return HX_SUCCESS;
-  DevMem acc;
-  HX_TRY(zeros(&acc, 8, s));
-  hipLaunchKernelGGL(k_count_nonempty, dim3(std::min(blocks_for(n), 512u)), dim3(TB), 0, s, ptr, n,
-                     acc.as<unsigned long long>());
+  hipLaunchKernelGGL(k_count_nonempty, dim3(std::min(blocks_for(n), 512u)), dim3(TB), 0, s, ptr, n, acc);
   HX_HIP(hipGetLastError());
-  unsigned long long h = 0;
-  HX_HIP(hipMemcpyAsync(&h, acc.p, 8, hipMemcpyDeviceToHost, s));
-  HX_HIP(hipStreamSynchronize(s));
-  *count = (int64_t)h;
   return HX_SUCCESS;
 }
 
-int dev_count_nonzero_flags(const int32_t* idx, int64_t n, int64_t domain, int64_t* distinct, hipStream_t s) {
-  *distinct = 0;
+int dev_count_distinct(const int32_t* idx, int64_t n, int64_t domain, DevMem* flags, unsigned long long* acc,
+                       hipStream_t s) {
   if (n <= 0 || domain <= 0) return HX_SUCCESS;
-  DevMem flags, acc;
   const int64_t nwords = (domain + 3) / 4;
-  HX_TRY(zeros(&flags, (size_t)nwords * 4, s));
-  HX_TRY(zeros(&acc, 8, s));
-  hipLaunchKernelGGL(k_flag, dim3(blocks_for(n)), dim3(TB), 0, s, idx, n, domain, flags.as<unsigned char>());
+  HX_TRY(zeros(flags, (size_t)nwords * 4, s));
+  hipLaunchKernelGGL(k_flag, dim3(blocks_for(n)), dim3(TB), 0, s, idx, n, domain, flags->as<unsigned char>());
   HX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_count_flags, dim3(std::min(blocks_for(nwords), 512u)), dim3(TB), 0, s, flags.as<uint32_t>(),
-                     nwords, acc.as<unsigned long long>());
+  hipLaunchKernelGGL(k_count_flags, dim3(std::min(blocks_for(nwords), 512u)), dim3(TB), 0, s, flags->as<uint32_t>(),
+                     nwords, acc);
   HX_HIP(hipGetLastError());
-  unsigned long long h = 0;
-  HX_HIP(hipMemcpyAsync(&h, acc.p, 8, hipMemcpyDeviceToHost, s));
-  HX_HIP(hipStreamSynchronize(s));
-  *distinct = (int64_t)h;
   return HX_SUCCESS;
 }
 
@@ -1394,13 +1398,15 @@ extern "C" int hx_plan_from_csr(int nranks, const int64_t* row_starts, const hx_
   int64_t budget = (int64_t)1 << 30;
   if (const char* e = std::getenv("HX_PLAN_BITMAP_BYTES")) budget = std::max<int64_t>(1, std::atoll(e));
   const int64_t group = std::max<int64_t>(1, std::min<int64_t>(nranks, budget / std::max<int64_t>(W * 4, 1)));
-  DevMem B, err, cnt, ent;
+  DevMem B, cnt, ent;  // cnt: [error word | set bits of each rank of the group]
   HX_TRY(B.alloc((size_t)std::max<int64_t>(group * W * 4, 4)));
-  HX_TRY(zeros(&err, 4, s));
-  HX_TRY(cnt.alloc((size_t)group * 8));
+  HX_TRY(cnt.alloc((size_t)(group + 1) * 8));
+  int* err = cnt.as<int>();
+  unsigned long long* bits = cnt.as<unsigned long long>() + 1;
   HX_TRY(ent.alloc((size_t)(group + 1) * 8));
   std::vector<int64_t> hoff(1, 0);
   std::vector<DevMem> parts;
+  DevMem off_d;  // the offsets of a group
   for (int r0 = 0; r0 < nranks; r0 += (int)group) {
     const int g = (int)std::min<int64_t>(group, nranks - r0);
     const int64_t i0 = row_starts[r0], rows = row_starts[r0 + g] - i0;
@@ -1410,46 +1416,45 @@ extern "C" int hx_plan_from_csr(int nranks, const int64_t* row_starts, const hx_
     const int64_t lds = std::min<int64_t>(W * 4, (int64_t)1 << (kMarkSegBits - 3));
     const bool in_lds = rows > 0 && nseg <= kMarkMaxSegs && g >= kMarkMinRanks && lds <= device_lds_per_block() - 1024;
     if (W > 0 && !in_lds) HX_HIP(hipMemsetAsync(B.p, 0, (size_t)g * W * 4, s));
-    HX_HIP(hipMemsetAsync(cnt.p, 0, (size_t)g * 8, s));
+    HX_HIP(hipMemsetAsync(cnt.p, 0, (size_t)(g + 1) * 8, s));
     if (rows > 0) {
       hipLaunchKernelGGL(k_rank_entries, dim3(std::min(blocks_for(std::max<int64_t>(rows, g + 1)), 2048u)), dim3(TB), 0,
-                         s, p->row_starts_d.as<int64_t>(), i0, rows, r0, g, row_ptr, ent.as<int64_t>(), err.as<int>());
+                         s, p->row_starts_d.as<int64_t>(), i0, rows, r0, g, row_ptr, ent.as<int64_t>(), err);
       if (in_lds)
         hipLaunchKernelGGL(k_mark_lds, dim3((unsigned)((g + 7) / 8 * 8 * nseg)), dim3(kMarkThreads), (size_t)lds, s,
                            p->row_starts_d.as<int64_t>(), n, r0, g, nseg, ent.as<int64_t>(), cols, B.as<uint32_t>(), W,
-                           cnt.as<unsigned long long>(), err.as<int>());
+                           bits, err);
       else
         hipLaunchKernelGGL(k_mark_csr, dim3((unsigned)(8 * device_cus())), dim3(TB), 0, s,
                            p->row_starts_d.as<int64_t>(), n, r0, g, ent.as<int64_t>(), cols, B.as<uint32_t>(), W,
-                           err.as<int>());
+                           err);
       HX_HIP(hipGetLastError());
     }
     if (!in_lds) {
-      hipLaunchKernelGGL(k_popc_rows, dim3(g), dim3(kBitThreads), 0, s, B.as<uint32_t>(), W, cnt.as<int64_t>());
+      hipLaunchKernelGGL(k_popc_rows, dim3(g), dim3(kBitThreads), 0, s, B.as<uint32_t>(), W, (int64_t*)bits);
       HX_HIP(hipGetLastError());
     }
-    HX_HIP(hipStreamSynchronize(s));
-    HX_TRY(check_err(err, "csr"));
     std::vector<int64_t> hc;
-    HX_TRY(to_host64(cnt, g, &hc));
+    HX_TRY(to_host64(cnt.p, g + 1, &hc, s));
+    HX_TRY(err_of((int)hc[0], "csr"));
+    hc.erase(hc.begin());
     std::vector<int64_t> off = prefix(hc);
     if (hoff.back() + off.back() >= INT32_MAX) return fail(HX_ERR_UNSUPPORTED, "total halo beyond 2^31 entries");
     for (int k = 0; k < g; ++k) hoff.push_back(hoff.back() + hc[k]);
     parts.emplace_back();
     if (off.back() > 0) {
-      DevMem off_d;
+      off_d.release();
       HX_TRY(upload_vec(off_d, off));
       HX_TRY(parts.back().alloc((size_t)off.back() * 4));
       hipLaunchKernelGGL(k_compact_bits, dim3(g), dim3(kBitThreads), 0, s, B.as<uint32_t>(), W, off_d.as<int64_t>(),
                          parts.back().as<int32_t>());
       HX_HIP(hipGetLastError());
-      HX_HIP(hipStreamSynchronize(s));
     }
   }
   B.release();
   DevMem hcol;
   if (parts.size() == 1) {
-    hcol = std::move(parts[0]);
+    hcol = std::move(parts[0]);  // (one group: its offsets are all ranks')
   } else {
     HX_TRY(hcol.alloc((size_t)hoff.back() * 4));
     int64_t at = 0;
@@ -1461,8 +1466,9 @@ extern "C" int hx_plan_from_csr(int nranks, const int64_t* row_starts, const hx_
     }
     HX_HIP(hipStreamSynchronize(s));
     parts.clear();
+    off_d.release();
   }
-  HX_TRY(build_from_halos(p.get(), hcol, hoff, 0, s));
+  HX_TRY(build_from_halos(p.get(), hcol, hoff, off_d, 0, s));
   *out = p.release();
   return HX_SUCCESS;
 }
@@ -1485,7 +1491,8 @@ extern "C" int hx_plan_from_halos(int nranks, const int64_t* row_starts, const h
   HX_TRY(hcol.alloc((size_t)nH * 4));
   if (nH) HX_HIP(hipMemcpyAsync(hcol.p, halo_cols, (size_t)nH * 4, hipMemcpyDeviceToDevice, s));
   std::vector<int64_t> hoff(halo_ptr, halo_ptr + nranks + 1);
-  HX_TRY(build_from_halos(p.get(), hcol, hoff, 1, s));
+  DevMem hoff_d;
+  HX_TRY(build_from_halos(p.get(), hcol, hoff, hoff_d, 1, s));
   *out = p.release();
   return HX_SUCCESS;
 }

@@ -164,9 +164,13 @@ __global__ void __launch_bounds__(TB) k_transfer_map(int64_t nmsg, int R, const 
   }
 }
 
-int check_maps(const DevMem& err) {
-  int h = 0;
-  HX_HIP(hipMemcpy(&h, err.p, sizeof h, hipMemcpyDeviceToHost));
+// words: [error bits | two counts]
+int check_maps(const unsigned long long* words, int64_t* c1 = nullptr, int64_t* c2 = nullptr) {
+  unsigned long long w[3];
+  HX_HIP(hipMemcpy(w, words, sizeof w, hipMemcpyDeviceToHost));
+  const int h = (int)w[0];
+  if (c1) *c1 = (int64_t)w[1];
+  if (c2) *c2 = (int64_t)w[2];
   if (h & ERR_LISTS) return fail(HX_ERR_ARG, "world transfer: send and receive lists do not match");
   const char* what = h & ERR_PACK       ? "pack map"
                      : h & ERR_PUSH     ? "pack transpose"
@@ -499,62 +503,63 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
   HX_TRY(b->send_all.alloc((size_t)(b->E1_tot + b->E2_tot) * rb));
   HX_TRY(b->recv_all.alloc((size_t)(b->R1_tot + b->R2_tot) * rb));
 
-  DevMem rs_d, s1o, s2o, r1o, r2o, ho, err;
-  HX_TRY(upload_vec(rs_d, b->row_starts));
-  HX_TRY(upload_vec(s1o, b->s1_off));
-  HX_TRY(upload_vec(s2o, b->s2_off));
-  HX_TRY(upload_vec(r1o, b->r1_off));
-  HX_TRY(upload_vec(r2o, b->r2_off));
-  HX_TRY(upload_vec(ho, b->halo_off));
-  HX_TRY(err.alloc(4));
-  HX_HIP(hipMemset(err.p, 0, 4));
-
-  // pack: x_global rows (pack indices count from the rank's first row, or
-  // from its node's first row for the 3-step plan)
+  // pack indices count from the rank's first row, or from its node's first row
+  // for the 3-step plan
   const bool v3 = p->variant == HX_LOCALITY_3STEP;
   std::vector<int64_t> pbase((size_t)R + 1, 0);
   for (int r = 0; r <= R; ++r) pbase[r] = v3 && r < R ? b->row_starts[(r / p->ppn) * p->ppn] : b->row_starts[r];
-  DevMem pbase_d;
-  HX_TRY(upload_vec(pbase_d, pbase));
+  // every offset list, and the words read back: error bits, distinct rows
+  // packed and redistributed
+  HostPack up;
+  const size_t at_words = up.add(std::vector<int64_t>(3, 0)), at_rs = up.add(b->row_starts), at_s1 = up.add(b->s1_off),
+               at_s2 = up.add(b->s2_off), at_r1 = up.add(b->r1_off), at_r2 = up.add(b->r2_off),
+               at_h = up.add(b->halo_off), at_pb = up.add(pbase), at_bt = up.add(p->off[HX_F_BT_PTR]),
+               at_rp1 = up.add(p->off[HX_F_R1_PROCS]), at_sp1 = up.add(p->off[HX_F_S1_PROCS]),
+               at_rp2 = up.add(p->off[HX_F_R2_PROCS]), at_sp2 = up.add(p->off[HX_F_S2_PROCS]);
+  HX_TRY(up.upload());
+  auto words = up.at<unsigned long long>(at_words);
+  int* err = (int*)words;
+  auto dev = [&](size_t at) { return up.at<int64_t>(at); };
+  const int64_t *rs_d = dev(at_rs), *s1o = dev(at_s1), *s2o = dev(at_s2), *r1o = dev(at_r1), *r2o = dev(at_r2),
+                *ho = dev(at_h), *pbase_d = dev(at_pb), *bto = dev(at_bt);
+
   HX_TRY(b->gidx_pack.alloc((size_t)b->E1_tot * 4));
   if (b->E1_tot)
     hipLaunchKernelGGL(k_add_rank_base, dim3(walk_blocks(b->E1_tot)), dim3(TB), 0, s, p->d[HX_F_S1_IDX].as<int32_t>(),
-                       b->E1_tot, s1o.as<int64_t>(), R, pbase_d.as<int64_t>(), b->n, (int)ERR_PACK,
-                       b->gidx_pack.as<int32_t>(), err.as<int>());
+                       b->E1_tot, s1o, R, pbase_d, b->n, (int)ERR_PACK,
+                       b->gidx_pack.as<int32_t>(), err);
   HX_HIP(hipGetLastError());
   // push form of the pack: global row -> send_all rows (ascending)
-  DevMem bto;
   HX_TRY(b->wp_ptr.alloc((size_t)(b->n + 1) * 4));
   HX_TRY(b->wp_idx.alloc((size_t)std::max<int64_t>(b->E1_tot, 1) * 4));
   if (v3) {
     // senders other than the owner: group the global pack map directly
-    HX_TRY(check_maps(err));
+    HX_TRY(check_maps(words));
     HX_TRY(dev_group_by_key(b->gidx_pack.as<int32_t>(), b->E1_tot, b->n, b->wp_ptr.as<int32_t>(),
-                            b->wp_idx.as<int32_t>(), s));
+                            b->wp_idx.as<int32_t>(), s, true));
   } else {
-    HX_TRY(upload_vec(bto, p->off[HX_F_BT_PTR]));
     hipLaunchKernelGGL(k_world_pack_ptr, dim3(walk_blocks(b->n)), dim3(TB), 0, s, p->d[HX_F_BT_PTR].as<int32_t>(),
-                       bto.as<int64_t>(), rs_d.as<int64_t>(), s1o.as<int64_t>(), R, b->n, b->E1_tot,
-                       b->wp_ptr.as<int32_t>(), err.as<int>());
+                       bto, rs_d, s1o, R, b->n, b->E1_tot,
+                       b->wp_ptr.as<int32_t>(), err);
     if (b->E1_tot)
       hipLaunchKernelGGL(k_add_rank_base, dim3(walk_blocks(b->E1_tot)), dim3(TB), 0, s,
-                         p->d[HX_F_BT_PERM].as<int32_t>(), b->E1_tot, s1o.as<int64_t>(), R, s1o.as<int64_t>(),
-                         b->E1_tot, (int)ERR_PUSH, b->wp_idx.as<int32_t>(), err.as<int>());
+                         p->d[HX_F_BT_PERM].as<int32_t>(), b->E1_tot, s1o, R, s1o,
+                         b->E1_tot, (int)ERR_PUSH, b->wp_idx.as<int32_t>(), err);
   }
   // redistribution: rows of recv_all (stage-1 part of the forwarder)
   HX_TRY(b->gidx_redist.alloc((size_t)b->E2_tot * 4));
   if (b->E2_tot)
     hipLaunchKernelGGL(k_add_rank_base, dim3(walk_blocks(b->E2_tot)), dim3(TB), 0, s, p->d[HX_F_S2_SRC].as<int32_t>(),
-                       b->E2_tot, s2o.as<int64_t>(), R, r1o.as<int64_t>(), b->R1_tot, (int)ERR_REDIST,
-                       b->gidx_redist.as<int32_t>(), err.as<int>());
+                       b->E2_tot, s2o, R, r1o, b->R1_tot, (int)ERR_REDIST,
+                       b->gidx_redist.as<int32_t>(), err);
   // unpack
   if (!b->unpack_identity) {
     HX_TRY(b->gidx_unpack.alloc((size_t)b->H_tot * 4));
     if (b->H_tot)
       hipLaunchKernelGGL(k_world_unpack, dim3(walk_blocks(b->H_tot)), dim3(TB), 0, s,
-                         p->d[HX_F_UNPACK_SRC].as<int32_t>(), b->H_tot, ho.as<int64_t>(), R, r1o.as<int64_t>(),
-                         r2o.as<int64_t>(), b->R1_tot, b->R1_tot + b->R2_tot, b->gidx_unpack.as<int32_t>(),
-                         err.as<int>());
+                         p->d[HX_F_UNPACK_SRC].as<int32_t>(), b->H_tot, ho, R, r1o,
+                         r2o, b->R1_tot, b->R1_tot + b->R2_tot, b->gidx_unpack.as<int32_t>(),
+                         err);
   } else if (b->R1_tot != b->H_tot || b->R2_tot != 0) {
     return fail(HX_ERR_ARG, "plain plan with a receive arena that is not the halo");
   }
@@ -562,30 +567,30 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
   // simulated transfers
   if (b->E1_tot != b->R1_tot || b->E2_tot != b->R2_tot)
     return fail(HX_ERR_ARG, "plan: sends and receives of a stage differ in size");
-  DevMem rp1, sp1, rp2, sp2;
-  HX_TRY(upload_vec(rp1, p->off[HX_F_R1_PROCS]));
-  HX_TRY(upload_vec(sp1, p->off[HX_F_S1_PROCS]));
-  HX_TRY(upload_vec(rp2, p->off[HX_F_R2_PROCS]));
-  HX_TRY(upload_vec(sp2, p->off[HX_F_S2_PROCS]));
   HX_TRY(b->gidx_to1.alloc((size_t)b->E1_tot * 4));
   HX_TRY(b->gidx_to2.alloc((size_t)b->E2_tot * 4));
-  auto transfer_map = [&](int f_s, int f_r, const DevMem& so, const DevMem& sp, const DevMem& ro, const DevMem& rp,
+  auto transfer_map = [&](int f_s, int f_r, const int64_t* so, size_t sp, const int64_t* ro, size_t rp,
                           int64_t base, int64_t hi, DevMem& out) {
     const int64_t nmsg = p->tot(f_s);
     if (nmsg == 0) return;
     const int64_t blocks = (nmsg + TB / kMsgLanes - 1) / (TB / kMsgLanes);
     hipLaunchKernelGGL(k_transfer_map, dim3((unsigned)std::min<int64_t>(blocks, 1 << 16)), dim3(TB), 0, s, nmsg, R,
-                       so.as<int64_t>(), sp.as<int64_t>(), p->d[f_s].as<int32_t>(), p->d[f_s + 1].as<int32_t>(),
-                       p->d[f_s + 2].as<int32_t>(), ro.as<int64_t>(), rp.as<int64_t>(), p->d[f_r].as<int32_t>(),
+                       so, dev(sp), p->d[f_s].as<int32_t>(), p->d[f_s + 1].as<int32_t>(),
+                       p->d[f_s + 2].as<int32_t>(), ro, dev(rp), p->d[f_r].as<int32_t>(),
                        p->d[f_r + 1].as<int32_t>(), p->d[f_r + 2].as<int32_t>(), base, hi, out.as<int32_t>(),
-                       err.as<int>());
+                       err);
   };
   static_assert(HX_F_S1_COUNTS == HX_F_S1_PROCS + 1 && HX_F_S1_DISPLS == HX_F_S1_PROCS + 2, "list fields");
-  transfer_map(HX_F_S1_PROCS, HX_F_R1_PROCS, s1o, sp1, r1o, rp1, 0, b->R1_tot, b->gidx_to1);
-  transfer_map(HX_F_S2_PROCS, HX_F_R2_PROCS, s2o, sp2, r2o, rp2, b->R1_tot, b->R1_tot + b->R2_tot, b->gidx_to2);
+  transfer_map(HX_F_S1_PROCS, HX_F_R1_PROCS, s1o, at_sp1, r1o, at_rp1, 0, b->R1_tot, b->gidx_to1);
+  transfer_map(HX_F_S2_PROCS, HX_F_R2_PROCS, s2o, at_sp2, r2o, at_rp2, b->R1_tot, b->R1_tot + b->R2_tot, b->gidx_to2);
   HX_HIP(hipGetLastError());
+  // distinct rows, for the algorithmic bytes
+  DevMem seen;
+  HX_TRY(dev_count_nonempty(b->wp_ptr.as<int32_t>(), b->n, words + 1, s));
+  HX_TRY(dev_count_distinct(b->gidx_redist.as<int32_t>(), b->E2_tot, b->R1_tot, &seen, words + 2, s));
   // every index a kernel will follow stays inside its source
-  HX_TRY(check_maps(err));
+  int64_t U1 = 0, U2 = 0;
+  HX_TRY(check_maps(words, &U1, &U2));
   // staged backward of a locality plan (the forward's stages reversed):
   //   reverse unpack   a relabelling: the gradient of receive slot k is the
   //                    halo gradient row that read it (inv_unpack[k])
@@ -642,9 +647,6 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
   }
   // algorithmic bytes per phase
   {
-    int64_t U1 = 0, U2 = 0;
-    HX_TRY(dev_count_nonempty(b->wp_ptr.as<int32_t>(), b->n, &U1, s));
-    HX_TRY(dev_count_nonzero_flags(b->gidx_redist.as<int32_t>(), b->E2_tot, b->R1_tot, &U2, s));
     const int64_t rbi = (int64_t)rb;
     b->bytes[PH_PACK] = (b->E1_tot + U1) * rbi + 4 * b->E1_tot;
     b->bytes[PH_REDIST] = (b->E2_tot + U2) * rbi + 4 * b->E2_tot;
