@@ -430,21 +430,14 @@ int hx_backward(hx_req* req, void* stream);
  * device [E1, ncols] (may be NULL when E1 = 0), g_x device [n_local, ncols],
  * both in the request's dtype; they are used by this call only and the
  * request's bound gradients are left as they are.
- * The segmented sum's launch table (job descriptor, tile prefix and each
- * tile's entry range) is written by a kernel on stream into a fixed
- * library-owned device area of HX_NOALLOC_SCRATCH_BYTES per GPU, held from
- * the first call on that GPU until the process ends, instead of device
- * memory allocated for the request: the call makes no allocation (neither
- * hipMalloc nor the installed allocator) and no memset, only two kernel
- * launches on stream.
+ * The call makes no allocation (neither hipMalloc nor the installed
+ * allocator), no memset and no table in device memory: it is one kernel launch
+ * on stream, its job in the launch's arguments.  Calls that overlap on one GPU
+ * (other streams or threads) are independent of each other.
  * Limit: the sum's tiles, ceil(n_local / tile_rows) with tile_rows between
  * 64 and 512 chosen from the row size (512 for rows of 128 bytes or less),
- * must fit the area: at most (HX_NOALLOC_SCRATCH_BYTES - 512) / 8 = 131008
- * tiles; beyond that the call fails with HX_ERR_UNSUPPORTED and launches
- * nothing.
- * Every call on a GPU uses that GPU's one area: calls issued in order on one
- * stream are safe, calls that overlap on one GPU (other streams, or threads
- * without ordering) race and give wrong results.
+ * at most (HX_NOALLOC_SCRATCH_BYTES - 512) / 8 = 131008 of them; beyond that
+ * the call fails with HX_ERR_UNSUPPORTED and launches nothing.
  * Errors: HX_ERR_ARG (null request, null g_send with E1 > 0, null g_x with
  * n_local > 0), HX_ERR_UNSUPPORTED, HX_ERR_HIP.
  * ------------------------------------------------------------------------- */

@@ -229,17 +229,11 @@ int build_gather_table(const std::vector<GatherJob>& jobs, int dtype, int row_by
                        const Sched& s, LaunchTable* t, int tag = TAG_TRANSFER);
 int build_segsum_table(const std::vector<SegSumJob>& jobs, int dtype, int row_bytes,
                        const Sched& s, LaunchTable* t, int tag = TAG_OWNER_SUM);
-// The same table for one job, written by a kernel on stream into caller-
-// provided device memory `area` of area_bytes (job descriptor, tile prefix,
-// tile entry ranges; nothing is allocated), then launched on stream.  The
-// area must stay untouched until the launch has run.  HX_ERR_UNSUPPORTED when
-// the tile entry ranges do not fit (limit: segsum_area_max_tiles).
-int launch_segsum_in_area(const SegSumJob& job, int dtype, int row_bytes, const Sched& s, void* area,
-                          size_t area_bytes, hipStream_t stream, int tag = TAG_OWNER_SUM);
-constexpr size_t kAreaHeadBytes = 512;  // job descriptor and tile prefix ahead of the entry ranges
-inline int64_t segsum_area_max_tiles(size_t area_bytes) {
-  return area_bytes <= kAreaHeadBytes ? 0 : (int64_t)((area_bytes - kAreaHeadBytes) / sizeof(int2));
-}
+// The sum of one job, launched on stream with the job in the launch's
+// arguments: nothing is allocated or written beside the sums.
+// HX_ERR_UNSUPPORTED beyond max_tiles tiles.
+int launch_segsum_one(const SegSumJob& job, int dtype, int row_bytes, const Sched& s, int64_t max_tiles,
+                      hipStream_t stream);
 int build_scatter_table(const std::vector<SegSumJob>& jobs, int dtype, int row_bytes,
                         const Sched& s, LaunchTable* t, int tag = TAG_PACK);
 struct LaunchOpt {
@@ -247,6 +241,7 @@ struct LaunchOpt {
   // a caller's buffers beside the named ones (kern::Beside); src: push packs
   // and copies that deliver, dst: copies and segmented sums
   int64_t src = 0, dst = 0;
+  const SegSumJob* one = nullptr;  // segmented sums: the table's one job, in the launch's arguments
 };
 int launch_table(const LaunchTable& t, hipStream_t stream, const LaunchOpt& o = LaunchOpt());
 

@@ -63,25 +63,6 @@ __global__ void __launch_bounds__(256) k_term_count(const SegSumJob* __restrict_
   if (acc) atomicAdd(total, acc);
 }
 
-// The launch table of a single segmented-sum job written in place: the job
-// descriptor, the tile prefix {0, ntiles} and every tile's entry range (as
-// k_tile_terms), all from the kernel's arguments and the job's row pointers.
-__global__ void __launch_bounds__(256) k_area_table(SegSumJob job, int64_t ntiles, int tile_rows,
-                                                    SegSumJob* __restrict__ jobs, int64_t* __restrict__ ts,
-                                                    int2* __restrict__ te) {
-  const int64_t first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (first == 0) {
-    jobs[0] = job;
-    ts[0] = 0;
-    ts[1] = ntiles;
-  }
-  for (int64_t t = first; t < ntiles; t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r0 = t * (int64_t)tile_rows;
-    const int64_t r1 = min(r0 + (int64_t)tile_rows, job.nrows);
-    te[t] = make_int2(job.ptr[r0], job.ptr[r1]);
-  }
-}
-
 // Clears the windows of jobs that hold less than half of their indices
 // and marks the jobs whose window holds all of them (device-side count).
 int drop_bad_windows(std::vector<GatherJob>* w) {
@@ -381,27 +362,21 @@ int build_segsum_table(const std::vector<SegSumJob>& jobs, int dtype, int row_by
   return fill_tile_terms(t);
 }
 
-int launch_segsum_in_area(const SegSumJob& job, int dtype, int row_bytes, const Sched& s, void* area,
-                          size_t area_bytes, hipStream_t stream, int tag) {
+int launch_segsum_one(const SegSumJob& job, int dtype, int row_bytes, const Sched& s, int64_t max_tiles,
+                      hipStream_t stream) {
   LaunchTable t;
   std::vector<SegSumJob> kept;
   std::vector<int64_t> ts;
-  HX_TRY(shape_segsum_table(std::vector<SegSumJob>(1, job), dtype, row_bytes, s, &t, tag, &kept, &ts));
+  Sched sc = s;
+  if (!sc.pair_rows) sc.lds_window = 0;  // (the windowed form reads launch tables only)
+  HX_TRY(shape_segsum_table(std::vector<SegSumJob>(1, job), dtype, row_bytes, sc, &t, TAG_OWNER_SUM, &kept, &ts));
   if (t.ntiles == 0) return HX_SUCCESS;
-  if (t.ntiles > segsum_area_max_tiles(area_bytes))
-    return fail(HX_ERR_UNSUPPORTED, "%lld tiles of %d rows exceed the %lld a %zu-byte area holds",
-                (long long)t.ntiles, t.sched.tile_rows, (long long)segsum_area_max_tiles(area_bytes), area_bytes);
-  if (area == nullptr || ((uintptr_t)area % 256) != 0) return fail(HX_ERR_ARG, "area must be 256-byte aligned");
-  static_assert(sizeof(SegSumJob) + 2 * sizeof(int64_t) <= kAreaHeadBytes, "area head");
-  char* base = static_cast<char*>(area);
-  t.jobs.borrow(base, sizeof(SegSumJob));
-  t.tile_start.borrow(base + 256, 2 * sizeof(int64_t));
-  t.tile_terms.borrow(base + kAreaHeadBytes, (size_t)t.ntiles * sizeof(int2));
-  const int grid = (int)std::min<int64_t>((t.ntiles + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_area_table, dim3(grid), dim3(256), 0, stream, kept[0], t.ntiles, t.sched.tile_rows,
-                     t.jobs.as<SegSumJob>(), t.tile_start.as<int64_t>(), t.tile_terms.as<int2>());
-  HX_HIP(hipGetLastError());
-  return launch_table(t, stream);
+  if (t.ntiles > max_tiles)
+    return fail(HX_ERR_UNSUPPORTED, "%lld tiles of %d rows exceed %lld", (long long)t.ntiles, t.sched.tile_rows,
+                (long long)max_tiles);
+  LaunchOpt o;
+  o.one = &kept[0];
+  return launch_table(t, stream, o);
 }
 
 int build_scatter_table(const std::vector<SegSumJob>& jobs, int dtype, int row_bytes, const Sched& s,
@@ -421,6 +396,7 @@ int launch_table(const LaunchTable& t, hipStream_t s, const LaunchOpt& o) {
   if (o.deliver && !t.deliver) return fail(HX_ERR_STATE, "a launch table without second destinations");
   if (t.kind == KIND_GATHER) launch_gather_kernels(t, s, o);
   else if (t.kind == KIND_SCATTER) launch_scatter_kernels(t, s, o);
+  else if (o.one) launch_segsum_one_kernels(t, s, o);
   else launch_segsum_kernels(t, s, o);
   HX_HIP(hipGetLastError());
   return HX_SUCCESS;

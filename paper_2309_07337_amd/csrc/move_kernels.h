@@ -966,6 +966,13 @@ __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ 
 // coalesced loads, so each row then costs one dependent global access (its
 // terms) instead of three.
 
+// ONE (here and in the forms below): the launch has one job, given in its
+// arguments (jobs points there; ts, te and njobs are not read), and a tile's
+// entry range comes from its row pointers.  Nothing has to be written to memory
+// before such a launch: a kernel of its own for the table cost 7 us of the 15
+// that the backward of one rank's 1024 rows took.  (A template parameter rather
+// than a job source passed in: with the table behind a struct the loads of its
+// entries lost their scalar form, 128-B rows 420 -> 550 us.)
 // A row's sum, also into the caller's buffer where there is one.
 template <class V, bool NT, class P>
 __device__ __forceinline__ void store_sum(P p, V v, const Beside& also) {
@@ -980,7 +987,7 @@ __device__ __forceinline__ CP term_row(CP in, CP in2, int32_t split, int32_t t, 
   return t < split ? in + (int64_t)t * (int64_t)rb : in2 + (int64_t)(t - split) * (int64_t)rb;
 }
 
-template <class T, int VB, int NV, int LPR, int U, bool NT>
+template <class T, int VB, int NV, int LPR, int U, bool NT, bool ONE>
 __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                             const int2* __restrict__ te, int njobs, int64_t ntiles,
                                             int tile_rows, int nv_rt, int cap_terms, Beside also) {
@@ -1004,9 +1011,10 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
   int64_t t0, t1;
   tile_range(ntiles, &t0, &t1);
   if (t0 >= t1) return;
-  int j = find_job(ts, njobs, t0);
+  int j = ONE ? 0 : find_job(ts, njobs, t0);
   for (int64_t t = t0; t < t1; ++t) {
-    while (t >= ts[j + 1]) ++j;
+    if constexpr (!ONE)
+      while (t >= ts[j + 1]) ++j;
     const char* __restrict__ in = jobs[j].in;
     // terms t >= split are rows t - split of the second input
     const int32_t split = jobs[j].split;
@@ -1015,7 +1023,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
     const int32_t* __restrict__ ptr = jobs[j].ptr;
     const int32_t* __restrict__ idx = jobs[j].idx;
     const int64_t nrows = jobs[j].nrows;
-    const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
+    const int64_t r0 = (t - (ONE ? 0 : ts[j])) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, nrows);
     const size_t rb = (size_t)nv * VB;
     if constexpr (NV > 0) {
@@ -1025,7 +1033,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
       bool stage_idx = false;
       const int nt = (int)(r1 - r0);
       if (stage_ptr) {
-        const int2 er = te[t];
+        const int2 er = ONE ? make_int2(ptr[r0], ptr[r1]) : te[t];
         P0 = er.x;
         const int32_t ne = er.y - P0;
         stage_idx = ne <= STAGE_ENTRIES;
@@ -1189,7 +1197,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
 // stream of vectors over the lanes (see the flat gather); other tiles, and a
 // row with more terms than the buffer holds, add straight from memory.  Each
 // lane adds its vector's terms in ascending entry order, the first term first.
-template <class T, int VB, int U, bool NT>
+template <class T, int VB, int U, bool NT, bool ONE>
 __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                                  const int2* __restrict__ te, int njobs, int64_t ntiles,
                                                  int tile_rows, int nv, int cap_terms, Beside also) {
@@ -1202,21 +1210,22 @@ __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ j
   int64_t t0, t1;
   tile_range(ntiles, &t0, &t1);
   if (t0 >= t1) return;
-  int j = find_job(ts, njobs, t0);
+  int j = ONE ? 0 : find_job(ts, njobs, t0);
   const int bd = blockDim.x, tid = threadIdx.x;
   const size_t rb = (size_t)nv * VB;
   for (int64_t t = t0; t < t1; ++t) {
-    while (t >= ts[j + 1]) ++j;
+    if constexpr (!ONE)
+      while (t >= ts[j + 1]) ++j;
     const char* __restrict__ in = jobs[j].in;
     const int32_t split = jobs[j].split;
     const char* __restrict__ in2 = jobs[j].in2;
     char* __restrict__ out = jobs[j].out;
     const int32_t* __restrict__ ptr = jobs[j].ptr;
     const int32_t* __restrict__ idx = jobs[j].idx;
-    const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
+    const int64_t r0 = (t - (ONE ? 0 : ts[j])) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
     const int nt = (int)(r1 - r0);
-    const int2 er = te[t];
+    const int2 er = ONE ? make_int2(ptr[r0], ptr[r1]) : te[t];
     const int32_t P0 = er.x;
     const int ne = er.y - P0;
     // sums of rows [r, r + n) straight from memory
@@ -1421,7 +1430,7 @@ __device__ __forceinline__ void segsum_win_body(const SegSumJob* __restrict__ jo
 // memory.  Per row the adds run in entry order from the first term (a lone
 // -0 stays -0); an empty row stores +0.
 // ---------------------------------------------------------------------------
-template <class T, int U, int D, bool NT>
+template <class T, int U, int D, bool NT, bool ONE>
 __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                                 int njobs, int64_t ntiles, int tile_rows, Beside also) {
   constexpr int RB = (int)sizeof(T);
@@ -1429,13 +1438,14 @@ __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jo
   int64_t t0, t1;
   tile_range(ntiles, &t0, &t1);
   if (t0 >= t1) return;
-  int j = find_job(ts, njobs, t0);
+  int j = ONE ? 0 : find_job(ts, njobs, t0);
   int staged = -1;
   uint32_t lds_a = 0;  // LDS byte of the staged window's first term (0..15)
   const int bd = blockDim.x, tid = threadIdx.x;
   const int64_t step = (int64_t)bd * U;  // rows per pass
   for (int64_t t = t0; t < t1; ++t) {
-    while (t >= ts[j + 1]) ++j;
+    if constexpr (!ONE)
+      while (t >= ts[j + 1]) ++j;
     const HX_G char* __restrict__ in = (const HX_G char*)jobs[j].in;
     const HX_G char* __restrict__ in2 = (const HX_G char*)jobs[j].in2;
     const int32_t split = jobs[j].split;
@@ -1445,7 +1455,7 @@ __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jo
     const int64_t nrows = jobs[j].nrows;
     const int32_t win_lo = (int32_t)jobs[j].win_lo;
     const uint32_t win_rows = (uint32_t)jobs[j].win_rows;
-    const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
+    const int64_t r0 = (t - (ONE ? 0 : ts[j])) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, nrows);
     const bool use_win = win_rows > 0;
     auto term = [&](int32_t tm) -> T {
@@ -1565,5 +1575,6 @@ __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jo
 void launch_gather_kernels(const LaunchTable& t, hipStream_t s, const LaunchOpt& o);
 void launch_scatter_kernels(const LaunchTable& t, hipStream_t s, const LaunchOpt& o);
 void launch_segsum_kernels(const LaunchTable& t, hipStream_t s, const LaunchOpt& o);
+void launch_segsum_one_kernels(const LaunchTable& t, hipStream_t s, const LaunchOpt& o);
 
 }  // namespace hx

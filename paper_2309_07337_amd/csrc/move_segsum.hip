@@ -13,7 +13,7 @@ namespace {
   __global__ void __launch_bounds__(1024)                                                            \
       NAME(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts, int njobs,            \
            const int2* __restrict__ te, int64_t ntiles, int tile_rows, int nv_rt, int cap_terms, Beside also) { \
-    segsum_body<T, VB, NV, LPR, U, NT>(jobs, ts, te, njobs, ntiles, tile_rows, nv_rt, cap_terms, also); \
+    segsum_body<T, VB, NV, LPR, U, NT, false>(jobs, ts, te, njobs, ntiles, tile_rows, nv_rt, cap_terms, also); \
   }                                                                                                  \
   template <class T, int VB, int NV, int LPR, int U, bool NT>                                        \
   __global__ void __launch_bounds__(512)                                                             \
@@ -25,17 +25,17 @@ namespace {
   __global__ void __launch_bounds__(1024)                                                            \
       NAME##_flat(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts, int njobs,     \
                   const int2* __restrict__ te, int64_t ntiles, int tile_rows, int nv, int cap_terms, Beside also) { \
-    segsum_flat_body<T, VB, U, NT>(jobs, ts, te, njobs, ntiles, tile_rows, nv, cap_terms, also);     \
+    segsum_flat_body<T, VB, U, NT, false>(jobs, ts, te, njobs, ntiles, tile_rows, nv, cap_terms, also); \
   }                                                                                                  \
   template <class T, int U, int D, bool NT>                                                          \
   __global__ void __launch_bounds__(1024)                                                            \
       NAME##_vec(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts, int njobs,      \
                  int64_t ntiles, int tile_rows, Beside also) {                                       \
-    segsum_vec_body<T, U, D, NT>(jobs, ts, njobs, ntiles, tile_rows, also);                          \
+    segsum_vec_body<T, U, D, NT, false>(jobs, ts, njobs, ntiles, tile_rows, also);                   \
   }                                                                                                  \
   struct NAME##_vgo {                                                                                \
     template <class T, int U, int D, bool NT>                                                        \
-    static void go(const LaunchTable& t, hipStream_t s, const LaunchOpt& o) {                                            \
+    static void go(const LaunchTable& t, hipStream_t s, const LaunchOpt& o) {                        \
       hipLaunchKernelGGL((NAME##_vec<T, U, D, NT>), dim3(t.grid), dim3(t.sched.block_threads),       \
                          (unsigned)t.win_bytes, s, t.jobs.as<SegSumJob>(), t.tile_start.as<int64_t>(), \
                          t.njobs, t.ntiles, t.sched.tile_rows, Beside{0, o.dst});                    \
@@ -44,9 +44,9 @@ namespace {
   template <class T>                                                                                 \
   struct NAME##_go {                                                                                 \
     template <int VB, int U, bool NT>                                                                \
-    static void flat(const LaunchTable& t, hipStream_t s, const LaunchOpt& o, int nv) {                                  \
+    static void flat(const LaunchTable& t, hipStream_t s, const LaunchOpt& o, int nv) {              \
       if constexpr ((size_t)VB < sizeof(T)) {                                                        \
-        (void)t; (void)s; (void)o; (void)nv; /* excluded when the table is built */                           \
+        (void)t; (void)s; (void)o; (void)nv; /* excluded when the table is built */                  \
       } else {                                                                                       \
         hipLaunchKernelGGL((NAME##_flat<T, VB, U, NT>), dim3(t.grid), dim3(t.sched.block_threads),   \
                            (unsigned)t.val_bytes, s, t.jobs.as<SegSumJob>(),                         \
@@ -55,11 +55,11 @@ namespace {
       }                                                                                              \
     }                                                                                                \
     template <int VB, int NV, int LPR, int U, bool NT>                                               \
-    static void go(const LaunchTable& t, hipStream_t s, const LaunchOpt& o, int nv) {                                    \
+    static void go(const LaunchTable& t, hipStream_t s, const LaunchOpt& o, int nv) {                \
       if constexpr ((size_t)VB < sizeof(T)) {                                                        \
-        (void)t; (void)s; (void)o; (void)nv; /* excluded when the table is built */                           \
+        (void)t; (void)s; (void)o; (void)nv; /* excluded when the table is built */                  \
       } else {                                                                                       \
-        if constexpr (NV > 0 && NV * VB <= 64) { /* term windows pay off for short rows only */    \
+        if constexpr (NV > 0 && NV * VB <= 64) { /* term windows pay off for short rows only */      \
           if (t.win_bytes > 0) {                                                                     \
             hipLaunchKernelGGL((NAME##_win<T, VB, NV, LPR, U, NT>), dim3(t.grid),                    \
                                dim3(t.sched.block_threads), (unsigned)t.win_bytes, s,                \
