@@ -54,15 +54,23 @@ __device__ __forceinline__ int guess_rank(const int64_t* __restrict__ starts, in
   return upper_rank(starts, R, v);
 }
 
-// Calls f(i, rank) for i in [first, first + n), a chunk of consecutive
-// elements per workgroup of kWalkThreads.  One search per chunk, then each
-// lane's rank only moves on: a search per element was a serial chain of ten
-// loads on 1024 ranks (8.4 M entries: 78 us a pass, 36 so).
+// Calls f(i, rank) for i in [0, n), a chunk of consecutive elements per
+// workgroup of kWalkThreads.  One search per chunk, then each lane's rank only
+// moves on; in a chunk of one rank (most, where ranks have more elements than a
+// chunk) nothing is looked up, and the lane's elements are in flight together.
+// A search per element was a serial chain of ten loads on 1024 ranks: 78 us a
+// pass over 8.4 M entries, 25 so.
 template <class F>
 __device__ __forceinline__ void for_ranked(int64_t n, const int64_t* __restrict__ starts, int R, F f) {
+  constexpr int kItems = kWalkChunk / kWalkThreads;
   for (int64_t c0 = (int64_t)blockIdx.x * kWalkChunk; c0 < n; c0 += (int64_t)gridDim.x * kWalkChunk) {
     const int64_t c1 = min(c0 + (int64_t)kWalkChunk, n);
     int r = upper_rank(starts, R, c0);
+    if (c0 + kWalkChunk <= n && (r + 1 >= R || starts[r + 1] >= c1)) {
+#pragma unroll
+      for (int k = 0; k < kItems; ++k) f(c0 + threadIdx.x + k * kWalkThreads, r);
+      continue;
+    }
     for (int64_t i = c0 + threadIdx.x; i < c1; i += kWalkThreads) {
       r = seek_rank(starts, R, r, i);
       f(i, r);
