@@ -220,7 +220,7 @@ struct LaunchTable {
   int64_t ntiles = 0;
   int grid = 0;
   DevMem jobs;        // GatherJob[] or SegSumJob[]
-  DevMem tile_start;  // int64_t[njobs + 1]
+  DevMem tile_start;  // int64_t[njobs + 1], then every tile's job: int32_t[ntiles]
   DevMem tile_terms;  // segmented sums, push pack: int2[ntiles], entry range {ptr[r0], ptr[r1]} of each tile
   bool empty() const { return ntiles == 0; }
 };

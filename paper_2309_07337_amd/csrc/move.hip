@@ -43,14 +43,10 @@ __global__ void __launch_bounds__(256) k_tile_terms(const SegSumJob* __restrict_
                                                     int tile_rows, int2* __restrict__ te) {
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < ntiles;
        t += (int64_t)gridDim.x * blockDim.x) {
-    int lo = 0, hi = njobs - 1;  // largest j with ts[j] <= t
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (ts[mid] <= t) lo = mid; else hi = mid - 1;
-    }
-    const int64_t r0 = (t - ts[lo]) * (int64_t)tile_rows;
-    const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[lo].nrows);
-    te[t] = make_int2(jobs[lo].ptr[r0], jobs[lo].ptr[r1]);
+    const int j = kern::job_of(ts, njobs, t);
+    const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
+    const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
+    te[t] = make_int2(jobs[j].ptr[r0], jobs[j].ptr[r1]);
   }
 }
 
@@ -156,10 +152,15 @@ int upload_table(const std::vector<J>& kept, const std::vector<int64_t>& ts, Lau
   if (t->ntiles == 0) return HX_SUCCESS;
   HostPack up;
   up.add(kept);
-  const size_t at_ts = up.add(ts);
+  // the tile prefix, then every tile's job
+  std::vector<int64_t> tiles(ts);
+  tiles.resize(ts.size() + ((size_t)t->ntiles + 1) / 2);
+  int32_t* job = reinterpret_cast<int32_t*>(tiles.data() + ts.size());
+  for (size_t j = 0; j + 1 < ts.size(); ++j) std::fill(job + ts[j], job + ts[j + 1], (int32_t)j);
+  const size_t at_ts = up.add(tiles);
   HX_TRY(up.upload());
   t->jobs = std::move(up.dev);
-  t->tile_start.borrow(t->jobs.as<char>() + at_ts, ts.size() * sizeof(int64_t));
+  t->tile_start.borrow(t->jobs.as<char>() + at_ts, tiles.size() * sizeof(int64_t));
   return HX_SUCCESS;
 }
 
