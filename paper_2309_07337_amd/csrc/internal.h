@@ -121,6 +121,11 @@ struct hx_batch {
   hx::DevMem send_all, recv_all;             // [S1 | S2], [RECV1 | RECV2] of all ranks
   hx::DevMem gidx_pack, gidx_redist, gidx_unpack;
   hx::DevMem gidx_to1, gidx_to2;             // stage-1 / stage-2 send slot -> the row of recv_all it is delivered to
+  // The stage-2 lists lie in memory as their slots do behind the E1_tot
+  // stage-1 ones (modulo 16 bytes of slots), so that one first row aligns both
+  // (16-byte row groups, build_gather_table).
+  int32_t* stage2(const hx::DevMem& m) const { return m.as<int32_t>() + (E1_tot & 3); }
+  size_t stage2_bytes() const { return (size_t)(E2_tot + 3) * 4; }
   hx::DevMem g_send_all;                     // plain worlds: gradients of every rank's send slots
   hx::DevMem halo_cols;                      // halo_all's columns, until the adjoint CSR is built from them
   hx::DevMem wb_ptr, wb_idx;                 // adjoint CSR: global column -> halo_all rows (world_adjoint)

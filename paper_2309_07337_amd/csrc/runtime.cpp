@@ -211,14 +211,18 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     } else if (w.rows >= 1 << 23) {
       // the job's window (if it has one) staged once per (up to) 16384-row tile
       // while the tile's indices are in flight (redistribution and unpack of 39
-      // M rows 476 -> 460, of 9 M FP32 ones 97 -> 89)
+      // M rows 476 -> 460; of 9 M FP32 ones 76 -> 72, with 512 lanes and twice
+      // the groups, which spill, 86)
       s.lds_window = 1;
       s.tile_rows = 16384;
-      s.block_threads = 512;
+      s.block_threads = rb == 8 ? 512 : 256;
+      if (rb == 4) s.unroll = 2;
     } else {
-      // what the windows hold is in the caches anyhow (4.7 M rows: 86 -> 66)
+      // what the windows hold is in the caches anyhow (4.7 M rows: 86 -> 66);
+      // one pass of the workgroup a tile
       s.tile_rows = 1024;
       s.block_threads = 256;
+      s.unroll = rb == 8 ? 2 : 1;
     }
   } else {
     // (24-B rows, packs 73 -> 66, redistribution and unpack 160 -> 150; 12 B

@@ -245,20 +245,20 @@ int world_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
       break;
     case PH_REDIST:
       if (merged && !sc.lds_window) {
-        GatherJob j{ra, (char*)sa + b->E1_tot * rb, b->gidx_redist.as<int32_t>(), b->E2_tot};
+        GatherJob j{ra, (char*)sa + b->E1_tot * rb, b->stage2(b->gidx_redist), b->E2_tot};
         j.dst2 = to;
-        j.idx2 = sim ? b->gidx_to2.as<int32_t>() : nullptr;
+        j.idx2 = sim ? b->stage2(b->gidx_to2) : nullptr;
         g->push_back({j});
       } else {
         // one job per rank: it forwards values from its own stage-1 receive arena
         std::vector<GatherJob> v;
         for (int r = 0; r < b->R; ++r)
           v.push_back(GatherJob{ra, (char*)sa + (b->E1_tot + b->s2_off[r]) * rb,
-                                b->gidx_redist.as<int32_t>() + b->s2_off[r], b->s2_off[r + 1] - b->s2_off[r],
+                                b->stage2(b->gidx_redist) + b->s2_off[r], b->s2_off[r + 1] - b->s2_off[r],
                                 b->r1_off[r], b->r1_off[r + 1] - b->r1_off[r]});
         for (int r = 0; r < b->R; ++r) {
           v[r].dst2 = to;
-          v[r].idx2 = sim ? b->gidx_to2.as<int32_t>() + b->s2_off[r] : nullptr;
+          v[r].idx2 = sim ? b->stage2(b->gidx_to2) + b->s2_off[r] : nullptr;
         }
         if (merged) g->push_back(v);
         else for (auto& x : v) g->push_back({x});
@@ -547,11 +547,11 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
                          b->E1_tot, (int)ERR_PUSH, b->wp_idx.as<int32_t>(), err);
   }
   // redistribution: rows of recv_all (stage-1 part of the forwarder)
-  HX_TRY(b->gidx_redist.alloc((size_t)b->E2_tot * 4));
+  HX_TRY(b->gidx_redist.alloc(b->stage2_bytes()));
   if (b->E2_tot)
     hipLaunchKernelGGL(k_add_rank_base, dim3(walk_blocks(b->E2_tot)), dim3(TB), 0, s, p->d[HX_F_S2_SRC].as<int32_t>(),
                        b->E2_tot, s2o, R, r1o, b->R1_tot, (int)ERR_REDIST,
-                       b->gidx_redist.as<int32_t>(), err);
+                       b->stage2(b->gidx_redist), err);
   // unpack
   if (!b->unpack_identity) {
     HX_TRY(b->gidx_unpack.alloc((size_t)b->H_tot * 4));
@@ -568,26 +568,27 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
   if (b->E1_tot != b->R1_tot || b->E2_tot != b->R2_tot)
     return fail(HX_ERR_ARG, "plan: sends and receives of a stage differ in size");
   HX_TRY(b->gidx_to1.alloc((size_t)b->E1_tot * 4));
-  HX_TRY(b->gidx_to2.alloc((size_t)b->E2_tot * 4));
+  HX_TRY(b->gidx_to2.alloc(b->stage2_bytes()));
   auto transfer_map = [&](int f_s, int f_r, const int64_t* so, size_t sp, const int64_t* ro, size_t rp,
-                          int64_t base, int64_t hi, DevMem& out) {
+                          int64_t base, int64_t hi, int32_t* out) {
     const int64_t nmsg = p->tot(f_s);
     if (nmsg == 0) return;
     const int64_t blocks = (nmsg + TB / kMsgLanes - 1) / (TB / kMsgLanes);
     hipLaunchKernelGGL(k_transfer_map, dim3((unsigned)std::min<int64_t>(blocks, 1 << 16)), dim3(TB), 0, s, nmsg, R,
                        so, dev(sp), p->d[f_s].as<int32_t>(), p->d[f_s + 1].as<int32_t>(),
                        p->d[f_s + 2].as<int32_t>(), ro, dev(rp), p->d[f_r].as<int32_t>(),
-                       p->d[f_r + 1].as<int32_t>(), p->d[f_r + 2].as<int32_t>(), base, hi, out.as<int32_t>(),
+                       p->d[f_r + 1].as<int32_t>(), p->d[f_r + 2].as<int32_t>(), base, hi, out,
                        err);
   };
   static_assert(HX_F_S1_COUNTS == HX_F_S1_PROCS + 1 && HX_F_S1_DISPLS == HX_F_S1_PROCS + 2, "list fields");
-  transfer_map(HX_F_S1_PROCS, HX_F_R1_PROCS, s1o, at_sp1, r1o, at_rp1, 0, b->R1_tot, b->gidx_to1);
-  transfer_map(HX_F_S2_PROCS, HX_F_R2_PROCS, s2o, at_sp2, r2o, at_rp2, b->R1_tot, b->R1_tot + b->R2_tot, b->gidx_to2);
+  transfer_map(HX_F_S1_PROCS, HX_F_R1_PROCS, s1o, at_sp1, r1o, at_rp1, 0, b->R1_tot, b->gidx_to1.as<int32_t>());
+  transfer_map(HX_F_S2_PROCS, HX_F_R2_PROCS, s2o, at_sp2, r2o, at_rp2, b->R1_tot, b->R1_tot + b->R2_tot,
+               b->stage2(b->gidx_to2));
   HX_HIP(hipGetLastError());
   // distinct rows, for the algorithmic bytes
   DevMem seen;
   HX_TRY(dev_count_nonempty(b->wp_ptr.as<int32_t>(), b->n, words + 1, s));
-  HX_TRY(dev_count_distinct(b->gidx_redist.as<int32_t>(), b->E2_tot, b->R1_tot, &seen, words + 2, s));
+  HX_TRY(dev_count_distinct(b->stage2(b->gidx_redist), b->E2_tot, b->R1_tot, &seen, words + 2, s));
   // every index a kernel will follow stays inside its source
   int64_t U1 = 0, U2 = 0;
   HX_TRY(check_maps(words, &U1, &U2));
@@ -617,7 +618,7 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
       hipLaunchKernelGGL(k_invert_range, dim3(blocks_for(b->H_tot)), dim3(TB), 0, s, b->gidx_unpack.as<int32_t>(),
                          b->H_tot, (int64_t)0, S, inv_unpack.as<int32_t>());
     if (b->E2_tot)
-      hipLaunchKernelGGL(k_compose, dim3(blocks_for(b->E2_tot)), dim3(TB), 0, s, b->gidx_to2.as<int32_t>(),
+      hipLaunchKernelGGL(k_compose, dim3(blocks_for(b->E2_tot)), dim3(TB), 0, s, b->stage2(b->gidx_to2),
                          b->E2_tot, inv_unpack.as<int32_t>(), b->gidx_back2.as<int32_t>());
     HX_HIP(hipGetLastError());
     // forwarder-sum CSR; own rows are inv_unpack over the stage-1 slots
@@ -625,7 +626,7 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
     HX_TRY(gperm.alloc((size_t)std::max<int64_t>(b->E2_tot, 1) * 4));
     HX_TRY(lens.alloc((size_t)(b->R1_tot + 1) * 4));
     HX_TRY(b->fwd_ptr.alloc((size_t)(b->R1_tot + 1) * 4));
-    HX_TRY(dev_group_by_key(b->gidx_redist.as<int32_t>(), b->E2_tot, b->R1_tot, gp.as<int32_t>(), gperm.as<int32_t>(),
+    HX_TRY(dev_group_by_key(b->stage2(b->gidx_redist), b->E2_tot, b->R1_tot, gp.as<int32_t>(), gperm.as<int32_t>(),
                             s));
     if (b->R1_tot)
       hipLaunchKernelGGL(k_forward_lens, dim3(blocks_for(b->R1_tot)), dim3(TB), 0, s, inv_unpack.as<int32_t>(),
