@@ -135,8 +135,9 @@ struct SegSumJob {
   // be staged in LDS (win_rows = 0: none)
   int64_t win_lo = 0;
   int64_t win_rows = 0;
-  // push pack: the value of entry e also goes to out2[idx2[e], :] where the
-  // launch asks for it (a message's delivery, simulated)
+  // where a launch delivers (a message's transfer, simulated).  Push pack: the
+  // value of entry e also goes to out2[idx2[e], :]; forwarder sums: row i goes
+  // to out2[idx2[i], :] instead of out[i, :]
   char* out2 = nullptr;
   const int32_t* idx2 = nullptr;
 };

@@ -100,8 +100,9 @@ struct hx_batch {
   hx::LaunchTable lt[4];
   std::vector<hx::LaunchTable> plain[4];
   bool plain_built[4] = {false, false, false, false};
-  hx::LaunchTable lt_back[2];               // the backward's simulated transfers: reverse of stage 1, of stage 2
-  hx::DevMem gidx_from1;                     // plain worlds: halo_all row -> the send slot it was delivered from
+  hx::LaunchTable lt_back, lt_back2;        // the backward's simulated transfers: plain worlds' reverse of stage 1,
+                                            // staged ones' of stage 2
+  hx::DevMem gidx_from1;                     // stage-1 receive slot -> the send slot it was delivered from
   hx::LaunchTable lt_back_copy;              // plain worlds: a caller's halo gradients into the bound ones and back
   int replay = HX_REPLAY_GRAPH;             // as set (hx_batch_set_replay)
   bool active = false;
@@ -171,7 +172,7 @@ int world_phase_jobs(const hx_batch* b, int phase, const Sched& sc, bool merged,
 
 // Builds the closed-form adjoint of a locality world, once.
 int world_adjoint(hx_batch* b);
-// Builds gidx_from1 of a plain world, once.
+// Builds gidx_from1, once.
 int world_from_map(hx_batch* b);
 
 // Device helpers implemented in plan.hip.

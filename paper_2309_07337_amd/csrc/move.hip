@@ -343,6 +343,9 @@ int build_segsum_table(const std::vector<SegSumJob>& jobs, int dtype, int row_by
   HX_TRY(shape_segsum_table(jobs, dtype, row_bytes, s, t, tag, &kept, &ts));
   if (t->ntiles == 0) return HX_SUCCESS;
   HX_TRY(upload_table(kept, ts, t));
+  t->deliver = tag == TAG_FWD_SUM ? 1 : 0;
+  for (const auto& j : kept)
+    if (j.out2 == nullptr) t->deliver = 0;
   if (t->vec16) {
     // one-value sums: 16 terms per row loaded together (one row per lane)
     // where rows average more than three terms (the owner sums of high

@@ -970,6 +970,16 @@ __device__ __forceinline__ void scatter_flat_body(const SegSumJob* __restrict__ 
 // that the backward of one rank's 1024 rows took.  (A template parameter rather
 // than a job source passed in: with the table behind a struct the loads of its
 // entries lost their scalar form, 128-B rows 420 -> 550 us.)
+// O: delivered sums, row r of a job goes to out2[idx2[r]].  The forwarder sums
+// of a world with the simulated transfer go straight to the send slots they
+// travel back to (runs of consecutive rows, a message each), instead of being
+// written, read and written again.
+template <bool O, class P>
+__device__ __forceinline__ int64_t out_row(P oidx, int64_t r) {
+  if constexpr (O) return oidx[r];
+  else return r;
+}
+
 // A row's sum, also into the caller's buffer where there is one.
 template <class V, bool NT, class P>
 __device__ __forceinline__ void store_sum(P p, V v, const Beside& also) {
@@ -984,7 +994,7 @@ __device__ __forceinline__ CP term_row(CP in, CP in2, int32_t split, int32_t t, 
   return t < split ? in + (int64_t)t * (int64_t)rb : in2 + (int64_t)(t - split) * (int64_t)rb;
 }
 
-template <class T, int VB, int NV, int LPR, int U, bool NT, bool ONE>
+template <class T, int VB, int NV, int LPR, int U, bool NT, bool ONE, bool O>
 __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                             const int2* __restrict__ te, int njobs, int64_t ntiles,
                                             int tile_rows, int nv_rt, int cap_terms, Beside also) {
@@ -1016,9 +1026,10 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
     // terms t >= split are rows t - split of the second input
     const int32_t split = jobs[j].split;
     const char* __restrict__ in2 = jobs[j].in2;
-    char* __restrict__ out = jobs[j].out;
+    char* __restrict__ out = O ? jobs[j].out2 : jobs[j].out;
     const int32_t* __restrict__ ptr = jobs[j].ptr;
     const int32_t* __restrict__ idx = jobs[j].idx;
+    const int32_t* __restrict__ oidx = O ? jobs[j].idx2 : nullptr;
     const int64_t nrows = jobs[j].nrows;
     const int64_t r0 = (t - (ONE ? 0 : ts[j])) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, nrows);
@@ -1062,7 +1073,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
             // straight from global memory, in order
             if (rsub == 0) {
               const int32_t a = s_ptr[ra] - P0, len = s_ptr[ra + 1] - s_ptr[ra];
-              V* dp = reinterpret_cast<V*>(out + (r0 + ra) * (int64_t)rb);
+              V* dp = reinterpret_cast<V*>(out + out_row<O>(oidx, r0 + ra) * (int64_t)rb);
 #pragma unroll
               for (int k = 0; k < NVPL; ++k) {
                 const int vi = lane_v + k * LPR;
@@ -1108,7 +1119,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
           __syncthreads();
           for (int r = ra + rsub; r < rq; r += rows_per_pass) {
             const int a = s_ptr[r] - P0 - ea, len = s_ptr[r + 1] - s_ptr[r];
-            V* dp = reinterpret_cast<V*>(out + (r0 + r) * (int64_t)rb);
+            V* dp = reinterpret_cast<V*>(out + out_row<O>(oidx, r0 + r) * (int64_t)rb);
 #pragma unroll
             for (int k = 0; k < NVPL; ++k) {
               const int vi = lane_v + k * LPR;
@@ -1163,7 +1174,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
             }
           }
         }
-        V* dp = reinterpret_cast<V*>(out + r * (int64_t)rb);
+        V* dp = reinterpret_cast<V*>(out + out_row<O>(oidx, r) * (int64_t)rb);
 #pragma unroll
         for (int k = 0; k < NVPL; ++k) {
           const int vi = lane_v + k * LPR;
@@ -1175,7 +1186,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
       for (int64_t r = r0 + rsub; r < r1; r += rows_per_pass) {
         const int32_t p0 = ptr[r];
         const int32_t p1 = ptr[r + 1];
-        V* dp = reinterpret_cast<V*>(out + r * rb);
+        V* dp = reinterpret_cast<V*>(out + out_row<O>(oidx, r) * (int64_t)rb);
         for (int vi = lane_v; vi < nv; vi += LPR) {
           V acc = (V)(T)0;
           for (int32_t e = p0; e < p1; ++e) {
@@ -1194,7 +1205,7 @@ __device__ __forceinline__ void segsum_body(const SegSumJob* __restrict__ jobs, 
 // stream of vectors over the lanes (see the flat gather); other tiles, and a
 // row with more terms than the buffer holds, add straight from memory.  Each
 // lane adds its vector's terms in ascending entry order, the first term first.
-template <class T, int VB, int U, bool NT, bool ONE>
+template <class T, int VB, int U, bool NT, bool ONE, bool O>
 __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                                  const int2* __restrict__ te, int njobs, int64_t ntiles,
                                                  int tile_rows, int nv, int cap_terms, Beside also) {
@@ -1216,9 +1227,10 @@ __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ j
     const char* __restrict__ in = jobs[j].in;
     const int32_t split = jobs[j].split;
     const char* __restrict__ in2 = jobs[j].in2;
-    char* __restrict__ out = jobs[j].out;
+    char* __restrict__ out = O ? jobs[j].out2 : jobs[j].out;
     const int32_t* __restrict__ ptr = jobs[j].ptr;
     const int32_t* __restrict__ idx = jobs[j].idx;
+    const int32_t* __restrict__ oidx = O ? jobs[j].idx2 : nullptr;
     const int64_t r0 = (t - (ONE ? 0 : ts[j])) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, jobs[j].nrows);
     const int nt = (int)(r1 - r0);
@@ -1227,7 +1239,6 @@ __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ j
     const int ne = er.y - P0;
     // sums of rows [r, r + n) straight from memory
     auto from_memory = [&](int64_t r, int n) {
-      V* dp = reinterpret_cast<V*>(out + r * (int64_t)rb);
       const int nvec = n * nv;
       for (int k = tid; k < nvec; k += bd) {
         const uint32_t q = div.row((uint32_t)k);
@@ -1238,7 +1249,7 @@ __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ j
           const V v = reinterpret_cast<const V*>(term_row(in, in2, split, ldv<int32_t, NT>(idx + e), rb))[c];
           acc = e == p0 ? v : acc + v;
         }
-        store_sum<V, NT>(dp + k, acc, also);
+        store_sum<V, NT>(reinterpret_cast<V*>(out + out_row<O>(oidx, r + q) * (int64_t)rb) + c, acc, also);
       }
     };
     if (nt > STAGE_ROWS || ne > STAGE_ENTRIES || cap_terms <= 0) {
@@ -1282,7 +1293,6 @@ __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ j
           if (base + u * bd < tvec) s_val[base + u * bd] = v[u];
       }
       __syncthreads();
-      V* dp = reinterpret_cast<V*>(out + (r0 + ra) * (int64_t)rb);
       const int nvec = (rq - ra) * nv;
       for (int k = tid; k < nvec; k += bd) {
         const uint32_t q = div.row((uint32_t)k);
@@ -1291,7 +1301,7 @@ __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ j
         V acc = (V)(T)0;
         if (len > 0) acc = s_val[a * nv + c];
         for (int d = 1; d < len; ++d) acc = acc + s_val[(a + d) * nv + c];
-        store_sum<V, NT>(dp + k, acc, also);
+        store_sum<V, NT>(reinterpret_cast<V*>(out + out_row<O>(oidx, r0 + ra + q) * (int64_t)rb) + c, acc, also);
       }
       __syncthreads();  // s_val, s_ptr and s_idx are reused next
       ra = rq;
@@ -1310,7 +1320,7 @@ __device__ __forceinline__ void segsum_flat_body(const SegSumJob* __restrict__ j
 // of at most 128 rows and 1536 entries; others read them from global
 // memory).  No term staging buffer, so two such workgroups fit per CU.
 // ---------------------------------------------------------------------------
-template <class T, int VB, int NV, int LPR, int U, bool NT>
+template <class T, int VB, int NV, int LPR, int U, bool NT, bool O>
 __device__ __forceinline__ void segsum_win_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                                 int njobs, int64_t ntiles, int tile_rows, int nv_rt, Beside also) {
   using V = typename NumVec<T, VB>::type;
@@ -1337,9 +1347,10 @@ __device__ __forceinline__ void segsum_win_body(const SegSumJob* __restrict__ jo
     const HX_G char* __restrict__ in = (const HX_G char*)jobs[j].in;
     const int32_t split = jobs[j].split;
     const HX_G char* __restrict__ in2 = (const HX_G char*)jobs[j].in2;
-    HX_G char* __restrict__ out = (HX_G char*)jobs[j].out;
+    HX_G char* __restrict__ out = (HX_G char*)(O ? jobs[j].out2 : jobs[j].out);
     const HX_G int32_t* __restrict__ ptr = (const HX_G int32_t*)jobs[j].ptr;
     const HX_G int32_t* __restrict__ idx = (const HX_G int32_t*)jobs[j].idx;
+    const HX_G int32_t* __restrict__ oidx = O ? (const HX_G int32_t*)jobs[j].idx2 : nullptr;
     const int64_t nrows = jobs[j].nrows;
     const int64_t r0 = (t - ts[j]) * (int64_t)tile_rows;
     const int64_t r1 = min(r0 + (int64_t)tile_rows, nrows);
@@ -1402,7 +1413,7 @@ __device__ __forceinline__ void segsum_win_body(const SegSumJob* __restrict__ jo
             }
           }
         }
-        HX_G V* dp = reinterpret_cast<HX_G V*>(out + r * (int64_t)rb);
+        HX_G V* dp = reinterpret_cast<HX_G V*>(out + out_row<O>(oidx, r) * (int64_t)rb);
 #pragma unroll
         for (int k = 0; k < NVPL; ++k) {
           const int vi = lane_v + k * LPR;
@@ -1427,7 +1438,7 @@ __device__ __forceinline__ void segsum_win_body(const SegSumJob* __restrict__ jo
 // memory.  Per row the adds run in entry order from the first term (a lone
 // -0 stays -0); an empty row stores +0.
 // ---------------------------------------------------------------------------
-template <class T, int U, int D, bool NT, bool ONE>
+template <class T, int U, int D, bool NT, bool ONE, bool O>
 __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jobs, const int64_t* __restrict__ ts,
                                                 int njobs, int64_t ntiles, int tile_rows, Beside also) {
   constexpr int RB = (int)sizeof(T);
@@ -1446,9 +1457,10 @@ __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jo
     const HX_G char* __restrict__ in = (const HX_G char*)jobs[j].in;
     const HX_G char* __restrict__ in2 = (const HX_G char*)jobs[j].in2;
     const int32_t split = jobs[j].split;
-    HX_G char* __restrict__ out = (HX_G char*)jobs[j].out;
+    HX_G char* __restrict__ out = (HX_G char*)(O ? jobs[j].out2 : jobs[j].out);
     const HX_G int32_t* __restrict__ ptr = (const HX_G int32_t*)jobs[j].ptr;
     const HX_G int32_t* __restrict__ idx = (const HX_G int32_t*)jobs[j].idx;
+    const HX_G int32_t* __restrict__ oidx = O ? (const HX_G int32_t*)jobs[j].idx2 : nullptr;
     const int64_t nrows = jobs[j].nrows;
     const int32_t win_lo = (int32_t)jobs[j].win_lo;
     const uint32_t win_rows = (uint32_t)jobs[j].win_rows;
@@ -1522,6 +1534,11 @@ __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jo
       // this pass's values first, then the next passes' prefetches (so that
       // waiting for the values never waits for the prefetches)
       T v[U][D];
+      int32_t orow[U];
+      if constexpr (O) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) orow[u] = ldv<int32_t, NT>(oidx + min(base + tid + (int64_t)u * bd, r1 - 1));
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -1551,7 +1568,7 @@ __device__ __forceinline__ void segsum_vec_body(const SegSumJob* __restrict__ jo
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t r = base + tid + (int64_t)u * bd;
-        if (r < r1) store_sum<T, NT>(reinterpret_cast<HX_G T*>(out + r * RB), acc[u], also);
+        if (r < r1) store_sum<T, NT>(reinterpret_cast<HX_G T*>(out + (O ? (int64_t)orow[u] : r) * RB), acc[u], also);
       }
       if (more) {
 #pragma unroll

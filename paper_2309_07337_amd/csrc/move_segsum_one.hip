@@ -10,16 +10,16 @@ namespace {
 template <class T, int VB, int NV, int LPR, int U, bool NT>
 __global__ void __launch_bounds__(1024)
     k_segsum_one(SegSumJob job, int64_t ntiles, int tile_rows, int nv_rt, int cap_terms) {
-  segsum_body<T, VB, NV, LPR, U, NT, true>(&job, nullptr, nullptr, 1, ntiles, tile_rows, nv_rt, cap_terms, Beside{0, 0});
+  segsum_body<T, VB, NV, LPR, U, NT, true, false>(&job, nullptr, nullptr, 1, ntiles, tile_rows, nv_rt, cap_terms, Beside{0, 0});
 }
 template <class T, int VB, int U, bool NT>
 __global__ void __launch_bounds__(1024)
     k_segsum_one_flat(SegSumJob job, int64_t ntiles, int tile_rows, int nv, int cap_terms) {
-  segsum_flat_body<T, VB, U, NT, true>(&job, nullptr, nullptr, 1, ntiles, tile_rows, nv, cap_terms, Beside{0, 0});
+  segsum_flat_body<T, VB, U, NT, true, false>(&job, nullptr, nullptr, 1, ntiles, tile_rows, nv, cap_terms, Beside{0, 0});
 }
 template <class T, int U, bool NT>
 __global__ void __launch_bounds__(1024) k_segsum_one_vec(SegSumJob job, int64_t ntiles, int tile_rows) {
-  segsum_vec_body<T, U, 4, NT, true>(&job, nullptr, 1, ntiles, tile_rows, Beside{0, 0});
+  segsum_vec_body<T, U, 4, NT, true, false>(&job, nullptr, 1, ntiles, tile_rows, Beside{0, 0});
 }
 
 template <class T>

@@ -768,6 +768,8 @@ static int build_fwd_sum_table(const hx_batch* b, const Sched& sc, LaunchTable* 
     fj.split = (int32_t)b->H_tot;
     fj.win_lo = b->H_tot + b->s2_off[q];
     fj.win_rows = b->s2_off[q + 1] - b->s2_off[q];
+    fj.out2 = b->g_send_all.as<char>();
+    fj.idx2 = b->gidx_from1.as<int32_t>() + k0;
     fjs.push_back(fj);
   }
   return build_segsum_table(fjs, b->dtype, (int)b->row_bytes, sc, t, TAG_FWD_SUM);
@@ -987,7 +989,7 @@ extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
     // simulated reverse transfer), then each rank sums its own slots
     HX_TRY(b->g_send_all.alloc((size_t)b->E1_tot * b->row_bytes));
     std::vector<GatherJob> xb{GatherJob{b->g_in, b->g_send_all.as<char>(), b->gidx_to1.as<int32_t>(), b->E1_tot}};
-    HX_TRY(build_gather_table(xb, b->dtype, rbi, gsc, &b->lt_back[0]));
+    HX_TRY(build_gather_table(xb, b->dtype, rbi, gsc, &b->lt_back));
     // the same from a caller's buffer, which the bound one gets a copy of
     HX_TRY(world_from_map(b));
     GatherJob cb{b->g_in, nullptr, nullptr, b->H_tot};
@@ -1003,10 +1005,8 @@ extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
     HX_TRY(b->g_r1.alloc((size_t)b->R1_tot * b->row_bytes));
     HX_TRY(b->g_send_all.alloc((size_t)b->E1_tot * b->row_bytes));
     std::vector<GatherJob> x2{GatherJob{b->g_in, b->g_s2.as<char>(), b->gidx_back2.as<int32_t>(), b->E2_tot}};
-    HX_TRY(build_gather_table(x2, b->dtype, rbi, gsc, &b->lt_back[1]));
-    std::vector<GatherJob> x1{GatherJob{b->g_r1.as<char>(), b->g_send_all.as<char>(), b->gidx_to1.as<int32_t>(),
-                                        b->E1_tot}};
-    HX_TRY(build_gather_table(x1, b->dtype, rbi, gsc, &b->lt_back[0]));
+    HX_TRY(build_gather_table(x2, b->dtype, rbi, gsc, &b->lt_back2));
+    HX_TRY(world_from_map(b));
   }
   // the backward's shape (and so its tuning-cache key) exists only now
   Sched cached;
@@ -1036,11 +1036,11 @@ static int run_backward(hx_batch* b, hipStream_t s, bool plain_form, int64_t g_i
     }
   }
   if (b->world && b->staged_bwd) {
-    if (sim) HX_TRY(launch_table(b->lt_back[1], s));
-    HX_TRY(launch_table(b->lt_fwd_sum, s));
-    if (sim) HX_TRY(launch_table(b->lt_back[0], s));
+    // (the sums are delivered to the send slots as they are made)
+    if (sim) HX_TRY(launch_table(b->lt_back2, s));
+    HX_TRY(launch_table(b->lt_fwd_sum, s, {sim, 0, 0}));
   } else if (plain_world && sim && g_in == 0) {
-    HX_TRY(launch_table(b->lt_back[0], s));
+    HX_TRY(launch_table(b->lt_back, s));
   }
   if (!plain_form) return launch_table(b->lt[PH_BWD], s, {false, 0, g_out});
   for (auto& t : b->plain[PH_BWD]) HX_TRY(launch_table(t, s));

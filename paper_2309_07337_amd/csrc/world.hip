@@ -598,7 +598,8 @@ extern "C" int hx_batch_from_plan(const hx_plan* p, const void* x_global, void* 
   //   reverse stage 2  g_s2[e] = g_halo[inv_unpack[to2[e]]]   (transport)
   //   forwarder sums   g_r1[k] = g_halo[own row of k] (when read), then
   //                    g_s2[e] for the entries e forwarding k, ascending
-  //   reverse stage 1  g_send[e] = g_r1[to1[e]]                      (transport)
+  //   reverse stage 1  g_send[from1[k]] = g_r1[k], written by the forwarder
+  //                    sums themselves                               (transport)
   //   owner sums       g_x = pack transpose over g_send (as the plain world)
   b->staged_bwd = (flags & HX_WORLD_STAGED_BACKWARD) && !b->unpack_identity;
   // locality worlds whose backward is the closed-form adjoint build it from the
