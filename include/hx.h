@@ -149,9 +149,10 @@ typedef struct {
                          staged while the tile's indices are in flight),
                          taken where every job's index list is congruent
                          with its destination (one first row aligns both);
-                         2 = one row per lane; 0 = default (1 for gathers of
-                         4- or 8-byte rows, and for sums of one value per
-                         row whose terms an XCD's L2 holds).  Jobs without
+                         2 = one row per lane; 0 = default (1 for packs that
+                         move 256 MiB or more and other gathers of 2^23 or
+                         more 4- or 8-byte rows, and for sums of one value
+                         per row whose terms an XCD's L2 holds).  Jobs without
                          an index list (the plain unpack) are copied as
                          contiguous bytes whatever this says */
 } hx_sched;

@@ -200,30 +200,29 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     // (400-B rows in tiles of 81 rows 181, of 40 155)
     s.tile_rows = rb <= 48 ? kStageRows : std::max(16, std::min(256, (rb <= 192 ? 32 << 10 : 16 << 10) / rb));
     s.block_threads = pow2 ? 256 : 512;
+  } else if (one && w.phase == PH_PACK && w.bytes >= (int64_t)256 << 20) {
+    // 16-byte row groups per lane; a rank's own rows are hot in the L2: no
+    // window (4096 ranks 200 -> 165)
+    s.pair_rows = 1;
+    s.nontemporal = 1;
+    s.tile_rows = 4096;
+    s.block_threads = 512;
+  } else if (one && w.phase != PH_PACK && w.rows >= 1 << 23) {
+    // row groups, the job's window (if it has one) staged once per (up to)
+    // 16384-row tile while the tile's indices are in flight (redistribution and
+    // unpack of 39 M rows 476 -> 460; of 9 M FP32 ones 76 -> 72, with 512 lanes
+    // and twice the groups, which spill, 86)
+    s.pair_rows = 1;
+    s.lds_window = 1;
+    s.tile_rows = 16384;
+    s.block_threads = rb == 8 ? 512 : 256;
+    if (rb == 4) s.unroll = 2;
   } else if (one) {
-    s.pair_rows = 1;  // 16-byte row groups per lane
-    if (w.phase == PH_PACK) {
-      // a rank's own rows are hot in the L2: no window (4096 ranks 200 -> 165)
-      s.nontemporal = w.bytes >= (int64_t)256 << 20 ? 1 : 0;
-      s.tile_rows = s.nontemporal ? 4096 : 2048;
-      s.block_threads = s.nontemporal ? 512 : 256;
-      if (rb == 4) s.unroll = 2;
-    } else if (w.rows >= 1 << 23) {
-      // the job's window (if it has one) staged once per (up to) 16384-row tile
-      // while the tile's indices are in flight (redistribution and unpack of 39
-      // M rows 476 -> 460; of 9 M FP32 ones 76 -> 72, with 512 lanes and twice
-      // the groups, which spill, 86)
-      s.lds_window = 1;
-      s.tile_rows = 16384;
-      s.block_threads = rb == 8 ? 512 : 256;
-      if (rb == 4) s.unroll = 2;
-    } else {
-      // what the windows hold is in the caches anyhow (4.7 M rows: 86 -> 66);
-      // one pass of the workgroup a tile
-      s.tile_rows = 1024;
-      s.block_threads = 256;
-      s.unroll = rb == 8 ? 2 : 1;
-    }
+    // what windows hold is in the caches anyhow (4.7 M rows: 86 -> 66), and one
+    // row per lane reads runs of consecutive rows as whole lines (27-point
+    // world of 766,000 rows 17.3 -> 15.0 a step); one pass of the workgroup a tile
+    s.tile_rows = 1024;
+    s.block_threads = 256;
   } else {
     // (24-B rows, packs 73 -> 66, redistribution and unpack 160 -> 150; 12 B
     // 45 -> 42)
