@@ -399,6 +399,8 @@ def kernel_symbol(P, b, phase, row_bytes, staged):
     if phase == 3:
         sfx = "_vec" if sch["pair_rows"] == 1 and row_bytes in (4, 8) else ""
         return f"k_segsum_fwd{sfx} + k_segsum{sfx}" if staged else f"k_segsum{sfx}"
+    if phase == 2 and P.hx_batch_bytes(b, 1) == 0:   # plain plans unpack contiguous bytes
+        return "k_unpack_copy"
     base = {0: "k_pack", 1: "k_redist", 2: "k_unpack"}[phase]
     if phase == 0 and sch["push_pack"] == 1:
         return "k_pack_push"
