@@ -17,9 +17,9 @@ __global__ void __launch_bounds__(1024)
     k_segsum_one_flat(SegSumJob job, int64_t ntiles, int tile_rows, int nv, int cap_terms) {
   segsum_flat_body<T, VB, U, NT, true, false>(&job, nullptr, nullptr, 1, ntiles, tile_rows, nv, cap_terms, Beside{0, 0});
 }
-template <class T, int U, bool NT>
+template <class T, int U, int D, bool NT>
 __global__ void __launch_bounds__(1024) k_segsum_one_vec(SegSumJob job, int64_t ntiles, int tile_rows) {
-  segsum_vec_body<T, U, 4, NT, true, false>(&job, nullptr, 1, ntiles, tile_rows, Beside{0, 0});
+  segsum_vec_body<T, U, D, NT, true, false>(&job, nullptr, 1, ntiles, tile_rows, Beside{0, 0});
 }
 
 template <class T>
@@ -41,7 +41,9 @@ struct one_go {
 
 template <class T, bool NT>
 void one_vec(const LaunchTable& t, hipStream_t s, const LaunchOpt& o) {
-  auto* kernel = unroll_bucket(t.sched.unroll) == 1 ? k_segsum_one_vec<T, 1, NT> : k_segsum_one_vec<T, 2, NT>;
+  auto* kernel = t.vec_depth > 4                       ? k_segsum_one_vec<T, 1, 16, NT>
+                 : unroll_bucket(t.sched.unroll) == 1 ? k_segsum_one_vec<T, 1, 4, NT>
+                                                      : k_segsum_one_vec<T, 2, 4, NT>;
   hipLaunchKernelGGL(kernel, dim3(t.grid), dim3(t.sched.block_threads), (unsigned)t.win_bytes, s, *o.one, t.ntiles,
                      t.sched.tile_rows);
 }

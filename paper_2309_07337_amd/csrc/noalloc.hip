@@ -22,6 +22,6 @@ extern "C" int hx_backward_noalloc(hx_req* r, const void* g_send, void* g_x, voi
   // many rows: the tiles the documented limit is stated in
   const int limit_rows = std::min(512, std::max(64, (64 << 10) / (int)r->row_bytes));
   if (sc.tile_rows > limit_rows || r->n_local / limit_rows >= 2 * hx::device_cus()) sc.tile_rows = limit_rows;
-  return hx::launch_segsum_one(job, r->dtype, (int)r->row_bytes, sc, (HX_NOALLOC_SCRATCH_BYTES - 512) / 8,
+  return hx::launch_segsum_one(job, r->E1, r->dtype, (int)r->row_bytes, sc, (HX_NOALLOC_SCRATCH_BYTES - 512) / 8,
                                (hipStream_t)stream);
 }

@@ -232,7 +232,8 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
   // few rows: smaller tiles, down to 4 KiB of output, until every CU has two
   // (a window would then be staged by every one of them)
   const int64_t cus = device_cus();
-  const int least = std::max(16, (4 << 10) / rb);
+  // (one-value sums: a row a lane)
+  const int least = kind == KIND_SEGSUM && s.pair_rows ? s.block_threads : std::max(16, (4 << 10) / rb);
   if (w.rows > 0 && w.jobs < cus && s.tile_rows > least && w.rows / s.tile_rows < 2 * cus) {
     while (s.tile_rows > least && w.rows / s.tile_rows < 2 * cus) s.tile_rows = std::max(least, s.tile_rows / 2);
     s.lds_window = 0;
