@@ -178,10 +178,15 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
       s.block_threads = 256;
     } else {
       // a persistent grid of 512-row tiles before: 8 B 143 -> 104, 12 B 101 ->
-      // 75, 16 B 91 -> 77, 32 B 71 -> 65, 40 B 76 -> 70, 56 B 77 -> 64
-      s.tile_rows = one ? kStageRows : 256;
-      s.block_threads = rb < 40 ? 256 : 512;
-      if (one) s.unroll = 2;
+      // 75, 16 B 91 -> 77, 32 B 71 -> 65, 40 B 76 -> 70, 56 B 77 -> 64. Where
+      // the terms are beyond the L2, tiles of 512 rows up to 40 B, half as many
+      // terms in flight (12 B 139 -> 122, 16 B 123 -> 103, 20 B 119 -> 114,
+      // 28 B 108 -> 101, 40 B 100 -> 94, 48 B 94 -> 90; two lanes a row of 32 B
+      // fill the smaller tile: 92, 90). From the L2 12 B 155, in 512 rows 168.
+      const bool far = w.source > kL2, two = rb == 32;
+      s.tile_rows = one || (far && rb <= 40 && !two) ? kStageRows : 256;
+      s.block_threads = rb < (far && !two ? 20 : 40) ? 256 : 512;
+      if (one || (far && rb <= 48)) s.unroll = 2;
     }
   } else if (w.identity) {
     // contiguous copies: 16 or 32 KiB a workgroup (one row per lane before:
@@ -199,7 +204,7 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     s.push_pack = 1;
     // (400-B rows in tiles of 81 rows 181, of 40 155)
     s.tile_rows = rb <= 48 ? kStageRows : std::max(16, std::min(256, (rb <= 192 ? 32 << 10 : 16 << 10) / rb));
-    s.block_threads = pow2 ? 256 : 512;
+    s.block_threads = pow2 || rb < 24 ? 256 : 512;  // (12 B 126 -> 119, 20 B 111 -> 106; 24 B 88, 82)
   } else if (one && w.phase == PH_PACK && w.bytes >= (int64_t)256 << 20) {
     // 16-byte row groups per lane; a rank's own rows are hot in the L2: no
     // window (4096 ranks 200 -> 165)
