@@ -65,13 +65,17 @@ def _beside(t: torch.Tensor, bound: torch.Tensor) -> bool:
     """Whether the library may copy between t and a bound buffer itself."""
     return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.layout == torch.strided and t.dtype == bound.dtype
             and t.device == bound.device and t.shape == bound.shape and t.is_contiguous() and not t.is_neg()
-            and t.numel() > 0 and (t.data_ptr() - bound.data_ptr()) % 16 == 0
+            and t.numel() > 0 and (not bound.is_inference() or torch.is_inference_mode_enabled())
+            and (t.data_ptr() - bound.data_ptr()) % 16 == 0
             and t.untyped_storage().data_ptr() != bound.untyped_storage().data_ptr())
 
 
 def _copy_in(t: torch.Tensor, bound: torch.Tensor):
-    """t if the library copies it into the bound buffer; otherwise copied here."""
+    """t if the library copies it into the bound buffer; otherwise copied here.
+    Either way autograd sees the buffer change: a backward that saved it for
+    another op raises instead of reading the new values."""
     if _beside(t, bound):
+        torch.autograd.graph.increment_version(bound)
         return t
     bound.copy_(t)
     return None
