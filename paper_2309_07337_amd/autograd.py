@@ -61,6 +61,16 @@ class HaloExchange:
         return self.g_x
 
 
+# Start + Wait and the backward as the library's fused calls run them; a
+# forward() or backward() of another class or object (one with a transport of
+# its own between Start and Wait, say) is called instead.
+_STEPS = {name: getattr(HaloExchange, name) for name in ("forward", "backward")}
+
+
+def _fused(ex: HaloExchange, name: str) -> bool:
+    return getattr(getattr(ex, name), "__func__", None) is _STEPS[name]
+
+
 def _beside(t: torch.Tensor, bound: torch.Tensor) -> bool:
     """Whether the library may copy between t and a bound buffer itself."""
     return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.layout == torch.strided and t.dtype == bound.dtype
@@ -94,9 +104,15 @@ def _copy_out(bound: torch.Tensor, run):
 class HaloGather(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x: torch.Tensor, ex: HaloExchange, copy_out: bool = True):
-        src = _copy_in(x, ex.x) if x.data_ptr() != ex.x.data_ptr() else None
         ctx.ex = ex
         ctx.copy_out = copy_out
+        if not _fused(ex, "forward"):
+            if x.data_ptr() != ex.x.data_ptr():
+                ex.x.copy_(x)
+            ex.forward()
+            ctx.generation = ex.generation
+            return ex.halo.clone() if copy_out else ex.halo.detach()
+        src = _copy_in(x, ex.x) if x.data_ptr() != ex.x.data_ptr() else None
         if copy_out:
             y = _copy_out(ex.halo, lambda out: L.hx_batch_exchange(ex.batch, src, out))
         else:
@@ -113,6 +129,11 @@ class HaloGather(torch.autograd.Function):
             raise RuntimeError("halo_gather: the aliased output of this forward was overwritten by a later "
                                "forward on the same exchange before its backward ran")
         own = g.data_ptr() == ex.g_halo.data_ptr() and g.is_contiguous()
+        if not _fused(ex, "backward"):
+            if not own:
+                ex.g_halo.copy_(g)
+            ex.backward()
+            return ex.g_x.clone(), None, None
         src = None if own else _copy_in(g, ex.g_halo)
         return _copy_out(ex.g_x, lambda out: L.hx_batch_adjoint(ex.batch, src, out)), None, None
 

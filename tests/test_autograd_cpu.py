@@ -79,3 +79,30 @@ def test_inference_buffers_stay_refused(ex):
         ex.x = torch.zeros(6, 4)
     with pytest.raises(RuntimeError, match="inference tensor"):
         A.halo_gather(torch.rand(6, 4), ex)
+
+
+@pytest.mark.parametrize("how", ["class", "object"])
+@pytest.mark.parametrize("copy_out", [True, False])
+def test_own_steps_are_called(ex, how, copy_out):
+    """forward() and backward() of a subclass or of the object itself (a caller's
+    own transport) run instead of the library's fused calls."""
+    class Transport(A.HaloExchange):
+        def forward(self, stream=None):
+            self.halo.copy_(2 * self.x[COLS])
+            self.generation += 1
+            return self.halo
+
+        def backward(self, stream=None):
+            self.g_x.zero_().index_add_(0, COLS, 2 * self.g_halo)
+            return self.g_x
+
+    if how == "class":
+        ex.__class__ = Transport
+    else:
+        ex.forward, ex.backward = Transport.forward.__get__(ex), Transport.backward.__get__(ex)
+    x, g = torch.rand(6, 4, requires_grad=True), torch.rand(4, 4)
+    y = A.halo_gather(x, ex, copy_out)
+    assert torch.equal(y, 2 * x[COLS]) and ex.generation == 1
+    assert (y.data_ptr() == ex.halo.data_ptr()) == (not copy_out)
+    y.backward(g)
+    assert torch.equal(x.grad, torch.zeros(6, 4).index_add_(0, COLS, 2 * g))
