@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -223,6 +224,9 @@ struct LaunchTable {
   DevMem jobs;        // GatherJob[] or SegSumJob[]
   DevMem tile_start;  // int64_t[njobs + 1], then every tile's job: int32_t[ntiles]
   DevMem tile_terms;  // segmented sums, push pack: int2[ntiles], entry range {ptr[r0], ptr[r1]} of each tile
+  // gathers of both kinds of jobs (the unpack of a batch of plain and locality
+  // requests): those without an index list, a launch of their own
+  std::unique_ptr<LaunchTable> copies;
   bool empty() const { return ntiles == 0; }
 };
 

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <memory>
+#include <new>
 
 #include "common.h"
 #include "move_kernels.h"
@@ -201,6 +203,18 @@ uintptr_t align_of(const std::vector<SegSumJob>& jobs, int row_bytes) {
 int build_gather_table(const std::vector<GatherJob>& jobs, int dtype, int row_bytes, const Sched& s, LaunchTable* t,
                        int tag) {
   t->tag = tag;
+  t->copies.reset();
+  std::vector<GatherJob> indexed, copied;
+  for (const auto& j : jobs)
+    if (j.nrows > 0) (j.idx ? indexed : copied).push_back(j);
+  if (!indexed.empty() && !copied.empty()) {
+    std::unique_ptr<LaunchTable> c(new (std::nothrow) LaunchTable);
+    if (!c) return fail(HX_ERR_NOMEM, "out of host memory");
+    HX_TRY(build_gather_table(copied, dtype, row_bytes, s, c.get(), tag));
+    HX_TRY(build_gather_table(indexed, dtype, row_bytes, s, t, tag));
+    t->copies = std::move(c);
+    return HX_SUCCESS;
+  }
   uintptr_t a = (uintptr_t)row_bytes;
   for (const auto& j : jobs) {
     if (j.nrows <= 0) continue;
@@ -249,9 +263,6 @@ int build_gather_table(const std::vector<GatherJob>& jobs, int dtype, int row_by
   t->identity = 0;
   for (const auto& j : w)
     if (j.nrows > 0 && j.idx == nullptr) t->identity = 1;
-  for (const auto& j : w)
-    if (j.nrows > 0 && t->identity && j.idx != nullptr)
-      return fail(HX_ERR_STATE, "copies and indexed gathers in one launch");
   if (t->identity) t->vec16 = 0;
   t->deliver = 1;
   for (const auto& j : w)
@@ -407,7 +418,7 @@ int launch_table(const LaunchTable& t, hipStream_t s, const LaunchOpt& o) {
   else if (o.one) launch_segsum_one_kernels(t, s, o);
   else launch_segsum_kernels(t, s, o);
   HX_HIP(hipGetLastError());
-  return HX_SUCCESS;
+  return t.copies ? launch_table(*t.copies, s, o) : HX_SUCCESS;
 }
 
 void split_gather_by_counts(const GatherJob& j, const std::vector<int32_t>& counts, size_t row_bytes,
