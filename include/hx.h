@@ -509,7 +509,7 @@ int hx_batch_backward_plain(hx_batch* b, void* stream);
  * bound g_out into g_out after).  NULL, or the bound buffer: no copy.  The
  * buffers have the bound ones' shapes, do not overlap them, and are aligned as
  * they are modulo 16 bytes (HX_ERR_ARG otherwise, as for a batch that is no
- * world).  HX_ERR_STATE while a Start is pending, or without bound gradients. */
+ * world); they may lie in the batch's arenas.  HX_ERR_STATE while a Start is pending, or without bound gradients. */
 int hx_batch_exchange(hx_batch* b, const void* x, void* halo, void* stream);
 int hx_batch_adjoint(hx_batch* b, const void* g_in, void* g_out, void* stream);
 int hx_batch_tune(hx_batch* b, void* stream);

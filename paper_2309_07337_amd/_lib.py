@@ -309,6 +309,10 @@ class Req(_Handle):
 class Batch(_Handle):
     _free_name = "hx_batch_free"
 
+    def __init__(self, ptr, keep=()):
+        super().__init__(ptr, keep)
+        self.bound = {}     # a world's tensors by argument name
+
 
 class Comm(_Handle):
     _free_name = "hx_comm_free"
@@ -488,7 +492,9 @@ def hx_batch_from_plan(plan: Plan, x_global, halo_all, flags: int = 0, sched=Non
     out = C.c_void_p()
     _check(load().hx_batch_from_plan(plan.ptr, _dptr(x_global), _dptr(halo_all), _dtype_of(x_global),
                                      _ncols(x_global), flags, _sched_ptr(sched), C.byref(out)))
-    return Batch(out, keep=(plan, x_global, halo_all))
+    b = Batch(out, keep=(plan, x_global, halo_all))
+    b.bound.update(x=x_global, halo=halo_all)
+    return b
 
 
 def hx_batch_start(b: Batch, stream=None) -> None:
@@ -510,6 +516,7 @@ def hx_batch_wait_plain(b: Batch, stream=None) -> None:
 def hx_batch_bind_grad(b: Batch, g_in, g_out) -> None:
     _check(load().hx_batch_bind_grad(b.ptr, _dptr(g_in), _dptr(g_out)))
     b._keep += [g_in, g_out]
+    b.bound.update(g_in=g_in, g_out=g_out)
 
 
 def hx_batch_backward(b: Batch, stream=None) -> None:
@@ -520,18 +527,27 @@ def hx_batch_backward_plain(b: Batch, stream=None) -> None:
     _check(load().hx_batch_backward_plain(b.ptr, _stream(stream)))
 
 
-def _ptr_or_none(t):
-    return None if t is None else t.data_ptr()
+def _beside(b: Batch, name: str, t) -> Optional[int]:
+    """Address of a caller's tensor that stands beside a bound one: the library
+    takes its layout from the bound one's."""
+    if t is None:
+        return None
+    bound = b.bound.get(name)
+    if bound is not None and not (t.dtype == bound.dtype and t.device == bound.device and t.numel() == bound.numel()
+                                  and t.is_contiguous() and not t.is_neg()):
+        raise HXError(HX_ERR_ARG, f"{name}: a {tuple(t.shape)} {t.dtype} tensor on {t.device} is not laid out as the "
+                                  f"bound one, {tuple(bound.shape)} {bound.dtype} on {bound.device}, contiguous")
+    return t.data_ptr()
 
 
 def hx_batch_exchange(b: Batch, x=None, halo=None, stream=None) -> None:
     """A world's Start + Wait; x copied into the bound vector, the bound halo into halo (tensors or None)."""
-    _check(load().hx_batch_exchange(b.ptr, _ptr_or_none(x), _ptr_or_none(halo), _stream(stream)))
+    _check(load().hx_batch_exchange(b.ptr, _beside(b, "x", x), _beside(b, "halo", halo), _stream(stream)))
 
 
 def hx_batch_adjoint(b: Batch, g_in=None, g_out=None, stream=None) -> None:
     """A world's backward; g_in copied into the bound gradients, the bound g_out into g_out (tensors or None)."""
-    _check(load().hx_batch_adjoint(b.ptr, _ptr_or_none(g_in), _ptr_or_none(g_out), _stream(stream)))
+    _check(load().hx_batch_adjoint(b.ptr, _beside(b, "g_in", g_in), _beside(b, "g_out", g_out), _stream(stream)))
 
 
 def hx_batch_launch_phase(b: Batch, phase: int, stream=None) -> None:

@@ -77,7 +77,7 @@ def _beside(t: torch.Tensor, bound: torch.Tensor) -> bool:
             and t.device == bound.device and t.shape == bound.shape and t.is_contiguous() and not t.is_neg()
             and t.numel() > 0 and (not bound.is_inference() or torch.is_inference_mode_enabled())
             and (t.data_ptr() - bound.data_ptr()) % 16 == 0
-            and t.untyped_storage().data_ptr() != bound.untyped_storage().data_ptr())
+            and abs(t.data_ptr() - bound.data_ptr()) >= bound.numel() * bound.element_size())
 
 
 def _copy_in(t: torch.Tensor, bound: torch.Tensor):

@@ -1019,9 +1019,10 @@ extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
   return batch_prepare(b);
 }
 
-static bool overlap(const void* p, size_t n, const DevMem& m) {
-  return (const char*)p < m.as<char>() + m.bytes && m.as<char>() < (const char*)p + n;
+static bool overlap(const void* p, size_t n, const void* q, size_t m) {
+  return (const char*)p < (const char*)q + m && (const char*)q < (const char*)p + n;
 }
+static bool overlap(const void* p, size_t n, const DevMem& m) { return overlap(p, n, m.p, m.bytes); }
 
 // Backward of a batch.  Plain worlds: with the simulated transport the
 // reverse stage-1 transfer first, then the owner sums.  Staged locality
@@ -1030,8 +1031,8 @@ static bool overlap(const void* p, size_t n, const DevMem& m) {
 static int run_backward(hx_batch* b, hipStream_t s, bool plain_form, int64_t g_in, int64_t g_out) {
   const bool sim = sim_transfer(b);
   const bool plain_world = b->world && b->unpack_identity;
+  const size_t gb = (size_t)b->H_tot * b->row_bytes, xb = (size_t)b->n * b->row_bytes;
   if (g_in != 0) {
-    const size_t gb = (size_t)b->H_tot * b->row_bytes;
     if (plain_world && sim && (b->lt_back_copy.empty() || b->lt_back_copy.deliver) &&
         !overlap(b->g_in + g_in, gb, b->g_send_all))
       HX_TRY(launch_table(b->lt_back_copy, s, {true, g_in, 0}));
@@ -1047,7 +1048,14 @@ static int run_backward(hx_batch* b, hipStream_t s, bool plain_form, int64_t g_i
   } else if (plain_world && sim && g_in == 0) {
     HX_TRY(launch_table(b->lt_back, s));
   }
-  if (!plain_form) return launch_table(b->lt[PH_BWD], s, {false, 0, g_out});
+  if (!plain_form) {
+    // (the owner sums copy theirs out as they go; not over what they still read)
+    char* const out = b->g_out + g_out;
+    const bool fused = g_out == 0 || !(overlap(out, xb, b->g_send_all) || overlap(out, xb, b->g_in, gb));
+    HX_TRY(launch_table(b->lt[PH_BWD], s, {false, 0, fused ? g_out : 0}));
+    if (!fused) HX_HIP(hipMemcpyAsync(out, b->g_out, xb, hipMemcpyDeviceToDevice, s));
+    return HX_SUCCESS;
+  }
   for (auto& t : b->plain[PH_BWD]) HX_TRY(launch_table(t, s));
   return HX_SUCCESS;
 }
@@ -1081,10 +1089,13 @@ int hx::batch_run_backward(hx_batch* b, hipStream_t s, int64_t g_in, int64_t g_o
   return run_backward(b, s, false, g_in, g_out);
 }
 
-// Bytes from a bound buffer to a caller's (null, or the bound one itself: 0).
-static int beside(const void* given, const void* bound, const char* what, int64_t* out) {
+// Bytes from a bound buffer to a caller's of as many bytes (null, or the bound
+// one itself: 0).
+static int beside(const void* given, const void* bound, size_t bytes, const char* what, int64_t* out) {
   *out = given ? (int64_t)((uintptr_t)given - (uintptr_t)bound) : 0;
   if (*out % 16 != 0) return fail(HX_ERR_ARG, "%s: not aligned as the bound buffer (modulo 16 bytes)", what);
+  if (*out != 0 && overlap(given, bytes, bound, bytes))
+    return fail(HX_ERR_ARG, "%s: overlaps the bound buffer", what);
   return HX_SUCCESS;
 }
 
@@ -1094,9 +1105,9 @@ extern "C" int hx_batch_exchange(hx_batch* b, const void* x, void* halo, void* s
   if (b->active) return fail(HX_ERR_STATE, "batch already active");
   hipStream_t s = (hipStream_t)stream;
   int64_t dx = 0, dh = 0;
-  HX_TRY(beside(x, b->x_global, "x_global", &dx));
-  HX_TRY(beside(halo, b->halo_all, "halo_all", &dh));
-  const size_t xb = (size_t)b->n * b->row_bytes;
+  const size_t xb = (size_t)b->n * b->row_bytes, hb = (size_t)b->H_tot * b->row_bytes;
+  HX_TRY(beside(x, b->x_global, xb, "x_global", &dx));
+  HX_TRY(beside(halo, b->halo_all, hb, "halo_all", &dh));
   // (a push pack copies the rows as it goes; not from an arena that it writes)
   if (dx != 0 && (b->lt[PH_PACK].empty() || b->lt[PH_PACK].kind != KIND_SCATTER || overlap(x, xb, b->send_all) ||
                   overlap(x, xb, b->recv_all))) {
@@ -1105,10 +1116,10 @@ extern "C" int hx_batch_exchange(hx_batch* b, const void* x, void* halo, void* s
   }
   HX_TRY(launch_table(b->lt[PH_PACK], s, {sim_transfer(b), dx, 0}));
   HX_TRY(launch_table(b->lt[PH_REDIST], s, {sim_transfer(b), 0, 0}));
-  const bool fused = b->lt[PH_UNPACK].identity != 0;
+  // (a contiguous unpack copies its rows as it goes; not over the arena it reads)
+  const bool fused = b->lt[PH_UNPACK].identity != 0 && !overlap(halo, hb, b->recv_all);
   HX_TRY(launch_table(b->lt[PH_UNPACK], s, {false, 0, fused ? dh : 0}));
-  if (dh != 0 && !fused)
-    HX_HIP(hipMemcpyAsync(halo, b->halo_all, (size_t)b->H_tot * b->row_bytes, hipMemcpyDeviceToDevice, s));
+  if (dh != 0 && !fused) HX_HIP(hipMemcpyAsync(halo, b->halo_all, hb, hipMemcpyDeviceToDevice, s));
   return HX_SUCCESS;
 }
 
@@ -1117,8 +1128,9 @@ extern "C" int hx_batch_adjoint(hx_batch* b, const void* g_in, void* g_out, void
   if (!b->world) return fail(HX_ERR_ARG, "not a world batch");
   if (!b->g_out) return fail(HX_ERR_STATE, "no gradient buffers bound");
   int64_t di = 0, dout = 0;
-  HX_TRY(beside(g_in, b->g_in, "g_in", &di));
-  HX_TRY(beside(g_out, b->g_out, "g_out", &dout));
+  const size_t rb = b->row_bytes;
+  HX_TRY(beside(g_in, b->g_in, (size_t)b->H_tot * rb, "g_in", &di));
+  HX_TRY(beside(g_out, b->g_out, (size_t)b->n * rb, "g_out", &dout));
   return batch_run_backward(b, (hipStream_t)stream, di, dout);
 }
 
