@@ -187,7 +187,8 @@ int dev_count_distinct(const int32_t* idx, int64_t n, int64_t domain, DevMem* fl
                        hipStream_t s);
 // Stable grouping of entries by key: for each key k in [0, nkeys), the
 // entries e with keys[e] == k in ascending e.  ptr [nkeys+1], perm [n].
-// checked: the keys are known to lie in [0, nkeys).
+// checked: the keys are known to lie in [0, nkeys); else HX_ERR_RANGE, with ptr
+// untouched, where one does not.
 int dev_group_by_key(const int32_t* keys, int64_t n, int64_t nkeys, int32_t* ptr, int32_t* perm,
                      hipStream_t s, bool checked = false);
 }  // namespace hx

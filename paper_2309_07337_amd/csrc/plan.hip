@@ -313,12 +313,14 @@ __global__ void __launch_bounds__(TB) k_radix_scatter(const int32_t* __restrict_
 // ptr[k] = first sorted entry with key >= k, for k in [0, nkeys].  Entry i
 // gives the keys after its predecessor's up to its own; runs of more than a
 // few keys without entries are filled by a wavefront each, the keys before
-// the first and after the last entry by the whole grid.
+// the first and after the last entry by the whole grid.  Writes nothing where a
+// key was found outside [0, nkeys) (err set): such a key is no place in ptr.
 constexpr int CHUNK = 2048;  // consecutive items a block takes at a time
 __global__ void __launch_bounds__(TB) k_group_ptr(const int32_t* __restrict__ skeys, int64_t n, int64_t nkeys,
-                                                  int32_t* __restrict__ ptr) {
+                                                  int32_t* __restrict__ ptr, const int* __restrict__ err) {
   __shared__ int32_t s_entry[CHUNK], s_from[CHUNK], s_to[CHUNK];  // runs to fill: keys (from, to]
   __shared__ int s_gaps;
+  if (err != nullptr && *err != 0) return;  // (uniform)
   const int64_t first = n > 0 ? min((int64_t)skeys[0], nkeys) : nkeys;
   const int64_t last = n > 0 ? min((int64_t)skeys[n - 1], nkeys) : nkeys;
   const int64_t gid = (int64_t)blockIdx.x * TB + threadIdx.x, gsz = (int64_t)gridDim.x * TB;
@@ -1377,7 +1379,7 @@ int dev_group_by_key(const int32_t* keys, int64_t n, int64_t nkeys, int32_t* ptr
     }
   }
   hipLaunchKernelGGL(k_group_ptr, dim3(blocks_for(std::max(n, (nkeys + 1) / 4), CHUNK)), dim3(TB), 0, s, sorted, n,
-                     nkeys, ptr);
+                     nkeys, ptr, checked ? nullptr : err);
   HX_HIP(hipGetLastError());
   if (err && !checked) {
     int h = 0;
