@@ -129,7 +129,8 @@ typedef struct {
                          to all its slots); 2 = pull form (gather per slot);
                          0 = default (push for rows of 64 bytes or more, and
                          for shorter ones packed from more than an XCD's L2
-                         holds, 4 MiB; else pull) */
+                         holds, 4 MiB, where at least half as many are
+                         packed as the source has; else pull) */
   int lds_window;     /* gathers: 1 = a job whose indices mostly stay inside
                          a known window of source rows (the pack: the rank's
                          own rows; the redistribution: its stage-1 receive

@@ -194,16 +194,25 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     s.block_threads = streams ? 512 : 256;
     s.tile_rows = std::max(1, (streams ? 32 << 10 : 16 << 10) / rb);
     s.nontemporal = streams ? 1 : 0;
-  } else if (w.phase == PH_PACK && (rb >= 64 || w.source > kL2)) {
+  } else if (w.phase == PH_PACK && (rb >= 64 || (w.source > kL2 && 2 * w.rows >= w.owned))) {
     // push: scattered full-line writes run as fast as scattered reads, and each
     // source row is read once; of shorter rows where the source is beyond the
     // L2, so that a pull's reads of parts of a line would go to memory (8 B
     // 103 -> 90, 16 B 70 -> 59, 24 B 68 -> 58, 40 B 67 -> 59; from a rank's own
-    // rows, in the L2, 24 B 66 pulled and 85 pushed).  Its writes merge in the
+    // rows, in the L2, 24 B 66 pulled and 85 pushed), and where at least half as
+    // many rows are packed as the source has: a push walks every source row's
+    // pointers.  4 M rows in 26 ascending messages, pulled and pushed: half of
+    // the rows 8 B 38 and 27, 16 B 43 and 28, 24 B 49 and 44, 40 B 58 and 54; a
+    // quarter 8 B 21 and 25, 24 B 27 and 40, 40 B 33 and 43; the surface of a
+    // cube of 160 rows a side 8 B 7 and 24, 24 B 8 and 36.  (In two messages
+    // half of the rows 8 B 16 and 26, 16 B 26 and 28.)  Its writes merge in the
     // L2: no streaming hints (24 B 58, 152 with)
     s.push_pack = 1;
-    // (400-B rows in tiles of 81 rows 181, of 40 155)
-    s.tile_rows = rb <= 48 ? kStageRows : std::max(16, std::min(256, (rb <= 192 ? 32 << 10 : 16 << 10) / rb));
+    // (400-B rows in tiles of 81 rows 181, of 40 155; where few of the rows are
+    // packed the walk is what counts: a 64th of 1 M rows of 256 B in tiles of 64
+    // rows 29, of 512 11, an eighth 43 and 21)
+    s.tile_rows = rb <= 48 || 4 * w.rows < w.owned ? kStageRows
+                  : std::max(16, std::min(256, (rb <= 192 ? 32 << 10 : 16 << 10) / rb));
     s.block_threads = pow2 || rb < 24 ? 256 : 512;  // (12 B 126 -> 119, 20 B 111 -> 106; 24 B 88, 82)
   } else if (one && w.phase == PH_PACK && w.bytes >= (int64_t)256 << 20) {
     // 16-byte row groups per lane; a rank's own rows are hot in the L2: no
@@ -239,8 +248,9 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
   const int64_t cus = device_cus();
   // (one-value sums: a row a lane)
   const int least = kind == KIND_SEGSUM && s.pair_rows ? s.block_threads : std::max(16, (4 << 10) / rb);
-  if (w.rows > 0 && w.jobs < cus && s.tile_rows > least && w.rows / s.tile_rows < 2 * cus) {
-    while (s.tile_rows > least && w.rows / s.tile_rows < 2 * cus) s.tile_rows = std::max(least, s.tile_rows / 2);
+  const int64_t walked = s.push_pack ? w.owned : w.rows;  // rows that the tiles cover
+  if (walked > 0 && w.jobs < cus && s.tile_rows > least && walked / s.tile_rows < 2 * cus) {
+    while (s.tile_rows > least && walked / s.tile_rows < 2 * cus) s.tile_rows = std::max(least, s.tile_rows / 2);
     s.lds_window = 0;
     if (!s.push_pack && kind == KIND_GATHER) {
       s.block_threads = 256;
@@ -356,7 +366,7 @@ SchedFor hx::req_sched_for(const hx_req* r, int phase) {
   w.jobs = 1;
   w.bytes = r->bytes[phase];
   switch (phase) {
-    case PH_PACK: w.rows = r->E1; w.source = r->n_local * rb; break;
+    case PH_PACK: w.rows = r->E1; w.owned = r->n_local; w.source = r->n_local * rb; break;
     case PH_REDIST: w.rows = r->E2; w.source = r->R1 * rb; break;
     case PH_UNPACK: w.rows = r->H; w.source = (r->R1 + r->R2) * rb; w.identity = r->unpack_identity; break;
     default: w.rows = r->n_local; w.source = r->E1 * rb; break;
@@ -711,7 +721,7 @@ SchedFor hx::batch_sched_for(const hx_batch* b, int phase) {
     w.fresh = true;
     const int64_t node = b->variant == HX_LOCALITY_3STEP ? b->ppn : 1;
     switch (phase) {
-      case PH_PACK: w.rows = b->E1_tot; w.source = b->n / R * node * rb; break;
+      case PH_PACK: w.rows = b->E1_tot; w.owned = b->n; w.source = b->n / R * node * rb; break;
       case PH_REDIST: w.rows = b->E2_tot; w.source = b->R1_tot / R * rb; break;
       case PH_UNPACK: w.rows = b->H_tot; w.source = b->R2_tot / R * rb; w.identity = b->unpack_identity; break;
       default:
@@ -725,6 +735,7 @@ SchedFor hx::batch_sched_for(const hx_batch* b, int phase) {
     for (const hx_req* r : b->members) {
       const SchedFor m = req_sched_for(r, phase);
       w.rows += m.rows;
+      w.owned += m.owned;
       w.jobs += m.rows > 0 ? 1 : 0;
       w.bytes += m.bytes;
       w.identity = m.identity;

@@ -1,0 +1,64 @@
+"""The rules of the default schedules, asked of the library on the CPU (a small
+program linked with it): what a pack, a copy or a sum of a given shape gets."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2309_07337_amd import build as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+FIELDS = ("tile_rows", "block_threads", "blocks_per_cu", "nontemporal", "unroll", "push_pack", "lds_window", "pair_rows")
+GATHER, SUM = 0, 1
+PACK, REDIST, UNPACK, BWD = range(4)
+CUS = 256       # without a device
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    if not os.path.exists(B.HIPCC):
+        pytest.skip("hipcc not installed")
+    if not os.path.exists(B.LIB):
+        B.build_library()
+    exe = str(tmp_path_factory.mktemp("sched") / "default_sched")
+    r = subprocess.run([B.HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", B.INCLUDE, "-I", B.CSRC,
+                        os.path.join(HERE, "sched", "default_sched.cpp"), "-o", exe,
+                        "-L", os.path.dirname(B.LIB), "-l:" + os.path.basename(B.LIB),
+                        "-Wl,-rpath," + os.path.dirname(B.LIB)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[:4000]
+
+    def ask(kind, row_bytes, phase, rows, owned=0, jobs=1, nbytes=None, source=0, identity=0, fresh=0):
+        line = [kind, row_bytes, phase, rows, owned, jobs, 2 * rows * row_bytes if nbytes is None else nbytes, source,
+                identity, fresh]
+        out = subprocess.run([exe], input=" ".join(map(str, line)), capture_output=True, text=True, check=True).stdout
+        return dict(zip(FIELDS, map(int, out.split())))
+    return ask
+
+
+@pytest.mark.parametrize("row_bytes", [4, 8, 12, 16, 24, 40, 56])
+@pytest.mark.parametrize("n", [2_000_000, 8_000_000])
+def test_packs_of_short_rows(rules, row_bytes, n):
+    """Pushed where at least half as many rows are packed as the source has: a
+    push walks every one of them."""
+    packed = lambda rows: rules(GATHER, row_bytes, PACK, rows, owned=n, source=n * row_bytes)["push_pack"]
+    assert n * row_bytes > 4 << 20
+    assert packed(n // 33) == 0 and packed(n // 4) == 0 and packed(n // 2 - 1) == 0
+    assert packed(n // 2) == 1 and packed(n) == 1 and packed(3 * n) == 1
+    assert rules(GATHER, row_bytes, PACK, 3000, owned=1000, source=1000 * row_bytes)["push_pack"] == 0
+
+
+@pytest.mark.parametrize("row_bytes", [64, 128, 256, 800])
+def test_pushed_tiles_cover_the_source(rules, row_bytes):
+    """Their size follows the rows they walk: few rows packed from many make no
+    more tiles than many do, and a small source still gives every CU two."""
+    def tile(rows, owned):
+        s = rules(GATHER, row_bytes, PACK, rows, owned=owned, source=owned * row_bytes)
+        assert s["push_pack"] == 1
+        return s["tile_rows"]
+
+    n = 1_000_000
+    dense = tile(n, n)
+    assert all(tile(n // k, n) >= dense for k in (2, 4, 16, 64, 1000))
+    least = max(16, 4096 // row_bytes)
+    for rows in (100, 3000):
+        assert 3000 // tile(rows, 3000) >= min(2 * CUS, 3000 // least)
