@@ -170,6 +170,8 @@ struct SchedFor {
   int phase = -1;        // hx::Phase
   int64_t rows = 0;      // output rows of all jobs
   int64_t owned = 0;     // pack: source rows of all jobs (a push walks every one)
+  int64_t terms = 0;     // sums: terms of all jobs
+  int values = 1;        // values per row
   int64_t jobs = 0;
   int64_t bytes = 0;     // bytes the phase moves (hx_batch_bytes)
   int64_t source = 0;    // source rows' bytes of a job, averaged over the bytes (a rank's own rows, ...)

@@ -341,9 +341,10 @@ int shape_segsum_table(const std::vector<SegSumJob>& jobs, int dtype, int row_by
   HX_TRY(shape_table(w, KIND_SEGSUM, dtype, row_bytes, s, t, a, kept, ts));
   t->win_bytes = t->ntiles > 0 ? (int)win_bytes : 0;
   // term buffer: about two terms per tile row, at least 4 KiB and at most
-  // kSegValueBytes, whole rows (small tiles leave LDS for more workgroups)
+  // kSegValueBytes, whole rows (small tiles leave LDS for more workgroups);
+  // none for tiles that stage no pointers, whose rows add straight from memory
   int64_t vb = std::min<int64_t>(kSegValueBytes, std::max<int64_t>(4096, 2 * (int64_t)s.tile_rows * row_bytes));
-  t->val_bytes = t->ntiles > 0 && row_bytes > 0 ? (int)(vb / row_bytes * row_bytes) : 0;
+  t->val_bytes = t->ntiles > 0 && s.tile_rows <= kStageRows ? (int)(vb / row_bytes * row_bytes) : 0;
   return HX_SUCCESS;
 }
 

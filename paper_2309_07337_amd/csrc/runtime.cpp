@@ -168,6 +168,25 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
       s.block_threads = 1024;
       s.unroll = 2;
       s.nontemporal = w.bytes >= (w.fresh ? (int64_t)256 << 20 : (int64_t)64 << 20) ? 1 : 0;
+    } else if (rb == 8 && w.values == 2) {
+      // two FP32 values: no row a lane; tiles whose pointers are staged in LDS
+      // (above kStageRows every row is a chain of three loads: 40 uneven requests
+      // 66 -> 21, 1024 ranks staged 129 -> 74, 4096 ranks staged 612 -> 388),
+      // unless hardly a row has a term (1 M rows of 4000 terms 6.4, staged 9.2).
+      // Rows of many terms fill the staging with few rows: their ranks' windows
+      // where they fit (4096 ranks plain, 7 terms a row, 216 -> 135, in 512 rows
+      // 265), else smaller tiles (100 ranks 34 -> 23, in 512 rows 29).  So do few
+      // rows (16,384 rows of 3 terms in 512 rows 8.3, in 64 4.9).
+      const bool many = w.terms > 6 * w.rows, none = 8 * w.terms <= w.rows;
+      s.block_threads = 256;
+      if (many && w.source <= kSegWinBytes) {
+        s.lds_window = 1;
+        s.tile_rows = 1024;
+        s.block_threads = 512;
+      } else {
+        s.tile_rows = many || w.rows < kStageRows * (int64_t)device_cus() ? 128 : none ? 1024 : kStageRows;
+        s.unroll = 2;
+      }
     } else if (one && w.source <= kL2) {
       // one row per lane, terms from LDS windows (1024 ranks staged backward,
       // FP32 189 -> 145, in tiles of 4096 rows 168: forwarders stage their
@@ -364,12 +383,13 @@ SchedFor hx::req_sched_for(const hx_req* r, int phase) {
   SchedFor w;
   w.phase = phase;
   w.jobs = 1;
+  w.values = r->ncols;
   w.bytes = r->bytes[phase];
   switch (phase) {
     case PH_PACK: w.rows = r->E1; w.owned = r->n_local; w.source = r->n_local * rb; break;
     case PH_REDIST: w.rows = r->E2; w.source = r->R1 * rb; break;
     case PH_UNPACK: w.rows = r->H; w.source = (r->R1 + r->R2) * rb; w.identity = r->unpack_identity; break;
-    default: w.rows = r->n_local; w.source = r->E1 * rb; break;
+    default: w.rows = r->n_local; w.terms = r->E1; w.source = r->E1 * rb; break;
   }
   return w;
 }
@@ -726,6 +746,7 @@ SchedFor hx::batch_sched_for(const hx_batch* b, int phase) {
       case PH_UNPACK: w.rows = b->H_tot; w.source = b->R2_tot / R * rb; w.identity = b->unpack_identity; break;
       default:
         w.rows = b->n;
+        w.terms = b->unpack_identity || b->staged_bwd ? b->E1_tot : b->H_tot;
         // (the closed-form adjoint reads every rank's halo)
         w.source = b->unpack_identity || b->staged_bwd ? b->E1_tot / R * rb : b->H_tot * rb;
         break;
@@ -736,6 +757,7 @@ SchedFor hx::batch_sched_for(const hx_batch* b, int phase) {
       const SchedFor m = req_sched_for(r, phase);
       w.rows += m.rows;
       w.owned += m.owned;
+      w.terms += m.terms;
       w.jobs += m.rows > 0 ? 1 : 0;
       w.bytes += m.bytes;
       w.identity = m.identity;
@@ -746,6 +768,7 @@ SchedFor hx::batch_sched_for(const hx_batch* b, int phase) {
     for (const hx_req* r : b->members) w.identity = w.identity && r->unpack_identity;
   }
   w.phase = phase;
+  w.values = b->ncols;
   return w;
 }
 

@@ -1,5 +1,5 @@
 // Prints the library's default schedules: a line of input per question,
-//   kind row_bytes phase rows owned jobs bytes source identity fresh
+//   kind row_bytes phase rows owned terms values jobs bytes source identity fresh
 // a line of output per answer,
 //   tile_rows block_threads blocks_per_cu nontemporal unroll push_pack lds_window pair_rows
 #include <cstdio>
@@ -7,14 +7,16 @@
 #include "common.h"
 
 int main() {
-  int kind, rb, phase, identity, fresh;
-  long long rows, owned, jobs, bytes, source;
-  while (std::scanf("%d %d %d %lld %lld %lld %lld %lld %d %d", &kind, &rb, &phase, &rows, &owned, &jobs, &bytes,
-                    &source, &identity, &fresh) == 10) {
+  int kind, rb, phase, values, identity, fresh;
+  long long rows, owned, terms, jobs, bytes, source;
+  while (std::scanf("%d %d %d %lld %lld %lld %d %lld %lld %lld %d %d", &kind, &rb, &phase, &rows, &owned, &terms,
+                    &values, &jobs, &bytes, &source, &identity, &fresh) == 12) {
     hx::SchedFor w;
     w.phase = phase;
     w.rows = rows;
     w.owned = owned;
+    w.terms = terms;
+    w.values = values;
     w.jobs = jobs;
     w.bytes = bytes;
     w.source = source;

@@ -27,9 +27,10 @@ def rules(tmp_path_factory):
                         "-Wl,-rpath," + os.path.dirname(B.LIB)], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[:4000]
 
-    def ask(kind, row_bytes, phase, rows, owned=0, jobs=1, nbytes=None, source=0, identity=0, fresh=0):
-        line = [kind, row_bytes, phase, rows, owned, jobs, 2 * rows * row_bytes if nbytes is None else nbytes, source,
-                identity, fresh]
+    def ask(kind, row_bytes, phase, rows, owned=0, terms=0, values=1, jobs=1, nbytes=None, source=0, identity=0,
+            fresh=0):
+        line = [kind, row_bytes, phase, rows, owned, terms, values, jobs,
+                2 * rows * row_bytes if nbytes is None else nbytes, source, identity, fresh]
         out = subprocess.run([exe], input=" ".join(map(str, line)), capture_output=True, text=True, check=True).stdout
         return dict(zip(FIELDS, map(int, out.split())))
     return ask
@@ -62,3 +63,24 @@ def test_pushed_tiles_cover_the_source(rules, row_bytes):
     least = max(16, 4096 // row_bytes)
     for rows in (100, 3000):
         assert 3000 // tile(rows, 3000) >= min(2 * CUS, 3000 // least)
+
+
+STAGE_ROWS, WIN_BYTES = 512, 72 << 10     # rows whose pointers a sum's tile stages; its largest window
+
+
+@pytest.mark.parametrize("terms_per_row", [0, 1, 5, 8, 40])
+@pytest.mark.parametrize("rows", [100, 20_000, 3_000_000])
+@pytest.mark.parametrize("jobs", [1, 40, 1000])
+@pytest.mark.parametrize("fresh", [0, 1])
+def test_sums_of_two_single_values(rules, terms_per_row, rows, jobs, fresh):
+    """Rows of two FP32 values are no one-value rows: their sums stage their
+    pointers (unless hardly one has a term), or read a window that fits, and
+    never go one row a lane."""
+    terms = rows * terms_per_row
+    for source in (terms * 8 // jobs, WIN_BYTES, 4 << 20):
+        s = rules(SUM, 8, BWD, rows, terms=terms, values=2, jobs=jobs, nbytes=(rows + terms) * 12, source=source,
+                  fresh=fresh)
+        assert s["pair_rows"] == 0
+        assert s["tile_rows"] <= STAGE_ROWS or (s["lds_window"] == 1 and source <= WIN_BYTES) or 8 * terms <= rows
+    one = rules(SUM, 8, BWD, rows, terms=terms, values=1, jobs=jobs, source=1 << 20)
+    assert one["pair_rows"] == 1
