@@ -239,9 +239,9 @@ int build_segsum_table(const std::vector<SegSumJob>& jobs, int dtype, int row_by
                        const Sched& s, LaunchTable* t, int tag = TAG_OWNER_SUM);
 // The sum of one job, launched on stream with the job in the launch's
 // arguments: nothing is allocated or written beside the sums.  terms: all its
-// rows' terms.  HX_ERR_UNSUPPORTED beyond max_tiles tiles.
+// rows' terms.
 int launch_segsum_one(const SegSumJob& job, int64_t terms, int dtype, int row_bytes, const Sched& s,
-                      int64_t max_tiles, hipStream_t stream);
+                      hipStream_t stream);
 int build_scatter_table(const std::vector<SegSumJob>& jobs, int dtype, int row_bytes,
                         const Sched& s, LaunchTable* t, int tag = TAG_PACK);
 struct LaunchOpt {

@@ -382,17 +382,17 @@ int build_segsum_table(const std::vector<SegSumJob>& jobs, int dtype, int row_by
 }
 
 int launch_segsum_one(const SegSumJob& job, int64_t terms, int dtype, int row_bytes, const Sched& s,
-                      int64_t max_tiles, hipStream_t stream) {
+                      hipStream_t stream) {
   LaunchTable t;
   std::vector<SegSumJob> kept;
   std::vector<int64_t> ts;
   Sched sc = s;
-  if (!sc.pair_rows) sc.lds_window = 0;  // (the windowed form reads launch tables only)
+  if (!sc.pair_rows && sc.lds_window) {  // (the windowed form reads launch tables only)
+    sc.lds_window = 0;
+    sc.tile_rows = std::min(sc.tile_rows, kStageRows);
+  }
   HX_TRY(shape_segsum_table(std::vector<SegSumJob>(1, job), dtype, row_bytes, sc, &t, TAG_OWNER_SUM, &kept, &ts));
   if (t.ntiles == 0) return HX_SUCCESS;
-  if (t.ntiles > max_tiles)
-    return fail(HX_ERR_UNSUPPORTED, "%lld tiles of %d rows exceed %lld", (long long)t.ntiles, t.sched.tile_rows,
-                (long long)max_tiles);
   t.vec_depth = depth_of(terms, job.nrows);
   LaunchOpt o;
   o.one = &kept[0];
