@@ -479,7 +479,8 @@ int hx_req_free(hx_req** req);
  * hx_batch_start_plain / hx_batch_wait_plain: the same work as one launch per
  *   member (the plain one-plan-per-launch form, for comparison).
  * hx_batch_tune: times candidate schedules on the batch's own buffers (the
- *   candidates write the same arenas/halos a start/wait would), keeps the
+ *   candidates write the same arenas/halos a start/wait would, the receive
+ *   arena with the simulated transfer among them), keeps the
  *   fastest, and records it in the tuning cache
  *   (file named by HX_TUNE_CACHE, if set).  Search per phase: tile size x
  *   rows per lane x pack form x LDS windows x rows per lane pairing (8-byte

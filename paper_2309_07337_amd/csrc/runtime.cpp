@@ -843,7 +843,13 @@ int hx::batch_run_wait(hx_batch* b, hipStream_t s) {
   return launch_table(b->lt[PH_UNPACK], s);
 }
 
-static std::string cache_key(const hx_batch* b, int phase) {
+// Whether a phase's kernels write each row to its receiver too (the staged
+// backward: its forwarder sums).
+static bool delivers(const hx_batch* b, int phase) {
+  return sim_transfer(b) && (phase == PH_PACK || phase == PH_REDIST || (phase == PH_BWD && b->staged_bwd));
+}
+
+static std::string cache_key(const hx_batch* b, int phase, bool delivering) {
   std::ostringstream k;
   int64_t rows = 0;
   int njobs = 0;
@@ -858,6 +864,7 @@ static std::string cache_key(const hx_batch* b, int phase) {
     << "|j" << ilog2(njobs + 1) << "|w" << (b->world ? 1 : 0);
   if (b->world) k << "|v" << b->variant;  // 2-step and 3-step worlds differ in shape
   if (phase == PH_BWD && b->staged_bwd) k << "|staged";  // forwarder + owner sums, not the closed form
+  if (delivering) k << "|deliver";  // other kernels, with twice the writes
   return k.str();
 }
 
@@ -882,6 +889,14 @@ static bool cache_lookup(const std::string& key, Sched* out) {
     if (k == key) { *out = s; found = true; }
   }
   return found;
+}
+
+// A phase's tuned schedule.  (Files written before deliveries had a key of
+// their own hold one for the shape.)
+static bool cache_lookup(const hx_batch* b, int phase, Sched* out) {
+  if (!cache_path()) return false;
+  if (delivers(b, phase) && cache_lookup(cache_key(b, phase, true), out)) return true;
+  return cache_lookup(cache_key(b, phase, false), out);
 }
 
 static void cache_store(const std::string& key, const Sched& s) {
@@ -909,7 +924,7 @@ int hx::batch_init_scheds(hx_batch* b, const hx_sched* sched) {
       b->sched[ph] = resolve_sched(sched, kind, (int)b->row_bytes, batch_sched_for(b, ph));
     } else {
       Sched s;
-      b->sched[ph] = cache_lookup(cache_key(b, ph), &s) ? s : default_sched(kind, (int)b->row_bytes, batch_sched_for(b, ph));
+      b->sched[ph] = cache_lookup(b, ph, &s) ? s : default_sched(kind, (int)b->row_bytes, batch_sched_for(b, ph));
     }
   }
   if (batch_has_ready(b)) b->sched[PH_PACK].push_pack = 0;
@@ -1049,7 +1064,7 @@ extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
   }
   // the backward's shape (and so its tuning-cache key) exists only now
   Sched cached;
-  if (b->sched_from_cache[PH_BWD] && cache_lookup(cache_key(b, PH_BWD), &cached)) b->sched[PH_BWD] = cached;
+  if (b->sched_from_cache[PH_BWD] && cache_lookup(b, PH_BWD, &cached)) b->sched[PH_BWD] = cached;
   return batch_prepare(b);
 }
 
@@ -1100,7 +1115,7 @@ static int refresh_member_grads(hx_batch* b) {
   if (b->world || member_grad_gens(b) == b->bwd_gens_built) return HX_SUCCESS;
   b->plain_built[PH_BWD] = false;
   Sched cached;  // gradients bound after the batch was made: the backward's cache key changes
-  if (b->sched_from_cache[PH_BWD] && cache_lookup(cache_key(b, PH_BWD), &cached)) b->sched[PH_BWD] = cached;
+  if (b->sched_from_cache[PH_BWD] && cache_lookup(b, PH_BWD, &cached)) b->sched[PH_BWD] = cached;
   return batch_prepare(b);
 }
 
@@ -1201,13 +1216,14 @@ extern "C" int hx_batch_bytes(const hx_batch* b, int phase, int64_t* bytes) {
 // ---------------------------------------------------------------------------
 // Average launch time of a table: `reps` back-to-back launches between two
 // events (queued faster than they run, so host launch cost stays hidden),
-// best of two trials after a warm-up launch.
-static int time_table(const LaunchTable& t, hipStream_t s, hipEvent_t e0, hipEvent_t e1, int reps, float* best) {
-  HX_TRY(launch_table(t, s));  // warm-up
+// best of two trials after a warm-up launch.  o: as a step launches it.
+static int time_table(const LaunchTable& t, hipStream_t s, const LaunchOpt& o, hipEvent_t e0, hipEvent_t e1, int reps,
+                      float* best) {
+  HX_TRY(launch_table(t, s, o));  // warm-up
   *best = 1e30f;
   for (int trial = 0; trial < 2; ++trial) {
     HX_HIP(hipEventRecord(e0, s));
-    for (int i = 0; i < reps; ++i) HX_TRY(launch_table(t, s));
+    for (int i = 0; i < reps; ++i) HX_TRY(launch_table(t, s, o));
     HX_HIP(hipEventRecord(e1, s));
     HX_HIP(hipEventSynchronize(e1));
     float ms = 0;
@@ -1250,12 +1266,12 @@ extern "C" int hx_batch_tune(hx_batch* b, void* stream) {
       rc = batch_build_table(b, ph, c, &t);
       if (rc != HX_SUCCESS) return;
       float ms = 0;
-      rc = time_table(t, s, e0, e1, 3, &ms);
+      rc = time_table(t, s, {ph != PH_BWD && delivers(b, ph), 0, 0}, e0, e1, 3, &ms);
       if (rc == HX_SUCCESS && ph == PH_BWD && b->staged_bwd) {  // forwarder sums share the schedule
         LaunchTable tf;
         float msf = 0;
         rc = build_fwd_sum_table(b, c, &tf);
-        if (rc == HX_SUCCESS) rc = time_table(tf, s, e0, e1, 3, &msf);
+        if (rc == HX_SUCCESS) rc = time_table(tf, s, {delivers(b, ph), 0, 0}, e0, e1, 3, &msf);
         ms += msf;
       }
       if (log)
@@ -1388,7 +1404,7 @@ extern "C" int hx_batch_tune(hx_batch* b, void* stream) {
     if (rc == HX_SUCCESS) {
       b->sched[ph] = best;
       b->sched_from_cache[ph] = false;  // tuned here: kept when gradients are bound again
-      cache_store(cache_key(b, ph), best);
+      cache_store(cache_key(b, ph, delivers(b, ph)), best);
     }
   }
   (void)hipEventDestroy(e0);
