@@ -905,9 +905,15 @@ __global__ void k_pack_keys(const int32_t* __restrict__ s1_idx, int64_t E, const
 // LDS atomics; the grouping by radix sort passes over keys and values three
 // times and needs its keys and results rewritten per rank: 8.6 M slots of 1024
 // ranks 311 -> 33 us, 0.9 M of 512 ranks 157 -> 18.
-// Rows of more than kSortLane slots are ranked by the whole workgroup, a slot's
-// place being the number of the row's slots below it.
-constexpr int kSortLane = 24;
+// (The slots of a row come nearly in order, so a lane's insertion sort is nearly
+// one pass.)  Rows of more than kSortLane slots are sorted by the workgroup, as
+// the set bits of a bitmap of the rank's slots.  The whole plan of 64 ranks of
+// 20,000 rows, one of them packed for all ranks: 360 us (ranked one row after
+// the other by the workgroup beyond 24 slots 2295, radix sort 479); of 64 ranks
+// of 900 rows, each packed for 25 ranks: 325 (1556, 441); of 4096 ranks of 1024
+// rows, one packed for all: 1579 (9833, 2328).
+constexpr int kSortLane = 256;
+constexpr int kMaxLong = (160 << 10) / 4 / (kSortLane + 1) + 1;  // such rows in one workgroup's LDS
 constexpr int kTransMinRanks = 8;
 constexpr int kTransThreads = 512;
 __global__ void __launch_bounds__(kTransThreads)
@@ -915,13 +921,14 @@ __global__ void __launch_bounds__(kTransThreads)
                      const int64_t* __restrict__ koff, const int64_t* __restrict__ bt_off, int32_t* __restrict__ bt_ptr,
                      int32_t* __restrict__ bt_perm, int* err) {
   extern __shared__ int32_t s_mem[];
-  __shared__ int s_nlong;
+  __shared__ int s_nlong, s_long[kMaxLong];
   const int q = blockIdx.x, tid = threadIdx.x;
   const int rows = (int)(koff[q + 1] - koff[q]), E = (int)(s1_off[q + 1] - s1_off[q]);
   const int32_t* __restrict__ idx = s1_idx + s1_off[q];
   int32_t* __restrict__ perm = bt_perm + s1_off[q];
   int32_t* s_next = s_mem;            // [rows + 1]
   int32_t* s_slot = s_mem + rows + 1; // [E]
+  uint32_t* s_bits = reinterpret_cast<uint32_t*>(s_slot + E);  // [(E + 31) / 32]
   for (int i = tid; i <= rows; i += kTransThreads) s_next[i] = 0;
   if (tid == 0) s_nlong = 0;
   __syncthreads();
@@ -956,7 +963,7 @@ __global__ void __launch_bounds__(kTransThreads)
   for (int r = tid; r < rows; r += kTransThreads) {
     const int a = r > 0 ? s_next[r - 1] : 0, b = s_next[r];
     if (b - a > kSortLane) {
-      s_nlong = 1;
+      s_long[atomicAdd(&s_nlong, 1)] = r;
       continue;
     }
     for (int i = a + 1; i < b; ++i) {
@@ -967,25 +974,24 @@ __global__ void __launch_bounds__(kTransThreads)
     }
   }
   __syncthreads();
-  if (s_nlong) {  // (uniform)
-    for (int r = 0; r < rows; ++r) {
-      const int a = r > 0 ? s_next[r - 1] : 0, b = s_next[r];
-      if (b - a <= kSortLane) continue;
-      for (int i = a + tid; i < b; i += kTransThreads) {
-        const int32_t v = s_slot[i];
-        int below = 0;
-        for (int k = a; k < b; ++k) below += s_slot[k] < v ? 1 : 0;
-        perm[a + below] = v;
-      }
+  const int words = (E + 31) / 32;
+  for (int g = 0; g < s_nlong; ++g) {  // (uniform)
+    const int r = s_long[g], a = r > 0 ? s_next[r - 1] : 0, b = s_next[r];
+    for (int i = tid; i < words; i += kTransThreads) s_bits[i] = 0;
+    __syncthreads();
+    for (int i = a + tid; i < b; i += kTransThreads) atomicOr(&s_bits[s_slot[i] >> 5], 1u << (s_slot[i] & 31));
+    __syncthreads();
+    int at = a;
+    for (int w0 = 0; w0 < words; w0 += kTransThreads) {
+      uint32_t bits = w0 + tid < words ? s_bits[w0 + tid] : 0u;
+      int tot;
+      int o = at + block_exscan((int)__popc(bits), &tot);
+      for (; bits != 0; bits &= bits - 1u) s_slot[o++] = (w0 + tid) * 32 + __ffs(bits) - 1;
+      at += tot;
     }
+    __syncthreads();
   }
-  // (the long rows are in place)
-  for (int r = tid >> 6; s_nlong && r < rows; r += kTransThreads / 64) {
-    const int a = r > 0 ? s_next[r - 1] : 0, b = s_next[r];
-    if (b - a <= kSortLane)
-      for (int i = a + (tid & 63); i < b; i += 64) perm[i] = s_slot[i];
-  }
-  for (int i = tid; !s_nlong && i < base; i += kTransThreads) perm[i] = s_slot[i];
+  for (int i = tid; i < base; i += kTransThreads) perm[i] = s_slot[i];
 }
 
 // Per-rank transpose arrays from that grouping (pack rows of rank q occupy
@@ -1258,8 +1264,11 @@ int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff,
   HX_TRY(p->d[HX_F_BT_PERM].alloc((size_t)E1 * 4));
   // in LDS where every rank's fits (and there are ranks enough to fill the chip)
   int64_t lds = 0;
-  for (int q = 0; q < R; ++q) lds = std::max(lds, 4 * (pack_rows[q] + 1 + s1_off[q + 1] - s1_off[q]));
-  const bool in_lds = lds <= device_lds_per_block() - 1024 && R >= kTransMinRanks;
+  for (int q = 0; q < R; ++q) {
+    const int64_t E = s1_off[q + 1] - s1_off[q];
+    lds = std::max(lds, 4 * (pack_rows[q] + 1 + E + (E + 31) / 32));
+  }
+  const bool in_lds = lds <= device_lds_per_block() - 2048 && R >= kTransMinRanks;
   if (in_lds)
     hipLaunchKernelGGL(k_pack_transpose, dim3(R), dim3(kTransThreads), (size_t)lds, s,
                        p->d[HX_F_S1_IDX].as<int32_t>(), s1o_d, koff_d, bto_d, p->d[HX_F_BT_PTR].as<int32_t>(),
