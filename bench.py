@@ -5,7 +5,8 @@ Headline workload ("batched256"): 256 independent persistent exchange plans,
 halo sizes log-uniform in [1e3, 1e6) rows, 1..4096 neighbors, 16 FP64
 columns per row.  One step = Start + Wait of all plans (pack, unpack) plus
 the backward of the pack (fixed-order transpose sum), each phase one
-multi-job kernel launched from a table prepared at init.
+multi-job kernel launched from a table prepared at init, the step replayed from
+a HIP graph.
 The same work as one launch per plan per phase ("plain") is timed beside it.
 
 With the headline workload the line also carries ``configs``: every other
@@ -28,7 +29,9 @@ dominant kernel against the HBM roofline):
 ``--workload`` runs one of them alone as the headline (``copy`` is the 1 GiB
 calibration copy for the PMC scale factors).  ``--sched-json`` applies
 recorded schedules instead of tuning (per phase, as hx_batch_get_sched
-reports them), ``--replay`` sets the replay mode (both launch the same tables).
+reports them).  The headline's timed step is captured in a HIP graph and
+replayed; the others' (shorter than a graph launch, some of them) are calls,
+which launch their tables directly.  ``--replay`` sets either for all.
 
 Prints one JSON line (rank 0, one GPU).
 """
@@ -282,8 +285,6 @@ def tune(args, torch, P, batch, name):
         P.hx_batch_tune(batch)
         torch.cuda.synchronize()
         log(f"{name}: tuned in {time.time() - t0:.1f}s")
-    if args.replay:
-        P.hx_batch_set_replay(batch, P.HX_REPLAY_DIRECT if args.replay == "direct" else P.HX_REPLAY_GRAPH)
 
 
 # ---------------------------------------------------------------------------
@@ -296,27 +297,35 @@ def step_fns(P, plain, sp):
     return {k: (lambda b, f=f: f(b, sp)) for k, f in fns.items()}
 
 
-def time_steps(torch, P, batch, steps, warmup, plain, phases):
+def time_steps(torch, P, batch, steps, warmup, plain, phases, graph=False):
     """Warm steps (Start + Wait [+ backward when 3 is in phases]): `steps`
     steps back to back between two synchronisations (wall clock, nothing
-    else in the loop), then the same steps with events around each phase for
+    else in the loop; graph: one step captured in a HIP graph, replayed), then the same steps with events around each phase for
     the breakdown; a backward outside the step is timed afterwards for the
     report only."""
     sp = torch.cuda.current_stream().cuda_stream   # passed explicitly: no stream lookup per call
     run = step_fns(P, plain, sp)
     with_bwd = 3 in phases
-    for _ in range(warmup):
+
+    def step():
         run[0](batch)
         run[2](batch)
         if with_bwd:
             run[3](batch)
+
+    for _ in range(warmup):
+        step()
     torch.cuda.synchronize()
+    if graph:
+        captured = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(captured, stream=torch.cuda.current_stream()):
+            step()
+        step = captured.replay
+        step()
+        torch.cuda.synchronize()
     t0 = time.perf_counter()
     for _ in range(steps):
-        run[0](batch)
-        run[2](batch)
-        if with_bwd:
-            run[3](batch)
+        step()
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     ev = [[torch.cuda.Event(enable_timing=True) for _ in range(4)] for _ in range(steps)]
@@ -415,7 +424,8 @@ def measure(name, S, args, torch, P, flush, plain=True):
     dominant kernel against the HBM roofline."""
     b = S["batch"]
     nbytes = {ph: P.hx_batch_bytes(b, ph) for ph in range(4)}
-    ms, ph = time_steps(torch, P, b, args.steps, args.warmup, False, S["phases"])
+    replay = args.replay or ("graph" if name == "batched256" else "direct")
+    ms, ph = time_steps(torch, P, b, args.steps, args.warmup, False, S["phases"], graph=replay == "graph")
     log(f"{name}: {ms:.4f} ms/step; phases (ms) {json.dumps({k: round(v, 4) for k, v in ph.items()})}")
     cold = time_cold(torch, P, b, S["phases"], flush) if flush is not None else None
     plain_ms = None
@@ -433,7 +443,6 @@ def measure(name, S, args, torch, P, flush, plain=True):
     # (a locality world's staged backward is reported aside, never the step's dominant kernel)
     kname = kernel_symbol(P, b, dom_p, row_bytes, staged=False)
     traffic = read_traffic(kname, name)
-    replay = P.hx_batch_get_replay(b)
     # steps that move a few MB last less than the launches they take: their
     # bandwidth measures launch cost, not memory, and is not set against the peak
     launch_bound = step_bytes < 64e6
@@ -453,7 +462,7 @@ def measure(name, S, args, torch, P, flush, plain=True):
         "roofline": {"bound": "launch" if launch_bound else "hbm", "kernel": f"{kname} ({NAMES[dom_p]})",
                      "achieved": round(achieved, 2), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": None if launch_bound else round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic},
-        "replay": "direct" if replay == P.HX_REPLAY_DIRECT else "graph",
+        "replay": replay,
         "note": (f"launch-bound: one step moves {step_bytes / 1e6:.2f} MB ({step_bytes / HBM_PEAK_GBPS / 1e3:.2f} us "
                  f"at 8 TB/s), less than the cost of its launches; not an HBM figure") if launch_bound else None,
         "sched": {NAMES[p]: P.hx_batch_get_sched(b, p) for p in range(4) if nbytes[p] > 0},
@@ -471,7 +480,6 @@ def time_halo_gather(S, args, torch, P):
     if args.sched_json or not args.no_tune:
         for p in (0, 2, 3):   # the schedules tuned for the batch of the same plan
             P.hx_batch_set_sched(ex.batch, p, P.hx_batch_get_sched(S["batch"], p))
-        P.hx_batch_set_replay(ex.batch, P.hx_batch_get_replay(S["batch"]))
     ex.x.copy_(S["keep"][1])
     ex.g_halo.fill_(1.0)
     x = ex.x.detach().requires_grad_(True)
@@ -599,7 +607,9 @@ def main():
     ap.add_argument("--no-cold", action="store_true", help="skip the flushed-cache median")
     ap.add_argument("--sched-json", default="", help="per-phase schedules to apply instead of tuning "
                                                      "(JSON text or file: {\"0\": {...}, ...})")
-    ap.add_argument("--replay", choices=["graph", "direct"], default="")
+    ap.add_argument("--replay", choices=["graph", "direct"], default="",
+                    help="timed steps replayed from a captured HIP graph (default of the headline workload) or as "
+                         "calls (of the others)")
     ap.add_argument("--cpu-plans", type=int, default=256)
     ap.add_argument("--cpu-seconds", type=float, default=8.0)
     args = ap.parse_args()

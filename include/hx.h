@@ -532,12 +532,17 @@ int hx_batch_get_sched(const hx_batch* b, int phase, hx_sched* out);
  * (null, bad phase, an invalid schedule: the batch then keeps its previous
  * one), HX_ERR_STATE while a Start is pending. */
 int hx_batch_set_sched(hx_batch* b, int phase, const hx_sched* sched);
-/* Replay of start / wait / backward.  Both modes (HX_REPLAY_GRAPH is the
- * default) launch the prepared launch tables one by one (no per-call setup,
- * same results): a graph launch has a fixed cost (about 15 us measured on
- * MI355X, whatever the graph holds) against about 3 us per directly launched
- * kernel, and no step has more than four.  The mode is kept and reported;
- * hx_batch_tune leaves it as it is.  Mode other than these two: HX_ERR_ARG. */
+/* Replay mode of start / wait / backward: kept and reported (HX_REPLAY_GRAPH
+ * until set), without effect.  The library captures no graph: in both modes the
+ * calls launch their prepared launch tables one by one (no per-call setup).  A
+ * graph launch has a fixed cost (about 15 us measured on MI355X, whatever the
+ * graph holds) against about 3 us per directly launched kernel, and no step has
+ * more than four.  A caller that wants a step in a graph captures the calls:
+ * after one step outside it (which builds what is built on first use) they only
+ * enqueue kernels, and device copies where hx_batch_exchange and
+ * hx_batch_adjoint fall back to them.  A replay moves what the bound buffers
+ * hold then; schedules set, gradients bound or the batch freed after the capture
+ * invalidate it.  Mode other than these two: HX_ERR_ARG. */
 enum { HX_REPLAY_GRAPH = 0, HX_REPLAY_DIRECT = 1 };
 int hx_batch_set_replay(hx_batch* b, int mode);
 int hx_batch_get_replay(const hx_batch* b, int* mode);

@@ -469,8 +469,8 @@ def hx_backward(req: Req, stream=None) -> None:
 
 
 def hx_backward_noalloc(req: Req, g_send, g_x, stream=None) -> None:
-    """The request's backward into g_x from g_send, allocating nothing (the
-    launch table goes to the library's fixed per-device area)."""
+    """The request's backward into g_x from g_send, allocating nothing (its one
+    job goes with the launch)."""
     _check(load().hx_backward_noalloc(req.ptr, _dptr(g_send), _dptr(g_x), _stream(stream)))
 
 
@@ -570,6 +570,7 @@ def hx_batch_set_sched(b: Batch, phase: int, sched) -> None:
 
 
 def hx_batch_set_replay(b: Batch, mode: int) -> None:
+    """Kept and reported only: both modes launch the prepared tables directly."""
     _check(load().hx_batch_set_replay(b.ptr, mode))
 
 
