@@ -115,7 +115,8 @@ typedef struct {
                          least tiles / #CUs (1 << 20 is the library's) gives
                          one workgroup per tile, dispatched by the hardware
                          in tile order */
-  int nontemporal;    /* 1: streaming (non-temporal) loads/stores of index and
+  int nontemporal;    /* 0: no hints (a default schedule may have them);
+                         1: streaming (non-temporal) loads/stores of index and
                          output (and of the terms in the chunked segmented
                          sum, and of the source rows in the push pack);
                          2: as 1, and gathers of 4- or 8-byte rows in
@@ -501,7 +502,10 @@ int hx_batch_wait(hx_batch* b, void* stream);
 int hx_batch_start_plain(hx_batch* b, void* stream);
 int hx_batch_wait_plain(hx_batch* b, void* stream);
 /* Backward: member batches use each member's bound gradients; worlds use
- * g_in = g_halo_all [sum H, ncols] and g_out = g_x_global [n, ncols]. */
+ * g_in = g_halo_all [sum H, ncols] and g_out = g_x_global [n, ncols].  Binding
+ * allocates what only the backward reads (its arenas and maps; a locality
+ * world's closed-form adjoint is built by the first call): HX_ERR_NOMEM leaves
+ * the batch as it was. */
 int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out);
 int hx_batch_backward(hx_batch* b, void* stream);
 int hx_batch_backward_plain(hx_batch* b, void* stream);

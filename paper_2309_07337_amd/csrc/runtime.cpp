@@ -1073,10 +1073,10 @@ static bool overlap(const void* p, size_t n, const void* q, size_t m) {
 }
 static bool overlap(const void* p, size_t n, const DevMem& m) { return overlap(p, n, m.p, m.bytes); }
 
-// Backward of a batch.  Plain worlds: with the simulated transport the
-// reverse stage-1 transfer first, then the owner sums.  Staged locality
-// worlds: [reverse stage-2 transfer], forwarder sums, [reverse stage-1
-// transfer], owner sums.  Others: the fixed-order sums.
+// Backward of a batch.  Plain worlds: with the simulated transport the reverse
+// transfer first, then the owner sums.  Staged locality worlds: [reverse
+// stage-2 transfer], forwarder sums (with the simulated transport written to the
+// send slots they travel back to), owner sums.  Others: the fixed-order sums.
 static int run_backward(hx_batch* b, hipStream_t s, bool plain_form, int64_t g_in, int64_t g_out) {
   const bool sim = sim_transfer(b);
   const bool plain_world = b->world && b->unpack_identity;
@@ -1091,7 +1091,6 @@ static int run_backward(hx_batch* b, hipStream_t s, bool plain_form, int64_t g_i
     }
   }
   if (b->world && b->staged_bwd) {
-    // (the sums are delivered to the send slots as they are made)
     if (sim) HX_TRY(launch_table(b->lt_back2, s));
     HX_TRY(launch_table(b->lt_fwd_sum, s, {sim, 0, 0}));
   } else if (plain_world && sim && g_in == 0) {
