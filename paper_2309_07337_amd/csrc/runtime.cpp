@@ -18,6 +18,7 @@
 #include <numeric>
 #include <sstream>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "common.h"
@@ -401,11 +402,11 @@ static int build_req_tables(hx_req* r) {
   // each way: 4 and 5 us)
   const bool one_wait =
       !r->unpack_identity && r->E2 > 0 && r->H > 0 && (r->E2 + r->H) * (int64_t)r->row_bytes <= 16 << 20;
+  LaunchTable lt[4];
   for (int ph = 0; ph < 4; ++ph) {
     std::vector<GatherJob> g;
     std::vector<SegSumJob> s;
     const int kind = ph == PH_BWD ? KIND_SEGSUM : KIND_GATHER;
-    r->lt[ph] = LaunchTable();
     if (one_wait && ph == PH_REDIST) continue;
     SchedFor w = req_sched_for(r, ph);
     if (one_wait && ph == PH_UNPACK) {
@@ -417,8 +418,9 @@ static int build_req_tables(hx_req* r) {
     const Sched sc = default_sched(kind, (int)r->row_bytes, w);
     if (one_wait && ph == PH_UNPACK) HX_TRY(req_phase_jobs(r, PH_REDIST, sc, &g, &s));
     HX_TRY(req_phase_jobs(r, ph, sc, &g, &s));
-    HX_TRY(build_phase_table(ph, sc, r->dtype, (int)r->row_bytes, g, s, &r->lt[ph]));
+    HX_TRY(build_phase_table(ph, sc, r->dtype, (int)r->row_bytes, g, s, &lt[ph]));
   }
+  std::move(lt, lt + 4, r->lt);  // (all or none: a call that fails leaves the request as it was)
   r->tables_built = true;
   return HX_SUCCESS;
 }
@@ -646,16 +648,22 @@ extern "C" int hx_req_bind_grad(hx_req* r, const void* g_send, void* g_x) {
   if (!r) return fail(HX_ERR_ARG, "null request");
   HX_TRY(req_usable(r));
   if ((r->E1 > 0 && !g_send) || (r->n_local > 0 && !g_x)) return fail(HX_ERR_ARG, "null gradient buffer");
-  r->g_send = static_cast<const char*>(g_send);
-  r->g_x = static_cast<char*>(g_x);
-  static std::atomic<uint64_t> bind_counter{0};
-  r->grad_gen = ++bind_counter;  // batches holding this member rebuild their backward
-  r->lt[PH_BWD] = LaunchTable();
+  const char* const old_send = std::exchange(r->g_send, static_cast<const char*>(g_send));
+  char* const old_x = std::exchange(r->g_x, static_cast<char*>(g_x));
+  LaunchTable t;
   std::vector<GatherJob> g;
   std::vector<SegSumJob> s;
   const Sched sc = default_sched(KIND_SEGSUM, (int)r->row_bytes, req_sched_for(r, PH_BWD));
-  HX_TRY(req_phase_jobs(r, PH_BWD, sc, &g, &s));
-  HX_TRY(build_segsum_table(s, r->dtype, (int)r->row_bytes, sc, &r->lt[PH_BWD]));
+  int rc = req_phase_jobs(r, PH_BWD, sc, &g, &s);
+  if (rc == HX_SUCCESS) rc = build_segsum_table(s, r->dtype, (int)r->row_bytes, sc, &t);
+  if (rc != HX_SUCCESS) {  // the request keeps its former gradients
+    r->g_send = old_send;
+    r->g_x = old_x;
+    return rc;
+  }
+  static std::atomic<uint64_t> bind_counter{0};
+  r->grad_gen = ++bind_counter;  // batches holding this member rebuild their backward
+  r->lt[PH_BWD] = std::move(t);
   return HX_SUCCESS;
 }
 
@@ -774,20 +782,20 @@ SchedFor hx::batch_sched_for(const hx_batch* b, int phase) {
 
 // One launch per member: the plain form, with the library's default schedule.
 int hx::batch_build_plain(hx_batch* b, int phase) {
-  b->plain[phase].clear();
   std::vector<std::vector<GatherJob>> g;
   std::vector<std::vector<SegSumJob>> s;
   const int kind = phase == PH_BWD ? KIND_SEGSUM : KIND_GATHER;
   const Sched sc = default_sched(kind, (int)b->row_bytes, batch_sched_for(b, phase));
   HX_TRY(batch_phase_jobs(b, phase, sc, false, &g, &s));
   const size_t nm = std::max(g.size(), s.size());
-  b->plain[phase].resize(nm);
+  std::vector<LaunchTable> t(nm);
   for (size_t m = 0; m < nm; ++m) {
     static const std::vector<GatherJob> no_g;
     static const std::vector<SegSumJob> no_s;
     HX_TRY(build_phase_table(phase, sc, b->dtype, (int)b->row_bytes, m < g.size() ? g[m] : no_g,
-                             m < s.size() ? s[m] : no_s, &b->plain[phase][m]));
+                             m < s.size() ? s[m] : no_s, &t[m]));
   }
+  b->plain[phase] = std::move(t);
   b->plain_built[phase] = true;
   return HX_SUCCESS;
 }
@@ -828,10 +836,16 @@ static std::vector<uint64_t> member_grad_gens(const hx_batch* b) {
 // launch whatever it holds, a kernel launched from its table 2.7 us, and the
 // longest of the three steps has four: captured graphs were never the faster
 // replay (27-point world of 512 ranks, Start + Wait: 45.2 us from graphs, 26.8 so).
+// All of the tables are replaced, or none: a call that fails leaves the batch with
+// those it had.
 int hx::batch_prepare(hx_batch* b) {
+  LaunchTable lt[4], fwd_sum;
+  for (int ph = 0; ph < 4; ++ph) HX_TRY(batch_build_table(b, ph, b->sched[ph], &lt[ph]));
+  HX_TRY(build_fwd_sum_table(b, b->sched[PH_BWD], &fwd_sum));
+  std::move(lt, lt + 4, b->lt);
+  b->lt_fwd_sum = std::move(fwd_sum);
   if (!b->world) b->bwd_gens_built = member_grad_gens(b);
-  for (int ph = 0; ph < 4; ++ph) HX_TRY(batch_build_table(b, ph, b->sched[ph], &b->lt[ph]));
-  return build_fwd_sum_table(b, b->sched[PH_BWD], &b->lt_fwd_sum);
+  return HX_SUCCESS;
 }
 
 int hx::batch_run_start(hx_batch* b, hipStream_t s) {
@@ -966,12 +980,14 @@ extern "C" int hx_batch_set_sched(hx_batch* b, int phase, const hx_sched* sched)
   const int kind = phase == PH_BWD ? KIND_SEGSUM : KIND_GATHER;
   const Sched old = b->sched[phase];
   b->sched[phase] = resolve_sched(sched, kind, (int)b->row_bytes, batch_sched_for(b, phase));
-  b->sched_from_cache[phase] = false;
   if (phase == PH_PACK && batch_has_ready(b)) b->sched[PH_PACK].push_pack = 0;
+  const bool deliveries = b->wp_to.p != nullptr;
   const int rc = batch_prepare(b);
   if (rc != HX_SUCCESS) {
-    b->sched[phase] = old;  // keep the batch usable with its previous schedule
-    (void)batch_prepare(b);
+    b->sched[phase] = old;
+    if (!deliveries) b->wp_to.release();
+  } else {
+    b->sched_from_cache[phase] = false;
   }
   return rc;
 }
@@ -1027,23 +1043,20 @@ extern "C" int hx_batch_wait_plain(hx_batch* b, void* stream) {
   return HX_SUCCESS;
 }
 
-extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
-  if (!b) return fail(HX_ERR_ARG, "null batch");
-  if (!b->world) return fail(HX_ERR_ARG, "member batches use each member's hx_req_bind_grad");
-  // (empty buffers may be null: a decomposition without halo entries, or without rows)
-  if ((!g_in && b->H_tot > 0) || (!g_out && b->n > 0)) return fail(HX_ERR_ARG, "null gradient buffer");
-  if (!b->unpack_identity && !b->staged_bwd) HX_TRY(world_adjoint(b));
-  b->g_in = static_cast<const char*>(g_in);
-  b->g_out = static_cast<char*>(g_out);
-  b->plain_built[PH_BWD] = false;
+// Tables of a world's backward for the gradients b names now.  The arenas do not
+// depend on them and are kept once made.
+static int bind_world_tables(hx_batch* b) {
   const int rbi = (int)b->row_bytes;
   const Sched gsc = default_sched(KIND_GATHER, rbi);
+  auto arena = [&](DevMem& m, int64_t rows) { return m.p ? HX_SUCCESS : m.alloc((size_t)rows * b->row_bytes); };
+  LaunchTable back, back_copy, back2;
+  if (!b->unpack_identity && !b->staged_bwd) HX_TRY(world_adjoint(b));
   if (b->unpack_identity) {
     // plain world: halo gradients travel back to the senders' slots (the
     // simulated reverse transfer), then each rank sums its own slots
-    HX_TRY(b->g_send_all.alloc((size_t)b->E1_tot * b->row_bytes));
+    HX_TRY(arena(b->g_send_all, b->E1_tot));
     std::vector<GatherJob> xb{GatherJob{b->g_in, b->g_send_all.as<char>(), b->gidx_to1.as<int32_t>(), b->E1_tot}};
-    HX_TRY(build_gather_table(xb, b->dtype, rbi, gsc, &b->lt_back));
+    HX_TRY(build_gather_table(xb, b->dtype, rbi, gsc, &back));
     // the same from a caller's buffer, which the bound one gets a copy of
     HX_TRY(world_from_map(b));
     GatherJob cb{b->g_in, nullptr, nullptr, b->H_tot};
@@ -1051,21 +1064,48 @@ extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
     cb.idx2 = b->gidx_from1.as<int32_t>();
     SchedFor cw;
     cw.identity = cw.fresh = true;
-    HX_TRY(build_gather_table({cb}, b->dtype, rbi, default_sched(KIND_GATHER, rbi, cw), &b->lt_back_copy));
+    HX_TRY(build_gather_table({cb}, b->dtype, rbi, default_sched(KIND_GATHER, rbi, cw), &back_copy));
   } else if (b->staged_bwd) {
     // locality world, staged: forwarder sums read the halo gradients (own
     // terms) and the stage-2 send-slot gradients (split = H)
-    HX_TRY(b->g_s2.alloc((size_t)b->E2_tot * b->row_bytes));
-    HX_TRY(b->g_r1.alloc((size_t)b->R1_tot * b->row_bytes));
-    HX_TRY(b->g_send_all.alloc((size_t)b->E1_tot * b->row_bytes));
+    HX_TRY(arena(b->g_s2, b->E2_tot));
+    HX_TRY(arena(b->g_r1, b->R1_tot));
+    HX_TRY(arena(b->g_send_all, b->E1_tot));
     std::vector<GatherJob> x2{GatherJob{b->g_in, b->g_s2.as<char>(), b->gidx_back2.as<int32_t>(), b->E2_tot}};
-    HX_TRY(build_gather_table(x2, b->dtype, rbi, gsc, &b->lt_back2));
+    HX_TRY(build_gather_table(x2, b->dtype, rbi, gsc, &back2));
     HX_TRY(world_from_map(b));
   }
+  HX_TRY(batch_prepare(b));
+  b->lt_back = std::move(back);
+  b->lt_back_copy = std::move(back_copy);
+  b->lt_back2 = std::move(back2);
+  return HX_SUCCESS;
+}
+
+extern "C" int hx_batch_bind_grad(hx_batch* b, const void* g_in, void* g_out) {
+  if (!b) return fail(HX_ERR_ARG, "null batch");
+  if (!b->world) return fail(HX_ERR_ARG, "member batches use each member's hx_req_bind_grad");
+  // (empty buffers may be null: a decomposition without halo entries, or without rows)
+  if ((!g_in && b->H_tot > 0) || (!g_out && b->n > 0)) return fail(HX_ERR_ARG, "null gradient buffer");
+  const bool first = !b->g_out;
+  const char* const old_in = std::exchange(b->g_in, static_cast<const char*>(g_in));
+  char* const old_out = std::exchange(b->g_out, static_cast<char*>(g_out));
+  const Sched old = b->sched[PH_BWD];
   // the backward's shape (and so its tuning-cache key) exists only now
   Sched cached;
   if (b->sched_from_cache[PH_BWD] && cache_lookup(b, PH_BWD, &cached)) b->sched[PH_BWD] = cached;
-  return batch_prepare(b);
+  const int rc = bind_world_tables(b);
+  if (rc != HX_SUCCESS) {  // the batch keeps its former gradients, or none
+    b->g_in = old_in;
+    b->g_out = old_out;
+    b->sched[PH_BWD] = old;
+    if (first)
+      for (DevMem* m : {&b->g_send_all, &b->g_s2, &b->g_r1, &b->gidx_from1, &b->wb_ptr, &b->wb_idx}) m->release();
+    return rc;
+  }
+  b->halo_cols.release();  // (the adjoint is built)
+  b->plain_built[PH_BWD] = false;
+  return HX_SUCCESS;
 }
 
 static bool overlap(const void* p, size_t n, const void* q, size_t m) {

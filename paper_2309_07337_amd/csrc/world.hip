@@ -185,11 +185,13 @@ int check_maps(const unsigned long long* words, int64_t* c1 = nullptr, int64_t* 
 
 // The push pack's deliveries: gidx_to1 in the order of wp_idx.
 int make_push_deliveries(const hx_batch* b) {
-  HX_TRY(b->wp_to.alloc((size_t)b->E1_tot * 4));
+  DevMem m;
+  HX_TRY(m.alloc((size_t)b->E1_tot * 4));
   hipLaunchKernelGGL(k_compose, dim3(blocks_for(b->E1_tot)), dim3(TB), 0, 0, b->wp_idx.as<int32_t>(), b->E1_tot,
-                     b->gidx_to1.as<int32_t>(), b->wp_to.as<int32_t>());
+                     b->gidx_to1.as<int32_t>(), m.as<int32_t>());
   HX_HIP(hipGetLastError());
   HX_HIP(hipStreamSynchronize(0));
+  b->wp_to = std::move(m);
   return HX_SUCCESS;
 }
 
@@ -342,7 +344,6 @@ int world_adjoint(hx_batch* b) {
   HX_TRY(dev_group_by_key(b->halo_cols.as<int32_t>(), b->H_tot, b->n, ptr.as<int32_t>(), idx.as<int32_t>(), nullptr));
   b->wb_ptr = std::move(ptr);
   b->wb_idx = std::move(idx);
-  b->halo_cols.release();
   return HX_SUCCESS;
 }
 
