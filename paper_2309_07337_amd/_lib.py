@@ -542,12 +542,22 @@ def _beside(b: Batch, name: str, t) -> Optional[int]:
 
 def hx_batch_exchange(b: Batch, x=None, halo=None, stream=None) -> None:
     """A world's Start + Wait; x copied into the bound vector, the bound halo into halo (tensors or None)."""
-    _check(load().hx_batch_exchange(b.ptr, _beside(b, "x", x), _beside(b, "halo", halo), _stream(stream)))
+    exchange_at(b, _beside(b, "x", x), _beside(b, "halo", halo), stream)
 
 
 def hx_batch_adjoint(b: Batch, g_in=None, g_out=None, stream=None) -> None:
     """A world's backward; g_in copied into the bound gradients, the bound g_out into g_out (tensors or None)."""
-    _check(load().hx_batch_adjoint(b.ptr, _beside(b, "g_in", g_in), _beside(b, "g_out", g_out), _stream(stream)))
+    adjoint_at(b, _beside(b, "g_in", g_in), _beside(b, "g_out", g_out), stream)
+
+
+def exchange_at(b: Batch, x: Optional[int], halo: Optional[int], stream=None) -> None:
+    """hx_batch_exchange with the addresses of buffers known to lie like the bound ones."""
+    _check(load().hx_batch_exchange(b.ptr, x, halo, _stream(stream)))
+
+
+def adjoint_at(b: Batch, g_in: Optional[int], g_out: Optional[int], stream=None) -> None:
+    """hx_batch_adjoint likewise."""
+    _check(load().hx_batch_adjoint(b.ptr, g_in, g_out, _stream(stream)))
 
 
 def hx_batch_launch_phase(b: Batch, phase: int, stream=None) -> None:

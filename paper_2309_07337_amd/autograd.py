@@ -71,34 +71,38 @@ def _fused(ex: HaloExchange, name: str) -> bool:
     return getattr(getattr(ex, name), "__func__", None) is _STEPS[name]
 
 
-def _beside(t: torch.Tensor, bound: torch.Tensor) -> bool:
-    """Whether the library may copy between t and a bound buffer itself."""
-    return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.layout == torch.strided and t.dtype == bound.dtype
-            and t.device == bound.device and t.shape == bound.shape and t.is_contiguous() and not t.is_neg()
-            and t.numel() > 0 and (not bound.is_inference() or torch.is_inference_mode_enabled())
-            and (t.data_ptr() - bound.data_ptr()) % 16 == 0
-            and abs(t.data_ptr() - bound.data_ptr()) >= bound.numel() * bound.element_size())
-
-
-def _copy_in(t: torch.Tensor, bound: torch.Tensor):
-    """t if the library copies it into the bound buffer; otherwise copied here.
-    Either way autograd sees the buffer change: a backward that saved it for
-    another op raises instead of reading the new values."""
-    if _beside(t, bound):
-        torch.autograd.graph.increment_version(bound)
-        return t
-    bound.copy_(t)
+def _beside(t: torch.Tensor, bound: torch.Tensor):
+    """The address of t where the library may copy between t and a bound buffer itself, else None."""
+    p = t.data_ptr()
+    off = p - bound.data_ptr()
+    if (off % 16 == 0 and type(t) in _PLAIN and t.dtype == bound.dtype and t.shape == bound.shape
+            and t.layout == torch.strided and t.is_contiguous() and t.device == bound.device and not t.is_neg()
+            and abs(off) >= t.nbytes > 0 and (not bound.is_inference() or torch.is_inference_mode_enabled())):
+        return p
     return None
 
 
+_PLAIN = (torch.Tensor, torch.nn.Parameter)
+
+
+def _copy_in(t: torch.Tensor, bound: torch.Tensor):
+    """The address of t if the library copies it into the bound buffer; otherwise
+    copied here.  Either way autograd sees the buffer change: a backward that
+    saved it for another op raises instead of reading the new values."""
+    p = _beside(t, bound)
+    if p is None:
+        bound.copy_(t)
+    else:
+        torch.autograd.graph.increment_version(bound)
+    return p
+
+
 def _copy_out(bound: torch.Tensor, run):
-    """A fresh copy of the bound buffer after run(tensor or None)."""
+    """A fresh copy of the bound buffer after run(its address or None)."""
     out = torch.empty_like(bound)
-    if _beside(out, bound):
-        run(out)
-        return out
-    run(None)
-    return bound.clone()
+    p = _beside(out, bound)
+    run(p)
+    return bound.clone() if p is None else out
 
 
 class HaloGather(torch.autograd.Function):
@@ -114,9 +118,9 @@ class HaloGather(torch.autograd.Function):
             return ex.halo.clone() if copy_out else ex.halo.detach()
         src = _copy_in(x, ex.x) if x.data_ptr() != ex.x.data_ptr() else None
         if copy_out:
-            y = _copy_out(ex.halo, lambda out: L.hx_batch_exchange(ex.batch, src, out))
+            y = _copy_out(ex.halo, lambda out: L.exchange_at(ex.batch, src, out))
         else:
-            L.hx_batch_exchange(ex.batch, src)
+            L.exchange_at(ex.batch, src, None)
             y = ex.halo.detach()
         ex.generation += 1
         ctx.generation = ex.generation
@@ -135,7 +139,7 @@ class HaloGather(torch.autograd.Function):
             ex.backward()
             return ex.g_x.clone(), None, None
         src = None if own else _copy_in(g, ex.g_halo)
-        return _copy_out(ex.g_x, lambda out: L.hx_batch_adjoint(ex.batch, src, out)), None, None
+        return _copy_out(ex.g_x, lambda out: L.adjoint_at(ex.batch, src, out)), None, None
 
 
 def halo_gather(x: torch.Tensor, ex: HaloExchange, copy_out: bool = True) -> torch.Tensor:
