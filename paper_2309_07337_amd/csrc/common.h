@@ -170,6 +170,7 @@ struct SchedFor {
   int phase = -1;        // hx::Phase
   int64_t rows = 0;      // output rows of all jobs
   int64_t owned = 0;     // pack: source rows of all jobs (a push walks every one)
+  int64_t runs = 0;      // pack: ascending runs of the jobs' source rows (0: long ones)
   int64_t terms = 0;     // sums: terms of all jobs
   int values = 1;        // values per row
   int64_t jobs = 0;

@@ -33,6 +33,7 @@ struct hx_req {
   std::vector<int32_t> s1_counts, s2_counts, r1_counts;  // message sizes (per-neighbor schedules)
   hx::DevMem s1_idx, s2_src, unpack_src, bt_ptr, bt_perm;
   hx::DevMem send, recv;  // [E1 | E2] and [R1 | R2] rows
+  int64_t pack_runs = 0;  // ascending runs of s1_idx (a message of a plan is one)
   int64_t U_pack = 0, U_redist = 0;  // distinct source rows of the pack / redistribution
   int64_t bytes[4] = {0, 0, 0, 0};
   const char* g_send = nullptr;

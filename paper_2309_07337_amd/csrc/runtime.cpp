@@ -157,6 +157,9 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
   // Infinity Cache (copies of 400 MB 76 -> 63 without), a request's was not
   // (copies of 262 MB 58 -> 51 with)
   const bool streams = w.bytes >= (w.fresh ? (int64_t)1 << 30 : (int64_t)64 << 20);
+  // a job's packed rows beyond the Infinity Cache, in short ascending runs
+  const double packed = w.owned > 0 ? (double)w.source * (double)w.rows / (double)w.owned : 0;
+  const bool scattered = packed > (double)(192 << 20) && 512 * w.runs > w.rows;
   Sched s;
   s.blocks_per_cu = kOneShotBpc;
   s.unroll = 4;
@@ -214,7 +217,7 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     s.block_threads = streams ? 512 : 256;
     s.tile_rows = std::max(1, (streams ? 32 << 10 : 16 << 10) / rb);
     s.nontemporal = streams ? 1 : 0;
-  } else if (w.phase == PH_PACK && (rb >= 64 || (w.source > kL2 && 2 * w.rows >= w.owned))) {
+  } else if (w.phase == PH_PACK && (rb >= 64 || (w.source > kL2 && 2 * w.rows >= w.owned && !scattered))) {
     // push: scattered full-line writes run as fast as scattered reads, and each
     // source row is read once; of shorter rows where the source is beyond the
     // L2, so that a pull's reads of parts of a line would go to memory (8 B
@@ -225,7 +228,12 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     // the rows 8 B 38 and 27, 16 B 43 and 28, 24 B 49 and 44, 40 B 58 and 54; a
     // quarter 8 B 21 and 25, 24 B 27 and 40, 40 B 33 and 43; the surface of a
     // cube of 160 rows a side 8 B 7 and 24, 24 B 8 and 36.  (In two messages
-    // half of the rows 8 B 16 and 26, 16 B 26 and 28.)  Its writes merge in the
+    // half of the rows 8 B 16 and 26, 16 B 26 and 28.)  Nor from lists in no
+    // order where what is packed is beyond the Infinity Cache: a push's writes of
+    // parts of a line then go to memory one by one (12 M rows in runs of 64
+    // ascending ones, 24 B, 274 MB, 295 and 378, of 512 294 and 303, of 4096 287
+    // and 228; 40 B, 457 MB, 384 and 574, 442, 318; 16 B, 183 MB, 257 and 245).
+    // Its writes merge in the
     // L2: no streaming hints (24 B 58, 152 with)
     s.push_pack = 1;
     // (400-B rows in tiles of 81 rows 181, of 40 155; where few of the rows are
@@ -387,7 +395,7 @@ SchedFor hx::req_sched_for(const hx_req* r, int phase) {
   w.values = r->ncols;
   w.bytes = r->bytes[phase];
   switch (phase) {
-    case PH_PACK: w.rows = r->E1; w.owned = r->n_local; w.source = r->n_local * rb; break;
+    case PH_PACK: w.rows = r->E1; w.owned = r->n_local; w.runs = r->pack_runs; w.source = r->n_local * rb; break;
     case PH_REDIST: w.rows = r->E2; w.source = r->R1 * rb; break;
     case PH_UNPACK: w.rows = r->H; w.source = (r->R1 + r->R2) * rb; w.identity = r->unpack_identity; break;
     default: w.rows = r->n_local; w.terms = r->E1; w.source = r->E1 * rb; break;
@@ -582,6 +590,8 @@ extern "C" int hx_neighbor_alltoallv_init(const void* x_local, int64_t n_local, 
   HX_TRY(upload_vec(r->bt_perm, perm));
   HX_TRY(r->send.alloc((size_t)E * r->row_bytes));
   HX_TRY(r->recv.alloc((size_t)H * r->row_bytes));
+  r->pack_runs = E > 0 ? 1 : 0;
+  for (int64_t k = 1; k < E; ++k) r->pack_runs += idx[(size_t)k] < idx[(size_t)k - 1] ? 1 : 0;
   r->U_pack = count_distinct_host(idx, n_local);
   r->U_redist = 0;
   req_compute_bytes(r.get());
@@ -765,6 +775,7 @@ SchedFor hx::batch_sched_for(const hx_batch* b, int phase) {
       const SchedFor m = req_sched_for(r, phase);
       w.rows += m.rows;
       w.owned += m.owned;
+      w.runs += m.runs;
       w.terms += m.terms;
       w.jobs += m.rows > 0 ? 1 : 0;
       w.bytes += m.bytes;

@@ -441,6 +441,7 @@ int hx::req_fill_from_plan(const hx_plan* p, int rank, const void* x_local, void
     for (int32_t v : bq)
       if (v < 0 || v >= r->E1) return fail(HX_ERR_RANGE, "plan: transpose entry outside the send arena");
   }
+  r->pack_runs = (int64_t)r->s1_counts.size();
   r->U_pack = distinct_count(s1, r->n_local);
   r->U_redist = distinct_count(s2, r->R1);
   HX_TRY(r->send.alloc((size_t)(r->E1 + r->E2) * r->row_bytes));

@@ -1,5 +1,5 @@
 // Prints the library's default schedules: a line of input per question,
-//   kind row_bytes phase rows owned terms values jobs bytes source identity fresh
+//   kind row_bytes phase rows owned runs terms values jobs bytes source identity fresh
 // a line of output per answer,
 //   tile_rows block_threads blocks_per_cu nontemporal unroll push_pack lds_window pair_rows
 #include <cstdio>
@@ -8,13 +8,14 @@
 
 int main() {
   int kind, rb, phase, values, identity, fresh;
-  long long rows, owned, terms, jobs, bytes, source;
-  while (std::scanf("%d %d %d %lld %lld %lld %d %lld %lld %lld %d %d", &kind, &rb, &phase, &rows, &owned, &terms,
-                    &values, &jobs, &bytes, &source, &identity, &fresh) == 12) {
+  long long rows, owned, runs, terms, jobs, bytes, source;
+  while (std::scanf("%d %d %d %lld %lld %lld %lld %d %lld %lld %lld %d %d", &kind, &rb, &phase, &rows, &owned, &runs, &terms,
+                    &values, &jobs, &bytes, &source, &identity, &fresh) == 13) {
     hx::SchedFor w;
     w.phase = phase;
     w.rows = rows;
     w.owned = owned;
+    w.runs = runs;
     w.terms = terms;
     w.values = values;
     w.jobs = jobs;

@@ -38,3 +38,29 @@ def test_default_pack(dtype_name, ncols, share):
         assert bits_equal(host(send), want)
         wait(h)
     b.free()
+
+
+@pytest.mark.parametrize("order", ["ascending", "none"])
+def test_large_lists(order):
+    """12 M packed rows of 24 bytes, beyond the Infinity Cache, in ascending order
+    and in none."""
+    need_gpu()
+    import torch
+    n = 12_000_000
+    say("large lists", order)
+    idx = (splitmix64(7, 0, n) % np.uint64(n)).astype(np.int32)
+    if order == "ascending":
+        idx.sort()
+    x = torch.rand((n, 3), dtype=torch.float64, device="cuda")
+    halo = torch.zeros((n, 3), dtype=torch.float64, device="cuda")
+    req = P.hx_neighbor_alltoallv_init(x, [n], None, idx, halo, [n], None, P.hx_topo_create(0, 2, [1], [1]))
+    b = P.hx_batch_init([req])
+    assert (P.hx_batch_get_sched(b, 0)["push_pack"] == 1) == (order == "ascending")
+    send = P.req_arena_view(req, P.HX_ARENA_SEND, 3, torch.float64)
+    want = x[torch.from_numpy(idx).cuda().long()]
+    for start, wait, h in ((P.hx_start, P.hx_wait, req), (P.hx_batch_start, P.hx_batch_wait, b)):
+        send.fill_(float("nan"))
+        start(h)
+        assert torch.equal(send, want)
+        wait(h)
+    b.free()

@@ -27,9 +27,9 @@ def rules(tmp_path_factory):
                         "-Wl,-rpath," + os.path.dirname(B.LIB)], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[:4000]
 
-    def ask(kind, row_bytes, phase, rows, owned=0, terms=0, values=1, jobs=1, nbytes=None, source=0, identity=0,
+    def ask(kind, row_bytes, phase, rows, owned=0, runs=1, terms=0, values=1, jobs=1, nbytes=None, source=0, identity=0,
             fresh=0):
-        line = [kind, row_bytes, phase, rows, owned, terms, values, jobs,
+        line = [kind, row_bytes, phase, rows, owned, runs, terms, values, jobs,
                 2 * rows * row_bytes if nbytes is None else nbytes, source, identity, fresh]
         out = subprocess.run([exe], input=" ".join(map(str, line)), capture_output=True, text=True, check=True).stdout
         return dict(zip(FIELDS, map(int, out.split())))
@@ -46,6 +46,23 @@ def test_packs_of_short_rows(rules, row_bytes, n):
     assert packed(n // 33) == 0 and packed(n // 4) == 0 and packed(n // 2 - 1) == 0
     assert packed(n // 2) == 1 and packed(n) == 1 and packed(3 * n) == 1
     assert rules(GATHER, row_bytes, PACK, 3000, owned=1000, source=1000 * row_bytes)["push_pack"] == 0
+
+
+@pytest.mark.parametrize("row_bytes", [4, 8, 12, 24, 40, 56])
+def test_lists_in_no_order(rules, row_bytes):
+    """Short rows in no order are pulled where the packed rows are beyond the
+    Infinity Cache; in messages of ascending rows, or fewer, they are pushed."""
+    def push(rows, run):
+        return rules(GATHER, row_bytes, PACK, rows, owned=rows, runs=rows // run, source=rows * row_bytes)["push_pack"]
+
+    small, large = (150 << 20) // row_bytes, (250 << 20) // row_bytes
+    assert push(small, 1) == 1 and push(small, 4096) == 1
+    assert push(large, 1) == 0 and push(large, 64) == 0
+    assert push(large, 4096) == 1
+    # (what a batch packs is spread over its jobs)
+    assert rules(GATHER, row_bytes, PACK, large, owned=large, runs=large, jobs=20,
+                 source=large * row_bytes // 20)["push_pack"] == 1
+    assert rules(GATHER, 64, PACK, large, owned=large, runs=large, source=large * 64)["push_pack"] == 1
 
 
 @pytest.mark.parametrize("row_bytes", [64, 128, 256, 800])
