@@ -204,10 +204,12 @@ int build_gather_table(const std::vector<GatherJob>& jobs, int dtype, int row_by
                        int tag) {
   t->tag = tag;
   t->copies.reset();
-  std::vector<GatherJob> indexed, copied;
+  bool kinds[2] = {false, false};
   for (const auto& j : jobs)
-    if (j.nrows > 0) (j.idx ? indexed : copied).push_back(j);
-  if (!indexed.empty() && !copied.empty()) {
+    if (j.nrows > 0) kinds[j.idx ? 1 : 0] = true;
+  if (kinds[0] && kinds[1]) {
+    std::vector<GatherJob> indexed, copied;
+    for (const auto& j : jobs) (j.idx ? indexed : copied).push_back(j);
     std::unique_ptr<LaunchTable> c(new (std::nothrow) LaunchTable);
     if (!c) return fail(HX_ERR_NOMEM, "out of host memory");
     HX_TRY(build_gather_table(copied, dtype, row_bytes, s, c.get(), tag));

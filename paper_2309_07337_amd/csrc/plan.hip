@@ -907,13 +907,13 @@ __global__ void k_pack_keys(const int32_t* __restrict__ s1_idx, int64_t E, const
 // ranks 311 -> 33 us, 0.9 M of 512 ranks 157 -> 18.
 // (The slots of a row come nearly in order, so a lane's insertion sort is nearly
 // one pass.)  Rows of more than kSortLane slots are sorted by the workgroup, as
-// the set bits of a bitmap of the rank's slots.  The whole plan of 64 ranks of
+// the set bits of a bitmap of the rank's slots (in the LDS that the slots leave:
+// room of its own costs the workgroup beside it, 33 us -> 44).  The whole plan of 64 ranks of
 // 20,000 rows, one of them packed for all ranks: 360 us (ranked one row after
 // the other by the workgroup beyond 24 slots 2295, radix sort 479); of 64 ranks
 // of 900 rows, each packed for 25 ranks: 325 (1556, 441); of 4096 ranks of 1024
 // rows, one packed for all: 1579 (9833, 2328).
 constexpr int kSortLane = 256;
-constexpr int kMaxLong = (160 << 10) / 4 / (kSortLane + 1) + 1;  // such rows in one workgroup's LDS
 constexpr int kTransMinRanks = 8;
 constexpr int kTransThreads = 512;
 __global__ void __launch_bounds__(kTransThreads)
@@ -921,16 +921,15 @@ __global__ void __launch_bounds__(kTransThreads)
                      const int64_t* __restrict__ koff, const int64_t* __restrict__ bt_off, int32_t* __restrict__ bt_ptr,
                      int32_t* __restrict__ bt_perm, int* err) {
   extern __shared__ int32_t s_mem[];
-  __shared__ int s_nlong, s_long[kMaxLong];
+  __shared__ int s_nlong, s_listed;
   const int q = blockIdx.x, tid = threadIdx.x;
   const int rows = (int)(koff[q + 1] - koff[q]), E = (int)(s1_off[q + 1] - s1_off[q]);
   const int32_t* __restrict__ idx = s1_idx + s1_off[q];
   int32_t* __restrict__ perm = bt_perm + s1_off[q];
   int32_t* s_next = s_mem;            // [rows + 1]
   int32_t* s_slot = s_mem + rows + 1; // [E]
-  uint32_t* s_bits = reinterpret_cast<uint32_t*>(s_slot + E);  // [(E + 31) / 32]
   for (int i = tid; i <= rows; i += kTransThreads) s_next[i] = 0;
-  if (tid == 0) s_nlong = 0;
+  if (tid == 0) s_nlong = s_listed = 0;
   __syncthreads();
   bool bad = false;
   for (int e = tid; e < E; e += kTransThreads) {
@@ -963,7 +962,7 @@ __global__ void __launch_bounds__(kTransThreads)
   for (int r = tid; r < rows; r += kTransThreads) {
     const int a = r > 0 ? s_next[r - 1] : 0, b = s_next[r];
     if (b - a > kSortLane) {
-      s_long[atomicAdd(&s_nlong, 1)] = r;
+      atomicAdd(&s_nlong, 1);
       continue;
     }
     for (int i = a + 1; i < b; ++i) {
@@ -974,24 +973,32 @@ __global__ void __launch_bounds__(kTransThreads)
     }
   }
   __syncthreads();
+  for (int i = tid; i < base; i += kTransThreads) perm[i] = s_slot[i];
+  if (s_nlong == 0) return;  // (uniform)
+  // the slots are all in perm: their place holds the bitmap, then the list of
+  // the long rows (E > kSortLane of them at least)
+  __syncthreads();
   const int words = (E + 31) / 32;
-  for (int g = 0; g < s_nlong; ++g) {  // (uniform)
-    const int r = s_long[g], a = r > 0 ? s_next[r - 1] : 0, b = s_next[r];
+  uint32_t* s_bits = reinterpret_cast<uint32_t*>(s_slot);
+  int32_t* s_long = s_slot + words;
+  for (int r = tid; r < rows; r += kTransThreads)
+    if (s_next[r] - (r > 0 ? s_next[r - 1] : 0) > kSortLane) s_long[atomicAdd(&s_listed, 1)] = r;
+  for (int g = 0; g < s_nlong; ++g) {
     for (int i = tid; i < words; i += kTransThreads) s_bits[i] = 0;
     __syncthreads();
-    for (int i = a + tid; i < b; i += kTransThreads) atomicOr(&s_bits[s_slot[i] >> 5], 1u << (s_slot[i] & 31));
+    const int r = s_long[g], a = r > 0 ? s_next[r - 1] : 0, b = s_next[r];
+    for (int i = a + tid; i < b; i += kTransThreads) atomicOr(&s_bits[perm[i] >> 5], 1u << (perm[i] & 31));
     __syncthreads();
     int at = a;
     for (int w0 = 0; w0 < words; w0 += kTransThreads) {
       uint32_t bits = w0 + tid < words ? s_bits[w0 + tid] : 0u;
       int tot;
       int o = at + block_exscan((int)__popc(bits), &tot);
-      for (; bits != 0; bits &= bits - 1u) s_slot[o++] = (w0 + tid) * 32 + __ffs(bits) - 1;
+      for (; bits != 0; bits &= bits - 1u) perm[o++] = (w0 + tid) * 32 + __ffs(bits) - 1;
       at += tot;
     }
     __syncthreads();
   }
-  for (int i = tid; i < base; i += kTransThreads) perm[i] = s_slot[i];
 }
 
 // Per-rank transpose arrays from that grouping (pack rows of rank q occupy
@@ -1264,11 +1271,8 @@ int build_from_halos(hx_plan* p, DevMem& hcol, const std::vector<int64_t>& hoff,
   HX_TRY(p->d[HX_F_BT_PERM].alloc((size_t)E1 * 4));
   // in LDS where every rank's fits (and there are ranks enough to fill the chip)
   int64_t lds = 0;
-  for (int q = 0; q < R; ++q) {
-    const int64_t E = s1_off[q + 1] - s1_off[q];
-    lds = std::max(lds, 4 * (pack_rows[q] + 1 + E + (E + 31) / 32));
-  }
-  const bool in_lds = lds <= device_lds_per_block() - 2048 && R >= kTransMinRanks;
+  for (int q = 0; q < R; ++q) lds = std::max(lds, 4 * (pack_rows[q] + 1 + s1_off[q + 1] - s1_off[q]));
+  const bool in_lds = lds <= device_lds_per_block() - 1024 && R >= kTransMinRanks;
   if (in_lds)
     hipLaunchKernelGGL(k_pack_transpose, dim3(R), dim3(kTransThreads), (size_t)lds, s,
                        p->d[HX_F_S1_IDX].as<int32_t>(), s1o_d, koff_d, bto_d, p->d[HX_F_BT_PTR].as<int32_t>(),
