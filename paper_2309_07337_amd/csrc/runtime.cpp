@@ -180,13 +180,16 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
       // Rows of many terms fill the staging with few rows: their ranks' windows
       // where they fit (4096 ranks plain, 7 terms a row, 216 -> 135, in 512 rows
       // 265), else smaller tiles (100 ranks 34 -> 23, in 512 rows 29).  So do few
-      // rows (16,384 rows of 3 terms in 512 rows 8.3, in 64 4.9).
+      // rows (16,384 rows of 3 terms in 512 rows 8.3, in 64 4.9).  A window's
+      // workgroup has a lane a row: half as many where a rank has few (6000
+      // requests of 100 rows of 8 terms 34 -> 23, 8000 of 30 rows of 20 59 -> 30;
+      // of 200 rows and more both alike to 4 %).
       const bool many = w.terms > 6 * w.rows, none = 8 * w.terms <= w.rows;
       s.block_threads = 256;
       if (many && w.source <= kSegWinBytes) {
         s.lds_window = 1;
         s.tile_rows = 1024;
-        s.block_threads = 512;
+        s.block_threads = w.rows <= 128 * w.jobs ? 256 : 512;
       } else {
         s.tile_rows = many || w.rows < kStageRows * (int64_t)device_cus() ? 128 : none ? 1024 : kStageRows;
         s.unroll = 2;

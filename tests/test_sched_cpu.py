@@ -101,3 +101,11 @@ def test_sums_of_two_single_values(rules, terms_per_row, rows, jobs, fresh):
         assert s["tile_rows"] <= STAGE_ROWS or (s["lds_window"] == 1 and source <= WIN_BYTES) or 8 * terms <= rows
     one = rules(SUM, 8, BWD, rows, terms=terms, values=1, jobs=jobs, source=1 << 20)
     assert one["pair_rows"] == 1
+
+
+@pytest.mark.parametrize("rows_a_job,lanes", [(1, 256), (100, 256), (128, 256), (129, 512), (1000, 512)])
+def test_windows_of_few_rows(rules, rows_a_job, lanes):
+    """A window's sums run a lane a row: no 512 lanes for jobs of fewer rows."""
+    jobs, terms = 6000, 8 * rows_a_job
+    s = rules(SUM, 8, BWD, jobs * rows_a_job, terms=jobs * terms, values=2, jobs=jobs, source=8 * terms)
+    assert (s["lds_window"], s["block_threads"]) == (1, lanes)
