@@ -160,6 +160,8 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
   // a job's packed rows beyond the Infinity Cache, in short ascending runs
   const double packed = w.owned > 0 ? (double)w.source * (double)w.rows / (double)w.owned : 0;
   const bool scattered = packed > (double)(192 << 20) && 512 * w.runs > w.rows;
+  // ascending runs that take every fourth of their source's rows, or more
+  const bool dense = w.runs > 0 && 4.0 * (double)w.rows * (double)w.jobs >= (double)w.runs * (double)w.owned;
   Sched s;
   s.blocks_per_cu = kOneShotBpc;
   s.unroll = 4;
@@ -210,7 +212,9 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
       // 28 B 108 -> 101, 40 B 100 -> 94, 48 B 94 -> 90; two lanes a row of 32 B
       // fill the smaller tile: 92, 90). From the L2 12 B 155, in 512 rows 168.
       const bool far = w.source > kL2, two = rb == 32;
-      s.tile_rows = one || (far && rb <= 40 && !two) ? kStageRows : 256;
+      // (hardly a term a row: 2.7 M rows of 40 B in tiles of 256 rows 46, of 512 34)
+      const bool none = w.rows > 0 && 8 * w.terms <= w.rows;
+      s.tile_rows = one || none || (far && rb <= 40 && !two) ? kStageRows : 256;
       s.block_threads = rb < (far && !two ? 20 : 40) ? 256 : 512;
       if (one || (far && rb <= 48)) s.unroll = 2;
     }
@@ -220,7 +224,17 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     s.block_threads = streams ? 512 : 256;
     s.tile_rows = std::max(1, (streams ? 32 << 10 : 16 << 10) / rb);
     s.nontemporal = streams ? 1 : 0;
-  } else if (w.phase == PH_PACK && (rb >= 64 || (w.source > kL2 && 2 * w.rows >= w.owned && !scattered))) {
+  } else if (w.phase == PH_PACK && rb >= 64 && rb <= 2048 && !w.fresh && 2 * w.rows <= w.owned) {
+    // a request that packs half of its rows or fewer: the pull reads few of them
+    // twice and walks no pointers (200 MB of rows packed in 6 messages, pushed and
+    // pulled: three tenths of the rows 128 B 20.8 and 17.4, 400 B 46 and 20, a
+    // tenth 12 and 7.4, 10.3 and 8.4, a fiftieth 8.8 and 3.9, 6.3 and 4.1; as many
+    // as there are 80 B in 26 messages 17 and 23, three times as many of 60 MB
+    // 128 B 37 and 44, 400 B 32 and 48; rows of 10 KB 8 and 12).  A world's packs
+    // copy a caller's rows as they push them.
+    s.tile_rows = std::max(16, (32 << 10) / rb);
+    s.block_threads = 256;
+  } else if (w.phase == PH_PACK && (rb >= 64 || (w.source > kL2 && 2 * w.rows >= w.owned && !scattered && !(dense && (one || w.rows <= w.owned))))) {
     // push: scattered full-line writes run as fast as scattered reads, and each
     // source row is read once; of shorter rows where the source is beyond the
     // L2, so that a pull's reads of parts of a line would go to memory (8 B
@@ -230,8 +244,11 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     // pointers.  4 M rows in 26 ascending messages, pulled and pushed: half of
     // the rows 8 B 38 and 27, 16 B 43 and 28, 24 B 49 and 44, 40 B 58 and 54; a
     // quarter 8 B 21 and 25, 24 B 27 and 40, 40 B 33 and 43; the surface of a
-    // cube of 160 rows a side 8 B 7 and 24, 24 B 8 and 36.  (In two messages
-    // half of the rows 8 B 16 and 26, 16 B 26 and 28.)  Nor from lists in no
+    // cube of 160 rows a side 8 B 7 and 24, 24 B 8 and 36.  Nor from messages
+    // that take every fourth row or more, which a pull reads as whole lines (half
+    // of the rows in two messages 8 B 16 and 26, 16 B 26 and 28; 1.2 M rows of 8 B
+    // eight times in 26 messages 36 and 69; not longer rows read several times, 2 M
+    // of 16 B thrice in 6 messages 36 and 24).  Nor from lists in no
     // order where what is packed is beyond the Infinity Cache: a push's writes of
     // parts of a line then go to memory one by one (12 M rows in runs of 64
     // ascending ones, 24 B, 274 MB, 295 and 378, of 512 294 and 303, of 4096 287
@@ -244,7 +261,9 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     // rows 29, of 512 11, an eighth 43 and 21)
     s.tile_rows = rb <= 48 || 4 * w.rows < w.owned ? kStageRows
                   : std::max(16, std::min(256, (rb <= 192 ? 32 << 10 : 16 << 10) / rb));
-    s.block_threads = pow2 || rb < 24 ? 256 : 512;  // (12 B 126 -> 119, 20 B 111 -> 106; 24 B 88, 82)
+    // (12 B 126 -> 119, 20 B 111 -> 106; 24 B 88, 82; a request's 200 B 104 -> 86,
+    // 400 B 88 -> 72, 800 B 86 -> 68, a world's that copies them 606, 624)
+    s.block_threads = pow2 || rb < 24 || (rb >= 64 && rb <= 2048 && !w.fresh) ? 256 : 512;
   } else if (one && w.phase == PH_PACK && w.bytes >= (int64_t)256 << 20) {
     // 16-byte row groups per lane; a rank's own rows are hot in the L2: no
     // window (4096 ranks 200 -> 165)
@@ -277,11 +296,23 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
   // few rows: smaller tiles, down to 4 KiB of output, until every CU has two
   // (a window would then be staged by every one of them)
   const int64_t cus = device_cus();
-  // (one-value sums: a row a lane)
-  const int least = kind == KIND_SEGSUM && s.pair_rows ? s.block_threads : std::max(16, (4 << 10) / rb);
+  int64_t want = 2 * cus;
+  int least = std::max(16, (4 << 10) / rb);
+  if (kind == KIND_SEGSUM) {
+    if (s.pair_rows) least = s.block_threads;  // (one-value sums: a row a lane)
+    else if (rb > 8 && rb <= 16) least = 64;       // (8700 rows of 12 B, 8 terms each: 341 rows 14, 64 6)
+  }
   const int64_t walked = s.push_pack ? w.owned : w.rows;  // rows that the tiles cover
-  if (walked > 0 && w.jobs < cus && s.tile_rows > least && walked / s.tile_rows < 2 * cus) {
-    while (s.tile_rows > least && walked / s.tile_rows < 2 * cus) s.tile_rows = std::max(least, s.tile_rows / 2);
+  if (walked > 0 && w.jobs < cus && s.tile_rows > least && walked / s.tile_rows < want) {
+    if (kind == KIND_SEGSUM && rb >= 64 && rb <= 2048 && w.terms <= 2 * w.rows) {
+      // few terms: 512 lanes, and a tile for every CU; 1024 lanes wait for each
+      // other twice a tile (8 MB of rows of 64, 128 and 400 B, a term or less each,
+      // 10.7 -> 5.4, 10.4 -> 5.3, 9.9 -> 5.2; 200 B of 8 terms each 72 -> 148)
+      s.block_threads = 512;
+      want = cus;
+      least = std::max(16, (1 << 10) / rb);
+    }
+    while (s.tile_rows > least && walked / s.tile_rows < want) s.tile_rows = std::max(least, s.tile_rows / 2);
     s.lds_window = 0;
     if (!s.push_pack && kind == KIND_GATHER) {
       s.block_threads = 256;
