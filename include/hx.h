@@ -128,10 +128,12 @@ typedef struct {
   int push_pack;      /* pack phase only: 1 = push form (walk the transpose of
                          the pack map, read each source row once and write it
                          to all its slots); 2 = pull form (gather per slot);
-                         0 = default (push for rows of 64 bytes or more, and
-                         for shorter ones packed from more than an XCD's L2
-                         holds, 4 MiB, where at least half as many are
-                         packed as the source has; else pull) */
+                         0 = default (push for rows of 64 bytes or more, but
+                         for requests that pack half of theirs or fewer, up
+                         to 2 KiB; and for shorter ones packed from more than
+                         an XCD's L2 holds, 4 MiB, where at least half as many
+                         are packed as the source has and no message takes
+                         every fourth of them; else pull) */
   int lds_window;     /* gathers: 1 = a job whose indices mostly stay inside
                          a known window of source rows (the pack: the rank's
                          own rows; the redistribution: its stage-1 receive

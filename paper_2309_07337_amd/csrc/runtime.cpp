@@ -303,11 +303,14 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     else if (rb > 8 && rb <= 16) least = 64;       // (8700 rows of 12 B, 8 terms each: 341 rows 14, 64 6)
   }
   const int64_t walked = s.push_pack ? w.owned : w.rows;  // rows that the tiles cover
-  if (walked > 0 && w.jobs < cus && s.tile_rows > least && walked / s.tile_rows < want) {
-    if (kind == KIND_SEGSUM && rb >= 64 && rb <= 2048 && w.terms <= 2 * w.rows) {
+  // (a world's ranks are one job where none reads a window)
+  const int64_t jobs = w.fresh && !s.lds_window ? 1 : w.jobs;
+  if (walked > 0 && jobs < cus && s.tile_rows > least && walked / s.tile_rows < want) {
+    if (kind == KIND_SEGSUM && rb >= 64 && rb <= 2048 && w.terms <= 3 * w.rows) {
       // few terms: 512 lanes, and a tile for every CU; 1024 lanes wait for each
       // other twice a tile (8 MB of rows of 64, 128 and 400 B, a term or less each,
-      // 10.7 -> 5.4, 10.4 -> 5.3, 9.9 -> 5.2; 200 B of 8 terms each 72 -> 148)
+      // 10.7 -> 5.4, 10.4 -> 5.3, 9.9 -> 5.2; 256 B of three each 13.9 -> 8.0; 27 MB
+      // of 200 B of 8 each, more than a tile stages, 72 -> 148)
       s.block_threads = 512;
       want = cus;
       least = std::max(16, (1 << 10) / rb);
@@ -799,7 +802,8 @@ SchedFor hx::batch_sched_for(const hx_batch* b, int phase) {
       default:
         w.rows = b->n;
         w.terms = b->unpack_identity || b->staged_bwd ? b->E1_tot : b->H_tot;
-        // (the closed-form adjoint reads every rank's halo)
+        // (the closed-form adjoint reads every rank's halo, as one job)
+        if (!b->unpack_identity && !b->staged_bwd) w.jobs = 1;
         w.source = b->unpack_identity || b->staged_bwd ? b->E1_tot / R * rb : b->H_tot * rb;
         break;
     }

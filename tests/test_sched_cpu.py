@@ -41,7 +41,7 @@ def rules(tmp_path_factory):
 def test_packs_of_short_rows(rules, row_bytes, n):
     """Pushed where at least half as many rows are packed as the source has: a
     push walks every one of them."""
-    packed = lambda rows: rules(GATHER, row_bytes, PACK, rows, owned=n, source=n * row_bytes)["push_pack"]
+    packed = lambda rows: rules(GATHER, row_bytes, PACK, rows, owned=n, runs=26, source=n * row_bytes)["push_pack"]
     assert n * row_bytes > 4 << 20
     assert packed(n // 33) == 0 and packed(n // 4) == 0 and packed(n // 2 - 1) == 0
     assert packed(n // 2) == 1 and packed(n) == 1 and packed(3 * n) == 1
@@ -70,7 +70,7 @@ def test_pushed_tiles_cover_the_source(rules, row_bytes):
     """Their size follows the rows they walk: few rows packed from many make no
     more tiles than many do, and a small source still gives every CU two."""
     def tile(rows, owned):
-        s = rules(GATHER, row_bytes, PACK, rows, owned=owned, source=owned * row_bytes)
+        s = rules(GATHER, row_bytes, PACK, rows, owned=owned, source=owned * row_bytes, fresh=1)
         assert s["push_pack"] == 1
         return s["tile_rows"]
 
@@ -109,3 +109,41 @@ def test_windows_of_few_rows(rules, rows_a_job, lanes):
     jobs, terms = 6000, 8 * rows_a_job
     s = rules(SUM, 8, BWD, jobs * rows_a_job, terms=jobs * terms, values=2, jobs=jobs, source=8 * terms)
     assert (s["lds_window"], s["block_threads"]) == (1, lanes)
+
+
+@pytest.mark.parametrize("row_bytes", [64, 100, 400, 2048])
+def test_long_rows_packed_by_halves(rules, row_bytes):
+    """A request that packs at most half of its long rows pulls them; a world's
+    push copies a caller's rows, so it stays; longer rows are pushed too."""
+    def push(rows, rb=row_bytes, **kw):
+        return rules(GATHER, rb, PACK, rows, owned=100_000, source=100_000 * rb, **kw)["push_pack"]
+
+    assert push(50_000) == 0 and push(10) == 0 and push(50_001) == 1 and push(300_000) == 1
+    assert push(10, fresh=1) == 1 and push(10, rb=2052) == 1
+
+
+@pytest.mark.parametrize("row_bytes", [4, 8, 12, 24, 56])
+def test_messages_of_every_fourth_row(rules, row_bytes):
+    """Dense messages of short rows are pulled, unless longer ones are read several times."""
+    n = 8_000_000
+    def push(rows, runs):
+        return rules(GATHER, row_bytes, PACK, rows, owned=n, runs=runs, source=n * row_bytes)["push_pack"]
+
+    assert push(n, 4) == 0 and push(n, 5) == 1
+    assert push(3 * n, 12) == (0 if row_bytes <= 8 else 1) and push(3 * n, 13) == 1
+
+
+@pytest.mark.parametrize("row_bytes", [64, 100, 256, 2048, 2052, 10_000])
+@pytest.mark.parametrize("jobs", [1, 1000])
+@pytest.mark.parametrize("fresh", [0, 1])
+def test_sums_of_few_long_rows(rules, row_bytes, jobs, fresh):
+    """512 lanes and a tile for every CU where there are few terms, and never
+    more of them in a tile than it stages; a world's ranks are one job."""
+    rows = 4 * CUS
+    few = rules(SUM, row_bytes, BWD, rows, terms=3 * rows, jobs=jobs, nbytes=1 << 20, source=1 << 16, fresh=fresh)
+    many = rules(SUM, row_bytes, BWD, rows, terms=3 * rows + 1, jobs=jobs, nbytes=1 << 20, source=1 << 16, fresh=fresh)
+    assert many["block_threads"] == 1024
+    shrunk = jobs == 1 or fresh == 1
+    assert few["block_threads"] == (512 if shrunk and row_bytes <= 2048 else 1024)
+    assert (few["tile_rows"] == 16) == shrunk
+    assert 3 * few["tile_rows"] <= 2048
