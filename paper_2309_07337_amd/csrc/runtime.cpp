@@ -155,7 +155,8 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
   // streaming hints, for phases that move more than this: what a world's phase
   // reads was just written by the one before and is still in the 256 MB
   // Infinity Cache (copies of 400 MB 76 -> 63 without), a request's was not
-  // (copies of 262 MB 58 -> 51 with)
+  // (copies of 262 MB 58 -> 51 with; of 100 MB a call, cold 57 -> 38, and still
+  // warm from the call before 27 -> 34)
   const bool streams = w.bytes >= (w.fresh ? (int64_t)1 << 30 : (int64_t)64 << 20);
   // a job's packed rows beyond the Infinity Cache, in short ascending runs
   const double packed = w.owned > 0 ? (double)w.source * (double)w.rows / (double)w.owned : 0;
@@ -303,7 +304,8 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     else if (rb > 8 && rb <= 16) least = 64;       // (8700 rows of 12 B, 8 terms each: 341 rows 14, 64 6)
   }
   const int64_t walked = s.push_pack ? w.owned : w.rows;  // rows that the tiles cover
-  // (a world's ranks are one job where none reads a window)
+  // (a world's ranks are one job where none reads a window: 1280 rows of 320 ranks
+  // in one tile of 8192 13.4, in five 4.7)
   const int64_t jobs = w.fresh && !s.lds_window ? 1 : w.jobs;
   if (walked > 0 && jobs < cus && s.tile_rows > least && walked / s.tile_rows < want) {
     if (kind == KIND_SEGSUM && rb >= 64 && rb <= 2048 && w.terms <= 3 * w.rows) {
