@@ -263,8 +263,9 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     s.tile_rows = rb <= 48 || 4 * w.rows < w.owned ? kStageRows
                   : std::max(16, std::min(256, (rb <= 192 ? 32 << 10 : 16 << 10) / rb));
     // (12 B 126 -> 119, 20 B 111 -> 106; 24 B 88, 82; a request's 200 B 104 -> 86,
-    // 400 B 88 -> 72, 800 B 86 -> 68, a world's that copies them 606, 624)
-    s.block_threads = pow2 || rb < 24 || (rb >= 64 && rb <= 2048 && !w.fresh) ? 256 : 512;
+    // 400 B 88 -> 72, 800 B 86 -> 68, of 200 B packed eight times 53,
+    // 66; a world's of 400 B that copies them 606, 624)
+    s.block_threads = pow2 || rb < 24 || (rb >= 64 && rb <= 2048 && !w.fresh && w.rows <= 4 * w.owned) ? 256 : 512;
   } else if (one && w.phase == PH_PACK && w.bytes >= (int64_t)256 << 20) {
     // 16-byte row groups per lane; a rank's own rows are hot in the L2: no
     // window (4096 ranks 200 -> 165)
@@ -308,16 +309,23 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
   // in one tile of 8192 13.4, in five 4.7)
   const int64_t jobs = w.fresh && !s.lds_window ? 1 : w.jobs;
   if (walked > 0 && jobs < cus && s.tile_rows > least && walked / s.tile_rows < want) {
-    if (kind == KIND_SEGSUM && rb >= 64 && rb <= 2048 && w.terms <= 3 * w.rows) {
-      // few terms: 512 lanes, and a tile for every CU; 1024 lanes wait for each
-      // other twice a tile (8 MB of rows of 64, 128 and 400 B, a term or less each,
-      // 10.7 -> 5.4, 10.4 -> 5.3, 9.9 -> 5.2; 256 B of three each 13.9 -> 8.0; 27 MB
-      // of 200 B of 8 each, more than a tile stages, 72 -> 148)
+    int64_t staged = 0;  // terms of a tile at most
+    if (kind == KIND_SEGSUM && rb >= 64 &&
+        (w.terms <= 3 * w.rows ? rb <= 2048 : rb <= 1024 && w.rows * rb <= 16 << 20)) {
+      // 512 lanes, and a tile for every CU with no more terms than it stages: 1024
+      // lanes wait for each other twice a tile (8 MB of rows of 64, 128 and 400 B, a
+      // term or less each, 10.7 -> 5.4, 10.4 -> 5.3, 9.9 -> 5.2; 256 B of three each
+      // 13.9 -> 8.0; 4 MB of five each, 64 to 800 B, 0.6 of the time.  27 MB of 200 B
+      // of 8 each, more than a tile of 327 rows stages, 72 -> 148, in 163 rows 70 and
+      // 84; 1600 B of five each 42 and 50)
       s.block_threads = 512;
       want = cus;
       least = std::max(16, (1 << 10) / rb);
+      staged = kStageEntries * 3 / 4;
     }
-    while (s.tile_rows > least && walked / s.tile_rows < want) s.tile_rows = std::max(least, s.tile_rows / 2);
+    while (s.tile_rows > least &&
+           (walked / s.tile_rows < want || (staged > 0 && s.tile_rows * w.terms > staged * w.rows)))
+      s.tile_rows = std::max(least, s.tile_rows / 2);
     s.lds_window = 0;
     if (!s.push_pack && kind == KIND_GATHER) {
       s.block_threads = 256;

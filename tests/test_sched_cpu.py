@@ -133,17 +133,18 @@ def test_messages_of_every_fourth_row(rules, row_bytes):
     assert push(3 * n, 12) == (0 if row_bytes <= 8 else 1) and push(3 * n, 13) == 1
 
 
-@pytest.mark.parametrize("row_bytes", [64, 100, 256, 2048, 2052, 10_000])
+@pytest.mark.parametrize("row_bytes", [64, 100, 256, 1024, 1028, 2048, 2052, 10_000])
 @pytest.mark.parametrize("jobs", [1, 1000])
 @pytest.mark.parametrize("fresh", [0, 1])
-def test_sums_of_few_long_rows(rules, row_bytes, jobs, fresh):
-    """512 lanes and a tile for every CU where there are few terms, and never
-    more of them in a tile than it stages; a world's ranks are one job."""
+@pytest.mark.parametrize("terms_per_row", [0, 1, 3, 4, 8, 40])
+def test_sums_of_few_long_rows(rules, row_bytes, jobs, fresh, terms_per_row):
+    """512 lanes and a tile for every CU where the rows are short for their
+    terms, with no more terms in it than a tile stages; a world's ranks are one job."""
     rows = 4 * CUS
-    few = rules(SUM, row_bytes, BWD, rows, terms=3 * rows, jobs=jobs, nbytes=1 << 20, source=1 << 16, fresh=fresh)
-    many = rules(SUM, row_bytes, BWD, rows, terms=3 * rows + 1, jobs=jobs, nbytes=1 << 20, source=1 << 16, fresh=fresh)
-    assert many["block_threads"] == 1024
+    s = rules(SUM, row_bytes, BWD, rows, terms=terms_per_row * rows, jobs=jobs, nbytes=1 << 20, source=1 << 16,
+              fresh=fresh)
     shrunk = jobs == 1 or fresh == 1
-    assert few["block_threads"] == (512 if shrunk and row_bytes <= 2048 else 1024)
-    assert (few["tile_rows"] == 16) == shrunk
-    assert 3 * few["tile_rows"] <= 2048
+    assert (s["block_threads"] == 512) == (shrunk and row_bytes <= (2048 if terms_per_row <= 3 else 1024))
+    assert (s["tile_rows"] < 64) == shrunk
+    large = rules(SUM, 64, BWD, 260_000, terms=260_000 * terms_per_row, source=1 << 24)
+    assert large["block_threads"] == 512 and large["tile_rows"] * terms_per_row <= 2048
