@@ -263,9 +263,9 @@ Sched default_sched(int kind, int row_bytes, const SchedFor& w) {
     s.tile_rows = rb <= 48 || 4 * w.rows < w.owned ? kStageRows
                   : std::max(16, std::min(256, (rb <= 192 ? 32 << 10 : 16 << 10) / rb));
     // (12 B 126 -> 119, 20 B 111 -> 106; 24 B 88, 82; a request's 200 B 104 -> 86,
-    // 400 B 88 -> 72, 800 B 86 -> 68, of 200 B packed eight times 53,
-    // 66; a world's of 400 B that copies them 606, 624)
-    s.block_threads = pow2 || rb < 24 || (rb >= 64 && rb <= 2048 && !w.fresh && w.rows <= 4 * w.owned) ? 256 : 512;
+    // 400 B 88 -> 72, 800 B 86 -> 68, of 80 B packed four times 80,
+    // 90, of 200 B eight times 53, 66; a world's of 400 B that copies them 606, 624)
+    s.block_threads = pow2 || rb < 24 || (rb >= 64 && rb <= 2048 && !w.fresh && w.rows <= 3 * w.owned) ? 256 : 512;
   } else if (one && w.phase == PH_PACK && w.bytes >= (int64_t)256 << 20) {
     // 16-byte row groups per lane; a rank's own rows are hot in the L2: no
     // window (4096 ranks 200 -> 165)

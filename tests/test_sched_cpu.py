@@ -148,3 +148,14 @@ def test_sums_of_few_long_rows(rules, row_bytes, jobs, fresh, terms_per_row):
     assert (s["tile_rows"] < 64) == shrunk
     large = rules(SUM, 64, BWD, 260_000, terms=260_000 * terms_per_row, source=1 << 24)
     assert large["block_threads"] == 512 and large["tile_rows"] * terms_per_row <= 2048
+
+
+@pytest.mark.parametrize("row_bytes", [64, 100, 2000, 2004])
+def test_lanes_of_pushed_long_rows(rules, row_bytes):
+    """256 for rows of a power of two, and for a request's others of up to 2 KiB
+    that are packed at most three times."""
+    def lanes(rows, **kw):
+        return rules(GATHER, row_bytes, PACK, rows, owned=100_000, source=100_000 * row_bytes, **kw)["block_threads"]
+
+    assert lanes(100_000) == lanes(300_000) == 256
+    assert lanes(300_001) == lanes(300_000, fresh=1) == (256 if row_bytes == 64 else 512)
